@@ -300,10 +300,10 @@ def gemm_phase_leg(lib, reps=3):
                        f"{c['cx_per_layer']} CX pairs per layer (p_nn {c['p_nn']}), single-amplitude "
                        "networks, 8 SA partitions", "planning_s": plan_s,
            "mfma_probe_tflops": probe, "mfma_probe_const_operands_tflops": probe_const}
-    # bf16 MFMA operations per effective complex flop: 4M = 12 products of
-    # 2 flops per 8 effective flops, 3M = 9 products
-    for name, flags, peak, mul in [("fp32_4m", 0, MFMA_PEAK_TFLOPS["fp32"], 1.0),
-                                   ("fp32_3m", lib.TN_FORM_3M, MFMA_PEAK_TFLOPS["fp32"], 0.75),
+    # bf16 MFMA operations per effective complex flop (8 per multiply-add): FP32
+    # 24 products of 2 flops, BF16x3 4M 12, 3M 9
+    for name, flags, peak, mul in [("fp32_4m", 0, MFMA_PEAK_TFLOPS["bf16x3"], 6.0),
+                                   ("fp32_3m", lib.TN_FORM_3M, MFMA_PEAK_TFLOPS["bf16x3"], 6.0),
                                    ("bf16x3_4m", lib.TN_PREC_BF16X3, MFMA_PEAK_TFLOPS["bf16x3"], 3.0),
                                    ("bf16x3_3m", lib.TN_PREC_BF16X3 | lib.TN_FORM_3M,
                                     MFMA_PEAK_TFLOPS["bf16x3"], 2.25)]:
@@ -341,7 +341,7 @@ def gemm_phase_leg(lib, reps=3):
         st = lib.tn_profile_read(ctx.handle, reset=True)
         g = st["gemm"]
         eff = g["algo_flops"] / g["seconds"] / 1e12
-        ach = probe["fp32" if name.startswith("fp32") else "bf16x3"]
+        ach = probe["bf16x3"]
         out[name] = {"gemm_effective_tflops": eff, "mfma_peak_tflops": peak,
                      "mfma_util": eff * mul / peak, "mfma_frac_of_achievable": eff * mul / ach,
                      "gemm_ms_per_amplitude": g["seconds"] / reps * 1e3,
@@ -506,12 +506,12 @@ def batch_mix_leg(lib, queries=512, reps=3):
     return out
 
 
-# bf16 (or f32) MFMA flops executed per effective complex flop (8 per complex
-# multiply-add): FP32 4M 8, FP32 3M 6; BF16x3 4M twelve bf16 products of 2
-# flops, 3M nine
-EXEC_PER_EFFECTIVE = {("fp32", "4m"): 1.0, ("fp32", "3m"): 0.75, ("bf16x3", "4m"): 3.0,
+# bf16 MFMA flops executed per effective complex flop (8 per complex
+# multiply-add): FP32 twenty-four bf16 products of 2 flops (four real
+# products of six terms), BF16x3 4M twelve, 3M nine
+EXEC_PER_EFFECTIVE = {("fp32", "4m"): 6.0, ("fp32", "3m"): 6.0, ("bf16x3", "4m"): 3.0,
                       ("bf16x3", "3m"): 2.25}
-GEMM_KERNEL = {("fp32", "4m"): "k_cgemm_f32_planes<0>", ("fp32", "3m"): "k_cgemm_f32_planes<1>",
+GEMM_KERNEL = {("fp32", "4m"): "k_cgemm_f32_planes", ("fp32", "3m"): "k_cgemm_f32_planes",
                ("bf16x3", "4m"): "k_cgemm_bf16x3_dma<0>", ("bf16x3", "3m"): "k_cgemm_bf16x3_dma<1>"}
 GEMM_SOURCE = {"fp32": "gemm_f32.hip", "bf16x3": "gemm_bf16.hip"}
 
@@ -725,13 +725,13 @@ def headline_random30(lib, torch, args):
     stats = lib.tn_profile_read(ctx.handle, reset=True)
     g = stats["gemm"]
     mul = EXEC_PER_EFFECTIVE[(prec, form)]
-    peak = MFMA_PEAK_TFLOPS[prec]
+    peak = MFMA_PEAK_TFLOPS["bf16x3"]
     eff = g["algo_flops"] / g["seconds"] / 1e12
     achieved = eff * mul
     nl = max(g["launches"], 1)
     kname = GEMM_KERNEL[(prec, form)]
     traffic = traffic_record(kname)
-    ach = lib.tn_probe_mfma(ctx.handle, lib.TN_PREC_FP32 if prec == "fp32" else lib.TN_PREC_BF16X3)
+    ach = lib.tn_probe_mfma(ctx.handle, lib.TN_PREC_BF16X3)
     roof = {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
             "traffic": traffic, "kernel": kname,
             "achievable_tflops": ach, "frac_of_achievable": achieved / ach,
@@ -739,8 +739,8 @@ def headline_random30(lib, torch, args):
             "algo_flops_per_launch": g["algo_flops"] / nl * mul,
             "algo_bytes_per_launch": g["algo_bytes"] / nl,
             "effective_tflops": eff,
-            "note": "achieved = MFMA flops of the form (8 M N K for 4M, 6 M N K for 3M, times 3 or 2.25 "
-                    "bf16 products for BF16x3) per launch / event-timed average launch, the split-k "
+            "note": "achieved = bf16 MFMA flops (48 M N K for FP32, 24 or 18 M N K for BF16x3 4M or 3M) "
+                    "per launch / event-timed average launch, the split-k "
                     "reduction of the one split vertex included; achievable_tflops = the rate the matrix "
                     "cores sustain on this device with no memory traffic on operands that change from "
                     "product to product (tn_probe_mfma)"}

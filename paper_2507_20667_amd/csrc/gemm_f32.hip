@@ -1,32 +1,48 @@
-// FP32 complex GEMM on v_mfma_f32_32x32x2_f32 from k-tiled float planes.
+// FP32 complex GEMM from k-tiled float planes, on the bfloat16 matrix cores.
 //
 // The permutation that puts a vertex's operands in GEMM order writes them as
 // two float planes (re, im), divided by 2^e of the operand's scale record and
 // k-tiled: row r, k sits at ((k / 16) * rows + r) * 16 + k % 16, so that one
 // 16-deep stage of a 128-row tile is a contiguous 8 KB block of each plane.
-// Stages stream straight from global memory into a ring of LDS slots
-// (global_load_lds_dwordx4, no staging registers): two slots, one stage
-// ahead, when two blocks share a CU (see TWO below), else four slots, three
-// stages ahead.  The wait for a stage is a vmcnt on the wave's own loads
-// followed by a barrier.  Past the last stage the requests repeat the last
-// stage into the free slot, so the number of loads in flight, and the wait,
-// never change.  The slots are distinct arrays named statically (the loop is
-// unrolled by the slot count), which lets the compiler see that a read of one
-// slot does not wait on loads into another.
+// Stages stream straight from global memory into two LDS slots
+// (global_load_lds_dwordx4, no staging registers), one stage ahead.  The wait
+// for a stage is a vmcnt on the wave's own loads followed by a barrier.  Past
+// the last stage the request repeats the last stage into the free slot, so
+// the number of loads in flight never changes.  The slots are distinct arrays
+// named statically (the loop is unrolled by two), which lets the compiler see
+// that a read of one slot does not wait on loads into the other.
 //
-// Block = 4 waves in a 2 x 2 grid over a 128 x 128 output tile, each wave
-// 64 x 64 outputs as 2 x 2 MFMA tiles.  For that instruction lane l supplies
-// A[l%32][kk] and B[kk][l%32] with kk = l/32 of a 2-deep step and holds
-// C[8(v/4) + 4(l/32) + v%4][l%32] in accumulator v.  Within a stage, step s
-// gives lane half h the k value 8h + s (A and B alike, so the sum over k is
-// unchanged): a lane's eight k of a row are two 16-byte LDS reads.  Rows are
-// 64 bytes; row r's chunk c sits at position c ^ swz(r), so the rows one LDS
-// access touches fall on distinct banks.  A stage is 128 MFMAs per wave (4M).
-// FORM = 4M: Re = ArBr - AiBi, Im = ArBi + AiBr (four products per complex
-// one).  FORM = 3M (Gauss): T1 = ArBr, T2 = AiBi, T3 = (Ar + Ai)(Br + Bi),
-// Re = T1 - T2, Im = T3 - T1 - T2; the sums are formed in registers from the
-// fragments (one add per value), so the planes and the LDS traffic are the
-// same as 4M's and the MFMA work is three quarters of it.
+// Products.  A value is the sum of three bfloat16 terms, x = h + m + l with
+// h = bf16(x), m = bf16(x - h), l = x - h - m, exactly (24 significant bits
+// are 3 times 8; |x| above 2^-110), and a product is ha hb + ha mb + ma hb +
+// ma mb + ha lb + la hb: the dropped terms are below 2^-25 of it, less than
+// the rounding of one FP32 addition.  bfloat16 has FP32's exponent range, so
+// this holds for entries of any size.  Six v_mfma_f32_32x32x16_bf16 do 16 k in
+// 192 cycles where eight v_mfma_f32_32x32x2_f32 took 512, and an accumulator
+// is rounded once per 16 k instead of per 2: the error against 64 bits is
+// smaller than the FP32 matrix cores' (2-norm, 256 x 192 outputs of normally
+// distributed entries: 0.68e-7 against 1.02e-7 at K = 16, 2.4e-7 against 2.9e-7 at
+// 128, 7.0e-7 against 8.1e-7 at 1024; positive entries 3.8e-7 against 6.0e-7
+// at 1024; entries spread over 2^20 5.4e-7 against 6.6e-7).  The terms are formed in registers
+// from the float fragments (seven instructions for two values, 32 rows x 16
+// k of each operand half per wave and stage), so the planes, the permutations
+// and the fused epilogues stay FP32 and no operand takes more memory.
+// The complex product takes four real ones whatever the form flag says
+// (Gauss's three would need a third accumulator set: one block per CU).
+//
+// Bound: the matrix cores, at the clock their power allows.  Eight 30-qubit
+// amplitudes: 76.7 -> 51.7 ms of GEMM against the FP32 matrix cores' 3M form
+// (12.9 -> 7.7 ms for one amplitude against 4M), 1540 TFLOP/s of bf16
+// products, matrix cores busy 0.70 at 2.05-2.15 GHz (they sustain 1794 TFLOP/s
+// with no memory traffic on operands that change).
+//
+// Block = 4 waves in a 2 x 2 grid over a 128 x 128 output tile, two blocks per
+// CU (64 KB of LDS, 248 registers): one block's splits, fragment reads and
+// barrier overlap the other's products.  Each wave has 64 x 64 outputs as 2 x 2
+// MFMA tiles: lane l supplies A[l%32][8(l/32) .. + 7] and the same k of column
+// l%32 of B, and holds C[8(v/4) + 4(l/32) + v%4][l%32] in accumulator v.  Rows
+// are 64 bytes; row r's chunk c sits at position c ^ swz(r), so the rows one
+// LDS access touches fall on distinct banks.  A stage is 96 MFMAs per wave.
 #include <type_traits>
 
 #include "tn_device.h"
@@ -35,6 +51,8 @@ namespace tn {
 
 typedef float v16f_c __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef unsigned int v4u_f __attribute__((ext_vector_type(4)));
+typedef __bf16 v8bf_f __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) void lds_void_f;
 
 constexpr int FBK = 16;               // k per stage
@@ -48,31 +66,44 @@ __device__ __forceinline__ int fswz(int r) {
   return ((((r >> 3) ^ (r >> 1)) & 1) << 1) | ((r >> 2) & 1);
 }
 
+__device__ __forceinline__ v16f_c mfma_bf(v4u_f a, v4u_f b, v16f_c c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_f, a), __builtin_bit_cast(v8bf_f, b), c, 0, 0, 0);
+}
+
+// term indices (0 = h, 1 = m, 2 = l) of the six products
+__device__ constexpr int kSplitA[6] = {1, 0, 2, 0, 1, 0};
+__device__ constexpr int kSplitB[6] = {1, 2, 0, 1, 0, 0};
+
 // WMW = waves along M (the four waves form a WMW x 4/WMW grid, 64 x 64
 // outputs each): 2 gives a 128 x 128 tile, 1 a 64 x 256 tile (for M <= 64),
 // 4 a 256 x 64 tile (for N <= 64).
-//
-// TWO: two blocks share a CU.  The ring then has two slots (64 KB of LDS for
-// the 128 x 128 tile) and a wave reads a stage's fragments in two halves of
-// eight k (32 fragment registers), so that a block fits in 256 registers;
-// one block's barrier and fragment reads overlap the other's products
-// (1.04-1.14 x on the 30-qubit shapes against one block with four slots).
-// The 3M form of the 64 x 256 and 256 x 64 tiles would not fit and keeps one
-// block per CU with the four-slot ring.
-template <int FORM, int WMW>
-__device__ __forceinline__ constexpr bool planes_two() { return FORM == kForm4M || WMW == 2; }
 
-template <int FORM, int WMW>
-__global__ __launch_bounds__(256, (FORM == kForm4M || WMW == 2) ? 2 : 1) void k_cgemm_f32_planes(GemmArgs g) {
-  constexpr bool TWO = planes_two<FORM, WMW>();
-  constexpr int NSLOT = TWO ? 2 : 4;
-  constexpr int NACC = FORM == kForm3M ? 3 : 2;
+// Two values split at once: v = h + m + l, each term the bfloat16 nearest to
+// what the terms before it leave (bits 0-15 of h, m, l: a's terms, bits 16-31:
+// b's).  a - h is one dot product of the pair h with (-1, 0), b - h with
+// (0, -1): exact, and an instruction less per value than widening h first.
+__device__ __forceinline__ void split3(float a, float b, uint32_t lo1, uint32_t hi1, uint32_t &h, uint32_t &m,
+                                       uint32_t &l) {
+  const tn_bf16x2 e0 = __builtin_bit_cast(tn_bf16x2, lo1), e1 = __builtin_bit_cast(tn_bf16x2, hi1);
+  const tn_bf16x2 hv = __builtin_convertvector((tn_f32x2{a, b}), tn_bf16x2);
+  const float ra = __builtin_amdgcn_fdot2_f32_bf16(hv, e0, a, false);
+  const float rb = __builtin_amdgcn_fdot2_f32_bf16(hv, e1, b, false);
+  const tn_bf16x2 mv = __builtin_convertvector((tn_f32x2{ra, rb}), tn_bf16x2);
+  const float sa = __builtin_amdgcn_fdot2_f32_bf16(mv, e0, ra, false);
+  const float sb = __builtin_amdgcn_fdot2_f32_bf16(mv, e1, rb, false);
+  h = __builtin_bit_cast(uint32_t, hv);
+  m = __builtin_bit_cast(uint32_t, mv);
+  l = __builtin_bit_cast(uint32_t, __builtin_convertvector((tn_f32x2{sa, sb}), tn_bf16x2));
+}
+
+template <int WMW>
+__global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
   constexpr int WNW = 4 / WMW;
   constexpr int BM = 64 * WMW, BN = 64 * WNW;          // tile rows of A and of B
   constexpr int APL = BM * FBK, BPL = BN * FBK;        // floats per plane tile
   constexpr int FSTAGE = 2 * (APL + BPL);              // A re, A im, B re, B im
   constexpr int JA = BM / 64, JB = BN / 64;            // load instructions per wave and plane
-  __shared__ __align__(16) float ring0[FSTAGE], ring1[FSTAGE], ring2[TWO ? 4 : FSTAGE], ring3[TWO ? 4 : FSTAGE];
+  __shared__ __align__(16) float ring0[FSTAGE], ring1[FSTAGE];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WNW, wn = wave % WNW;
   const int q = blockIdx.y;
@@ -90,13 +121,13 @@ __global__ __launch_bounds__(256, (FORM == kForm4M || WMW == 2) ? 2 : 1) void k_
   const int ea = tn_scale_exp(sa->maxbits), eb = tn_scale_exp(sb->maxbits);
   if (blockIdx.x == 0 && tid == 0) sc->log2s = sa->log2s + sb->log2s + (double)(ea + eb);
 
-  v16f_c acc[2][2][NACC];
+  v16f_c acc[2][2][2];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int c = 0; c < NACC; ++c)
+      for (int c = 0; c < 2; ++c)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[a][b][c][v] = 0.0f;
 
@@ -122,7 +153,7 @@ __global__ __launch_bounds__(256, (FORM == kForm4M || WMW == 2) ? 2 : 1) void k_
     boff[j] = (uint32_t)((rb_ * FBK + c * 4) * 4);
   }
   const int64_t nk = (kend - kbeg) / FBK;
-#define TN_FRING(S) ((S) == 0 ? ring0 : (S) == 1 ? ring1 : (S) == 2 ? ring2 : ring3)
+#define TN_FRING(S) ((S) == 0 ? ring0 : ring1)
   auto issue = [&](auto slot, int64_t stg) {
     constexpr int S = decltype(slot)::value;
     float *rb = TN_FRING(S);
@@ -142,130 +173,118 @@ __global__ __launch_bounds__(256, (FORM == kForm4M || WMW == 2) ? 2 : 1) void k_
             (lds_void_f *)(rb + 2 * APL + pl * BPL + ((BN / 4) * wave + 16 * j) * FBK), 16, 0, 0);
     }
   };
-  // fragments: lane half h reads k 8h .. 8h+7 of its row (logical chunks 2h
-  // and 2h + 1) from each plane
+  // a lane's eight k (8h .. 8h + 7 of lane half h) of row `row` of a plane
+  // tile: logical chunks 2h and 2h + 1
   const int fr = lane & 31, fh = lane >> 5;
   const int fp0 = ((2 * fh) ^ fswz(fr)) * 4, fp1 = ((2 * fh + 1) ^ fswz(fr)) * 4;
-  auto fread = [&](auto slot, int h, v4f (&a)[2][2], v4f (&b)[2][2]) {
+  // the constant pairs of split3, kept in scalar registers (opaque, so that
+  // they are not folded into packed inline constants)
+  uint32_t lo1 = 0x0000bf80u, hi1 = 0xbf800000u;
+  asm volatile("" : "+s"(lo1), "+s"(hi1));
+  auto split = [&](const float *row, v4u_f (&t3)[3]) {
+    const v4f x = *(const v4f *)(row + fp0), y = *(const v4f *)(row + fp1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t h, m, l;
+      split3(i < 2 ? x[2 * i] : y[2 * i - 4], i < 2 ? x[2 * i + 1] : y[2 * i - 3], lo1, hi1, h, m, l);
+      t3[0][i] = h;
+      t3[1][i] = m;
+      t3[2][i] = l;
+    }
+  };
+  auto stage = [&](auto slot, int64_t kt) {
     constexpr int S = decltype(slot)::value;
     const float *rb = TN_FRING(S);
-    const int fp = h ? fp1 : fp0;
+    __builtin_amdgcn_s_waitcnt(f_wait_imm(0));
+    __builtin_amdgcn_s_barrier();
+    issue(std::integral_constant<int, 1 - S>(), kt + 1);
+    v4u_f a[2][2][3];
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-      for (int pl = 0; pl < 2; ++pl)
-        a[mb][pl] = *(const v4f *)(rb + pl * APL + (wm * 64 + mb * 32 + fr) * FBK + fp);
+      for (int pl = 0; pl < 2; ++pl) split(rb + pl * APL + (wm * 64 + mb * 32 + fr) * FBK, a[mb][pl]);
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
+    for (int nb = 0; nb < 2; ++nb) {
+      v4u_f b[2][3];
 #pragma unroll
-      for (int pl = 0; pl < 2; ++pl)
-        b[nb][pl] = *(const v4f *)(rb + 2 * APL + pl * BPL + (wn * 64 + nb * 32 + fr) * FBK + fp);
-  };
-#undef TN_FRING
-  // the four k of one fragment half (k 8h + 4c + s of lane half c), in order
-  auto mma = [&](const v4f (&a)[2][2], const v4f (&b)[2][2]) {
+      for (int pl = 0; pl < 2; ++pl) split(rb + 2 * APL + pl * BPL + (wn * 64 + nb * 32 + fr) * FBK, b[pl]);
+      // the six products of total order at most two, smallest first
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      float ar[2], ai[2], br[2], bi[2];
+      for (int pi = 0; pi < 6; ++pi) {
+        const int x = kSplitA[pi], y = kSplitB[pi];
 #pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        ar[x] = a[x][0][s];
-        ai[x] = a[x][1][s];
-        br[x] = b[x][0][s];
-        bi[x] = b[x][1][s];
-      }
-      if (FORM == kForm4M) {
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-          for (int nb = 0; nb < 2; ++nb)
-            acc[mb][nb][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar[mb], br[nb], acc[mb][nb][0], 0, 0, 0);
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-          for (int nb = 0; nb < 2; ++nb)
-            acc[mb][nb][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar[mb], bi[nb], acc[mb][nb][1], 0, 0, 0);
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-          for (int nb = 0; nb < 2; ++nb)
-            acc[mb][nb][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(-ai[mb], bi[nb], acc[mb][nb][0], 0, 0, 0);
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-          for (int nb = 0; nb < 2; ++nb)
-            acc[mb][nb][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ai[mb], br[nb], acc[mb][nb][1], 0, 0, 0);
-      } else {
-        float as[2], bs[2];
-#pragma unroll
-        for (int x = 0; x < 2; ++x) {
-          as[x] = ar[x] + ai[x];
-          bs[x] = br[x] + bi[x];
+        for (int mb = 0; mb < 2; ++mb) {
+          acc[mb][nb][0] = mfma_bf(a[mb][0][x], b[0][y], acc[mb][nb][0]);
+          acc[mb][nb][1] = mfma_bf(a[mb][1][x], b[0][y], acc[mb][nb][1]);
         }
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-          for (int nb = 0; nb < 2; ++nb)
-            acc[mb][nb][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar[mb], br[nb], acc[mb][nb][0], 0, 0, 0);
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-          for (int nb = 0; nb < 2; ++nb)
-            acc[mb][nb][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ai[mb], bi[nb], acc[mb][nb][1], 0, 0, 0);
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-          for (int nb = 0; nb < 2; ++nb)
-            acc[mb][nb][2] = __builtin_amdgcn_mfma_f32_32x32x2f32(as[mb], bs[nb], acc[mb][nb][NACC - 1], 0, 0, 0);
       }
-    }
-  };
-  // one stage: wait for it (the loads of the NSLOT - 2 stages after it may
-  // stay in flight), barrier, request stage kt + NSLOT - 1 into the slot
-  // stage kt - 1 used, then the stage's products.  TWO: the two halves of the
-  // stage's k one after the other (read, multiply); otherwise both halves'
-  // fragments first (one set of 64 registers), then the products.
-  v4f fa[2][2], fb[2][2], ga[2][2], gb[2][2];
-  auto stage = [&](auto slot, int64_t kt) {
-    constexpr int S = decltype(slot)::value;
-    __builtin_amdgcn_s_waitcnt(f_wait_imm((NSLOT - 2) * 2 * (JA + JB)));
-    __builtin_amdgcn_s_barrier();
-    issue(std::integral_constant<int, (S + NSLOT - 1) % NSLOT>(), kt + NSLOT - 1);
-    if constexpr (TWO) {
-      fread(slot, 0, fa, fb);
-      mma(fa, fb);
-      fread(slot, 1, fa, fb);
-      mma(fa, fb);
-    } else {
-      fread(slot, 0, fa, fb);
-      fread(slot, 1, ga, gb);
-      mma(fa, fb);
-      mma(ga, gb);
+#pragma unroll
+      for (int pi = 0; pi < 6; ++pi) {
+        const int x = kSplitA[pi], y = kSplitB[pi];
+        const v4u_f bn = b[1][y] ^ 0x80008000u;
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) {
+          acc[mb][nb][1] = mfma_bf(a[mb][0][x], b[1][y], acc[mb][nb][1]);
+          acc[mb][nb][0] = mfma_bf(a[mb][1][x], bn, acc[mb][nb][0]);
+        }
+      }
     }
     __builtin_amdgcn_sched_barrier(0);
   };
+  // the same stage on the FP32 matrix cores (four real products per complex
+  // one): a split of infinity is not one, so an operand that holds one
+  // (its scale record says) takes this path
+  auto stage32 = [&](auto slot, int64_t kt) {
+    constexpr int S = decltype(slot)::value;
+    const float *rb = TN_FRING(S);
+    __builtin_amdgcn_s_waitcnt(f_wait_imm(0));
+    __builtin_amdgcn_s_barrier();
+    issue(std::integral_constant<int, 1 - S>(), kt + 1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int fp = h ? fp1 : fp0;
+      v4f a[2][2], b[2][2];
+#pragma unroll
+      for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int pl = 0; pl < 2; ++pl) {
+          a[mb][pl] = *(const v4f *)(rb + pl * APL + (wm * 64 + mb * 32 + fr) * FBK + fp);
+          b[mb][pl] = *(const v4f *)(rb + 2 * APL + pl * BPL + (wn * 64 + mb * 32 + fr) * FBK + fp);
+        }
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+          for (int nb = 0; nb < 2; ++nb) {
+            const float ar = a[mb][0][s], ai = a[mb][1][s], br = b[nb][0][s], bi = b[nb][1][s];
+            acc[mb][nb][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar, br, acc[mb][nb][0], 0, 0, 0);
+            acc[mb][nb][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar, bi, acc[mb][nb][1], 0, 0, 0);
+            acc[mb][nb][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(-ai, bi, acc[mb][nb][0], 0, 0, 0);
+            acc[mb][nb][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ai, br, acc[mb][nb][1], 0, 0, 0);
+          }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#undef TN_FRING
   const std::integral_constant<int, 0> s0;
   const std::integral_constant<int, 1> s1;
-  const std::integral_constant<int, 2> s2;
-  const std::integral_constant<int, 3> s3;
   __builtin_amdgcn_s_waitcnt(0);  // nothing else in flight when the ring starts
   issue(s0, 0);
-  if constexpr (NSLOT == 4) {
-    issue(s1, 1);
-    issue(s2, 2);
-  }
   int64_t kt = 0;
-  for (; kt + NSLOT <= nk; kt += NSLOT) {
-    stage(s0, kt);
-    stage(s1, kt + 1);
-    if constexpr (NSLOT == 4) {
-      stage(s2, kt + 2);
-      stage(s3, kt + 3);
+  if (max(sa->maxbits, sb->maxbits) < 0x7f000000u) {
+    for (; kt + 2 <= nk; kt += 2) {
+      stage(s0, kt);
+      stage(s1, kt + 1);
     }
+    if (kt < nk) stage(s0, kt);
+  } else {
+    for (; kt + 2 <= nk; kt += 2) {
+      stage32(s0, kt);
+      stage32(s1, kt + 1);
+    }
+    if (kt < nk) stage32(s0, kt);
   }
-  if (kt < nk) stage(s0, kt);
-  if (NSLOT == 4 && kt + 1 < nk) stage(s1, kt + 1);
-  if (NSLOT == 4 && kt + 2 < nk) stage(s2, kt + 2);
   __builtin_amdgcn_s_waitcnt(0);  // no load may still write LDS when the block ends
 
   const bool partial = g.ksplit > 1;
@@ -288,17 +307,7 @@ __global__ __launch_bounds__(256, (FORM == kForm4M || WMW == 2) ? 2 : 1) void k_
         const int row = wm * 64 + mb * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
         const int col = wn * 64 + nb * 32 + (lane & 31);
         const int64_t cm = m0 + row, cn = n0 + col;
-        float re, im;
-        if (FORM == kForm4M) {
-          re = acc[mb][nb][0][v];
-          im = acc[mb][nb][1][v];
-        } else {
-          const float t1 = acc[mb][nb][0][v], t2 = acc[mb][nb][1][v], t3 = acc[mb][nb][NACC - 1][v];
-          re = t1 - t2;
-          im = t3 - t1 - t2;
-        }
-        re *= post;
-        im *= post;
+        const float re = acc[mb][nb][0][v] * post, im = acc[mb][nb][1][v] * post;
         if (cm < g.M && cn < g.N) {
           if (fo) {
             const uint32_t d = po.at(mb, nb, v);
@@ -337,16 +346,10 @@ hipError_t launch_gemm_f32_planes(hipStream_t st, const GemmArgs &g0, int form, 
   const int64_t blocks = (int64_t)g.tiles_m * g.tiles_n * g.ksplit;
   if (blocks <= 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks, nbatch);
-#define TN_F32P(F, W) hipLaunchKernelGGL((k_cgemm_f32_planes<F, W>), grid, dim3(256), 0, st, g)
-  if (form == kForm4M) {
-    if (g.tile == 0) TN_F32P(kForm4M, 2);
-    else if (g.tile == 1) TN_F32P(kForm4M, 1);
-    else TN_F32P(kForm4M, 4);
-  } else {
-    if (g.tile == 0) TN_F32P(kForm3M, 2);
-    else if (g.tile == 1) TN_F32P(kForm3M, 1);
-    else TN_F32P(kForm3M, 4);
-  }
+#define TN_F32P(W) hipLaunchKernelGGL((k_cgemm_f32_planes<W>), grid, dim3(256), 0, st, g)
+  if (g.tile == 0) TN_F32P(2);
+  else if (g.tile == 1) TN_F32P(1);
+  else TN_F32P(4);
 #undef TN_F32P
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || g.ksplit == 1) return e;
