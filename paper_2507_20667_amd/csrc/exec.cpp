@@ -295,6 +295,14 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
   }
   std::shared_ptr<ExecLayout> Lp = cached_layout(p, ovr, share, conc);
   const ExecLayout &L = *Lp;
+  // the divisors of the plan's own leaves: an override takes a leaf's place
+  // undivided, but a sliced plan's own slices are cut from the divided entries
+  LeafFactor fac = L.fac;
+  if (sum) {
+    fac = LeafFactor();
+    for (int t = 0; t < nv; ++t)
+      if (!sum->ovr[t]) fac.mul(p->leaf_div[t]);
+  }
   const double t_layout = dbg ? ms_since(t_enter) : 0.0;
   Profiler idle_prof;
   Profiler &prof = rs.prof ? *rs.prof : idle_prof;
@@ -653,7 +661,8 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
               if (s && s->dtype != TN_C64_DEVICE)
                 to_c64(*s, n, dst);
               else if (!s)
-                memcpy(dst, p->leaf_host.data() + p->leaf_off[t], sizeof(float2) * n);
+                memcpy(dst, p->leaf_raw_off[t] < 0 ? p->leaf_host.data() + p->leaf_off[t]
+                                                   : p->leaf_raw.data() + p->leaf_raw_off[t], sizeof(float2) * n);
             }
           TN_HIP(hipMemcpyAsync(ovr_base, h, ovr_bytes * Q, hipMemcpyHostToDevice, st),
                  "override upload");
@@ -764,6 +773,8 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
         tl.res = res_out;
         tl.dres = direct ? so->dout + (int64_t)q0 * so->dout_stride : nullptr;
         tl.dres_stride = so ? so->dout_stride : 0;
+        tl.fac_m = fac.m;
+        tl.fac_e = fac.e;
         if (L.n_tree_shared && rcm != RC_READ) {
           tl.nq = 1;
           tl.qw = 1;
@@ -958,7 +969,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       }
       // device results not written by the subtree kernel: from the records
       if (devout && !direct)
-        TN_HIP(launch_results_to_c128(st, res, root_shared ? 0 : 1, Q,
+        TN_HIP(launch_results_to_c128(st, res, root_shared ? 0 : 1, Q, fac.m, fac.e,
                                       so->dout + (int64_t)q0 * so->dout_stride, so->dout_stride),
                "result conversion");
       // slices: their sum, on the device, into the staging buffer
@@ -1018,20 +1029,29 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       if (sum) {
         if (dot_root) {
           const Result &r = *(const Result *)h;
-          const double v[2] = {r.re, r.im};
-          sum->add(v, 1, r.log2s);
+          const double v[2] = {r.re * fac.m, r.im * fac.m};
+          sum->add(v, 1, r.log2s + fac.e);
         } else {
-          sum->add((const double *)h, relems, *(const double *)(h + relems * 16));
+          double *v = (double *)h;
+          for (size_t i = 0; i < 2 * relems; ++i) v[i] *= fac.m;
+          sum->add(v, relems, *(const double *)(h + relems * 16) + fac.e);
         }
       }
       for (int qi = 0; qi < Q && !direct && !devout && !sum; ++qi) {
         const QueryIO &q = qs[q0 + qi];
         const bool keep = (flags & TN_FLAG_KEEP_SCALE) != 0;
         if (dot_root) {
-          const Result &r = hr[root_shared ? 0 : qi];
+          Result r = hr[root_shared ? 0 : qi];
+          r.re *= fac.m;
+          r.im *= fac.m;
+          r.log2s += fac.e;
           if (keep) {
-            write_out(q.out, out_dtype, 0, r.re, r.im);
-            if (q.log2s) *q.log2s = r.log2s;
+            // a mantissa of [0.5, 1) in the larger part again
+            int x = 0;
+            const double big = std::max(std::fabs(r.re), std::fabs(r.im));
+            if (fac.m != 1.0 && big > 0.0 && std::isfinite(big)) std::frexp(big, &x);
+            write_out(q.out, out_dtype, 0, std::ldexp(r.re, -x), std::ldexp(r.im, -x));
+            if (q.log2s) *q.log2s = r.log2s + x;
           } else {
             const int e = (int)r.log2s;
             if (e >= -1022 && e <= 1023) {
@@ -1044,16 +1064,16 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
           }
         } else {
           const int src = root_shared ? 0 : qi;
-          const Slot &s = hs[src];
+          const double log2s = hs[src].log2s + fac.e;
           const float2 *v = hv + (size_t)src * relems;
           for (size_t i = 0; i < relems; ++i) {
+            const double re = v[i].x * fac.m, im = v[i].y * fac.m;
             if (keep)
-              write_out(q.out, out_dtype, i, v[i].x, v[i].y);
+              write_out(q.out, out_dtype, i, re, im);
             else
-              write_out(q.out, out_dtype, i, std::ldexp((double)v[i].x, (int)s.log2s),
-                        std::ldexp((double)v[i].y, (int)s.log2s));
+              write_out(q.out, out_dtype, i, std::ldexp(re, (int)log2s), std::ldexp(im, (int)log2s));
           }
-          if (q.log2s) *q.log2s = keep ? s.log2s : 0.0;
+          if (q.log2s) *q.log2s = keep ? log2s : 0.0;
         }
         if (q.status) *q.status = TN_OK;
       }

@@ -771,20 +771,20 @@ hipError_t scratch_address(int device, void **ptr) {
 }
 
 // Closed-root result records to complex128 values with the scale folded in
-// (as the host does for tn_contract): out[q * stride] = (re, im) * 2^log2s.
-__global__ void k_results_to_c128(const Result *res, int64_t rbs, int nq, double2 *out,
+// (as the host does for tn_contract): out[q * stride] = (re, im) * fm * 2^(log2s + fe).
+__global__ void k_results_to_c128(const Result *res, int64_t rbs, int nq, double fm, int fe, double2 *out,
                                   int64_t stride) {
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= nq) return;
   const Result r = res[q * rbs];
-  const int e = (int)r.log2s;
-  out[(int64_t)q * stride] = make_double2(ldexp(r.re, e), ldexp(r.im, e));
+  const int e = (int)r.log2s + fe;
+  out[(int64_t)q * stride] = make_double2(ldexp(r.re * fm, e), ldexp(r.im * fm, e));
 }
 
-hipError_t launch_results_to_c128(hipStream_t st, const Result *res, int64_t rbs, int nq,
+hipError_t launch_results_to_c128(hipStream_t st, const Result *res, int64_t rbs, int nq, double fm, int fe,
                                   double2 *out, int64_t stride) {
   if (nq <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_results_to_c128, dim3((nq + 255) / 256), dim3(256), 0, st, res, rbs, nq, out,
+  hipLaunchKernelGGL(k_results_to_c128, dim3((nq + 255) / 256), dim3(256), 0, st, res, rbs, nq, fm, fe, out,
                      stride);
   return hipGetLastError();
 }

@@ -980,12 +980,29 @@ tn_status build_plan(tn_plan *p, const tn_plan_desc *d) {
     off += (p->leaf[v].size() + 31) & ~(int64_t)31;  // 256-byte aligned leaves
   }
   p->leaf_host.assign(off, make_float2(0.f, 0.f));
+  p->leaf_div.assign(nv, 1.0);
+  p->leaf_raw_off.assign(nv, -1);
   for (int v = 0; v < nv; ++v) {
     int64_t n = p->leaf[v].size();
     float2 *dst = p->leaf_host.data() + p->leaf_off[v];
     if (d->data_dtype == TN_C128) {
       const double *s = (const double *)d->data[v];
       for (int64_t i = 0; i < n; ++i) dst[i] = make_float2((float)s[2 * i], (float)s[2 * i + 1]);
+      if (n > kStreamMax || (p->flags & TN_PREC_BF16X3)) continue;
+      bool rounds = false;
+      double big = 0.0;
+      for (int64_t i = 0; i < 2 * n; ++i) {
+        rounds = rounds || (double)(float)s[i] != s[i];
+        big = std::max(big, std::fabs(s[i]));
+      }
+      // (sizes for which neither the divisor nor a quotient leaves the normal range)
+      if (!rounds || !(big > 1e-30 && big < 1e30)) continue;
+      p->leaf_div[v] = big;
+      p->leaf_raw_off[v] = (int64_t)p->leaf_raw.size();
+      for (int64_t i = 0; i < n; ++i) {
+        p->leaf_raw.push_back(dst[i]);
+        dst[i] = make_float2((float)(s[2 * i] / big), (float)(s[2 * i + 1] / big));
+      }
     } else {
       memcpy(dst, d->data[v], sizeof(float2) * n);
     }
@@ -2096,6 +2113,8 @@ ExecLayout make_exec_layout(const tn_plan *p, const std::vector<int> &overridden
       ob += (p->leaf[t].size() * 8 + 255) & ~(int64_t)255;
     }
   L.ovr_bytes = ob;
+  for (int t = 0; t < nv; ++t)
+    if (!ovr[t]) L.fac.mul(p->leaf_div[t]);
   for (int v = 0; v < nv; ++v) L.shared[v] = ovr[v] ? 0 : 1;
   for (const Node &n : p->nodes) L.shared[n.id] = L.shared[n.c1] && L.shared[n.c2];
   if (!share)  // plain execution: every intermediate belongs to the query

@@ -193,6 +193,7 @@ tn_status make_sliced_plan(tn_ctx *ctx, const tn_plan *p, std::vector<int64_t> l
   tn_plan *s = nullptr;
   tn_status st = tn_plan_load(ctx, &d, p->flags, &s);
   if (st != TN_OK) return st;
+  s->leaf_div = p->leaf_div;  // the slices are cut from the divided entries
   s->nslices = nslices;
   s->slice_labels = labels;
   s->slice_radix = radix;
@@ -272,6 +273,8 @@ tn_status run_sliced(tn_ctx *ctx, tn_plan *p, int32_t novr, const tn_leaf *ovr, 
     qs[sl].out = dummy.data();
   }
   SliceSum sum;
+  sum.ovr.assign(p->nv, 0);
+  for (int32_t i = 0; i < novr; ++i) sum.ovr[ovr[i].tensor] = 1;
   tn_status rc = run_group(ctx, p, qs, TN_C128, 0, true, rs, nullptr, &sum);
   if (rc != TN_OK) return rc;
   const size_t n = sum.acc.size() / 2;

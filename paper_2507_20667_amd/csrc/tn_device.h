@@ -338,6 +338,8 @@ struct TreeLaunch {
   // as complex128 (scaled to 1) instead of a Result record
   double2 *dres;
   int64_t dres_stride;
+  double fac_m;         // that value is multiplied by fac_m 2^fac_e
+  int32_t fac_e;
   int32_t nq;           // queries in this launch
   int32_t qw;           // queries per workgroup
 };
@@ -426,8 +428,8 @@ hipError_t launch_slice_sum_tensors(hipStream_t st, Operand R, int nq, int64_t n
 hipError_t launch_probe_mfma(hipStream_t st, int prec, bool random, float *out, int blocks, int iters,
                              double *flops);
 // closed-root records of nq queries (query q's at res[q * rbs]) to
-// complex128 values at out[q * stride]
-hipError_t launch_results_to_c128(hipStream_t st, const Result *res, int64_t rbs, int nq,
+// complex128 values, multiplied by fm 2^fe, at out[q * stride]
+hipError_t launch_results_to_c128(hipStream_t st, const Result *res, int64_t rbs, int nq, double fm, int fe,
                                   double2 *out, int64_t stride);
 
 // Tile shape variants of the GEMM (index into a table in the kernel file).

@@ -102,6 +102,19 @@ struct Node {
   int dot_blocks = 1;
 };
 
+// What a result of the stored leaves is multiplied by: m * 2^e (m in [0.5, 1),
+// or 1 with e = 0).
+struct LeafFactor {
+  double m = 1.0;
+  int e = 0;
+  void mul(double f) {
+    if (f == 1.0) return;
+    int x = 0;
+    m = std::frexp(m * f, &x);
+    e += x;
+  }
+};
+
 // Where every tensor of one execution lives.  Intermediates and scratch are
 // either in the shared part (computed once for all queries of a batch) or in
 // the per-query part (one copy per query, `perq_stride` bytes apart).
@@ -110,6 +123,7 @@ struct ExecLayout {
   std::vector<uint8_t> shared;    // per tensor id
   std::vector<int64_t> scr_a, scr_b, partial;  // per node index j (partial: dot blocks or split-k)
   std::vector<int64_t> ovr_off;   // per leaf: offset of its per-query override copy, or -1
+  LeafFactor fac;                 // the divisors of the leaves no override replaces
   int64_t shared_bytes = 0;
   int64_t perq_bytes = 0;
   int64_t ovr_bytes = 0;          // bytes of one query's override block
@@ -314,6 +328,11 @@ struct tn_plan {
   // leaves as complex64 on the host (for per-query copies) and on the device
   std::vector<float2> leaf_host;
   std::vector<int64_t> leaf_off;  // element offset of each leaf in leaf_host / the leaf region
+  // what each leaf's entries were divided by (1: nothing), and the undivided
+  // entries of the divided ones (offset in leaf_raw, or -1)
+  std::vector<double> leaf_div;
+  std::vector<float2> leaf_raw;
+  std::vector<int64_t> leaf_raw_off;
   std::vector<uint8_t> desc_blob;
   int64_t dev_leaf = -1, dev_desc = -1;  // arena offsets
   size_t dev_leaf_bytes = 0, dev_desc_bytes = 0;
@@ -397,6 +416,7 @@ struct ExecRes {
 // their results on the device (FP64, scales aligned) instead of returning
 // them one by one, and adds each chunk's sum here on the host.
 struct SliceSum {
+  std::vector<char> ovr;    // the caller's overridden tensors
   std::vector<double> acc;  // interleaved complex128 mantissas
   double log2s = 0.0;
   bool any = false;
