@@ -326,8 +326,8 @@ def gemm_phase_leg(lib, reps=3):
         for _ in range(reps):
             lib.tn_contract(p, ovr, flags=lib.TN_FLAG_CONCURRENT)
         camp_ms = (time.perf_counter() - t1) / reps * 1e3
-        # the same amplitude through the batched path (one query): the small
-        # vertices run in the subtree kernel instead of one launch each
+        # the same amplitude through the batched path (one query): the shared
+        # part comes from the cache
         lib.tn_contract_batch(ctx.handle, [(p, ovr)], [()])
         t1 = time.perf_counter()
         for _ in range(reps):
@@ -747,8 +747,8 @@ def headline_random30(lib, torch, args):
     perm = stats["permute"]
     perm_gbs = perm["algo_bytes"] / perm["seconds"] / 1e9 if perm["seconds"] else None
     kern_s = sum(v["seconds"] for v in stats.values())
-    # the plain FP32 4M path (tn_contract, one query at a time, one launch per
-    # vertex) on the same network and plan
+    # the plain FP32 4M path (tn_contract, one query at a time) on the same
+    # network and plan
     pp = ctx.plan_load(net.legs, net.dims, net.tensors, plan.partition_of, 8, plan.tree, None, 0)
     ovr0 = amplitude_overrides(net, circ, gx[1])
     lib.tn_contract(pp, ovr0)

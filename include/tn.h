@@ -214,22 +214,27 @@ tn_status tn_plan_slice(tn_plan *plan, int32_t num_labels, const int64_t *labels
                         int64_t max_intermediate, tn_plan **out);
 
 /*
- * Contract the plan's network once (the plain path: one launch sequence per
- * tree vertex, nothing cached).  Leaves listed in `overrides` are replaced
- * for this call only.  Synchronous: returns when `out` (host memory, the
- * product of the output dimensions elements of out_dtype, in output-leg order)
- * holds the result.  With TN_FLAG_KEEP_SCALE in `flags` the mantissa is
- * written and *log2_scale receives the FP64 exponent (value = out *
- * 2^log2_scale); otherwise the scale is folded in and log2_scale, if not
- * NULL, receives 0.
- * TN_FLAG_CONCURRENT: the partitions are independent until the
- * cross-partition tree (§3, eqs. con_par and con_dist), so each partition's
- * subtree runs on a stream of its own, side by side, and the cross-partition
- * vertices run on the context's stream once the partitions they read are
- * done.  Each partition takes memory of its own (the workspace is the sum of
- * the partitions' live peaks plus the reduction path's, not their maximum).
- * The results are bit-identical to the serial order: every vertex computes
- * the same values either way.  Without effect on a plan of one partition.
+ * Contract the plan's network once, every vertex computed in the call (no
+ * shared part is kept).  Small vertices run in the subtree kernels, as for
+ * one query of tn_contract_batch; when the arena has no room for that
+ * layout's workspace and programs, or the plan already keeps programs for 16
+ * sets of overridden leaves, every vertex is a launch of its own.  The
+ * programs stay in the arena, but give way to any other call that needs the
+ * room.  Leaves listed in `overrides` are replaced for this call only.
+ * Synchronous: returns when `out` (host memory, the product of the output
+ * dimensions elements of out_dtype, in output-leg order) holds the result.
+ * With TN_FLAG_KEEP_SCALE in `flags` the mantissa is written and *log2_scale
+ * receives the FP64 exponent (value = out * 2^log2_scale); otherwise the
+ * scale is folded in and log2_scale, if not NULL, receives 0.
+ * TN_FLAG_CONCURRENT: the partitions are independent until the cross-
+ * partition tree (§3, eqs. con_par and con_dist), so each partition's subtree
+ * runs on a stream of its own, side by side, and the cross-partition vertices
+ * run on the context's stream once the partitions they read are done.  Each
+ * partition takes memory of its own (the workspace is the sum of the
+ * partitions' live peaks plus the reduction path's, not their maximum). The
+ * results are bit-identical to the serial order: every vertex computes the
+ * same values either way (where the arena holds both layouts).  Without
+ * effect on a plan of one partition.
  * Errors: TN_E_INVALID_ARG (host-only plan, bad override or flag), TN_E_NOMEM
  * (the arena cannot hold the workspace), TN_E_DEVICE.
  */

@@ -136,7 +136,7 @@ tn_status tn_probe_mfma(tn_ctx *ctx, uint32_t precision, double *tflops) {
   }
   const int blocks = 4 * cus;  // four blocks of four waves per CU: four waves per SIMD
   const size_t bytes = Arena::round((size_t)blocks * 256 * sizeof(float));
-  const int64_t off = ctx->arena.alloc(bytes);
+  const int64_t off = arena_alloc(ctx, bytes, false);
   if (off < 0) {
     set_error("tn_probe_mfma: arena cannot hold %zu bytes", bytes);
     return TN_E_NOMEM;
@@ -195,8 +195,8 @@ tn_status tn_plan_load(tn_ctx *ctx, const tn_plan_desc *desc, uint32_t flags, tn
     p->ctx = ctx;
     p->dev_leaf_bytes = std::max<size_t>(p->leaf_host.size() * sizeof(float2), 256);
     p->dev_desc_bytes = std::max<size_t>(p->desc_blob.size(), 256);
-    p->dev_leaf = ctx->arena.alloc(p->dev_leaf_bytes, true);
-    p->dev_desc = ctx->arena.alloc(p->dev_desc_bytes, true);
+    p->dev_leaf = arena_alloc(ctx, p->dev_leaf_bytes, true);
+    p->dev_desc = arena_alloc(ctx, p->dev_desc_bytes, true);
     if (p->dev_leaf < 0 || p->dev_desc < 0) {
       ctx->arena.release(p->dev_leaf, p->dev_leaf_bytes, true);
       ctx->arena.release(p->dev_desc, p->dev_desc_bytes, true);
@@ -272,6 +272,7 @@ tn_status tn_plan_free(tn_plan *p) {
     ctx->arena.release(p->dev_leaf, p->dev_leaf_bytes, true);
     ctx->arena.release(p->dev_desc, p->dev_desc_bytes, true);
     for (auto &kv : p->layouts) {
+      single_forget(ctx, *kv.second);
       if (kv.second->tree_dev >= 0)
         ctx->arena.release(kv.second->tree_dev, kv.second->tree_dev_bytes, true);
       rcache_drop(ctx, *kv.second);
@@ -311,6 +312,7 @@ tn_status tn_contract(tn_plan *p, int32_t num_overrides, const tn_leaf *override
   q.log2s = log2_scale;
   std::lock_guard<std::mutex> g(p->ctx->exec_mu);
   ExecRes r = ctx_res(p->ctx);
+  r.single = true;
   return run_group(p->ctx, p, {q}, out_dtype, flags, false, r);
 }
 
@@ -433,7 +435,7 @@ tn_status tn_contract_strided_noalloc(tn_plan *p, int32_t num_queries, int32_t n
   {
     std::shared_ptr<ExecLayout> L = cached_layout(p, ovr, true);
     std::lock_guard<std::mutex> g(p->cache_mu);
-    if (L->n_tree_shared + L->n_tree_perq > 0 && L->tree_dev < 0) {
+    if (L->n_tree_shared + L->n_tree_perq > 0 && !programs_kept(ctx, *L)) {
       set_error("tn_contract_strided_noalloc: the plan's subtree programs for these overridden "
                 "leaves are not on the device yet; run tn_contract_strided once with them first");
       return TN_E_INVALID_ARG;

@@ -155,28 +155,111 @@ void rcache_drop(tn_ctx *ctx, ExecLayout &L) {
   L.rc_state = 0;
 }
 
-// First use of a layout: its subtree programs go to the arena (persistent,
-// kept with the plan).  The caller holds the plan's cache_mu.
-tn_status upload_tree_programs(tn_ctx *ctx, const ExecLayout &L, hipStream_t st) {
-  if (L.n_tree_shared + L.n_tree_perq == 0 || L.tree_dev >= 0) return TN_OK;
-  ExecLayout &Lm = const_cast<ExecLayout &>(L);
-  Lm.tree_dev_bytes = std::max<size_t>(L.tree_blob.size(), 256);
-  Lm.tree_dev = ctx->arena.alloc(Lm.tree_dev_bytes, true);
-  if (Lm.tree_dev < 0) {
-    set_error("arena cannot hold the subtree programs (%zu bytes)", Lm.tree_dev_bytes);
-    return TN_E_NOMEM;
+// Subtree programs that only single calls (tn_contract) have used so far stay
+// in the arena for the next one, but give way to any allocation that fails:
+// they take room from no other call.  ctx->singles lists their layouts; a call
+// that runs one pins it.  Both, and the fields they guard, under rcache_mu.
+bool drop_single_programs(tn_ctx *ctx) {
+  std::lock_guard<std::mutex> g(ctx->rcache_mu);
+  bool any = false;
+  for (size_t i = 0; i < ctx->singles.size();) {
+    ExecLayout *e = ctx->singles[i];
+    if (e->single_pins > 0) {
+      ++i;
+      continue;
+    }
+    ctx->arena.release(e->tree_dev, e->tree_dev_bytes, true);
+    e->tree_dev = -1;
+    e->single_prog = false;
+    ctx->singles.erase(ctx->singles.begin() + (long)i);
+    any = true;
   }
-  hipError_t e = hipMemcpyAsync(ctx->arena.base() + Lm.tree_dev, L.tree_blob.data(), L.tree_blob.size(),
-                                hipMemcpyHostToDevice, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (e != hipSuccess) {
-    ctx->arena.release(Lm.tree_dev, Lm.tree_dev_bytes, true);
-    Lm.tree_dev = -1;
+  return any;
+}
+
+// the layout's programs are no longer a single call's alone (rcache_mu held)
+static void single_keep(tn_ctx *ctx, ExecLayout &L) {
+  if (!L.single_prog) return;
+  L.single_prog = false;
+  ctx->singles.erase(std::find(ctx->singles.begin(), ctx->singles.end(), &L));
+}
+
+void single_forget(tn_ctx *ctx, ExecLayout &L) {
+  std::lock_guard<std::mutex> g(ctx->rcache_mu);
+  single_keep(ctx, L);
+}
+
+bool programs_kept(tn_ctx *ctx, const ExecLayout &L) {
+  std::lock_guard<std::mutex> g(ctx->rcache_mu);
+  return L.tree_dev >= 0 && !L.single_prog;
+}
+
+size_t work_capacity(tn_ctx *ctx) {
+  std::lock_guard<std::mutex> g(ctx->rcache_mu);
+  size_t b = ctx->arena.work_capacity();
+  for (const ExecLayout *e : ctx->singles) b += Arena::round(e->tree_dev_bytes);
+  return b;
+}
+
+int64_t arena_alloc(tn_ctx *ctx, size_t bytes, bool persistent) {
+  int64_t off = ctx->arena.alloc(bytes, persistent);
+  if (off < 0 && drop_single_programs(ctx)) off = ctx->arena.alloc(bytes, persistent);
+  return off;
+}
+
+// First use of a layout: its subtree programs go to the arena (persistent,
+// kept with the plan, or, for a single call, until room is short).  The
+// caller holds the plan's cache_mu.  A single call's programs are pinned.
+tn_status upload_tree_programs(tn_ctx *ctx, const ExecLayout &L, hipStream_t st, bool single) {
+  if (L.n_tree_shared + L.n_tree_perq == 0) return TN_OK;
+  ExecLayout &Lm = const_cast<ExecLayout &>(L);
+  {
+    std::lock_guard<std::mutex> g(ctx->rcache_mu);
+    if (single)
+      Lm.single_pins++;
+    else
+      single_keep(ctx, Lm);
+    if (L.tree_dev >= 0) return TN_OK;
+  }
+  const size_t bytes = std::max<size_t>(L.tree_blob.size(), 256);
+  const int64_t off = arena_alloc(ctx, bytes, true);
+  hipError_t e = hipSuccess;
+  if (off >= 0) {
+    e = hipMemcpyAsync(ctx->arena.base() + off, L.tree_blob.data(), L.tree_blob.size(), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+  }
+  std::lock_guard<std::mutex> g(ctx->rcache_mu);
+  if (off < 0 || e != hipSuccess) {
+    if (single) Lm.single_pins--;
+    ctx->arena.release(off, bytes, true);
+    if (off < 0) {
+      set_error("arena cannot hold the subtree programs (%zu bytes)", bytes);
+      return TN_E_NOMEM;
+    }
     set_error("subtree program upload: %s", hipGetErrorString(e));
     return TN_E_DEVICE;
   }
+  Lm.tree_dev = off;
+  Lm.tree_dev_bytes = bytes;
+  if (single) {
+    Lm.single_prog = true;
+    ctx->singles.push_back(&Lm);
+  }
   return TN_OK;
 }
+
+// Pin of a single call on its layout's programs, released when the call ends.
+struct SinglePin {
+  tn_ctx *ctx = nullptr;
+  ExecLayout *L = nullptr;
+  void release() {
+    if (!L) return;
+    std::lock_guard<std::mutex> g(ctx->rcache_mu);
+    L->single_pins--;
+    L = nullptr;
+  }
+  ~SinglePin() { release(); }
+};
 
 // Device bytes of one execution chunk of Q queries (carved in run_group).
 size_t group_workspace_bytes(const tn_plan *p, const ExecLayout &L, int Q) {
@@ -293,7 +376,38 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
     tn_status cs = ensure_part_streams(ctx, p->K);
     if (cs != TN_OK) return cs;
   }
-  std::shared_ptr<ExecLayout> Lp = cached_layout(p, ovr, share, conc);
+  std::shared_ptr<ExecLayout> Lp;
+  SinglePin pin;
+  if (rs.single) {
+    // small vertices in the subtree kernels where the arena has room for their
+    // programs and this layout's workspace (concurrent partitions: in the
+    // layout with a region per partition), else one launch per vertex
+    Lp = cached_layout(p, ovr, !conc, conc, true, kSingleLayouts);
+    if (Lp && Lp->n_tree_shared + Lp->n_tree_perq > 0) {
+      std::lock_guard<std::mutex> g(p->cache_mu);
+      const tn_status us = upload_tree_programs(ctx, *Lp, rs.st, true);
+      if (us == TN_OK) {
+        pin.ctx = ctx;
+        pin.L = Lp.get();
+        const size_t need = group_workspace_bytes(p, *Lp, 1) + 8192;
+        if (ctx->arena.largest_free() < need && !(drop_single_programs(ctx) && ctx->arena.largest_free() >= need))
+          Lp = nullptr;
+      } else if (us == TN_E_NOMEM) {
+        Lp = nullptr;
+      } else {
+        return us;
+      }
+    }
+    if (Lp) {
+      share = !conc;
+    } else {
+      pin.release();
+      drop_single_programs(ctx);
+      Lp = cached_layout(p, ovr, false, conc, false);
+    }
+  } else {
+    Lp = cached_layout(p, ovr, share, conc);
+  }
   const ExecLayout &L = *Lp;
   // the divisors of the plan's own leaves: an override takes a leaf's place
   // undivided, but a sliced plan's own slices are cut from the divided entries
@@ -313,7 +427,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
   const size_t ovr_bytes = (size_t)L.ovr_bytes;
   const bool trees = L.n_tree_shared + L.n_tree_perq > 0;
   std::unique_lock<std::mutex> upload_lock(p->cache_mu);
-  {
+  if (!rs.single) {
     const tn_status us = upload_tree_programs(ctx, L, st);
     if (us != TN_OK) return us;
   }
@@ -391,6 +505,8 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
     }
   } else {
     size_t avail = ctx->arena.largest_free();
+    if (avail < shared_fixed + (per_query + 1024) * qs.size() + 4096 && drop_single_programs(ctx))
+      avail = ctx->arena.largest_free();
     if (avail < shared_fixed + per_query + 4096) {
       set_error("arena too small: need %zu bytes for one query, largest free block %zu",
                 shared_fixed + per_query + 4096, avail);
@@ -458,7 +574,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       if (E.layout != &L || E.Q != Q || E.ws_bytes != total) {
         hipStreamSynchronize(st);
         release_graph(ctx, E);
-        E.ws = ctx->arena.alloc(total, true);
+        E.ws = arena_alloc(ctx, total, true);
         E.ws_bytes = total;
         if (E.ws < 0 || hipHostMalloc(&E.pinned, rb_bytes, hipHostMallocDefault) != hipSuccess) {
           if (E.ws >= 0 && !E.pinned) (void)hipGetLastError();
@@ -473,7 +589,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       }
     }
     const bool own_ws = rs.ws < 0 && !rs.ext_ws && !gmode;
-    int64_t ws = rs.ext_ws ? 0 : gmode ? p->graph->ws : own_ws ? ctx->arena.alloc(total) : rs.ws;
+    int64_t ws = rs.ext_ws ? 0 : gmode ? p->graph->ws : own_ws ? arena_alloc(ctx, total, false) : rs.ws;
     // the free space measured above may have been taken meanwhile (serve
     // workers share the arena): fewer queries per chunk
     while (ws < 0 && own_ws && Q > 1) {
@@ -498,7 +614,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
     // result is then one shared computation), and never filled by a call
     // that must not allocate
     int rcm = RC_NONE;
-    if (share && !gmode && !L.shared[p->root] && ctx->rcache_budget > 0) {
+    if (share && !rs.single && !gmode && !L.shared[p->root] && ctx->rcache_budget > 0) {
       bool any = L.n_tree_shared > 0;
       for (size_t k = 0; k < p->order.size() && !any; ++k) {
         const int id = p->nodes[p->order[k]].id;

@@ -972,7 +972,14 @@ tn_status build_plan(tn_plan *p, const tn_plan_desc *d) {
     }
   }
 
-  // leaves as complex64 (rounded once from complex128 input)
+  // Leaves as complex64, rounded once from complex128 input.  A small leaf (a
+  // gate) that rounding would change is divided by its largest component
+  // first, and every result is multiplied by the product of these divisors
+  // (FP64): a circuit repeats its gates, so one gate's rounding error enters
+  // as often as the gate does, always with the same sign (103 Hadamard gates
+  // of entries 1/sqrt 2: 2.1e-6 of the amplitude, against 1.8e-7 with the
+  // entries stored as 1).  A BF16x3 plan, whose products keep 16 bits, takes
+  // its leaves as they are.
   p->leaf_off.resize(nv);
   int64_t off = 0;
   for (int v = 0; v < nv; ++v) {
@@ -1650,6 +1657,10 @@ static void build_tree_programs(const tn_plan *p, ExecLayout &L, const std::vect
   }
   L.lds_perq = tree_lds_bytes(L.tree_qw, max_scale_q, max_sh_q, max_pq_q, L.tree_wave);
   L.lds_perq1 = tree_lds_bytes(1, max_scale_q, max_sh_q, max_pq_q);
+  if (L.lds_perq1 > lim) {
+    L.tree_error = true;
+    return;
+  }
   // blob
   auto put = [&](const void *src, size_t bytes) {
     size_t off = (L.tree_blob.size() + 255) & ~(size_t)255;
@@ -2119,10 +2130,7 @@ ExecLayout make_exec_layout(const tn_plan *p, const std::vector<int> &overridden
   for (const Node &n : p->nodes) L.shared[n.id] = L.shared[n.c1] && L.shared[n.c2];
   if (!share)  // plain execution: every intermediate belongs to the query
     for (int v = nv; v < nn; ++v) L.shared[v] = 0;
-  const bool trees = allow_trees && share && !p->tree_roots.empty();
-  auto is_root = [&](int v) {
-    return std::find(p->tree_roots.begin(), p->tree_roots.end(), v) != p->tree_roots.end();
-  };
+  const bool trees = allow_trees && !p->tree_roots.empty();
   Packer pk[2];  // 0: per-query, 1: shared
   std::vector<Packer> pkp(conc ? p->K : 0);  // concurrent partitions
   auto packer_of = [&](const Node &n) -> Packer & {
@@ -2161,7 +2169,9 @@ ExecLayout make_exec_layout(const tn_plan *p, const std::vector<int> &overridden
     // of the workspace (their whole lifetime), which keeps each query's LDS
     // small enough for more queries per CU
     L.spill.clear();
-    const int64_t spill_at = p->knobs.spill;  // the plan's choice (tuning table, TN_TREE_SPILL)
+    // (the plan's choice: tuning table, TN_TREE_SPILL; a layout without a
+    // shared part runs one query, alone in its CU)
+    const int64_t spill_at = share ? p->knobs.spill : kTreeMaxElems + 1;
     for (int r : p->tree_roots) {
       if (L.shared[r]) continue;
       std::vector<int> stack{p->nodes[r - nv].c1, p->nodes[r - nv].c2};
@@ -2221,7 +2231,6 @@ ExecLayout make_exec_layout(const tn_plan *p, const std::vector<int> &overridden
       }
     }
   }
-  (void)is_root;
   L.peak_intermediate = pk[0].peak();
   L.perq_bytes = pk[0].peak();
   L.shared_bytes = pk[1].peak();
@@ -2256,14 +2265,15 @@ ExecLayout make_exec_layout(const tn_plan *p, const std::vector<int> &overridden
   return L;
 }
 
-std::shared_ptr<ExecLayout> cached_layout(tn_plan *p, const std::vector<int> &overridden,
-                                          bool share, bool conc) {
+std::shared_ptr<ExecLayout> cached_layout(tn_plan *p, const std::vector<int> &overridden, bool share,
+                                          bool conc, bool trees, size_t max_new) {
   std::lock_guard<std::mutex> g(p->cache_mu);
   std::vector<int> key = overridden;
-  key.push_back(share ? -1 : conc ? -3 : -2);
+  key.push_back(share ? -1 : conc ? (trees ? -3 : -4) : -2);
   auto it = p->layouts.find(key);
   if (it != p->layouts.end()) return it->second;
-  auto L = std::make_shared<ExecLayout>(make_exec_layout(p, overridden, share, true, conc));
+  if (trees && p->layouts.size() >= max_new) return nullptr;
+  auto L = std::make_shared<ExecLayout>(make_exec_layout(p, overridden, share, trees, conc));
   if (L->tree_error)  // fall back to one launch per vertex
     L = std::make_shared<ExecLayout>(make_exec_layout(p, overridden, share, false, conc));
   if (getenv("TN_DEBUG"))

@@ -71,9 +71,9 @@ class DeviceBackend : public sched::Backend {
       if (is[t]) ovr.push_back(t);
     return cached_layout(p, ovr, true);
   }
-  int64_t reserve(size_t bytes) override { return ctx_->arena.alloc(bytes); }
+  int64_t reserve(size_t bytes) override { return arena_alloc(ctx_, bytes, false); }
   void release(int64_t off, size_t bytes) override { ctx_->arena.release(off, bytes); }
-  size_t capacity() override { return ctx_->arena.work_capacity(); }
+  size_t capacity() override { return work_capacity(ctx_); }
   uint64_t releases() override { return ctx_->arena.releases(); }
 
   void *worker_begin() override {
@@ -230,8 +230,8 @@ tn_status tn_serve_submit(tn_ctx *ctx, const tn_query *query, uint64_t *ticket) 
   // subtree programs) already in the arena.
   {
     std::vector<sched::Req *> one{r};
-    if (p->nslices == 0 &&
-        DeviceBackend::request_bytes(p, one, 1, ctx->arena.work_capacity()) > ctx->arena.work_capacity()) {
+    const size_t room = work_capacity(ctx);
+    if (p->nslices == 0 && DeviceBackend::request_bytes(p, one, 1, room) > room) {
       std::lock_guard<std::mutex> g(p->slice_mu);
       for (int64_t target = p->largest / 2; !p->auto_sliced && target >= 1; target /= 2) {
         tn_plan *sl = nullptr;
@@ -242,7 +242,7 @@ tn_status tn_serve_submit(tn_ctx *ctx, const tn_query *query, uint64_t *ticket) 
           std::lock_guard<std::mutex> gl(sl->cache_mu);
           (void)upload_tree_programs(ctx, *L, ctx->stream);
         }
-        const size_t cap = ctx->arena.work_capacity();
+        const size_t cap = work_capacity(ctx);
         if (DeviceBackend::request_bytes(sl, one, 1, cap) <= cap) {
           p->auto_sliced = sl;
         } else {

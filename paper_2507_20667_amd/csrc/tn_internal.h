@@ -160,6 +160,9 @@ struct ExecLayout {
   int rc_state = 0;        // 0 empty, 1 being filled by one call, 2 valid
   int rc_pins = 0;         // calls reading or filling it (not evictable)
   uint64_t rc_used = 0;    // last use (LRU clock)
+  // programs uploaded by single calls only (also guarded by rcache_mu)
+  bool single_prog = false;
+  int single_pins = 0;
 };
 
 struct tn_plan_impl;
@@ -290,6 +293,8 @@ struct tn_ctx {
   std::vector<tn::ExecLayout *> rcache;
   size_t rcache_bytes = 0, rcache_budget = 0;
   uint64_t rcache_clock = 0;
+  // layouts whose subtree programs give way to a failing allocation
+  std::vector<tn::ExecLayout *> singles;
 };
 
 namespace tn {
@@ -370,8 +375,12 @@ namespace tn {
 tn_status build_plan(tn_plan *p, const tn_plan_desc *d);
 ExecLayout make_exec_layout(const tn_plan *p, const std::vector<int> &overridden, bool share,
                             bool allow_trees, bool conc = false);
-std::shared_ptr<ExecLayout> cached_layout(tn_plan *p, const std::vector<int> &overridden,
-                                          bool share, bool conc = false);
+// the plan's layout for this set of overridden leaves, made on first use;
+// trees: small vertices in the subtree kernels (a layout that is not shared
+// and not concurrent has none); nullptr instead of a new layout with subtrees
+// when the plan already keeps max_new
+std::shared_ptr<ExecLayout> cached_layout(tn_plan *p, const std::vector<int> &overridden, bool share,
+                                          bool conc = false, bool trees = true, size_t max_new = SIZE_MAX);
 const char *last_error();
 
 // exec.cpp
@@ -411,7 +420,13 @@ struct ExecRes {
   // and size; the whole group must fit it
   uint8_t *ext_ws = nullptr;
   size_t ext_ws_bytes = 0;
+  // a single call (tn_contract): no shared part is kept for later calls, and
+  // one launch per vertex serves when the arena has no room for the layout
+  // with subtrees
+  bool single = false;
 };
+// a single call makes no new layout with subtrees when the plan keeps this many
+constexpr size_t kSingleLayouts = 16;
 // The queries of one group are the slices of a sliced plan: run_group adds
 // their results on the device (FP64, scales aligned) instead of returning
 // them one by one, and adds each chunk's sum here on the host.
@@ -444,7 +459,16 @@ tn_status make_sliced_plan(tn_ctx *ctx, const tn_plan *p, std::vector<int64_t> l
 tn_status run_sliced(tn_ctx *ctx, tn_plan *p, int32_t novr, const tn_leaf *ovr, void *out,
                      tn_dtype out_dtype, double *log2_scale, uint32_t flags, ExecRes &rs);
 size_t group_workspace_bytes(const tn_plan *p, const ExecLayout &L, int Q);
-tn_status upload_tree_programs(tn_ctx *ctx, const ExecLayout &L, hipStream_t st);
+tn_status upload_tree_programs(tn_ctx *ctx, const ExecLayout &L, hipStream_t st, bool single = false);
+// arena allocation; subtree programs only single calls use give way to it
+int64_t arena_alloc(tn_ctx *ctx, size_t bytes, bool persistent);
+bool drop_single_programs(tn_ctx *ctx);
+// what transient allocations could ever hold: all but the persistent blocks
+// that do not give way
+size_t work_capacity(tn_ctx *ctx);
+void single_forget(tn_ctx *ctx, ExecLayout &L);  // its plan is freed
+// whether the layout's programs are on the device to stay
+bool programs_kept(tn_ctx *ctx, const ExecLayout &L);
 size_t result_elems(const tn_plan *p);
 // drops a captured graph with its workspace and pinned buffer (stream idle)
 void release_graph(tn_ctx *ctx, GraphEntry &g);
