@@ -961,6 +961,31 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
                                                    outop(n.id), nb);
                             }),
                  "stream contraction");
+        } else if (n.kind == NK_GEMM && n.small) {
+          const Operand A = operand(n.ga), B = operand(n.gb);
+          const OutOperand C = outop(n.id);
+          SmallGemm g;
+          g.A = A.p;
+          g.B = B.p;
+          g.C = C.p;
+          g.sa = A.slot;
+          g.sb = B.slot;
+          g.sc = C.slot;
+          g.tab = (const int32_t *)(desc_base + n.tab_off);
+          g.abs = A.bs;
+          g.bbs = B.bs;
+          g.cbs = C.bs;
+          g.sabs = A.sbs;
+          g.sbbs = B.sbs;
+          g.scbs = C.sbs;
+          g.M = (int32_t)n.M;
+          g.N = (int32_t)n.N;
+          g.K = (int32_t)n.K;
+          const int prec = (p->flags & TN_PREC_BF16X3) ? kPrecBF16x3 : kPrecFP32;
+          const int form = (p->flags & TN_FORM_3M) ? kForm3M : kForm4M;
+          TN_HIP(prof.timed(xs, TN_KCLASS_GEMM_SMALL, nodeb, wflops,
+                            [&] { return launch_gemm_small(xs, g, prec, form, nb); }),
+                 "complex GEMM");
         } else if (n.kind == NK_GEMM) {
           Operand A = operand(n.ga), B = operand(n.gb);
           uint8_t *pbase = sh ? shared_base : perq_base;

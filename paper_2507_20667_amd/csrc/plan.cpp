@@ -338,6 +338,38 @@ static void interleave_rows(std::vector<int64_t> &FB, int npc, const Layout &B, 
   FB = out;
 }
 
+// Whether a GEMM vertex runs on k_cgemm_small: its multiply-adds cost the
+// vector units less than the launches of two permutations and a matrix core
+// kernel.  k up to 15 (the kernels on k-tiled planes need a multiple of 16):
+// 1024 x 2048 at k = 8 takes 15 us against 20 + 21 us of permutations, 64 x
+// 128 at k = 4 4.4 us against 7.6 + 6.5.  Longer k, up to 128 (8 rounds),
+// while the products are few (2^21: a block of each CU 8 k each, 16 x 64 at k = 64 8
+// us against 14 + 15); beyond that the matrix cores win.  Operands are
+// limited to 2^18 entries, which the L2 holds.
+static bool small_gemm(int64_t M, int64_t N, int64_t K) {
+  if (M > 1 << 15 || N > 1 << 15 || M * K > 1 << 18 || N * K > 1 << 18) return false;
+  return K < 16 || (K <= 128 && M * N * K <= 1 << 21);
+}
+
+// Offsets of the index space of `legs` (row-major) in a tensor.
+static bool put_offsets(const Layout &X, const std::vector<int64_t> &legs, std::vector<int32_t> &tab) {
+  const std::vector<int64_t> st = X.strides();
+  std::vector<int64_t> off(1, 0);
+  for (int64_t l : legs) {
+    const int i = X.find(l);
+    std::vector<int64_t> o2;
+    o2.reserve(off.size() * X.dim[i]);
+    for (int64_t o : off)
+      for (int64_t d = 0; d < X.dim[i]; ++d) o2.push_back(o + d * st[i]);
+    off.swap(o2);
+  }
+  for (int64_t o : off) {
+    if (o > INT32_MAX) return false;
+    tab.push_back((int32_t)o);
+  }
+  return true;
+}
+
 static tn_status schedule_gemm(tn_plan *p, Node &n, const Layout &A, const Layout &B,
                                const std::set<int64_t> &pcon, const std::set<int64_t> &pcon2) {
   n.kind = NK_GEMM;
@@ -411,6 +443,21 @@ static tn_status schedule_gemm(tn_plan *p, Node &n, const Layout &A, const Layou
   for (int64_t l : FA) n.M *= A.dim[A.find(l)];
   for (int64_t l : FB) n.N *= B.dim[B.find(l)];
   for (int64_t l : sorder) n.K *= A.dim[A.find(l)];
+  if (small_gemm(n.M, n.N, n.K)) {
+    std::vector<int32_t> tab;
+    if (put_offsets(A, FA, tab) && put_offsets(B, FB, tab) && put_offsets(A, sorder, tab) &&
+        put_offsets(B, sorder, tab)) {
+      n.small = true;
+      n.planes = 0;
+      n.tab_off = p->desc_blob.size();
+      p->desc_blob.resize((n.tab_off + tab.size() * 4 + 15) & ~(size_t)15);
+      memcpy(p->desc_blob.data() + n.tab_off, tab.data(), tab.size() * 4);
+      std::vector<int64_t> out = FA;
+      out.insert(out.end(), FB.begin(), FB.end());
+      n.out = make_layout(out, A, B);
+      return TN_OK;
+    }
+  }
   if (permA) {
     std::vector<int64_t> lab = FA;
     lab.insert(lab.end(), sorder.begin(), sorder.end());
@@ -596,6 +643,21 @@ static bool node_in_bounds(const tn_plan *p, const Node &n, const std::vector<La
   if (n.kind == NK_GEMM) {
     if (!perm_ok(n.pa, lay[n.ga]) || !perm_ok(n.pb, lay[n.gb])) return false;
     const int64_t sa = lay[n.ga].size(), sb = lay[n.gb].size();
+    if (n.small) {
+      const int32_t *t = (const int32_t *)(blob + n.tab_off);
+      if (n.tab_off + 4 * (size_t)(n.M + n.N + 2 * n.K) > p->desc_blob.size()) return false;
+      auto top = [&](int64_t cnt) {
+        int64_t m = 0;
+        for (int64_t i = 0; i < cnt; ++i) {
+          if (t[i] < 0) return INT64_MAX / 4;
+          m = std::max<int64_t>(m, t[i]);
+        }
+        t += cnt;
+        return m;
+      };
+      const int64_t row = top(n.M), col = top(n.N), ka = top(n.K), kb = top(n.K);
+      return n.M * n.K == sa && n.K * n.N == sb && row + ka < sa && col + kb < sb && n.M * n.N == n.out.size();
+    }
     const int64_t ea = n.opA == 0 ? (n.M - 1) * n.lda + n.K - 1 : (n.K - 1) * n.lda + n.M - 1;
     const int64_t eb = n.opB == 0 ? (n.K - 1) * n.ldb + n.N - 1 : (n.N - 1) * n.ldb + n.K - 1;
     const int64_t ec = (n.M - 1) * n.ldc + n.N - 1;

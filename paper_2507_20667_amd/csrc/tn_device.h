@@ -151,6 +151,22 @@ struct PlaneOut {
   }
 };
 
+// A GEMM that reads its operands in place (k_cgemm_small): entry (m, k) of A at
+// A[row[m] + ka[k]], entry (k, n) of B at B[col[n] + kb[k]], C row-major M x N.
+// tab: row (M), col (N), ka (K), kb (K), one after the other.
+struct SmallGemm {
+  const float2 *A;
+  const float2 *B;
+  float2 *C;
+  const Slot *sa;
+  const Slot *sb;
+  Slot *sc;
+  const int32_t *tab;
+  int64_t abs, bbs, cbs;
+  int64_t sabs, sbbs, scbs;
+  int32_t M, N, K;
+};
+
 // Block -> (k chunk ks, output tile t) of a GEMM launch.  Blocks go to the
 // eight XCDs round robin (block b on XCD b % 8), each XCD with its own L2.
 // Without k chunks each XCD takes a contiguous run of tiles, M-tiles
@@ -353,6 +369,15 @@ __device__ __forceinline__ int tn_scale_exp(uint32_t bits) {
   return bits == 0u ? 0 : e;
 }
 
+// Folds a block's or wave's maximum (a non-negative float, given by one lane)
+// into a scale record.  Every block of a launch meets the same record, and
+// atomics on one address go one after the other (a few ns each: 8192 waves
+// spent 20 us there), so one that cannot raise it only reads it.
+__device__ __forceinline__ void slot_max(uint32_t *maxbits, float v) {
+  const uint32_t b = __float_as_uint(v);
+  if (b > __hip_atomic_load(maxbits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(maxbits, b);
+}
+
 // Split x = h + l with h = bf16(x) and l = bf16(x - h), both rounded to nearest
 // even (finite inputs; the hardware conversion): the two terms carry 16
 // significant bits of x.
@@ -389,6 +414,7 @@ hipError_t launch_permute(hipStream_t st, const PermDesc *d_desc, const PermDesc
                           int64_t sbs = 0, KTile kt = KTile{0, 0, -1, 0});
 hipError_t launch_gemm(hipStream_t st, const GemmArgs &g, int prec, int form, int variant,
                        int nbatch);
+hipError_t launch_gemm_small(hipStream_t st, const SmallGemm &g, int prec, int form, int nbatch);
 hipError_t launch_gemm_bf16x3(hipStream_t st, const GemmArgs &g, int form, int nbatch);
 hipError_t launch_gemm_f32_planes(hipStream_t st, const GemmArgs &g, int form, int nbatch);
 int gemm_planes_tile_m(int v);

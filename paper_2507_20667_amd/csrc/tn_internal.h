@@ -96,6 +96,9 @@ struct Node {
   int fo_nbits = 0, fo_mbits = 0;
   int64_t fo_plane = 0;
   uint8_t fo_d[48] = {0};
+  // read in place through offset tables, no permutation (k_cgemm_small)
+  bool small = false;
+  size_t tab_off = 0;
   // NK_DOT
   size_t ddesc_off = 0;
   int64_t nelem = 0;
