@@ -307,7 +307,7 @@ __global__ __launch_bounds__(256) void k_cgemm_bf16x3(GemmArgs g) {
   if (!partial) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    if (lane == 0) atomicMax(&sc->maxbits, __float_as_uint(mx));
+    if (lane == 0) slot_max(&sc->maxbits, mx);
   }
 }
 
@@ -559,7 +559,7 @@ __global__ __launch_bounds__(256, FORM == kForm3M ? 1 : 2) void k_cgemm_bf16x3_d
   if (!partial) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    if (lane == 0) atomicMax(&sc->maxbits, __float_as_uint(mx));
+    if (lane == 0) slot_max(&sc->maxbits, mx);
   }
 }
 
@@ -810,7 +810,7 @@ __global__ __launch_bounds__(512, 1) void k_cgemm_bf16x3_pp(GemmArgs g) {
   if (!partial) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    if (lane == 0) atomicMax(&sc->maxbits, __float_as_uint(mx));
+    if (lane == 0) slot_max(&sc->maxbits, mx);
   }
 }
 

@@ -322,7 +322,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
   if (!partial) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    if (lane == 0) atomicMax(&sc->maxbits, __float_as_uint(mx));
+    if (lane == 0) slot_max(&sc->maxbits, mx);
   }
 }
 

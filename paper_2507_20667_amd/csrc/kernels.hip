@@ -22,7 +22,7 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 __device__ __forceinline__ void wave_atomic_max(uint32_t *p, float v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-  if ((threadIdx.x & 63) == 0) atomicMax(p, __float_as_uint(v));
+  if ((threadIdx.x & 63) == 0) slot_max(p, v);
 }
 
 __device__ __forceinline__ float absmax2(float2 v) { return fmaxf(fabsf(v.x), fabsf(v.y)); }
