@@ -10,6 +10,7 @@
 // Every kernel reads the scale records of its operands, multiplies by the
 // power of two that brings their maxima to [1, 2), writes the scale of its
 // output and contributes to the output's running max (Slot).
+#include <cstring>
 #include <mutex>
 
 #include "tn_device.h"
@@ -254,140 +255,183 @@ __global__ __launch_bounds__(256) void k_perm_generic(const PermDesc *__restrict
 }
 
 // Tiled bit permutation.  With every extent a power of two the permutation
-// moves index bits: output bit j takes input bit inbit[j].  A tile spans the
-// lowest input bits and the input bits that feed the lowest output bits
-// (nu <= 10 bits, <= 1024 complex values = 8 KiB of LDS); the remaining
-// "outer" bits select the tile.  Loads run along the input's low bits and
-// stores along the output's low bits, so both sides move whole 256-byte runs.
-// A workgroup moves two tiles per round (3.65 -> 4.02 TB/s on the 30-qubit
-// operands against one).
+// (and the k-tiled order of planes) moves index bits: output bit j takes input
+// bit src[j].  A tile spans kTileBits bits, among them the lowest input bits
+// and those that feed the lowest output bits; the other, outer, bits select
+// the tile.  Loads run along the input's low bits and stores along the
+// output's, so both sides move runs of 128 or 256 bytes.  A thread moves
+// pairs: two entries along input bit 0 in, two along output bit 0 out.
+//
+// The bound is HBM traffic, and for small operands the latency of one round
+// trip: every bit's stride comes ready in the kernel's arguments, read with
+// fixed indices (a loop over bit numbers instead cost a chain of scalar loads
+// of 8 us whatever the size).  A workgroup has two tiles' loads in flight.
+// Into float planes: 2^16 entries 12.4 -> 4.5 us, 2^21 24.4 -> 9 us.
+constexpr int kTileBits = 10;
+constexpr int kTileMaxOuter = 38;
 struct BitTile {
-  int32_t nu;          // tile bits
-  int32_t nouter;      // outer bits
-  int32_t u_in[12];    // tile bit k -> input bit
-  int32_t u_out[12];   // tile bit k -> output bit
-  int32_t g_to_k[12];  // output-ordered tile bit -> tile bit
-  int32_t o_in[48];    // outer bit -> input bit
-  int32_t o_out[48];   // outer bit -> output bit
+  int32_t nouter;
+  int32_t src[kTileBits];       // output-ordered tile bit -> entry of the tile
+  int64_t in_s[kTileBits];      // tile bit (input order) -> input stride
+  int64_t out_s[kTileBits];     // tile bit (output order) -> output stride
+  int64_t o_in[kTileMaxOuter + 2], o_out[kTileMaxOuter + 2];  // outer bits, zero past nouter
 };
+
+// an entry's place in LDS: the low five bits rotate with the high ones, so
+// lanes that vary over either meet distinct banks
+__device__ __forceinline__ int tile_at(int e) { return e ^ (e >> 5); }
+
+// the two consecutive entries idx, idx + 1 of the output
+template <int NP>
+__device__ __forceinline__ void perm_emit2(void *out, int64_t pstride, int64_t idx, float2 v, float2 w, float fs) {
+  if (NP == 0) {
+    ((float2 *)out)[idx] = v;
+    ((float2 *)out)[idx + 1] = w;
+  } else if (NP == 2) {
+    float *o = (float *)out;
+    *(float2 *)(o + idx) = make_float2(v.x * fs, w.x * fs);
+    *(float2 *)(o + pstride + idx) = make_float2(v.y * fs, w.y * fs);
+  } else {
+    uint16_t *o = (uint16_t *)out;
+    uint32_t h, l;
+    v.x *= fs;
+    v.y *= fs;
+    w.x *= fs;
+    w.y *= fs;
+    tn_split_bf16x2(v.x, w.x, h, l);
+    *(uint32_t *)(o + idx) = h;
+    *(uint32_t *)(o + pstride + idx) = l;
+    tn_split_bf16x2(v.y, w.y, h, l);
+    *(uint32_t *)(o + 2 * pstride + idx) = h;
+    *(uint32_t *)(o + 3 * pstride + idx) = l;
+    if (NP == 6) {
+      tn_split_bf16x2(v.x + v.y, w.x + w.y, h, l);
+      *(uint32_t *)(o + 4 * pstride + idx) = h;
+      *(uint32_t *)(o + 5 * pstride + idx) = l;
+    }
+  }
+}
 
 template <int NP>
 __global__ __launch_bounds__(256) void k_perm_tiled(BitTile t, const float2 *in, int64_t ibs,
                                                     void *out, int64_t obs, int64_t pstride,
-                                                    const Slot *sl, int64_t sbs, KTile kt) {
-  // two tiles per round: the loads of both are in flight before the barrier,
-  // twice the bytes in flight per workgroup of one round trip
-  __shared__ float2 tile[2][1024 + 32];
+                                                    const Slot *sl, int64_t sbs) {
+  __shared__ float2 tile[2][1 << kTileBits];
   const int tid = threadIdx.x;
   const int q = blockIdx.y;
   in += q * ibs;
   void *ob = perm_out_base<NP>(out, obs, q);
   const float fs = perm_scale<NP>(sl, sbs, q);
-  const int nt = 1 << t.nu;
-  // per-thread offsets of the tile elements this thread loads and stores
-  int64_t lin[4], lout[4];
-  int le[4], ge[4];
-  int cnt = 0;
-  for (int e = tid; e < nt; e += 256, ++cnt) {
-    int64_t a = 0;
-    for (int k = 0; k < t.nu; ++k)
-      if ((e >> k) & 1) a += (int64_t)1 << t.u_in[k];
-    lin[cnt] = a;
-    le[cnt] = e + (e >> 5);
-    // output-ordered index g = e: g bit i corresponds to tile bit g_to_k[i]
-    int src = 0;
-    int64_t b = 0;
-    for (int i = 0; i < t.nu; ++i)
-      if ((e >> i) & 1) {
-        const int k = t.g_to_k[i];
-        src |= 1 << k;
-        b += (int64_t)1 << t.u_out[k];
-      }
-    lout[cnt] = b;
-    ge[cnt] = src + (src >> 5);
-  }
+  // this thread's pairs: tile bits 1-8 from its number, bit 9 from c
+  int64_t lin = 0, lout = 0;
+  int src = 0;
+#pragma unroll
+  for (int k = 1; k < kTileBits - 1; ++k)
+    if ((tid >> (k - 1)) & 1) {
+      lin += t.in_s[k];
+      lout += t.out_s[k];
+      src |= t.src[k];
+    }
+  const int64_t in9 = t.in_s[kTileBits - 1], out9 = t.out_s[kTileBits - 1];
+  const int src0 = t.src[0], src9 = t.src[kTileBits - 1];
   const int64_t ntiles = (int64_t)1 << t.nouter;
   auto base = [&](int64_t w, int64_t &bin, int64_t &bout) {
     bin = 0;
     bout = 0;
-    for (int k = 0; k < t.nouter; ++k)
-      if ((w >> k) & 1) {
-        bin += (int64_t)1 << t.o_in[k];
-        bout += (int64_t)1 << t.o_out[k];
+    for (int k0 = 0; k0 < t.nouter; k0 += 8) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int64_t on = -((w >> (k0 + k)) & 1);
+        bin += t.o_in[k0 + k] & on;
+        bout += t.o_out[k0 + k] & on;
       }
+    }
   };
   for (int64_t w = blockIdx.x; w < ntiles; w += 2 * (int64_t)gridDim.x) {
-    const int64_t w2 = w + gridDim.x;
-    const bool two = w2 < ntiles;
-    int64_t bin, bout, bin2 = 0, bout2 = 0;
-    base(w, bin, bout);
-    if (two) base(w2, bin2, bout2);
-    for (int c = 0; c < cnt; ++c) tile[0][le[c]] = in[bin + lin[c]];
-    if (two)
-      for (int c = 0; c < cnt; ++c) tile[1][le[c]] = in[bin2 + lin[c]];
+    const bool two = w + gridDim.x < ntiles;
+    int64_t bin[2], bout[2];
+    base(w, bin[0], bout[0]);
+    base(two ? w + gridDim.x : w, bin[1], bout[1]);
+    float4 v[2][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const float2 *p = in + bin[h] + lin + (c ? in9 : 0);
+        if (h == 0 || two) {
+          const float2 a = p[0], b = p[1];
+          v[h][c] = make_float4(a.x, a.y, b.x, b.y);
+        }
+      }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        if (h == 0 || two) {
+          const int e = 2 * tid + (c << (kTileBits - 1));
+          tile[h][tile_at(e)] = make_float2(v[h][c].x, v[h][c].y);
+          tile[h][tile_at(e + 1)] = make_float2(v[h][c].z, v[h][c].w);
+        }
     __syncthreads();
-    for (int c = 0; c < cnt; ++c) perm_emit<NP>(ob, pstride, ktile_index(kt, bout + lout[c]), tile[0][ge[c]], fs);
-    if (two)
-      for (int c = 0; c < cnt; ++c)
-        perm_emit<NP>(ob, pstride, ktile_index(kt, bout2 + lout[c]), tile[1][ge[c]], fs);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        if (h == 0 || two) {
+          const int e = src | (c ? src9 : 0);
+          perm_emit2<NP>(ob, pstride, bout[h] + lout + (c ? out9 : 0), tile[h][tile_at(e)],
+                         tile[h][tile_at(e | src0)], fs);
+        }
     __syncthreads();
   }
 }
 
-static bool build_bit_tile(const PermDesc &h, BitTile &t) {
+static bool build_bit_tile(const PermDesc &h, int np, const KTile &kt, BitTile &t) {
   const int r = h.bits;
-  if (r <= 0 || r > 47) return false;
-  int outpos[48];
-  for (int j = 0; j < r; ++j) outpos[h.inbit[j]] = j;
-  // innermost output bits already innermost in the input: nothing to tile
-  int same = 0;
-  while (same < r && h.inbit[same] == same) ++same;
-  if (same >= 5 || same == r) return false;
-  bool inu[48] = {false};
+  if (r < kTileBits || r > kTileBits + kTileMaxOuter) return false;
+  // output bit of each index bit: in place, or in the k-tiled order
+  // ((k / 16) rows + row) 16 + k % 16
+  int src[64], dst[64];  // output bit -> input bit and back
+  if (kt.on && (kt.kshift < 4 || kt.rows != ((int64_t)1 << (r - kt.kshift)))) return false;
+  for (int j = 0; j < r; ++j) {
+    int o = j;
+    if (kt.on) o = j >= kt.kshift ? 4 + j - kt.kshift : j < 4 ? j : j + r - kt.kshift;
+    src[o] = h.inbit[j];
+    dst[h.inbit[j]] = o;
+  }
+  // six low output bits of planes (runs of 256 bytes of floats, 128 of bf16),
+  // five of complex64, then low input bits (at least four: 128 bytes)
+  bool in_tile[64] = {false};
   int nu = 0;
-  int u_in[12];
-  const int b = r < 5 ? r : 5;
-  for (int i = 0; i < b; ++i) {
-    inu[i] = true;
-    u_in[nu++] = i;
+  for (int j = 0; j < (np == 0 ? 5 : 6); ++j) {
+    in_tile[src[j]] = true;
+    ++nu;
   }
-  for (int j = 0; j < b; ++j) {
-    const int i = h.inbit[j];
-    if (!inu[i]) {
-      inu[i] = true;
-      u_in[nu++] = i;
+  for (int i = 0; i < r && nu < kTileBits; ++i)
+    if (!in_tile[i]) {
+      in_tile[i] = true;
+      ++nu;
     }
-  }
-  for (int i = 0; i < r && nu < 10; ++i)
-    if (!inu[i]) {
-      inu[i] = true;
-      u_in[nu++] = i;
-    }
-  t.nu = nu;
-  for (int k = 0; k < nu; ++k) {
-    t.u_in[k] = u_in[k];
-    t.u_out[k] = outpos[u_in[k]];
-  }
-  // output-ordered tile bits: sort tile bits by output position
-  int order[12];
-  for (int k = 0; k < nu; ++k) order[k] = k;
-  for (int a = 0; a < nu; ++a)
-    for (int c = a + 1; c < nu; ++c)
-      if (t.u_out[order[c]] < t.u_out[order[a]]) {
-        const int tmp = order[a];
-        order[a] = order[c];
-        order[c] = tmp;
-      }
-  for (int i = 0; i < nu; ++i) t.g_to_k[i] = order[i];
-  int no = 0;
+  memset(&t, 0, sizeof(t));
+  int entry[64];  // input bit -> its weight in the tile's entry number
+  int k = 0, g = 0;
   for (int i = 0; i < r; ++i)
-    if (!inu[i]) {
-      t.o_in[no] = i;
-      t.o_out[no] = outpos[i];
-      ++no;
+    if (in_tile[i]) {
+      entry[i] = 1 << k;
+      t.in_s[k++] = (int64_t)1 << i;
     }
-  t.nouter = no;
-  return true;
+  for (int o = 0; o < r; ++o)
+    if (in_tile[src[o]]) {
+      t.src[g] = entry[src[o]];
+      t.out_s[g++] = (int64_t)1 << o;
+    }
+  for (int i = 0; i < r; ++i)
+    if (!in_tile[i]) {
+      t.o_in[t.nouter] = (int64_t)1 << i;
+      t.o_out[t.nouter++] = (int64_t)1 << dst[i];
+    }
+  // a thread's pairs are consecutive in memory
+  return t.in_s[0] == 1 && t.out_s[0] == 1;
 }
 
 hipError_t launch_permute(hipStream_t st, const PermDesc *d_desc, const PermDesc &h, const float2 *in,
@@ -399,17 +443,16 @@ hipError_t launch_permute(hipStream_t st, const PermDesc *d_desc, const PermDesc
                 (kt.kshift >= 0 && ((int64_t)1 << kt.kshift) != kt.kdim)))
     return hipErrorInvalidValue;
   BitTile t;
-  if (h.nelem >= 4096 && build_bit_tile(h, t)) {
+  // (planes are written two entries at a time: an even plane stride)
+  if (h.nelem >= 4096 && pstride % 2 == 0 && build_bit_tile(h, np, kt, t)) {
     const int64_t ntiles = (int64_t)1 << t.nouter;
     const dim3 grid(grid_for(ntiles, 1, 8192), nbatch);
-    if (np == 0)
-      hipLaunchKernelGGL(k_perm_tiled<0>, grid, dim3(256), 0, st, t, in, ibs, out, obs, pstride, sl, sbs, kt);
-    else if (np == 2)
-      hipLaunchKernelGGL(k_perm_tiled<2>, grid, dim3(256), 0, st, t, in, ibs, out, obs, pstride, sl, sbs, kt);
-    else if (np == 4)
-      hipLaunchKernelGGL(k_perm_tiled<4>, grid, dim3(256), 0, st, t, in, ibs, out, obs, pstride, sl, sbs, kt);
-    else
-      hipLaunchKernelGGL(k_perm_tiled<6>, grid, dim3(256), 0, st, t, in, ibs, out, obs, pstride, sl, sbs, kt);
+#define TN_PERM(NP) hipLaunchKernelGGL(k_perm_tiled<NP>, grid, dim3(256), 0, st, t, in, ibs, out, obs, pstride, sl, sbs)
+    if (np == 0) TN_PERM(0);
+    else if (np == 2) TN_PERM(2);
+    else if (np == 4) TN_PERM(4);
+    else TN_PERM(6);
+#undef TN_PERM
     return hipGetLastError();
   }
   const dim3 grid(grid_for(h.nelem, 256, 16384), nbatch);
