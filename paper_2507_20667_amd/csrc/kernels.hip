@@ -4,7 +4,7 @@
 //   k_perm_*       leg permutation (the T steps of TTGT, Section 5.1)
 //   k_cgemm_*      complex GEMM on the matrix cores (the G step of TTGT),
 //                  4M and 3M forms, FP32 and three-term split BF16
-//   k_dot_*        full inner product with FP64 accumulation (the closed
+//   k_dot          full inner product with FP64 accumulation (the closed
 //                  network's last contraction)
 //
 // Every kernel reads the scale records of its operands, multiplies by the
@@ -689,69 +689,82 @@ hipError_t launch_gemm(hipStream_t st, const GemmArgs &g0, int prec, int form, i
 }
 
 // ------------------------------------------------------------------- dot
-// Partial sums per block in FP64, then one block per query adds the partials
-// in a fixed order (deterministic), normalises the FP64 value to a mantissa in
-// [0.5, 1) and writes both the FP64 result and a complex64 copy.
-__global__ __launch_bounds__(256) void k_dot_partial(const DotDesc *__restrict__ d, Operand A,
-                                                     Operand B, double2 *partials, int nblocks) {
+// Partial sums per block in FP64; the last block of a query to arrive adds
+// the partials in a fixed order (deterministic), normalises the FP64 value to
+// a mantissa in [0.5, 1) and writes both the FP64 result and a complex64 copy.
+// Arrivals are counted in the result's scale record (its pad word, zero when
+// the call starts and again afterwards).  The operands are small: the launch
+// is bound by latency, so a block has 1024 threads of two entries each and
+// there is no second launch (16384 entries: 12.4 + 4.2 us in two launches of
+// 256 threads, 8.8 us in this one).
+constexpr int kDotThreads = 1024;
+
+// the sum of every thread's (re, im), in thread 0
+__device__ __forceinline__ double2 dot_block_sum(double re, double im, double2 *red) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    re += __shfl_xor(re, off, 64);
+    im += __shfl_xor(im, off, 64);
+  }
+  const int tid = threadIdx.x;
+  if ((tid & 63) == 0) red[tid >> 6] = make_double2(re, im);
+  __syncthreads();
+  double2 s = make_double2(0.0, 0.0);
+  if (tid == 0)
+    for (int w = 0; w < kDotThreads / 64; ++w) {
+      s.x += red[w].x;
+      s.y += red[w].y;
+    }
+  return s;
+}
+
+__global__ __launch_bounds__(kDotThreads) void k_dot(const DotDesc *__restrict__ d, Operand A, Operand B,
+                                                     OutOperand C, Result *res, int64_t rbs, double2 *partials,
+                                                     int nblocks) {
   __shared__ SegLds L;
-  __shared__ double red_re[256], red_im[256];
+  __shared__ double2 red[kDotThreads / 64];
+  __shared__ bool last;
   const int tid = threadIdx.x;
   const int q = blockIdx.y;
   const float2 *ap = A.p + q * A.bs;
   const float2 *bp = B.p + q * B.bs;
+  Slot *sc = C.slot + q * C.sbs;
   seg_stage(L, d->map, tid);
   __syncthreads();
   const int nseg = d->map.nseg;
   const bool p2 = d->map.pow2 != 0;
+  const int64_t n = d->nelem;
   double re = 0.0, im = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + tid; i < d->nelem; i += (int64_t)nblocks * 256) {
+  for (int64_t i = (int64_t)blockIdx.x * kDotThreads + tid; i < n; i += (int64_t)nblocks * kDotThreads) {
     int64_t ao, bo;
     seg_decode(L, nseg, p2, i, ao, bo);
     const float2 a = ap[ao], b = bp[bo];
     re += (double)a.x * (double)b.x - (double)a.y * (double)b.y;
     im += (double)a.x * (double)b.y + (double)a.y * (double)b.x;
   }
-  red_re[tid] = re;
-  red_im[tid] = im;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (tid < s) {
-      red_re[tid] += red_re[tid + s];
-      red_im[tid] += red_im[tid + s];
+  double2 s = dot_block_sum(re, im, red);
+  if (nblocks > 1) {
+    double *part = (double *)(partials + (int64_t)q * nblocks);
+    if (tid == 0) {
+      __hip_atomic_store(part + 2 * blockIdx.x, s.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(part + 2 * blockIdx.x + 1, s.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last = __hip_atomic_fetch_add(&sc->pad, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
+             (uint32_t)nblocks - 1;
     }
     __syncthreads();
-  }
-  if (tid == 0) partials[(int64_t)q * nblocks + blockIdx.x] = make_double2(red_re[0], red_im[0]);
-}
-
-__global__ __launch_bounds__(256) void k_dot_final(const double2 *partials, int nblocks, Operand A,
-                                                   Operand B, OutOperand C, Result *res,
-                                                   int64_t rbs) {
-  __shared__ double red_re[256], red_im[256];
-  const int tid = threadIdx.x;
-  const int q = blockIdx.x;
-  double re = 0.0, im = 0.0;
-  for (int i = tid; i < nblocks; i += 256) {
-    const double2 p = partials[(int64_t)q * nblocks + i];
-    re += p.x;
-    im += p.y;
-  }
-  red_re[tid] = re;
-  red_im[tid] = im;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (tid < s) {
-      red_re[tid] += red_re[tid + s];
-      red_im[tid] += red_im[tid + s];
+    if (!last) return;
+    re = im = 0.0;
+    for (int i = tid; i < nblocks; i += kDotThreads) {
+      re += __hip_atomic_load(part + 2 * i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      im += __hip_atomic_load(part + 2 * i + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __syncthreads();
+    s = dot_block_sum(re, im, red);
   }
   if (tid == 0) {
     const Slot *sa = A.slot + q * A.sbs;
     const Slot *sb = B.slot + q * B.sbs;
     double log2s = sa->log2s + sb->log2s;
-    double vr = red_re[0], vi = red_im[0];
+    double vr = s.x, vi = s.y;
     const double m = fmax(fabs(vr), fabs(vi));
     if (m > 0.0 && isfinite(m)) {
       int e;
@@ -769,9 +782,9 @@ __global__ __launch_bounds__(256) void k_dot_final(const double2 *partials, int 
     }
     const float2 c = make_float2((float)vr, (float)vi);
     C.p[q * C.bs] = c;
-    Slot *sc = C.slot + q * C.sbs;
     sc->log2s = log2s;
     sc->maxbits = __float_as_uint(fmaxf(fabsf(c.x), fabsf(c.y)));
+    sc->pad = 0u;
   }
 }
 
@@ -780,12 +793,8 @@ int dot_blocks_for(int64_t nelem) { return grid_for(nelem, 256 * 8, 512); }
 hipError_t launch_dot(hipStream_t st, const DotDesc *d_desc, int64_t nelem, Operand A, Operand B,
                       OutOperand C, Result *res, int64_t rbs, double2 *partials, int nblocks,
                       int nbatch) {
-  hipLaunchKernelGGL(k_dot_partial, dim3(nblocks, nbatch), dim3(256), 0, st, d_desc, A, B, partials,
+  hipLaunchKernelGGL(k_dot, dim3(nblocks, nbatch), dim3(kDotThreads), 0, st, d_desc, A, B, C, res, rbs, partials,
                      nblocks);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_dot_final, dim3(nbatch), dim3(256), 0, st, partials, nblocks, A, B, C, res,
-                     rbs);
   return hipGetLastError();
 }
 
