@@ -261,8 +261,41 @@ struct SinglePin {
   ~SinglePin() { release(); }
 };
 
+// k chunks of a GEMM launch over nb queries: the plan's, or more when its
+// blocks leave CUs without work.  A block runs a stage of 16 k in about 2 us
+// however few rows it has, so the chip's time for a skinny result is its
+// chunk's length: up to one block per CU, chunks of at least 64 (M 32 x N 512 x
+// K 16384: 151 us in 16 chunks, 45 in 128; M 8 x N 128 x K 512: 75 in one, 21 in
+// eight; past one block per CU the partial sums' traffic costs more, M 64 x
+// N 4096 x K 32768: 358 us in 32 chunks, 377 in 64).  The partial sums (at most
+// 256 tiles, 34 MB) lie in a region of their own that is not part of
+// the layouts, so a call that has no room for it runs the plan's chunks.
+static int wide_split(const Node &n, int nb, int64_t &kchunk) {
+  kchunk = n.kchunk;
+  if (!n.wide_ok || n.fo) return n.ksplit;
+  int64_t s = n.ksplit;
+  while ((int64_t)n.tiles * nb * s * 2 <= 256 && n.K / (s * 2) >= 64) s *= 2;
+  if (s == n.ksplit) return n.ksplit;
+  kchunk = ((n.K + s - 1) / s + 31) / 32 * 32;
+  return (int)((n.K + kchunk - 1) / kchunk);
+}
+
+// Bytes of the wide region for Q queries (one region per partition, and the
+// reduction path's, when they run side by side).
+static size_t wide_bytes(const tn_plan *p, const ExecLayout &L, int Q) {
+  size_t most = 0;
+  for (const Node &n : p->nodes) {
+    if (n.kind != NK_GEMM || !n.wide_ok || n.fo) continue;
+    const int nb = L.shared[n.id] ? 1 : Q;
+    int64_t kc;
+    const int s = wide_split(n, nb, kc);
+    if (s != n.ksplit) most = std::max(most, rnd((size_t)s * n.M * n.N * 8 * nb));
+  }
+  return most;
+}
+
 // Device bytes of one execution chunk of Q queries (carved in run_group).
-size_t group_workspace_bytes(const tn_plan *p, const ExecLayout &L, int Q) {
+size_t group_workspace_bytes(const tn_plan *p, const ExecLayout &L, int Q, bool wide) {
   const int nn = 2 * p->nv - 1;
   const size_t relems = result_elems(p);
   const size_t final_bytes = p->fperm.needed ? rnd(relems * 8) : 0;
@@ -271,7 +304,7 @@ size_t group_workspace_bytes(const tn_plan *p, const ExecLayout &L, int Q) {
     if (n.kind == NK_DOT) max_blocks = std::max(max_blocks, n.dot_blocks);
   return rnd(L.shared_bytes) + rnd(rnd(L.perq_bytes) * Q) + rnd((size_t)nn * sizeof(Slot) * (Q + 1)) +
          rnd((size_t)L.ovr_bytes * Q) + rnd(sizeof(Result) * Q) + rnd(final_bytes * Q) +
-         rnd((size_t)max_blocks * 16 * Q);
+         rnd((size_t)max_blocks * 16 * Q) + (wide ? wide_bytes(p, L, Q) * (L.conc ? p->K + 1 : 1) : 0);
 }
 
 static void to_c64(const tn_leaf &l, int64_t n, float2 *dst) {
@@ -474,8 +507,10 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
   const size_t shared_fixed = rnd(L.shared_bytes) + rnd(slot_bytes);
   const size_t per_query = perq + slot_bytes + ovr_bytes + sizeof(Result) + final_bytes +
                            (size_t)max_blocks * 16;
-  // queries per chunk that fit the arena (or the caller's reserved workspace)
+  // queries per chunk that fit the arena (or the caller's reserved workspace);
+  // wide: the whole group fits with room for wide_split's partial sums
   size_t chunk;
+  bool wide = false;
   if (rs.ext_ws) {
     const size_t need = group_workspace_bytes(p, L, (int)qs.size());
     if (need > rs.ext_ws_bytes) {
@@ -484,8 +519,10 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       return TN_E_NOMEM;
     }
     chunk = qs.size();
+    wide = group_workspace_bytes(p, L, (int)qs.size(), true) <= rs.ext_ws_bytes;
   } else if (rs.ws >= 0) {
     chunk = qs.size();
+    wide = group_workspace_bytes(p, L, (int)qs.size(), true) <= rs.ws_bytes;
     if (group_workspace_bytes(p, L, (int)chunk) > rs.ws_bytes) {
       // the slices of a sliced request run in chunks of the reserved
       // workspace: the most queries whose workspace fits it
@@ -515,6 +552,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
     chunk = (avail - shared_fixed - 4096) / (per_query + 1024);
     chunk = std::min<size_t>(chunk, 65535);
     chunk = std::max<size_t>(chunk, 1);
+    wide = chunk >= qs.size() && group_workspace_bytes(p, L, (int)qs.size(), true) + 4096 <= avail;
   }
   tn_status rc = TN_OK;
   // TN_FLAG_GRAPH (the whole group in one chunk, not profiled, not serving):
@@ -545,7 +583,8 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
     const hipStream_t st = gst ? gst : rs.st;
     // carve the workspace of Q queries
     size_t r_shared = 0, r_perq = 0, r_slots = 0, r_ovr = 0, r_res = 0, r_final = 0, r_part = 0,
-           total = 0;
+           r_wide = 0, total = 0;
+    const size_t wide_part = wide ? wide_bytes(p, L, Q) : 0;
     auto carve_all = [&](int nq) {
       size_t o = 0;
       auto carve = [&](size_t b) {
@@ -560,6 +599,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       r_res = carve(sizeof(Result) * nq);
       r_final = carve(final_bytes * nq);
       r_part = carve((size_t)max_blocks * 16 * nq);
+      r_wide = carve((wide ? wide_part : 0) * (L.conc ? p->K + 1 : 1));
       total = o;
     };
     carve_all(Q);
@@ -592,6 +632,11 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
     int64_t ws = rs.ext_ws ? 0 : gmode ? p->graph->ws : own_ws ? arena_alloc(ctx, total, false) : rs.ws;
     // the free space measured above may have been taken meanwhile (serve
     // workers share the arena): fewer queries per chunk
+    if (ws < 0 && own_ws && wide) {
+      wide = false;
+      carve_all(Q);
+      ws = arena_alloc(ctx, total, false);
+    }
     while (ws < 0 && own_ws && Q > 1) {
       Q = (Q + 1) / 2;
       chunk = (size_t)Q;
@@ -1069,7 +1114,14 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
             memcpy(g.fo_d, n.fo_d, sizeof(g.fo_d));
           }
           g.kchunk = n.kchunk;
-          if (n.ksplit > 1) {
+          int64_t kc = n.kchunk;
+          const int ks = wide ? wide_split(n, nb, kc) : n.ksplit;
+          if (ks != n.ksplit) {
+            g.ksplit = ks;
+            g.kchunk = kc;
+            g.part = (float2 *)(base + r_wide + (conc ? wide_part * (size_t)(n.part + 1) : 0));
+            g.partbs = (int64_t)ks * n.M * n.N;
+          } else if (n.ksplit > 1) {
             g.part = (float2 *)(pbase + L.partial[j]);
             g.partbs = sh ? 0 : perq_el;
           }

@@ -538,6 +538,9 @@ static tn_status schedule_gemm(tn_plan *p, Node &n, const Layout &A, const Layou
   }
   n.ktile = n.planes > 0 && n.K % 16 == 0 &&
             (n.ksplit == 1 || n.kchunk % 16 == 0);
+  n.tiles = (int)std::min<int64_t>(((n.M + tile_m(n.tile) - 1) / tile_m(n.tile)) *
+                                       ((n.N + tile_n(n.tile) - 1) / tile_n(n.tile)), INT32_MAX);
+  n.wide_ok = n.ktile && !getenv("TN_GEMM_FORCE");
   // fusion with the chosen child: its epilogue writes this GEMM's operand
   // planes (unscaled; this GEMM scales its result instead)
   if (fx && fuse_on && n.ktile) {

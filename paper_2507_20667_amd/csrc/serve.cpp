@@ -51,7 +51,9 @@ class DeviceBackend : public sched::Backend {
                               size_t cap) {
     std::shared_ptr<ExecLayout> L = layout_of(p, batch, n);
     int64_t nq = p->nslices > 0 ? p->nslices * (int64_t)n : (int64_t)n;
-    size_t b = Arena::round(group_workspace_bytes(p, *L, (int)nq));
+    // with room for the partial sums of skinny products where that fits
+    size_t b = Arena::round(group_workspace_bytes(p, *L, (int)nq, true));
+    if (b > cap / 4) b = Arena::round(group_workspace_bytes(p, *L, (int)nq));
     while (p->nslices > 0 && nq > 1 && b > cap / 2) {
       nq = (nq + 1) / 2;
       b = Arena::round(group_workspace_bytes(p, *L, (int)nq));

@@ -84,6 +84,8 @@ struct Node {
   bool ktile = false;  // planes k-tiled for the direct-to-LDS 4M GEMM
   int ksplit = 1;    // k chunks (partials reduced after the GEMM)
   int64_t kchunk = 0;
+  int tiles = 0;     // output tiles
+  bool wide_ok = false;  // may take more chunks at run time (wide_split)
   int64_t M = 0, N = 0, K = 0, lda = 0, ldb = 0, ldc = 0;
   int variant = 0;
   int tile = 0;      // FP32 plane kernel tile shape (GemmArgs::tile)
@@ -461,7 +463,8 @@ tn_status make_sliced_plan(tn_ctx *ctx, const tn_plan *p, std::vector<int64_t> l
                            int64_t max_intermediate, tn_plan **out);
 tn_status run_sliced(tn_ctx *ctx, tn_plan *p, int32_t novr, const tn_leaf *ovr, void *out,
                      tn_dtype out_dtype, double *log2_scale, uint32_t flags, ExecRes &rs);
-size_t group_workspace_bytes(const tn_plan *p, const ExecLayout &L, int Q);
+// workspace of Q queries; wide: with room for wide_split's partial sums
+size_t group_workspace_bytes(const tn_plan *p, const ExecLayout &L, int Q, bool wide = false);
 tn_status upload_tree_programs(tn_ctx *ctx, const ExecLayout &L, hipStream_t st, bool single = false);
 // arena allocation; subtree programs only single calls use give way to it
 int64_t arena_alloc(tn_ctx *ctx, size_t bytes, bool persistent);
