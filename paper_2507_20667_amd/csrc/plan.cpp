@@ -344,11 +344,12 @@ static void interleave_rows(std::vector<int64_t> &FB, int npc, const Layout &B, 
 // 1024 x 2048 at k = 8 takes 15 us against 20 + 21 us of permutations, 64 x
 // 128 at k = 4 4.4 us against 7.6 + 6.5.  Longer k, up to 128 (8 rounds),
 // while the products are few (2^21: a block of each CU 8 k each, 16 x 64 at k = 64 8
-// us against 14 + 15); beyond that the matrix cores win.  Operands are
-// limited to 2^18 entries, which the L2 holds.
-static bool small_gemm(int64_t M, int64_t N, int64_t K) {
+// us against 14 + 15); beyond that the matrix cores win, and so does a vertex
+// that can read or write its operand planes without a permutation (fused: see
+// schedule_gemm).  Operands are limited to 2^18 entries, which the L2 holds.
+static bool small_gemm(int64_t M, int64_t N, int64_t K, bool fusable) {
   if (M > 1 << 15 || N > 1 << 15 || M * K > 1 << 18 || N * K > 1 << 18) return false;
-  return K < 16 || (K <= 128 && M * N * K <= 1 << 21);
+  return K < 16 || (!fusable && K <= 128 && M * N * K <= 1 << 21);
 }
 
 // Offsets of the index space of `legs` (row-major) in a tensor.
@@ -443,7 +444,13 @@ static tn_status schedule_gemm(tn_plan *p, Node &n, const Layout &A, const Layou
   for (int64_t l : FA) n.M *= A.dim[A.find(l)];
   for (int64_t l : FB) n.N *= B.dim[B.find(l)];
   for (int64_t l : sorder) n.K *= A.dim[A.find(l)];
-  if (small_gemm(n.M, n.N, n.K)) {
+  // planes from a GEMM child, or for a GEMM parent (whose k the legs of pcon
+  // are), of a size that is fused
+  int64_t pk = 1;
+  for (int64_t l : pcon) pk *= A.find(l) >= 0 ? A.dim[A.find(l)] : B.find(l) >= 0 ? B.dim[B.find(l)] : 1;
+  const bool fusable_in = fx && (fx == 1 ? A : B).size() > kTreeMaxElems;
+  const bool fusable_out = !pcon.empty() && pk % 16 == 0 && n.M * n.N > kTreeMaxElems;
+  if (small_gemm(n.M, n.N, n.K, fusable_in || fusable_out)) {
     std::vector<int32_t> tab;
     if (put_offsets(A, FA, tab) && put_offsets(B, FB, tab) && put_offsets(A, sorder, tab) &&
         put_offsets(B, sorder, tab)) {
