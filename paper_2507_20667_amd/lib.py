@@ -197,25 +197,56 @@ def tn_plan_slice(plan, labels=(), max_intermediate=0):
 
 # -------------------------------------------------------------- contraction
 
-def _leaves(overrides):
-    keep = []
-    arr = (tn_leaf * max(1, len(overrides)))()
-    for i, (t, data) in enumerate(sorted(overrides.items())):
-        a = np.ascontiguousarray(data, dtype=np.complex128)
-        keep.append(a)
-        arr[i] = tn_leaf(int(t), a.ctypes.data, TN_C128)
-    return arr, keep
+# tn_leaf and tn_query as record arrays: one assignment per field instead of
+# one ctypes object per override (24 overridden leaves: 72 -> 22 us)
+_LEAF = np.dtype({"names": ["tensor", "data", "dtype"], "formats": ["i4", "u8", "i4"],
+                  "offsets": [tn_leaf.tensor.offset, tn_leaf.data.offset, tn_leaf.dtype.offset],
+                  "itemsize": ctypes.sizeof(tn_leaf)})
+_QUERY = np.dtype({"names": ["plan", "num_overrides", "overrides"], "formats": ["u8", "i4", "u8"],
+                   "offsets": [tn_query.plan.offset, tn_query.num_overrides.offset, tn_query.overrides.offset],
+                   "itemsize": ctypes.sizeof(tn_query)})
+
+
+def _addr(a):
+    return a.__array_interface__["data"][0]
+
+
+def _leaves(queries):
+    """tn_leaf records of every query's overrides (dicts), one query after the
+    other, each in increasing tensor id; the array that holds their data as
+    complex128; and each query's first record (with the count at the end)."""
+    ids, data, first = [], [], [0]
+    for o in queries:
+        if o:
+            keys = sorted(o)
+            ids += keys
+            data += [o[t] for t in keys]
+        first.append(len(ids))
+    rec = np.zeros(max(1, len(ids)), dtype=_LEAF)
+    if not ids:
+        return rec, None, first
+    try:
+        ends = np.cumsum([d.size for d in data])
+    except AttributeError:  # not arrays
+        data = [np.asarray(d, dtype=np.complex128) for d in data]
+        ends = np.cumsum([d.size for d in data])
+    buf = np.concatenate(data, axis=None, dtype=np.complex128, casting="unsafe")
+    base = _addr(buf)
+    rec["tensor"] = ids
+    rec["dtype"] = TN_C128
+    at = rec["data"]
+    at[0] = base
+    at[1:] = base + 16 * ends[:-1]
+    return rec, buf, first
 
 
 def tn_contract(plan, overrides=None, result_shape=(), out_dtype=TN_C128, flags=0):
     """Returns (result array, log2 scale)."""
-    overrides = overrides or {}
-    arr, keep = _leaves(overrides)
-    out = np.zeros(result_shape, dtype=np.complex128 if out_dtype == TN_C128 else np.complex64)
-    out = np.ascontiguousarray(out)
+    rec, keep, first = _leaves([overrides])
+    # (a closed network's result has shape (1,))
+    out = np.ascontiguousarray(np.zeros(result_shape, dtype=np.complex128 if out_dtype == TN_C128 else np.complex64))
     l2 = ctypes.c_double(0.0)
-    _check(load().tn_contract(ctypes.c_void_p(plan), len(overrides), ctypes.cast(arr, ctypes.c_void_p),
-                              _p(out), out_dtype, ctypes.byref(l2), flags))
+    _check(load().tn_contract(plan, first[1], _addr(rec), _addr(out), out_dtype, ctypes.byref(l2), flags))
     return out, l2.value
 
 
@@ -223,21 +254,18 @@ def tn_contract_batch(ctx, queries, result_shapes, out_dtype=TN_C128, flags=0):
     """queries: list of (plan, overrides dict).  Returns (results, log2 scales,
     per-query statuses)."""
     n = len(queries)
-    qarr = (tn_query * max(1, n))()
-    keep = []
-    outs = []
-    for i, (plan, ovr) in enumerate(queries):
-        arr, k = _leaves(ovr or {})
-        keep.append((arr, k))
-        qarr[i] = tn_query(plan, len(ovr or {}), ctypes.cast(arr, ctypes.c_void_p).value)
-        outs.append(np.zeros(result_shapes[i], dtype=np.complex128 if out_dtype == TN_C128
-                             else np.complex64))
-    optrs = (ctypes.c_void_p * max(1, n))(*[o.ctypes.data for o in outs])
+    dt = np.dtype(np.complex128 if out_dtype == TN_C128 else np.complex64)
+    rec, keep, first = _leaves([ovr for _, ovr in queries])
+    q = np.zeros(max(1, n), dtype=_QUERY)
+    if n:
+        q["plan"] = [plan or 0 for plan, _ in queries]
+        q["num_overrides"] = np.diff(first)
+        q["overrides"] = _addr(rec) + _LEAF.itemsize * np.array(first[:-1])
+    outs = [np.zeros(shape, dtype=dt) for shape in result_shapes]
+    optrs = np.array([_addr(o) for o in outs] or [0], dtype=np.uint64)
     l2 = np.zeros(max(1, n), dtype=np.float64)
     st = np.zeros(max(1, n), dtype=np.int32)
-    _check(load().tn_contract_batch(ctypes.c_void_p(ctx), n, ctypes.cast(qarr, ctypes.c_void_p),
-                                    ctypes.cast(optrs, ctypes.c_void_p), out_dtype, _p(l2), _p(st),
-                                    flags))
+    _check(load().tn_contract_batch(ctx, n, _addr(q), _addr(optrs), out_dtype, _addr(l2), _addr(st), flags))
     return outs, l2[:n], st[:n]
 
 
@@ -299,11 +327,10 @@ def tn_contract_strided_noalloc(plan, num_queries, overrides, out_ptr, out_strid
 
 
 def tn_serve_submit(ctx, plan, overrides=None) -> int:
-    overrides = overrides or {}
-    arr, keep = _leaves(overrides)
-    q = tn_query(plan, len(overrides), ctypes.cast(arr, ctypes.c_void_p).value)
+    rec, keep, first = _leaves([overrides])
+    q = tn_query(plan, first[1], _addr(rec))
     t = ctypes.c_uint64()
-    _check(load().tn_serve_submit(ctypes.c_void_p(ctx), ctypes.byref(q), ctypes.byref(t)))
+    _check(load().tn_serve_submit(ctx, ctypes.byref(q), ctypes.byref(t)))
     return t.value
 
 
