@@ -338,18 +338,30 @@ static void interleave_rows(std::vector<int64_t> &FB, int npc, const Layout &B, 
   FB = out;
 }
 
-// Whether a GEMM vertex runs on k_cgemm_small: its multiply-adds cost the
-// vector units less than the launches of two permutations and a matrix core
-// kernel.  k up to 15 (the kernels on k-tiled planes need a multiple of 16):
-// 1024 x 2048 at k = 8 takes 15 us against 20 + 21 us of permutations, 64 x
-// 128 at k = 4 4.4 us against 7.6 + 6.5.  Longer k, up to 128 (8 rounds),
-// while the products are few (2^21: a block of each CU 8 k each, 16 x 64 at k = 64 8
-// us against 14 + 15); beyond that the matrix cores win, and so does a vertex
-// that can read or write its operand planes without a permutation (fused: see
-// schedule_gemm).  Operands are limited to 2^18 entries, which the L2 holds.
-static bool small_gemm(int64_t M, int64_t N, int64_t K, bool fusable) {
-  if (M > 1 << 15 || N > 1 << 15 || M * K > 1 << 18 || N * K > 1 << 18) return false;
-  return K < 16 || (!fusable && K <= 128 && M * N * K <= 1 << 21);
+// Whether a GEMM vertex runs on k_cgemm_small (M, N up to 2^15: the size of
+// its tables).  Times are of one vertex with its permutations, two queries.
+//   k up to 15: the kernels on k-tiled planes need a multiple of 16, and the
+//     result's bytes bound the vertex: 1024 x 2048 at k = 8 takes 15 us against
+//     41.  Operands up to 2^18 entries, which the L2 holds.
+//   a longer k that is no multiple of 16: in FP32 always (the alternative's
+//     FP32 matrix core kernel has no rate to set against it: 200 x 200 x 50 11 us
+//     against 34, 407 x 523 x 405 65 against 177, 1400 x 1400 x 1400 717 against 852);
+//     BF16x3's split products cost the vector units three times as much, so
+//     k up to 128 and 2^24 multiply-adds (300 x 300 x 100 31 against 58, 600 x 600 x
+//     333 199 against 152).
+//   a multiple of 16, where no operand's planes can be shared (fused, see
+//     schedule_gemm): while the products cost less than two permutations and
+//     a matrix core launch, FP32 2^24 multiply-adds with k up to 128 (512 x 512 x
+//     64 15 against 33, 64 x 64 x 256 30 against 36), BF16x3 2^23 with k up to 64
+//     (256 x 256 x 64 22 against 30, 256 x 256 x 128 37 against 34) and 2^19 with k
+//     up to 128 (a serving burst of such plans 783 against 841 us).
+static bool small_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool fusable) {
+  if (M > 1 << 15 || N > 1 << 15) return false;
+  const int64_t macs = K <= 1 << 15 ? M * N * K : INT64_MAX;
+  if (K < 16) return M * K <= 1 << 18 && N * K <= 1 << 18;
+  if (K % 16 != 0) return K <= 1 << 15 && (!bf16 || (K <= 128 && macs <= 1 << 24));
+  if (fusable || K > 128) return false;
+  return bf16 ? macs <= (K <= 64 ? 1 << 23 : 1 << 19) : macs <= 1 << 24;
 }
 
 // Offsets of the index space of `legs` (row-major) in a tensor.
@@ -371,8 +383,10 @@ static bool put_offsets(const Layout &X, const std::vector<int64_t> &legs, std::
   return true;
 }
 
+// pcon: the legs the parent contracts, pcon2: those of its result the
+// grandparent contracts; sibling: entries of the parent's other operand
 static tn_status schedule_gemm(tn_plan *p, Node &n, const Layout &A, const Layout &B,
-                               const std::set<int64_t> &pcon, const std::set<int64_t> &pcon2) {
+                               const std::set<int64_t> &pcon, const std::set<int64_t> &pcon2, double sibling) {
   n.kind = NK_GEMM;
   n.ga = n.c1;
   n.gb = n.c2;
@@ -449,8 +463,13 @@ static tn_status schedule_gemm(tn_plan *p, Node &n, const Layout &A, const Layou
   int64_t pk = 1;
   for (int64_t l : pcon) pk *= A.find(l) >= 0 ? A.dim[A.find(l)] : B.find(l) >= 0 ? B.dim[B.find(l)] : 1;
   const bool fusable_in = fx && (fx == 1 ? A : B).size() > kTreeMaxElems;
-  const bool fusable_out = !pcon.empty() && pk % 16 == 0 && n.M * n.N > kTreeMaxElems;
-  if (small_gemm(n.M, n.N, n.K, fusable_in || fusable_out)) {
+  // (a result of 2^14 entries for a parent with another operand of GEMM size and
+  // 2^18 multiply-adds: below that both run in small launches; and k up to 32:
+  // deeper, the small kernel or k chunks, which a fused result cannot have,
+  // save more than the permutation, 4-10 us, costs)
+  const bool fusable_out = !pcon.empty() && pk % 16 == 0 && n.K <= 32 && n.M * n.N >= 1 << 14 &&
+                           sibling > kStreamMax && (double)n.M * (double)n.N * sibling / (double)pk >= 1 << 18;
+  if (small_gemm(n.M, n.N, n.K, (p->flags & TN_PREC_BF16X3) != 0, fusable_in || fusable_out)) {
     std::vector<int32_t> tab;
     if (put_offsets(A, FA, tab) && put_offsets(B, FB, tab) && put_offsets(A, sorder, tab) &&
         put_offsets(B, sorder, tab)) {
@@ -919,8 +938,10 @@ tn_status build_plan(tn_plan *p, const tn_plan_desc *d) {
   // children's), known before the vertices are scheduled, so that a GEMM can
   // order its result's legs by what its parent contracts
   std::vector<std::vector<int64_t>> legset(nn);
+  std::unordered_map<int64_t, int64_t> leg_dim;
   for (int v = 0; v < nv; ++v) {
     legset[v] = lay[v].lab;
+    for (int i = 0; i < lay[v].rank(); ++i) leg_dim[lay[v].lab[i]] = lay[v].dim[i];
     std::sort(legset[v].begin(), legset[v].end());
   }
   for (int j = 0; j < nv - 1; ++j) {
@@ -986,7 +1007,11 @@ tn_status build_plan(tn_plan *p, const tn_plan_desc *d) {
       };
       std::set<int64_t> pcon, pcon2;
       if (contracted(n.id, pcon)) contracted(parent[n.id], pcon2);
-      st = schedule_gemm(p, n, A, B, pcon, pcon2);
+      double sibling = 1.0;
+      if (const int pv = parent[n.id]; pv >= 0)
+        for (int64_t l : legset[p->tree[2 * (pv - nv)] == n.id ? p->tree[2 * (pv - nv) + 1] : p->tree[2 * (pv - nv)]])
+          sibling *= (double)leg_dim[l];
+      st = schedule_gemm(p, n, A, B, pcon, pcon2, sibling);
       p->num_gemm++;
     }
     if (st) return st;

@@ -55,10 +55,10 @@ def entries(rng, shape, kind):
 
 
 # tiles are 128 x 128, 64 x 256 (M <= 64) and 256 x 64 (N <= 64); k chunks of 16
-SHAPES = [(128, 128, 144), (129, 127, 144), (257, 383, 32), (2048, 513, 16), (65, 64, 528), (64, 257, 160),
-          (33, 500, 144), (300, 64, 112), (511, 17, 256), (97, 130, 4096), (40, 40, 16384)]
+SHAPES = [(128, 128, 144), (129, 127, 144), (513, 1025, 32), (2048, 515, 16), (65, 64, 528), (64, 257, 160),
+          (33, 500, 144), (300, 64, 144), (511, 17, 256), (97, 130, 4096), (40, 40, 16384)]
 # in place: 64 x 64 and 32 x 32 tiles, rounds of 16 k
-SMALL = [(128, 128, 48), (65, 64, 80), (33, 127, 128), (1024, 1023, 8), (2049, 511, 15), (200, 300, 7), (500, 133, 1),
+SMALL = [(128, 128, 48), (65, 64, 64), (33, 127, 64), (1024, 1023, 8), (2049, 511, 15), (200, 300, 7), (500, 133, 1),
          (23, 5003, 3), (129, 130, 16), (1000, 40, 17)]
 
 
@@ -90,6 +90,16 @@ def test_small_vertex(ctx, M, N, K, flags):
         tol += 2.0 ** -12
     over = np.abs(got - ref) / (tol * (np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64)))
     assert over.max() <= 1.0, over.max()
+
+
+@pytest.mark.parametrize("M,N,K", [(203, 330, 405), (65, 1000, 33), (67, 64, 1001)])
+def test_small_vertex_long_k(ctx, M, N, K):
+    """FP32: a long k that is no multiple of 16."""
+    rng = np.random.default_rng([M, N, K])
+    A, B = entries(rng, (M, K), "normal"), entries(rng, (K, N), "normal")
+    got = run_pair(ctx, A, B, 0, "gemm_small")
+    size = np.abs(A).astype(np.float64) @ np.abs(B).astype(np.float64)
+    assert (np.abs(got - A.astype(np.complex128) @ B) <= 8 * np.sqrt(4 * K + 4) * 2.0 ** -23 * size).all()
 
 
 @pytest.mark.parametrize("flags", [0, lib.TN_PREC_BF16X3])
