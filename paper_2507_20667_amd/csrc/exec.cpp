@@ -607,11 +607,17 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
     // (a group whose workspace cannot be kept runs without a graph)
     bool gmode = want_graph;
     const double t_carve = dbg ? ms_since(t_enter) : 0.0;
-    size_t rb_bytes = (size_t)Q * (relems * 8 + sizeof(Slot) + sizeof(Result));
+    // result staging: open results in the caller's type, scale records (when
+    // the caller wants them) or closed-root records
+    const size_t esz = out_dtype == TN_C128 ? 16 : 8;
+    const bool keep = (flags & TN_FLAG_KEEP_SCALE) != 0;
+    const int out_mode = (out_dtype == TN_C128 ? 1 : 0) | (keep ? 2 : 0);
+    auto staging_bytes = [&](int nq) { return (size_t)nq * (relems * esz + sizeof(Slot) + sizeof(Result)); };
+    size_t rb_bytes = staging_bytes(Q);
     if (gmode) {
       if (!p->graph) p->graph.reset(new GraphEntry());
       GraphEntry &E = *p->graph;
-      if (E.layout != &L || E.Q != Q || E.ws_bytes != total) {
+      if (E.layout != &L || E.Q != Q || E.ws_bytes != total || E.out_mode != out_mode) {
         hipStreamSynchronize(st);
         release_graph(ctx, E);
         E.ws = arena_alloc(ctx, total, true);
@@ -625,6 +631,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
           E.pinned_bytes = rb_bytes;
           E.layout = &L;
           E.Q = Q;
+          E.out_mode = out_mode;
         }
       }
     }
@@ -641,7 +648,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       Q = (Q + 1) / 2;
       chunk = (size_t)Q;
       carve_all(Q);
-      rb_bytes = (size_t)Q * (relems * 8 + sizeof(Slot) + sizeof(Result));
+      rb_bytes = staging_bytes(Q);
       ws = ctx->arena.alloc(total);
     }
     const double t_alloc = dbg ? ms_since(t_enter) : 0.0;
@@ -843,7 +850,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       // still read it)
       const bool root_shared = L.shared[p->root] != 0;
       const bool dot_root = nv > 1 && p->nodes[p->root - nv].kind == NK_DOT;
-      size_t rb_vals = (size_t)Q * relems * 8, rb_slots = (size_t)Q * sizeof(Slot);
+      size_t rb_vals = (size_t)Q * relems * esz, rb_slots = (size_t)Q * sizeof(Slot);
       // results into device memory (no host staging at all)
       const bool devout = so && so->device_out;
       uint8_t *h = nullptr;
@@ -855,7 +862,6 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
         if (rc) goto done;
         h = (uint8_t *)*rs.pinned;
       }
-      float2 *hv = (float2 *)h;
       Slot *hs = (Slot *)(h + rb_vals);
       Result *hr = (Result *)(h + rb_vals + rb_slots);
       // a closed root's records go straight to the pinned staging buffer
@@ -1181,23 +1187,20 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
                  "slice sum");
         }
       }
-      // read back
+      // open results, converted on the way out
       if (!dot_root && !devout && !sum) {
         const int rq = root_shared ? 1 : Q;
+        Operand S = R;
         if (p->fperm.needed) {
-          // the permuted results lie final_bytes apart (256-byte rounded)
-          TN_HIP(hipMemcpy2DAsync(hv, relems * 8, fin, final_bytes, relems * 8, rq,
-                                  hipMemcpyDeviceToHost, st),
-                 "result copy");
-        } else {
-          const size_t pitch = R.bs ? (size_t)R.bs * 8 : relems * 8;
-          TN_HIP(hipMemcpy2DAsync(hv, relems * 8, R.p, pitch, relems * 8, rq,
-                                  hipMemcpyDeviceToHost, st),
-                 "result copy");
+          S.p = fin;
+          S.bs = (int64_t)(final_bytes / 8);
         }
-        TN_HIP(hipMemcpy2DAsync(hs, sizeof(Slot), R.slot, (R.sbs ? R.sbs : 1) * sizeof(Slot),
-                                sizeof(Slot), rq, hipMemcpyDeviceToHost, st),
-               "scale copy");
+        TN_HIP(launch_results_out(st, S, rq, (int64_t)relems, fac.m, fac.e, keep, out_dtype == TN_C128, h),
+               "result copy");
+        if (keep)
+          TN_HIP(hipMemcpy2DAsync(hs, sizeof(Slot), R.slot, (R.sbs ? R.sbs : 1) * sizeof(Slot),
+                                  sizeof(Slot), rq, hipMemcpyDeviceToHost, st),
+                 "scale copy");
       }
       if (capturing) {
         hipGraph_t g = nullptr;
@@ -1232,7 +1235,6 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       }
       for (int qi = 0; qi < Q && !direct && !devout && !sum; ++qi) {
         const QueryIO &q = qs[q0 + qi];
-        const bool keep = (flags & TN_FLAG_KEEP_SCALE) != 0;
         if (dot_root) {
           Result r = hr[root_shared ? 0 : qi];
           r.re *= fac.m;
@@ -1257,16 +1259,8 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
           }
         } else {
           const int src = root_shared ? 0 : qi;
-          const double log2s = hs[src].log2s + fac.e;
-          const float2 *v = hv + (size_t)src * relems;
-          for (size_t i = 0; i < relems; ++i) {
-            const double re = v[i].x * fac.m, im = v[i].y * fac.m;
-            if (keep)
-              write_out(q.out, out_dtype, i, re, im);
-            else
-              write_out(q.out, out_dtype, i, std::ldexp(re, (int)log2s), std::ldexp(im, (int)log2s));
-          }
-          if (q.log2s) *q.log2s = keep ? log2s : 0.0;
+          memcpy(q.out, h + (size_t)src * relems * esz, relems * esz);
+          if (q.log2s) *q.log2s = keep ? hs[src].log2s + fac.e : 0.0;
         }
         if (q.status) *q.status = TN_OK;
       }

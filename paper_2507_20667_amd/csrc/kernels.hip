@@ -863,6 +863,42 @@ hipError_t launch_results_to_c128(hipStream_t st, const Result *res, int64_t rbs
   return hipGetLastError();
 }
 
+// Open results in the caller's type: out[q * n + i] = v_q[i] fm (2^(l_q + fe)
+// folded in unless `keep`), rounded once from FP64, straight into the call's
+// pinned staging, from where the host only copies bytes: its loop over two
+// ldexp an entry took 2.1 ms for 426k entries.
+template <class T2, class T>
+__global__ __launch_bounds__(256) void k_results_out(Operand R, int64_t n, double fm, int fe, int keep, T2 *out) {
+  const int q = blockIdx.y;
+  const float2 *v = R.p + q * R.bs;
+  const int e = (int)(R.slot[q * R.sbs].log2s + fe);
+  T2 *o = out + q * n;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const float2 x = v[i];
+    double re = x.x * fm, im = x.y * fm;
+    if (!keep) {
+      re = ldexp(re, e);
+      im = ldexp(im, e);
+    }
+    T2 y;
+    y.x = (T)re;
+    y.y = (T)im;
+    o[i] = y;
+  }
+}
+
+hipError_t launch_results_out(hipStream_t st, Operand R, int nq, int64_t n, double fm, int fe, bool keep, bool c128,
+                              void *out) {
+  if (nq < 1 || n < 1) return hipSuccess;
+  if (nq > 65535) return hipErrorInvalidValue;
+  const dim3 grid(grid_for(n, 256, 1024), nq);
+  if (c128)
+    hipLaunchKernelGGL((k_results_out<double2, double>), grid, dim3(256), 0, st, R, n, fm, fe, keep ? 1 : 0, (double2 *)out);
+  else
+    hipLaunchKernelGGL((k_results_out<float2, float>), grid, dim3(256), 0, st, R, n, fm, fe, keep ? 1 : 0, (float2 *)out);
+  return hipGetLastError();
+}
+
 // ----------------------------------------------------------- slice sums
 // Slicing: the full contraction is the sum of its slices' (Section 2.2, a sum
 // over every bound index in any grouping).  The slice results carry scales

@@ -458,6 +458,12 @@ hipError_t launch_probe_mfma(hipStream_t st, int prec, bool random, float *out, 
 hipError_t launch_results_to_c128(hipStream_t st, const Result *res, int64_t rbs, int nq, double fm, int fe,
                                   double2 *out, int64_t stride);
 
+// open results of nq queries (n entries each, scale records R.slot) multiplied by
+// fm 2^fe, the scale folded in unless keep, as complex128 or complex64 at
+// out[q * n + i]
+hipError_t launch_results_out(hipStream_t st, Operand R, int nq, int64_t n, double fm, int fe, bool keep, bool c128,
+                              void *out);
+
 // Tile shape variants of the GEMM (index into a table in the kernel file).
 int gemm_num_variants();
 int gemm_variant_tile_m(int v);
