@@ -952,11 +952,14 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
         if (L.n_tree_perq) {
           tl.hdr = (const TreeHdr *)tb + L.n_tree_shared;
           tl.nq = Q;
-          // a single query runs the level kernel (its waves share the query)
-          const bool wave = L.tree_wave && Q > 1, single = L.tree_wave && Q == 1;
+          // a single query runs the level kernel (its waves share the query),
+          // and so do a few where that is faster and each has a CU of its own
+          // (make_exec_layout's estimate)
+          const bool few = Q == 1 || (L.tree_few && (int64_t)Q * L.n_tree_perq <= kTreeFew);
+          const bool wave = L.tree_wave && !few, single = L.tree_wave && few;
           tl.qw = single ? 1 : L.tree_qw;
           const size_t lds = single ? L.lds_perq1 : L.lds_perq;
-          TN_HIP(prof.timed(st, wave ? TN_KCLASS_TREE_BATCH : TN_KCLASS_TREE, tree_bytes_q * Q,
+          TN_HIP(prof.timed(st, L.tree_wave && Q > 1 ? TN_KCLASS_TREE_BATCH : TN_KCLASS_TREE, tree_bytes_q * Q,
                             tree_flops_q * Q,
                             [&] {
                               return wave ? launch_tree_wave(st, tl, L.n_tree_perq, lds)

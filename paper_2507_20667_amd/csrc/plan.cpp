@@ -1195,7 +1195,7 @@ static size_t tree_lds_bytes(int qw, int nscale, int shared_elems, int perq_elem
   size_t b = 0;
   if (!wave) {
     b += (size_t)2 * kTreeChunk * kTreeStepWords * 4;  // two chunk buffers
-    b += 256 * 16;                                      // FP64 reduction buffer
+    b += kTreeThreads / 64 * 16;                        // FP64 partial sums, one a wave
   }
   b += 8 * (size_t)r2((int64_t)qw * nscale);  // scale records
   b += 8 * (size_t)r2(shared_elems);
@@ -2132,6 +2132,39 @@ static void build_tree_programs(const tn_plan *p, ExecLayout &L, const std::vect
         fprintf(stderr, "[tn]   subtree root %d: batch program of %d steps (kind 5 chains: %d links; "
                 "kind 6 pairs: %d)\n", h.root_slot, h.wnsteps, (int)(crec.size() / 64), npairs);
     }
+  }
+  // Which kernel is the faster for queries that each have a CU of their own
+  // (TreeLaunch of at most one workgroup per CU).  In tenths of a
+  // microsecond: a level of the level kernel costs one barrier round (8; 11
+  // where the steps do not all fit in LDS), a step of the batch kernel 8.5, a
+  // chain link 4, and 64 result entries' term of a larger step 0.75, which
+  // the level kernel spreads over its 8 waves.  Measured at 2 queries, level
+  // against batch kernel: random 22/16 20.3 us against 50.6, phase 12/8 33.4
+  // against 126, random 18/10 20.2 against 22.2; brick 17/11 29.4 against
+  // 30.0; chains of gates the other way: brick 20/14 50.8 against 33.2.
+  L.tree_few = false;
+  if (L.tree_wave) {
+    double level = 0.0, batch = 0.0;  // of the subtree that takes longest
+    for (size_t hi = (size_t)L.n_tree_shared; hi < hdrs.size(); ++hi) {
+      const TreeHdr &h = hdrs[hi];
+      double wl = 0.0, wb = 0.0, steps_b = 0.0;
+      auto terms = [](const TreeStep &st) {
+        return ((st.nc + 63) / 64) * (st.kind == 2 ? (double)(1 << st.ns) : (double)st.ns);
+      };
+      for (int k = h.step0; k < h.step0 + h.nsteps; ++k)
+        if (steps[k].kind != 4) wl += terms(steps[k]);
+      for (int k = h.wstep0; k < h.wstep0 + h.wnsteps; ++k) {
+        if (steps[k].kind == 5) {
+          steps_b += 4.0 * steps[k].nc;
+        } else {
+          steps_b += 8.5;
+          if (steps[k].kind != 4) wb += terms(steps[k]);
+        }
+      }
+      level = std::max(level, (h.nsteps <= 2 * kTreeChunk ? 8.0 : 11.0) * h.nchunks + 0.75 * wl / 8);
+      batch = std::max(batch, steps_b + 0.75 * wb);
+    }
+    L.tree_few = level < batch;
   }
   if (getenv("TN_DEBUG"))
     for (const TreeHdr &h : hdrs) {

@@ -223,6 +223,9 @@ struct Result {
 constexpr int kTreeSeg = 6;
 constexpr int32_t kPerQuery = 1 << 30;
 constexpr int kTreeMaxElems = 4096;
+constexpr int kTreeThreads = 512;  // a workgroup of the level kernel
+// workgroups of per-query subtrees that run one to a CU (of 256) at once
+constexpr int kTreeFew = 256;
 constexpr int kTreeChunk = 16;     // steps of one level run between two barriers
 constexpr int kTreeMaxOvr = 64;    // overridden leaves read in place per launch
 // a per-query subtree's intermediates of at least this many entries live in

@@ -150,6 +150,7 @@ struct ExecLayout {
   size_t lds_perq1 = 0;                    // the per-query launch of a single query
   int tree_qw = 1;                         // queries per workgroup (per-query launch)
   bool tree_wave = false;                  // batches of queries run the wave kernel
+  bool tree_few = false;                   // but those of one workgroup per CU the level kernel
   bool conc = false;                       // partitions in regions of their own (concurrent)
   std::vector<int> spill;                  // per-query subtree vertices kept in device memory
   bool tree_reads_ovr = false;             // per-query subtrees load overridden leaves

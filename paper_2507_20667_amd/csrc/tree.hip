@@ -12,8 +12,9 @@
 // closed root, the FP64 inner product.
 //
 // Two ways to run the program:
-//  * k_tree (one query per launch: the shared subtrees, single queries): the
-//    four waves share the query.  The program runs level by level; the
+//  * k_tree (the shared subtrees, single queries, and a few queries of a CU
+//    each where a program's levels take less time than its steps one by one):
+//    the eight waves share the query.  The program runs level by level; the
 //    contractions of one level are independent, so up to kTreeChunk of them
 //    share one barrier.  The descriptors of the next chunk are fetched while
 //    the current one computes.
@@ -1008,36 +1009,37 @@ __device__ __forceinline__ void tree_emit_result(const TreeLaunch &t, int q, dou
 // the overridden leaves copied per query.  Loads are issued in groups of four
 // per thread before any of them is stored, so each part costs about one
 // round trip.  The caller places a barrier after it.
+template <int NT>
 __device__ __forceinline__ void tree_prologue(const TreeLaunch &t, KernargLaunch ka, const TreeHdr &h,
                                               int tid, int qw, int nqw, int q0, int2 *scl,
                                               float2 *shr, float2 *pq, int perq) {
   // the shared intermediates' records (indices below nsloads) are written
   // below, every other record starts at zero
-  for (int i = tid; i < qw * h.nscale; i += 256) {
+  for (int i = tid; i < qw * h.nscale; i += NT) {
     const int r = i % h.nscale;
     if (r >= h.nsloads) scl[i] = make_int2(0, 0);
   }
   const float2 *img = t.image + h.image_off;
-  for (int i0 = 0; i0 < h.nimg; i0 += 1024) {
+  for (int i0 = 0; i0 < h.nimg; i0 += 4 * NT) {
     float2 v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int i = i0 + tid + 256 * j;
+      const int i = i0 + tid + NT * j;
       if (i < h.nimg) v[j] = img[i];
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int i = i0 + tid + 256 * j;
+      const int i = i0 + tid + NT * j;
       if (i < h.nimg) shr[i] = v[j];
     }
   }
   const float2 *sbase = (const float2 *)t.shared_base;
-  for (int e0 = 0; e0 < h.nsg; e0 += 1024) {
+  for (int e0 = 0; e0 < h.nsg; e0 += 4 * NT) {
     int2 g[4];
     float2 v[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int e = e0 + tid + 256 * j;
+      const int e = e0 + tid + NT * j;
       g[j] = e < h.nsg ? t.sgather[h.sg0 + e] : make_int2(-1, 0);
     }
 #pragma unroll
@@ -1047,13 +1049,13 @@ __device__ __forceinline__ void tree_prologue(const TreeLaunch &t, KernargLaunch
     for (int j = 0; j < 4; ++j)
       if (g[j].x >= 0) shr[g[j].x] = v[j];
   }
-  for (int e = tid; e < h.nsloads * nqw; e += 256) {
+  for (int e = tid; e < h.nsloads * nqw; e += NT) {
     const int k = e / nqw, q = e - k * nqw;
     const int slot = t.sloads[h.sload0 + k].slot;
     const Slot z = t.slots_sh[slot];
     scl[q * h.nscale + k] = make_int2((int)z.log2s, (int)z.maxbits);
   }
-  for (int w = tid; w < h.nloads * nqw; w += 256) {
+  for (int w = tid; w < h.nloads * nqw; w += NT) {
     const int li = w / nqw, q = w - li * nqw;
     const TreeLeafLoad L = t.loads[h.load0 + li];
     const float2 *op = ka->ovr[L.src].p;
@@ -1065,10 +1067,11 @@ __device__ __forceinline__ void tree_prologue(const TreeLaunch &t, KernargLaunch
 }
 
 template <bool DEV>
-__global__ __launch_bounds__(256) void k_tree(TreeLaunch t) {
+__global__ __launch_bounds__(kTreeThreads) void k_tree(TreeLaunch t) {
   constexpr int W = kTreeStepWords;
   constexpr int CW = kTreeChunk * W;
-  constexpr int PRE = (CW + 255) / 256;
+  constexpr int NT = kTreeThreads;
+  constexpr int PRE = (CW + NT - 1) / NT;
   const int tid = threadIdx.x;
   const TreeHdr h = t.hdr[blockIdx.x];
   const int qw = t.qw;
@@ -1078,11 +1081,11 @@ __global__ __launch_bounds__(256) void k_tree(TreeLaunch t) {
   // argument segment rather than from a private copy of the argument
   KernargLaunch ka = (KernargLaunch)__builtin_amdgcn_kernarg_segment_ptr();
 
-  // LDS: [2 chunk buffers][reduction: 256 double2][scales: qw * nscale int2]
+  // LDS: [2 chunk buffers][partial sums: a double2 per wave][scales: qw * nscale int2]
   //      [shared region][qw per-query regions]
   int32_t *sbuf = (int32_t *)tree_lds;
   double2 *red = (double2 *)(tree_lds + 2 * CW * 4);
-  int2 *scl = (int2 *)(red + 256);
+  int2 *scl = (int2 *)(red + NT / 64);
   float2 *shr = (float2 *)(scl + ((qw * h.nscale + 1) & ~1));
   float2 *pq = shr + ((h.shared_elems + 1) & ~1);
   const int perq = (h.perq_elems + 1) & ~1;
@@ -1091,7 +1094,7 @@ __global__ __launch_bounds__(256) void k_tree(TreeLaunch t) {
   float2 *gq = (float2 *)(t.perq_base + (int64_t)q0 * t.perq_stride);
   const int64_t gstride = t.perq_stride / 8;
 
-  tree_prologue(t, ka, h, tid, qw, nqw, q0, scl, shr, pq, perq);
+  tree_prologue<NT>(t, ka, h, tid, qw, nqw, q0, scl, shr, pq, perq);
   // the program's kind 4 lane records: copied after the query regions
   // (16-byte aligned; the host sized the LDS for it) or read from device memory
   const TreeLaneRec *lrec = t.lanes;
@@ -1100,7 +1103,7 @@ __global__ __launch_bounds__(256) void k_tree(TreeLaunch t) {
     const size_t off = ((size_t)((const unsigned char *)(pq + qw * perq) - tree_lds) + 15) & ~(size_t)15;
     uint4 *dst = (uint4 *)(tree_lds + off);
     const uint4 *src = (const uint4 *)(t.lanes + h.rec0);
-    for (int i = tid; i < 2 * h.nrec; i += 256) dst[i] = src[i];
+    for (int i = tid; i < 2 * h.nrec; i += NT) dst[i] = src[i];
     lrec = (const TreeLaneRec *)dst;
     lrec0 = h.rec0;
   }
@@ -1116,7 +1119,7 @@ __global__ __launch_bounds__(256) void k_tree(TreeLaunch t) {
     cur = t.chunks[h.chunk0].nsteps;
     if (h.nchunks > 1) nxt = t.chunks[h.chunk0 + 1].nsteps;
     const int n = (whole ? h.nsteps : cur) * W;
-    for (int i = tid; i < n; i += 256) sbuf[i] = gw[(int64_t)s_cur * W + i];
+    for (int i = tid; i < n; i += NT) sbuf[i] = gw[(int64_t)s_cur * W + i];
   }
   __syncthreads();
 
@@ -1130,7 +1133,7 @@ __global__ __launch_bounds__(256) void k_tree(TreeLaunch t) {
       const int64_t s_nxt = s_cur + cur;
 #pragma unroll
       for (int j = 0; j < PRE; ++j) {
-        const int i = tid + 256 * j;
+        const int i = tid + NT * j;
         pre[j] = i < nxt * W ? gw[s_nxt * W + i] : 0;
       }
       if (k + 2 < h.nchunks) nxt2 = t.chunks[h.chunk0 + k + 2].nsteps;
@@ -1152,7 +1155,7 @@ __global__ __launch_bounds__(256) void k_tree(TreeLaunch t) {
         const float2 *A = (st.a & kPerQuery) ? base + (st.a & ~kPerQuery) : shr + st.a;
         const float2 *B = (st.b & kPerQuery) ? base + (st.b & ~kPerQuery) : shr + st.b;
         double re = 0.0, im = 0.0;
-        for (int s = tid; s < st.ns; s += 256) {
+        for (int s = tid; s < st.ns; s += NT) {
           int sa, sb;
           if (p2)
             seg2r<true>(ext, s0, s1, lg, st.nss, s, sa, sb);
@@ -1162,16 +1165,18 @@ __global__ __launch_bounds__(256) void k_tree(TreeLaunch t) {
           re += (double)x.x * y.x - (double)x.y * y.y;
           im += (double)x.x * y.y + (double)x.y * y.x;
         }
-        red[tid] = make_double2(re, im);
-        __syncthreads();
-        for (int r = 128; r > 0; r >>= 1) {
-          if (tid < r) {
-            red[tid].x += red[tid + r].x;
-            red[tid].y += red[tid + r].y;
-          }
-          __syncthreads();
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+          re += __shfl_xor(re, off, 64);
+          im += __shfl_xor(im, off, 64);
         }
+        if ((tid & 63) == 0) red[tid >> 6] = make_double2(re, im);
+        __syncthreads();
         if (tid == 0) {
+          for (int w = 1; w < NT / 64; ++w) {
+            red[0].x += red[w].x;
+            red[0].y += red[w].y;
+          }
           const int2 *sc = scl + q * h.nscale;
           const int2 za = st.asl >= 0 ? sc[st.asl] : make_int2(0, 0);
           const int2 zb = st.bsl >= 0 ? sc[st.bsl] : make_int2(0, 0);
@@ -1181,19 +1186,19 @@ __global__ __launch_bounds__(256) void k_tree(TreeLaunch t) {
       }
     } else if (cur == 1) {
       // one step (a spine contraction): the whole workgroup on it
-      tree_step<DEV>(S, tid, 256, nqw, pq, perq, shr, scl, h.nscale, gq, gstride, lrec, lrec0);
+      tree_step<DEV>(S, tid, NT, nqw, pq, perq, shr, scl, h.nscale, gq, gstride, lrec, lrec0);
     } else {
       // several independent steps of one level (largest first): one wave per
       // step, round robin
       const int wave = tid >> 6, lane = tid & 63;
-      for (int i = wave; i < cur; i += 4)
+      for (int i = wave; i < cur; i += NT / 64)
         tree_step<DEV>(S + i, lane, 64, nqw, pq, perq, shr, scl, h.nscale, gq, gstride, lrec, lrec0);
     }
     if (k + 1 < h.nchunks && !whole) {
       int32_t *dst = sbuf + ((k + 1) & 1) * CW;
 #pragma unroll
       for (int j = 0; j < PRE; ++j) {
-        const int i = tid + 256 * j;
+        const int i = tid + NT * j;
         if (i < nxt * W) dst[i] = pre[j];
       }
     }
@@ -1206,7 +1211,7 @@ __global__ __launch_bounds__(256) void k_tree(TreeLaunch t) {
   // the subtree's result and its scale record to device memory
   if (!h.final_dot) {
     const int rl = h.root_loc & ~kPerQuery;
-    for (int w = tid; w < nqw * h.root_elems; w += 256) {
+    for (int w = tid; w < nqw * h.root_elems; w += NT) {
       const int q = w / h.root_elems, i = w - q * h.root_elems;
       uint8_t *part = h.root_in_perq ? t.perq_base + (int64_t)(q0 + q) * t.perq_stride : t.shared_base;
       ((float2 *)(part + h.root_off))[i] = pq[q * perq + rl + i];
@@ -1249,7 +1254,7 @@ __global__ __launch_bounds__(256) void k_tree_wave(TreeLaunch t) {
     shr = (float2 *)(scl + ((qw * h.nscale + 1) & ~1));
     pq = shr + ((h.shared_elems + 1) & ~1);
     perq = (h.perq_elems + 1) & ~1;
-    tree_prologue(t, ka, h, tid, qw, nqw, q0, scl, shr, pq, perq);
+    tree_prologue<256>(t, ka, h, tid, qw, nqw, q0, scl, shr, pq, perq);
   }
   __syncthreads();
 
@@ -1413,9 +1418,9 @@ hipError_t launch_tree(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds
   if (lds_bytes > tree_lds_limit()) return hipErrorInvalidValue;
   const int groups = (t.nq + t.qw - 1) / t.qw;
   if (dev)
-    hipLaunchKernelGGL(k_tree<true>, dim3(nsub, groups), dim3(256), lds_bytes, st, t);
+    hipLaunchKernelGGL(k_tree<true>, dim3(nsub, groups), dim3(kTreeThreads), lds_bytes, st, t);
   else
-    hipLaunchKernelGGL(k_tree<false>, dim3(nsub, groups), dim3(256), lds_bytes, st, t);
+    hipLaunchKernelGGL(k_tree<false>, dim3(nsub, groups), dim3(kTreeThreads), lds_bytes, st, t);
   return hipGetLastError();
 }
 
