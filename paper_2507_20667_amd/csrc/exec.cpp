@@ -920,6 +920,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
         tl.sgather = (const int2 *)(tb + L.tree_sg_off);
         tl.image = (const float2 *)(tb + L.tree_img_off);
         tl.lanes = (const TreeLaneRec *)(tb + L.tree_lane_off);
+        tl.wsegs = (const TreeSeg *)(tb + L.tree_seg_off);
         // overridden leaves in id order: read in place or from the staging block
         for (size_t k = 0; k < ovr.size() && k < (size_t)kTreeMaxOvr; ++k) {
           const int t = ovr[k];
@@ -952,18 +953,18 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
         if (L.n_tree_perq) {
           tl.hdr = (const TreeHdr *)tb + L.n_tree_shared;
           tl.nq = Q;
-          // a single query runs the level kernel (its waves share the query),
-          // and so do a few where that is faster and each has a CU of its own
-          // (make_exec_layout's estimate)
-          const bool few = Q == 1 || (L.tree_few && (int64_t)Q * L.n_tree_perq <= kTreeFew);
+          // one query or a few run the level kernel (a workgroup's waves share
+          // the query) where that is faster and each has a CU of its own
+          // (build_tree_programs' estimate)
+          const bool few = L.tree_few && (int64_t)Q * L.n_tree_perq <= kTreeFew;
           const bool wave = L.tree_wave && !few, single = L.tree_wave && few;
           tl.qw = single ? 1 : L.tree_qw;
           const size_t lds = single ? L.lds_perq1 : L.lds_perq;
           TN_HIP(prof.timed(st, L.tree_wave && Q > 1 ? TN_KCLASS_TREE_BATCH : TN_KCLASS_TREE, tree_bytes_q * Q,
                             tree_flops_q * Q,
                             [&] {
-                              return wave ? launch_tree_wave(st, tl, L.n_tree_perq, lds)
-                                          : launch_tree(st, tl, L.n_tree_perq, lds, true);
+                              return wave ? launch_tree_wave(st, tl, L.n_tree_perq, lds, !L.spill.empty())
+                                          : launch_tree(st, tl, L.n_tree_perq, lds, !L.spill.empty());
                             }),
                  "subtree kernel");
         }

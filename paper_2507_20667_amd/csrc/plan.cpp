@@ -1927,7 +1927,7 @@ static void build_tree_programs(const tn_plan *p, ExecLayout &L, const std::vect
   // (a gate chain: one consumer per vertex, so no other step reads the
   // results inside the run) becomes one kind 5 step whose running tensor
   // stays in registers.  Its records: 64 per link (lanes past a link's
-  // entries are copies of its first record), w[6] = ns | nc << 8; after the
+  // entries are copies of its first record); after the
   // first link the X terms name the lanes of the link before that hold them
   // (lane * 4, the ds_bpermute address).  The level kernel, which runs the
   // same programs for single queries and the shared subtrees, keeps the
@@ -1940,6 +1940,7 @@ static void build_tree_programs(const tn_plan *p, ExecLayout &L, const std::vect
   // Q's products (checked here by enumerating them), and no other step reads
   // T or its scale record.  The batch kernel then keeps T in registers
   // (tree_pair).  TN_TREE_PAIR=0 turns pairs off.
+  std::vector<TreeLaneRec> crec;  // kind 5 links
   {
     const bool chain_on = !getenv("TN_TREE_CHAIN") || atoi(getenv("TN_TREE_CHAIN")) != 0;
     const bool pair_on = !getenv("TN_TREE_PAIR") || atoi(getenv("TN_TREE_PAIR")) != 0;
@@ -1977,7 +1978,7 @@ static void build_tree_programs(const tn_plan *p, ExecLayout &L, const std::vect
         return true;
       };
       std::vector<TreeStep> prog;
-      std::vector<TreeLaneRec> crec;
+      const size_t crec0 = crec.size();
       bool any = false;
       int npairs = 0;
       const int kend = h.step0 + h.nsteps;
@@ -2099,7 +2100,7 @@ static void build_tree_programs(const tn_plan *p, ExecLayout &L, const std::vect
         ps.kind = 5;
         ps.nc = k2 - k + 1;  // links
         ps.ns = 4;
-        ps.tab = (int32_t)(lanes.size() + crec.size());
+        ps.tab = (int32_t)crec.size();
         for (int j = k; j <= k2; ++j) {
           const TreeStep &st = steps[j];
           std::map<uint32_t, int> m;
@@ -2114,8 +2115,8 @@ static void build_tree_programs(const tn_plan *p, ExecLayout &L, const std::vect
               r.w[0] = a[0] | a[1] << 16;
               r.w[4] = a[2] | a[3] << 16;
             }
-            r.w[6] = (uint32_t)st.ns | (uint32_t)st.nc << 8;
-            r.w[7] = 0;
+            r.w[6] = (uint32_t)st.ns | (uint32_t)st.nc << 8 |
+                     ((j > k ? kBlkChained : 0u) | (j == k2 ? kBlkStore : 0u)) << 16;
             crec.push_back(r);
           }
         }
@@ -2127,21 +2128,52 @@ static void build_tree_programs(const tn_plan *p, ExecLayout &L, const std::vect
       h.wstep0 = (int32_t)steps.size();
       h.wnsteps = (int32_t)prog.size();
       steps.insert(steps.end(), prog.begin(), prog.end());
-      lanes.insert(lanes.end(), crec.begin(), crec.end());
       if (getenv("TN_DEBUG"))
         fprintf(stderr, "[tn]   subtree root %d: batch program of %d steps (kind 5 chains: %d links; "
-                "kind 6 pairs: %d)\n", h.root_slot, h.wnsteps, (int)(crec.size() / 64), npairs);
+                "kind 6 pairs: %d)\n", h.root_slot, h.wnsteps, (int)((crec.size() - crec0) / 64), npairs);
     }
   }
+  // The batch kernel's streams (TreeSeg)
+  std::vector<TreeSeg> segs;
+  for (size_t hi = (size_t)L.n_tree_shared; hi < hdrs.size() && L.tree_wave; ++hi) {
+    TreeHdr &h = hdrs[hi];
+    h.wrec0 = (int32_t)lanes.size();
+    h.wseg0 = (int32_t)segs.size();
+    TreeSeg sg{0, -1};
+    const int nw = h.wnsteps - (h.final_dot ? 1 : 0);
+    for (int k = 0; k < nw; ++k) {
+      const TreeStep &st = steps[h.wstep0 + k];
+      if (st.kind == 4) {
+        for (int l = 0; l < 64; ++l) {
+          TreeLaneRec r = lanes[st.tab + (l < st.nc ? l : 0)];
+          r.w[6] = (uint32_t)st.ns | (uint32_t)st.nc << 8 | (st.nss ? kBlkStore : kBlkPacked) << 16;
+          lanes.push_back(r);
+        }
+        ++sg.nblk;
+      } else if (st.kind == 5) {
+        lanes.insert(lanes.end(), crec.begin() + st.tab, crec.begin() + st.tab + 64 * (size_t)st.nc);
+        sg.nblk += st.nc;
+      } else {
+        sg.step = k;
+        segs.push_back(sg);
+        sg = TreeSeg{0, -1};
+        if (st.kind == 6) ++k;  // with its consumer
+      }
+    }
+    if (sg.nblk) segs.push_back(sg);
+    h.nwseg = (int32_t)segs.size() - h.wseg0;
+  }
+  if (!segs.empty()) lanes.resize(lanes.size() + kBlkAhead * 64);
   // Which kernel is the faster for queries that each have a CU of their own
   // (TreeLaunch of at most one workgroup per CU).  In tenths of a
   // microsecond: a level of the level kernel costs one barrier round (8; 11
-  // where the steps do not all fit in LDS), a step of the batch kernel 8.5, a
-  // chain link 4, and 64 result entries' term of a larger step 0.75, which
-  // the level kernel spreads over its 8 waves.  Measured at 2 queries, level
-  // against batch kernel: random 22/16 20.3 us against 50.6, phase 12/8 33.4
-  // against 126, random 18/10 20.2 against 22.2; brick 17/11 29.4 against
-  // 30.0; chains of gates the other way: brick 20/14 50.8 against 33.2.
+  // where the steps do not all fit in LDS), a block of the batch kernel's
+  // stream 4.3, another step 8.5, and 64 result entries' term of such a step
+  // 0.75, which the level kernel spreads over its 8 waves.  Measured at 2
+  // queries, level against batch kernel: random 22/16 20.3 us against 50.6,
+  // phase 12/8 33.4 against 126, random 18/10 20.2 against 20.5; gate
+  // sequences the other way: brick 17/11 29.4 against 20.4, brick 20/14 50.8
+  // against 27.4.
   L.tree_few = false;
   if (L.tree_wave) {
     double level = 0.0, batch = 0.0;  // of the subtree that takes longest
@@ -2154,11 +2186,11 @@ static void build_tree_programs(const tn_plan *p, ExecLayout &L, const std::vect
       for (int k = h.step0; k < h.step0 + h.nsteps; ++k)
         if (steps[k].kind != 4) wl += terms(steps[k]);
       for (int k = h.wstep0; k < h.wstep0 + h.wnsteps; ++k) {
-        if (steps[k].kind == 5) {
-          steps_b += 4.0 * steps[k].nc;
+        if (steps[k].kind == 4 || steps[k].kind == 5) {
+          steps_b += 4.3 * (steps[k].kind == 5 ? steps[k].nc : 1);
         } else {
           steps_b += 8.5;
-          if (steps[k].kind != 4) wb += terms(steps[k]);
+          wb += terms(steps[k]);
         }
       }
       level = std::max(level, (h.nsteps <= 2 * kTreeChunk ? 8.0 : 11.0) * h.nchunks + 0.75 * wl / 8);
@@ -2227,6 +2259,7 @@ static void build_tree_programs(const tn_plan *p, ExecLayout &L, const std::vect
   L.tree_sg_off = put(sgather.data(), sgather.size() * sizeof(int2));
   L.tree_img_off = put(image.data(), image.size() * sizeof(float2));
   L.tree_lane_off = put(lanes.data(), lanes.size() * sizeof(TreeLaneRec));
+  L.tree_seg_off = put(segs.data(), segs.size() * sizeof(TreeSeg));
 }
 
 ExecLayout make_exec_layout(const tn_plan *p, const std::vector<int> &overridden, bool share,

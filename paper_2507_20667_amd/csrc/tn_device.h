@@ -272,7 +272,7 @@ struct TreeStep {
 };
 
 // A kind 4 lane's record (32 bytes); kind 5 links use the same layout (see
-// tree_chain in tree.hip).  Each address is a 16-bit byte offset in
+// tree_block in tree.hip).  Each address is a 16-bit byte offset in
 // its operand's LDS region.  w[0]: xa_0 | xa_1 << 16, w[1]: ya_0 | ya_1 << 16,
 // w[2]: c (query region) | csl << 16 | (the step's first entry) << 31,
 // w[3]: asl | (X in the shared region) << 15 | bsl << 16 | (Y in the shared
@@ -317,8 +317,22 @@ struct TreeHdr {
   int32_t rec0, nrec;                // kind 4 lane records [rec0, rec0 + nrec)
   int32_t rec_lds;                   // the level kernel copies them into LDS
   int32_t wstep0, wnsteps;           // the batch kernel's program (kind 5 chains)
-  int32_t pad;
+  int32_t wrec0;                     // its stream: lane records, 64 a block
+  int32_t wseg0, nwseg;              // (TreeSeg [wseg0, wseg0 + nwseg))
 };
+
+// The batch kernel's program as it reads it: the kind 4 steps and kind 5 links
+// in program order, one block of 64 lane records each (lanes past a block's
+// entries hold copies of its first), cut where another kind of step stands.
+// w[6] of each record: ns | nc << 8 | flags << 16.
+struct TreeSeg {
+  int32_t nblk;  // blocks of this segment
+  int32_t step;  // the step that follows them, from wstep0 (-1: none)
+};
+constexpr uint32_t kBlkChained = 1;  // X terms in the lanes of the block before
+constexpr uint32_t kBlkStore = 2;    // writes its entries and scale record
+constexpr uint32_t kBlkPacked = 4;   // entries of several steps
+constexpr int kBlkAhead = 3;         // blocks in flight, readable past a stream's end
 
 // A shared intermediate that a per-query subtree takes as an input: computed
 // once by the shared launch, read from the shared part into the LDS shared
@@ -345,6 +359,7 @@ struct TreeLaunch {
   const int2 *sgather;  // (LDS float2 offset, shared-part float2 offset) per entry
   const float2 *image;  // shared leaves of every subtree, each in its LDS order
   const TreeLaneRec *lanes;  // kind 4 lane records
+  const TreeSeg *wsegs;      // the batch kernel's segments
   OvrSrc ovr[kTreeMaxOvr];
   uint8_t *shared_base;
   uint8_t *perq_base;
@@ -437,7 +452,7 @@ hipError_t launch_dot(hipStream_t st, const DotDesc *d_desc, int64_t nelem, Oper
 hipError_t launch_tree(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes, bool dev);
 // Per-query launches: every wave takes ceil(qw / 4) queries of its workgroup
 // through the whole program on its own (no barrier after the leaves load).
-hipError_t launch_tree_wave(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes);
+hipError_t launch_tree_wave(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes, bool dev);
 size_t tree_lds_limit();
 
 // The static scratch array of tn_contract_strided_noalloc (kernels.hip): its

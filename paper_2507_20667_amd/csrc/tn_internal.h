@@ -137,6 +137,7 @@ struct ExecLayout {
   std::vector<uint8_t> tree_blob;
   size_t tree_chunk_off = 0, tree_step_off = 0, tree_load_off = 0, tree_img_off = 0;
   size_t tree_lane_off = 0;  // kind 4 lane records
+  size_t tree_seg_off = 0;   // the batch kernel's segments
   // algorithmic bytes and flops of the shared and of one query's subtree
   // launch (profiler), filled on first use under the plan's cache lock
   bool tree_acct = false;

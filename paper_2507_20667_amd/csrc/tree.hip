@@ -21,11 +21,15 @@
 //  * k_tree_wave (a batch of queries): every wave takes its own queries
 //    through the whole program, one step after the other, with no barrier
 //    after the leaves are in LDS: a wave's LDS accesses complete in order, so
-//    a step reads what the wave's earlier steps wrote.  The descriptors are
-//    uniform across the wave and are read with scalar loads.  A chain of
-//    small contractions (a gate sequence) then costs one wave's latency per
-//    step instead of a workgroup barrier and a descriptor round trip, and the
-//    other waves of the CU fill the gaps.
+//    a step reads what the wave's earlier steps wrote.  A small contraction (a
+//    gate) then costs one wave's latency per step instead of a workgroup
+//    barrier, and the other waves of the CU fill the gaps.  The gates come as
+//    a stream of lane records read three blocks ahead; only the other steps
+//    read a descriptor, with scalar loads.  (With a descriptor and a record
+//    read one step ahead, every step waited for both: 0.75 us a step, now
+//    0.43.  Kernel times at 1024 queries: brick 17/11 30.9 -> 20.8 us, brick
+//    20/14 34.5 -> 29.0; at 4096 brick 20/14 45 -> 42, where the waves' issue
+//    slots are shared by four.)
 //
 // Scales: every intermediate keeps a running integer log2 scale and the IEEE
 // bits of its max |re|/|im|; a consumer multiplies its operands by 2^-e
@@ -39,6 +43,7 @@ extern __shared__ __align__(16) unsigned char tree_lds[];
 typedef const TreeLaunch __attribute__((address_space(4))) *KernargLaunch;
 // step descriptors through the scalar cache (read only, uniform per wave)
 typedef const TreeStep __attribute__((address_space(4))) *CStep;
+typedef const TreeSeg __attribute__((address_space(4))) *CSeg;
 
 // Index arithmetic: every offset, stride and index of a subtree is far below
 // 2^24, so the full-rate 24-bit multiply-add serves (the 32-bit integer
@@ -601,111 +606,82 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
   return max(max(r0, r1), max(r2, r3));
 }
 
-// Kind 4 holding one whole kind 2 step (nss = 1), run by a whole wave (lanes
-// past nc inactive in the arithmetic only): the operand scales are the same
-// for every lane, and the wave writes the result's scale record with one
-// store, its max reduced across the wave, instead of one LDS atomic per lane
-// on one word.
-template <int NS>
-__device__ __forceinline__ void tree_lane_whole(uint4 r0, uint4 r1, bool act, int lane, float2 *pq,
-                                                const float2 *shr, int2 *scl) {
-  const uint32_t w3 = (uint32_t)__builtin_amdgcn_readfirstlane((int)r0.w);  // lane 0 is active
-  const uint32_t wz = (uint32_t)__builtin_amdgcn_readfirstlane((int)r0.z);
-  const int2 za = scl[w3 & 0x7fffu], zb = scl[(w3 >> 16) & 0x7fffu];
-  const int zax = __builtin_amdgcn_readfirstlane(za.x), zay = __builtin_amdgcn_readfirstlane(za.y);
-  const int zbx = __builtin_amdgcn_readfirstlane(zb.x), zby = __builtin_amdgcn_readfirstlane(zb.y);
-  const int e = tn_scale_exp((uint32_t)zay) + tn_scale_exp((uint32_t)zby);
-  float m = 0.f;
-  if (act) {
-    const char *xb = (const char *)((w3 & 0x8000u) ? shr : pq);
-    const char *yb = (const char *)((w3 >> 31) ? shr : pq);
-    auto at = [](const char *base, uint32_t off) -> float2 { return *(const float2 *)(base + off); };
-    float2 x[NS], y[NS];
-    x[0] = at(xb, r0.x & 0xffffu);
-    y[0] = at(yb, r0.y & 0xffffu);
-    if (NS >= 2) {
-      x[1] = at(xb, r0.x >> 16);
-      y[1] = at(yb, r0.y >> 16);
+// One block of the batch kernel's stream (a kind 4 step or a kind 5 link), run
+// by a whole wave; r0, r1: the lane's record.
+//
+// A whole kind 2 step (kind 4, nss = 1): the operand scales are the same for
+// every lane, and the wave writes the result's scale record with one store,
+// its max reduced across the wave, instead of one LDS atomic per lane on one
+// word.
+//
+// A link of a kind 5 chain, in which every step after the first takes the
+// previous one's result as its X operand: the running tensor stays in
+// registers (vre, vim; lane l holds the entry its record names) and its scale
+// record in scalar registers (zx, zy).  A link reads its X terms from the
+// lanes that hold them (ds_bpermute, w[0] and w[4] the source lanes times 4,
+// prepared on the host), its Y terms (the gate's entries) from LDS.  Only the
+// last link writes its result and scale record to LDS: no other step reads
+// the others (each vertex has one consumer).  Term order, scaling and the
+// wave-wide max are those of the kind 4 steps it replaces, so the results are
+// the same bit for bit.
+//
+// Every choice is uniform across the wave, and the forms share this one body:
+// the stream's loop holds it kBlkAhead times.
+__device__ __forceinline__ void tree_block(uint4 r0, uint4 r1, int lane, float2 *pq, const float2 *shr,
+                                           int2 *scl, float &vre, float &vim, int &zx, int &zy) {
+  const uint32_t w6 = (uint32_t)__builtin_amdgcn_readfirstlane((int)r1.z);
+  const int ns = w6 & 0xffu;
+  const bool act = lane < (int)((w6 >> 8) & 0xffu);
+  if (w6 & kBlkPacked << 16) {
+    if (act) {
+      if (ns == 1)
+        tree_lane_exec<1>(r0, r1, pq, shr, scl);
+      else if (ns == 2)
+        tree_lane_exec<2>(r0, r1, pq, shr, scl);
+      else
+        tree_lane_exec<4>(r0, r1, pq, shr, scl);
     }
-    if (NS == 4) {
-      x[2] = at(xb, r1.x & 0xffffu);
-      x[3] = at(xb, r1.x >> 16);
+    return;
+  }
+  const uint32_t w3 = (uint32_t)__builtin_amdgcn_readfirstlane((int)r0.w);
+  const uint32_t wz = (uint32_t)__builtin_amdgcn_readfirstlane((int)r0.z);
+  const int2 zb = scl[(w3 >> 16) & 0x7fffu];
+  const char *yb = (const char *)((w3 >> 31) ? shr : pq);
+  auto at = [](const char *base, uint32_t off) -> float2 { return *(const float2 *)(base + off); };
+  float2 x[4], y[4];
+  y[0] = at(yb, r0.y & 0xffffu);
+  if (ns >= 2) {
+    y[1] = at(yb, r0.y >> 16);
+    if (ns == 4) {
       y[2] = at(yb, r1.y & 0xffffu);
       y[3] = at(yb, r1.y >> 16);
     }
-    const float f = ldexpf(1.0f, -e);
-    float re = 0.f, im = 0.f;
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      re = fmaf(x[s].x, y[s].x, re);
-      re = fmaf(-x[s].y, y[s].y, re);
-      im = fmaf(x[s].x, y[s].y, im);
-      im = fmaf(x[s].y, y[s].x, im);
-    }
-    re *= f;
-    im *= f;
-    *(float2 *)((char *)pq + (r0.z & 0xffffu)) = make_float2(re, im);
-    m = fmaxf(fabsf(re), fabsf(im));
   }
-  const unsigned mx = wave_max_u32(__float_as_uint(m));
-  if (lane == 0) scl[(wz >> 16) & 0x7fffu] = make_int2(zax + zbx + e, (int)mx);
-}
-
-// Kind 5 (the batch kernel's program only): a chain of whole-vertex gate
-// steps in which every step after the first takes the previous one's result
-// as its X operand.  The running tensor stays in registers (lane l holds the
-// entry its record names); a link reads its X terms from the lanes that hold
-// them (ds_bpermute, the source lanes prepared on the host), its Y terms (the
-// gate's entries) from LDS, and its X scale record from the link before (in
-// scalar registers).  Only the last link writes its result and scale record
-// to LDS: no other step reads the others (each vertex has one consumer).
-// Term order, scaling and the wave-wide max are those of the kind 4 steps it
-// replaces, so the results are the same bit for bit.  Link j's records are
-// the 64 at rec + 64 j: w[0], w[4] the X terms (link 0: byte offsets in the
-// X region; later links: source lane * 4), w[1], w[5] the Y byte offsets,
-// w[2], w[3] as in kind 4, w[6] = ns | nc << 8 (lanes past nc are padding
-// with valid offsets, inactive in the result).
-template <int NS, bool FIRST, bool LAST>
-__device__ __forceinline__ void chain_link(uint4 a0, uint4 a1, int lane, float2 *pq, const float2 *shr,
-                                           int2 *scl, float &vre, float &vim, int &zx, int &zy) {
-  const uint32_t w3 = (uint32_t)__builtin_amdgcn_readfirstlane((int)a0.w);
-  const uint32_t wz = (uint32_t)__builtin_amdgcn_readfirstlane((int)a0.z);
-  const int nc = (__builtin_amdgcn_readfirstlane((int)a1.z) >> 8) & 0xff;
-  const bool act = lane < nc;
-  const int2 zb = scl[(w3 >> 16) & 0x7fffu];
-  int2 za = make_int2(0, 0);
-  if (FIRST) za = scl[w3 & 0x7fffu];
-  const char *yb = (const char *)((w3 >> 31) ? shr : pq);
-  auto at = [](const char *base, uint32_t off) -> float2 { return *(const float2 *)(base + off); };
-  float2 x[NS], y[NS];
-  y[0] = at(yb, a0.y & 0xffffu);
-  if (NS >= 2) y[1] = at(yb, a0.y >> 16);
-  if (NS == 4) {
-    y[2] = at(yb, a1.y & 0xffffu);
-    y[3] = at(yb, a1.y >> 16);
-  }
-  if (FIRST) {
-    const char *xb = (const char *)((w3 & 0x8000u) ? shr : pq);
-    x[0] = at(xb, a0.x & 0xffffu);
-    if (NS >= 2) x[1] = at(xb, a0.x >> 16);
-    if (NS == 4) {
-      x[2] = at(xb, a1.x & 0xffffu);
-      x[3] = at(xb, a1.x >> 16);
-    }
-  } else {
+  if (w6 & kBlkChained << 16) {
     const int ir = __float_as_int(vre), ii = __float_as_int(vim);
     auto from = [&](uint32_t addr) {
       return make_float2(__int_as_float(__builtin_amdgcn_ds_bpermute((int)addr, ir)),
                          __int_as_float(__builtin_amdgcn_ds_bpermute((int)addr, ii)));
     };
-    x[0] = from(a0.x & 0xffffu);
-    if (NS >= 2) x[1] = from(a0.x >> 16);
-    if (NS == 4) {
-      x[2] = from(a1.x & 0xffffu);
-      x[3] = from(a1.x >> 16);
+    x[0] = from(r0.x & 0xffffu);
+    if (ns >= 2) {
+      x[1] = from(r0.x >> 16);
+      if (ns == 4) {
+        x[2] = from(r1.x & 0xffffu);
+        x[3] = from(r1.x >> 16);
+      }
     }
-  }
-  if (FIRST) {
+  } else {
+    const int2 za = scl[w3 & 0x7fffu];
+    const char *xb = (const char *)((w3 & 0x8000u) ? shr : pq);
+    x[0] = at(xb, r0.x & 0xffffu);
+    if (ns >= 2) {
+      x[1] = at(xb, r0.x >> 16);
+      if (ns == 4) {
+        x[2] = at(xb, r1.x & 0xffffu);
+        x[3] = at(xb, r1.x >> 16);
+      }
+    }
     zx = __builtin_amdgcn_readfirstlane(za.x);
     zy = __builtin_amdgcn_readfirstlane(za.y);
   }
@@ -713,12 +689,19 @@ __device__ __forceinline__ void chain_link(uint4 a0, uint4 a1, int lane, float2 
   const int e = tn_scale_exp((uint32_t)zy) + tn_scale_exp((uint32_t)zby);
   const float f = ldexpf(1.0f, -e);
   float re = 0.f, im = 0.f;
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    re = fmaf(x[s].x, y[s].x, re);
-    re = fmaf(-x[s].y, y[s].y, re);
-    im = fmaf(x[s].x, y[s].y, im);
-    im = fmaf(x[s].y, y[s].x, im);
+  auto term = [&](const float2 &a, const float2 &b) {
+    re = fmaf(a.x, b.x, re);
+    re = fmaf(-a.y, b.y, re);
+    im = fmaf(a.x, b.y, im);
+    im = fmaf(a.y, b.x, im);
+  };
+  term(x[0], y[0]);
+  if (ns >= 2) {
+    term(x[1], y[1]);
+    if (ns == 4) {
+      term(x[2], y[2]);
+      term(x[3], y[3]);
+    }
   }
   re *= f;
   im *= f;
@@ -726,48 +709,12 @@ __device__ __forceinline__ void chain_link(uint4 a0, uint4 a1, int lane, float2 
   const unsigned mx = wave_max_u32(__float_as_uint(m));
   zx = zx + zbx + e;
   zy = (int)mx;
-  if (LAST) {
-    if (act) *(float2 *)((char *)pq + (a0.z & 0xffffu)) = make_float2(re, im);
+  if (w6 & kBlkStore << 16) {
+    if (act) *(float2 *)((char *)pq + (r0.z & 0xffffu)) = make_float2(re, im);
     if (lane == 0) scl[(wz >> 16) & 0x7fffu] = make_int2(zx, zy);
   }
   vre = re;
   vim = im;
-}
-
-template <bool FIRST, bool LAST>
-__device__ __forceinline__ void chain_link_ns(int ns, uint4 a0, uint4 a1, int lane, float2 *pq,
-                                              const float2 *shr, int2 *scl, float &vre, float &vim, int &zx,
-                                              int &zy) {
-  if (ns == 1)
-    chain_link<1, FIRST, LAST>(a0, a1, lane, pq, shr, scl, vre, vim, zx, zy);
-  else if (ns == 2)
-    chain_link<2, FIRST, LAST>(a0, a1, lane, pq, shr, scl, vre, vim, zx, zy);
-  else
-    chain_link<4, FIRST, LAST>(a0, a1, lane, pq, shr, scl, vre, vim, zx, zy);
-}
-
-// A whole kind 5 step: `nlinks` links, link 0's record prefetched in r0, r1;
-// each later link's record is loaded while the link before runs.
-__device__ __forceinline__ void tree_chain(const TreeLaneRec *rec, int nlinks, uint4 r0, uint4 r1, int lane,
-                                           float2 *pq, const float2 *shr, int2 *scl) {
-  float vre = 0.f, vim = 0.f;
-  int zx = 0, zy = 0;
-  uint4 n0 = r0, n1 = r1;
-  for (int j = 0; j < nlinks; ++j) {
-    const uint4 a0 = n0, a1 = n1;
-    if (j + 1 < nlinks) {
-      const uint4 *nx = (const uint4 *)(rec + (j + 1) * 64 + lane);
-      n0 = nx[0];
-      n1 = nx[1];
-    }
-    const int ns = __builtin_amdgcn_readfirstlane((int)a1.z) & 0xff;
-    if (j == 0)
-      chain_link_ns<true, false>(ns, a0, a1, lane, pq, shr, scl, vre, vim, zx, zy);
-    else if (j + 1 < nlinks)
-      chain_link_ns<false, false>(ns, a0, a1, lane, pq, shr, scl, vre, vim, zx, zy);
-    else
-      chain_link_ns<false, true>(ns, a0, a1, lane, pq, shr, scl, vre, vim, zx, zy);
-  }
 }
 
 template <int NS>
@@ -778,8 +725,8 @@ __device__ __forceinline__ void tree_lane_step(const TreeLaneRec *rec, int lane,
   tree_lane_exec<NS>(r[0], NS == 4 ? r[1] : make_uint4(0u, 0u, 0u, 0u), pq, shr, scl);
 }
 
-// DEV: the program may hold kind 3 steps (per-query subtrees; a shared
-// subtree never does, and its launch leaves that code out)
+// DEV: the program may hold kind 3 steps (per-query subtrees with
+// intermediates in device memory; other launches leave that code out)
 // A kind 3 step (operands in the query's device workspace), whatever its
 // kind field says (a kind 6 pair runs as two of these when a wave holds more
 // than one query).
@@ -1228,7 +1175,8 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree(TreeLaunch t) {
   }
 }
 
-__global__ __launch_bounds__(256) void k_tree_wave(TreeLaunch t) {
+template <bool DEV>
+__global__ __launch_bounds__(256, DEV ? 3 : 4) void k_tree_wave(TreeLaunch t) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1239,7 +1187,7 @@ __global__ __launch_bounds__(256) void k_tree_wave(TreeLaunch t) {
   const int nqw = min(qw, t.nq - q0);
   KernargLaunch ka = (KernargLaunch)__builtin_amdgcn_kernarg_segment_ptr();
 
-  int nscale, nsteps, step0, final_dot;
+  int nscale, nsteps, step0, final_dot, wrec0, wseg0, nwseg;
   int2 *scl;
   float2 *shr, *pq;
   int perq;
@@ -1248,6 +1196,9 @@ __global__ __launch_bounds__(256) void k_tree_wave(TreeLaunch t) {
     nscale = h.nscale;
     nsteps = h.wnsteps;  // this kernel's form of the program (with kind 5 chains)
     step0 = h.wstep0;
+    wrec0 = h.wrec0;
+    wseg0 = h.wseg0;
+    nwseg = h.nwseg;
     final_dot = h.final_dot;
     // LDS: [scales: qw * nscale int2][shared region][qw per-query regions]
     scl = (int2 *)tree_lds;
@@ -1265,68 +1216,60 @@ __global__ __launch_bounds__(256) void k_tree_wave(TreeLaunch t) {
   float2 *wpq = pq + wq0 * perq;
   int2 *wscl = scl + wq0 * nscale;
   const CStep prog = (CStep)t.steps + step0;
-  // a closed root is the program's last step (checked on the host): it runs
-  // after the loop
-  const int nloop = nsteps - (final_dot ? 1 : 0);
   float2 *wgq = (float2 *)(t.perq_base + (int64_t)(q0 + wq0) * t.perq_stride);
   const int64_t gstride = t.perq_stride / 8;
-  // a kind 4 step's lane record is loaded one step ahead, so that its
-  // latency overlaps the step before
-  uint4 n0 = make_uint4(0u, 0u, 0u, 0u), n1 = n0;
-  auto fetch = [&](int k) {
-    const CStep S = prog + k;
-    if (S->kind == 5) {  // link 0 of a chain (64 records a link)
-      const uint4 *r = (const uint4 *)(t.lanes + S->tab + lane);
-      n0 = r[0];
-      n1 = r[1];
-    } else if (S->kind == 4 && lane < S->nc) {
-      const uint4 *r = (const uint4 *)(t.lanes + S->tab + lane);
-      n0 = r[0];
-      if (S->ns == 4) n1 = r[1];
+  // The stream's records come from L2, about as long a way as a block takes to
+  // run, and no block may wait for them or for a step descriptor: kBlkAhead
+  // blocks are in flight, in registers of their own (a rotation would wait for
+  // the loads).
+  const CSeg segs = (CSeg)t.wsegs + wseg0;
+  const uint4 *rec = (const uint4 *)(t.lanes + wrec0 + lane);
+  constexpr int BS = 64 * (int)sizeof(TreeLaneRec) / 16;  // a block in uint4
+  float vre = 0.f, vim = 0.f;
+  int zx = 0, zy = 0;
+  for (int g = 0; g < nwseg; ++g) {
+    const int n = segs[g].nblk, step = segs[g].step;
+    if (n > 0) {
+      const uint4 *r = rec;
+      rec += n * BS;
+      uint4 a0 = r[0], a1 = r[1], b0 = r[BS], b1 = r[BS + 1], c0 = r[2 * BS], c1 = r[2 * BS + 1];
+      for (int left = n;;) {
+        r += kBlkAhead * BS;
+        tree_block(a0, a1, lane, wpq, shr, wscl, vre, vim, zx, zy);
+        if (--left == 0) break;
+        a0 = r[0];
+        a1 = r[1];
+        tree_block(b0, b1, lane, wpq, shr, wscl, vre, vim, zx, zy);
+        if (--left == 0) break;
+        b0 = r[BS];
+        b1 = r[BS + 1];
+        tree_block(c0, c1, lane, wpq, shr, wscl, vre, vim, zx, zy);
+        if (--left == 0) break;
+        c0 = r[2 * BS];
+        c1 = r[2 * BS + 1];
+      }
     }
-  };
-  if (nloop > 0) fetch(0);
-  for (int k = 0; k < nloop; ++k) {
-    const CStep S = prog + k;
-    const uint4 c0 = n0, c1 = n1;
-    if (k + 1 < nloop) fetch(k + 1);
-    if (S->kind == 5) {
-      tree_chain(t.lanes + S->tab, S->nc, c0, c1, lane, wpq, shr, wscl);
-    } else if (S->kind == 6) {
+    if (step < 0) continue;
+    const CStep S = prog + step;
+    if (DEV && S->kind == 6 && wn == 1) {
       // a kind 3 pair: this step and the next
-      if (wn == 1) {
-        tree_pair(S, S + 1, lane, wpq, shr, wscl);
-      } else {
-        tree_kind3(S, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
-        tree_kind3(S + 1, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
-      }
-      ++k;
-      if (k + 1 < nloop) fetch(k + 1);
-    } else if (S->kind == 4) {
-      if (S->nss) {  // one whole step: the whole wave, one scale store
-        const bool act = lane < S->nc;
-        if (S->ns == 1)
-          tree_lane_whole<1>(c0, c1, act, lane, wpq, shr, wscl);
-        else if (S->ns == 2)
-          tree_lane_whole<2>(c0, c1, act, lane, wpq, shr, wscl);
-        else
-          tree_lane_whole<4>(c0, c1, act, lane, wpq, shr, wscl);
-      } else if (lane < S->nc) {
-        if (S->ns == 1)
-          tree_lane_exec<1>(c0, c1, wpq, shr, wscl);
-        else if (S->ns == 2)
-          tree_lane_exec<2>(c0, c1, wpq, shr, wscl);
-        else
-          tree_lane_exec<4>(c0, c1, wpq, shr, wscl);
-      }
+      tree_pair(S, S + 1, lane, wpq, shr, wscl);
+    } else if (DEV && S->kind == 6) {
+      tree_kind3(S, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
+      tree_kind3(S + 1, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
+    } else if (DEV && S->kind == 3) {
+      tree_kind3(S, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
+    } else if (wn == 1) {
+      tree_step_q<true>(S, lane, 64, 1, wpq, perq, shr, wscl, nscale);
     } else {
-      tree_step<true>(S, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride, t.lanes, 0);
+      tree_step_q<false>(S, lane, 64, wn, wpq, perq, shr, wscl, nscale);
     }
   }
 
   if (final_dot) {
     // closed root: FP64 inner product, reduced across the wave
-    const CStep S = prog + nloop;
+    // (the program's last step, checked on the host)
+    const CStep S = prog + nsteps - 1;
     const bool p2 = S->pow2 != 0;
     const int ns = S->ns, nss = S->nss, a = S->a, b = S->b;
     int32_t ext[kTreeSeg], s0[kTreeSeg], s1[kTreeSeg], lg[kTreeSeg];
@@ -1405,7 +1348,9 @@ size_t tree_lds_limit() {
                              (int)l) != hipSuccess ||
          hipFuncSetAttribute((const void *)k_tree<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)l) != hipSuccess ||
-         hipFuncSetAttribute((const void *)k_tree_wave, hipFuncAttributeMaxDynamicSharedMemorySize,
+         hipFuncSetAttribute((const void *)k_tree_wave<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)l) != hipSuccess ||
+         hipFuncSetAttribute((const void *)k_tree_wave<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              (int)l) != hipSuccess))
       l = 65536;
     limit = l;
@@ -1424,11 +1369,14 @@ hipError_t launch_tree(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds
   return hipGetLastError();
 }
 
-hipError_t launch_tree_wave(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes) {
+hipError_t launch_tree_wave(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes, bool dev) {
   if (nsub <= 0 || t.nq <= 0) return hipSuccess;
   if (lds_bytes > tree_lds_limit() || t.qw < 1 || t.qw > 16) return hipErrorInvalidValue;
   const int groups = (t.nq + t.qw - 1) / t.qw;
-  hipLaunchKernelGGL(k_tree_wave, dim3(nsub, groups), dim3(256), lds_bytes, st, t);
+  if (dev)
+    hipLaunchKernelGGL(k_tree_wave<true>, dim3(nsub, groups), dim3(256), lds_bytes, st, t);
+  else
+    hipLaunchKernelGGL(k_tree_wave<false>, dim3(nsub, groups), dim3(256), lds_bytes, st, t);
   return hipGetLastError();
 }
 
