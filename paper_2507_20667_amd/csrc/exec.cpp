@@ -261,20 +261,45 @@ struct SinglePin {
   ~SinglePin() { release(); }
 };
 
+static int64_t tiles_of(const Node &n, int tile) {
+  const int64_t m = gemm_planes_tile_m(tile), w = gemm_planes_tile_n(tile);
+  return ((n.M + m - 1) / m) * ((n.N + w - 1) / w);
+}
+
+// Tile of an FP32 GEMM launch over nb queries.  A stage of 16 k of the plan's
+// tile keeps its CU's matrix cores busy for 1.5 us, of a 64 x 64 tile for 0.4
+// us, so where the plan's tile leaves CUs without a block the small one takes
+// less than half the time (M 128 x N 512 x K 256, 3 queries: 46 us against 21);
+// from one block per CU on, its twofold reads bring nothing.  A result of up to
+// 32 rows or columns fills half of the 64-wide tiles' products or less: 32 x
+// 128 or 128 x 32 once its blocks, k chunks of 64 included, give every CU one
+// (16 queries of 16 x 128 x 8192: 85 us against 33; M 32 x N 512 x K 16384: 28
+// against 20).
+static int launch_tile(const Node &n, int nb) {
+  if (n.planes != 2 || !n.wide_ok) return n.tile;
+  if (n.M <= 32 || n.N <= 32) {
+    const int t = n.M <= 32 ? 4 : 5;
+    if (tiles_of(n, t) * nb * (n.fo ? 1 : std::max<int64_t>(n.ksplit, n.K / 64)) >= 256) return t;
+  }
+  return (int64_t)n.tiles * nb * n.ksplit < 256 ? 3 : n.tile;
+}
+
 // k chunks of a GEMM launch over nb queries: the plan's, or more when its
 // blocks leave CUs without work.  A block runs a stage of 16 k in about 2 us
 // however few rows it has, so the chip's time for a skinny result is its
-// chunk's length: up to one block per CU, chunks of at least 64 (M 32 x N 512 x
-// K 16384: 151 us in 16 chunks, 45 in 128; M 8 x N 128 x K 512: 75 in one, 21 in
-// eight; past one block per CU the partial sums' traffic costs more, M 64 x
-// N 4096 x K 32768: 358 us in 32 chunks, 377 in 64).  The partial sums (at most
+// chunk's length: up to one block per CU, chunks of at least 64 (with the
+// 64-wide tiles, M 32 x N 512 x K 16384: 151 us in 16 chunks, 45 in 128; M 8 x
+// N 128 x K 512: 75 in one, 21 in eight; past one block per CU the partial sums'
+// traffic costs more, M 64 x N 4096 x K 32768: 358 us in 32 chunks, 377 in 64).  The partial sums (at most
 // 256 tiles, 34 MB) lie in a region of their own that is not part of
 // the layouts, so a call that has no room for it runs the plan's chunks.
 static int wide_split(const Node &n, int nb, int64_t &kchunk) {
   kchunk = n.kchunk;
   if (!n.wide_ok || n.fo) return n.ksplit;
+  const int tile = launch_tile(n, nb);
+  const int64_t tiles = tile == n.tile ? n.tiles : tiles_of(n, tile);
   int64_t s = n.ksplit;
-  while ((int64_t)n.tiles * nb * s * 2 <= 256 && n.K / (s * 2) >= 64) s *= 2;
+  while (tiles * nb * s * 2 <= 256 && n.K / (s * 2) >= 64) s *= 2;
   if (s == n.ksplit) return n.ksplit;
   kchunk = ((n.K + s - 1) / s + 31) / 32 * 32;
   return (int)((n.K + kchunk - 1) / kchunk);
@@ -1104,7 +1129,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
           g.pb = n.N * n.K;
           g.ksplit = n.ksplit;
           g.ktile = n.ktile ? 1 : 0;
-          g.tile = n.tile;
+          g.tile = launch_tile(n, nb);
           // an operand whose planes a GEMM child wrote (unscaled): its batch
           // stride in plane entries, two floats or four bf16 to a complex64
           if (n.fuse_a) {

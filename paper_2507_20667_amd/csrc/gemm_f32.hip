@@ -5,11 +5,12 @@
 // k-tiled: row r, k sits at ((k / 16) * rows + r) * 16 + k % 16, so that one
 // 16-deep stage of a 128-row tile is a contiguous 8 KB block of each plane.
 // Stages stream straight from global memory into two LDS slots
-// (global_load_lds_dwordx4, no staging registers), one stage ahead.  The wait
+// (global_load_lds_dwordx4, no staging registers), one stage ahead (the 32-wide
+// wave tiles: four slots, three stages ahead).  The wait
 // for a stage is a vmcnt on the wave's own loads followed by a barrier.  Past
 // the last stage the request repeats the last stage into the free slot, so
 // the number of loads in flight never changes.  The slots are distinct arrays
-// named statically (the loop is unrolled by two), which lets the compiler see
+// named statically (the loop is unrolled by their number), which lets the compiler see
 // that a read of one slot does not wait on loads into the other.
 //
 // Products.  A value is the sum of three bfloat16 terms, x = h + m + l with
@@ -74,9 +75,14 @@ __device__ __forceinline__ v16f_c mfma_bf(v4u_f a, v4u_f b, v16f_c c) {
 __device__ constexpr int kSplitA[6] = {1, 0, 2, 0, 1, 0};
 __device__ constexpr int kSplitB[6] = {1, 2, 0, 1, 0, 0};
 
-// WMW = waves along M (the four waves form a WMW x 4/WMW grid, 64 x 64
-// outputs each): 2 gives a 128 x 128 tile, 1 a 64 x 256 tile (for M <= 64),
-// 4 a 256 x 64 tile (for N <= 64).
+// WMW = waves along M (the four waves form a WMW x 4/WMW grid, WT x WT
+// outputs each).  WT = 64: 2 gives a 128 x 128 tile, 1 a 64 x 256 tile (for
+// M <= 64), 4 a 256 x 64 tile (for N <= 64).  WT = 32: 64 x 64, 32 x 128 and 128 x
+// 32, for launches of few blocks and for skinny results (24 MFMAs a stage and
+// wave).  Those wait on the stages' way from memory rather than on the matrix
+// cores, so four slots keep three stages in flight (64 or 80 KB, two blocks
+// per CU).  M 128 x N 512 x K 256, 3 queries: 46 -> 21 us against the 128 x 128
+// tile; 16 queries of 16 x 128 x 8192 85 -> 33 us, 4.1 TB/s.
 
 // Two values split at once: v = h + m + l, each term the bfloat16 nearest to
 // what the terms before it leave (bits 0-15 of h, m, l: a's terms, bits 16-31:
@@ -96,14 +102,21 @@ __device__ __forceinline__ void split3(float a, float b, uint32_t lo1, uint32_t 
   l = __builtin_bit_cast(uint32_t, __builtin_convertvector((tn_f32x2{sa, sb}), tn_bf16x2));
 }
 
-template <int WMW>
+template <int WMW, int WT>
 __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
   constexpr int WNW = 4 / WMW;
-  constexpr int BM = 64 * WMW, BN = 64 * WNW;          // tile rows of A and of B
+  constexpr int MB = WT / 32;                          // MFMA tiles a wave has each way
+  constexpr int BM = WT * WMW, BN = WT * WNW;          // tile rows of A and of B
   constexpr int APL = BM * FBK, BPL = BN * FBK;        // floats per plane tile
   constexpr int FSTAGE = 2 * (APL + BPL);              // A re, A im, B re, B im
-  constexpr int JA = BM / 64, JB = BN / 64;            // load instructions per wave and plane
+  // load instructions per wave and plane (a 32-row plane takes two waves; the
+  // other two load the other plane)
+  constexpr int JA = BM > 32 ? BM / 64 : 1, JB = BN > 32 ? BN / 64 : 1;
+  constexpr int PA = BM > 32 ? 2 : 1, PB = BN > 32 ? 2 : 1;
+  constexpr int NSLOT = WT == 64 ? 2 : 4;
+  constexpr int NLOAD = PA * JA + PB * JB;             // a wave's loads of a stage
   __shared__ __align__(16) float ring0[FSTAGE], ring1[FSTAGE];
+  __shared__ __align__(16) float ring2[NSLOT == 4 ? FSTAGE : 4], ring3[NSLOT == 4 ? FSTAGE : 4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WNW, wn = wave % WNW;
   const int q = blockIdx.y;
@@ -121,39 +134,44 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
   const int ea = tn_scale_exp(sa->maxbits), eb = tn_scale_exp(sb->maxbits);
   if (blockIdx.x == 0 && tid == 0) sc->log2s = sa->log2s + sb->log2s + (double)(ea + eb);
 
-  v16f_c acc[2][2][2];
+  v16f_c acc[MB][MB][2];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < MB; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < MB; ++b)
 #pragma unroll
       for (int c = 0; c < 2; ++c)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[a][b][c][v] = 0.0f;
 
   // this lane's loads: instruction j covers rows (R / 4) * wave + 16 * j +
-  // lane / 4 of an R-row plane tile; position lane % 4 of the row holds
+  // lane / 4 of an R-row plane tile (R = 32: 16 * (wave % 2) + lane / 4 of
+  // plane wave / 2); position lane % 4 of the row holds
   // logical chunk (lane % 4) ^ fswz(row) (rows past M or N clamped to the
   // last one)
   const uint8_t *abase = (const uint8_t *)(A + m0 * FBK);
   const uint8_t *bbase = (const uint8_t *)(B + n0 * FBK);
   uint32_t aoff[JA], boff[JB];
+  constexpr int WA = BM > 32 ? BM / 4 : 16, WB = BN > 32 ? BN / 4 : 16;
+  const int wa = BM > 32 ? wave : wave & 1, wb = BN > 32 ? wave : wave & 1;
+  // the plane this wave loads where it loads one
+  const int apl = BM > 32 ? 0 : wave >> 1, bpl = BN > 32 ? 0 : wave >> 1;
 #pragma unroll
   for (int j = 0; j < JA; ++j) {
-    const int r = (BM / 4) * wave + 16 * j + (lane >> 2);
+    const int r = WA * wa + 16 * j + (lane >> 2);
     const int c = (lane & 3) ^ fswz(r);
     const int64_t ra_ = m0 + r < g.M ? r : g.M - 1 - m0;
     aoff[j] = (uint32_t)((ra_ * FBK + c * 4) * 4);
   }
 #pragma unroll
   for (int j = 0; j < JB; ++j) {
-    const int r = (BN / 4) * wave + 16 * j + (lane >> 2);
+    const int r = WB * wb + 16 * j + (lane >> 2);
     const int c = (lane & 3) ^ fswz(r);
     const int64_t rb_ = n0 + r < g.N ? r : g.N - 1 - n0;
     boff[j] = (uint32_t)((rb_ * FBK + c * 4) * 4);
   }
   const int64_t nk = (kend - kbeg) / FBK;
-#define TN_FRING(S) ((S) == 0 ? ring0 : ring1)
+#define TN_FRING(S) ((S) == 0 ? ring0 : (S) == 1 ? ring1 : (S) == 2 ? ring2 : ring3)
   auto issue = [&](auto slot, int64_t stg) {
     constexpr int S = decltype(slot)::value;
     float *rb = TN_FRING(S);
@@ -161,16 +179,21 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
     const uint8_t *ak = abase + kb * g.M * FBK * 4, *bk = bbase + kb * g.N * FBK * 4;
 #pragma unroll
     for (int pl = 0; pl < 2; ++pl) {
+      if (pl < PA) {
+        const int p = pl + apl;
 #pragma unroll
-      for (int j = 0; j < JA; ++j)
-        __builtin_amdgcn_global_load_lds((const void *)(ak + pl * g.pa * 4 + aoff[j]),
-                                         (lds_void_f *)(rb + pl * APL + ((BM / 4) * wave + 16 * j) * FBK),
-                                         16, 0, 0);
+        for (int j = 0; j < JA; ++j)
+          __builtin_amdgcn_global_load_lds((const void *)(ak + p * g.pa * 4 + aoff[j]),
+                                           (lds_void_f *)(rb + p * APL + (WA * wa + 16 * j) * FBK), 16, 0, 0);
+      }
+      if (pl < PB) {
+        const int p = pl + bpl;
 #pragma unroll
-      for (int j = 0; j < JB; ++j)
-        __builtin_amdgcn_global_load_lds(
-            (const void *)(bk + pl * g.pb * 4 + boff[j]),
-            (lds_void_f *)(rb + 2 * APL + pl * BPL + ((BN / 4) * wave + 16 * j) * FBK), 16, 0, 0);
+        for (int j = 0; j < JB; ++j)
+          __builtin_amdgcn_global_load_lds((const void *)(bk + p * g.pb * 4 + boff[j]),
+                                           (lds_void_f *)(rb + 2 * APL + p * BPL + (WB * wb + 16 * j) * FBK),
+                                           16, 0, 0);
+      }
     }
   };
   // a lane's eight k (8h .. 8h + 7 of lane half h) of row `row` of a plane
@@ -195,25 +218,25 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
   auto stage = [&](auto slot, int64_t kt) {
     constexpr int S = decltype(slot)::value;
     const float *rb = TN_FRING(S);
-    __builtin_amdgcn_s_waitcnt(f_wait_imm(0));
+    __builtin_amdgcn_s_waitcnt(f_wait_imm((NSLOT - 2) * NLOAD));
     __builtin_amdgcn_s_barrier();
-    issue(std::integral_constant<int, 1 - S>(), kt + 1);
-    v4u_f a[2][2][3];
+    issue(std::integral_constant<int, (S + NSLOT - 1) % NSLOT>(), kt + NSLOT - 1);
+    v4u_f a[MB][2][3];
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-      for (int pl = 0; pl < 2; ++pl) split(rb + pl * APL + (wm * 64 + mb * 32 + fr) * FBK, a[mb][pl]);
+      for (int pl = 0; pl < 2; ++pl) split(rb + pl * APL + (wm * WT + mb * 32 + fr) * FBK, a[mb][pl]);
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
+    for (int nb = 0; nb < MB; ++nb) {
       v4u_f b[2][3];
 #pragma unroll
-      for (int pl = 0; pl < 2; ++pl) split(rb + 2 * APL + pl * BPL + (wn * 64 + nb * 32 + fr) * FBK, b[pl]);
+      for (int pl = 0; pl < 2; ++pl) split(rb + 2 * APL + pl * BPL + (wn * WT + nb * 32 + fr) * FBK, b[pl]);
       // the six products of total order at most two, smallest first
 #pragma unroll
       for (int pi = 0; pi < 6; ++pi) {
         const int x = kSplitA[pi], y = kSplitB[pi];
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
+        for (int mb = 0; mb < MB; ++mb) {
           acc[mb][nb][0] = mfma_bf(a[mb][0][x], b[0][y], acc[mb][nb][0]);
           acc[mb][nb][1] = mfma_bf(a[mb][1][x], b[0][y], acc[mb][nb][1]);
         }
@@ -223,7 +246,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
         const int x = kSplitA[pi], y = kSplitB[pi];
         const v4u_f bn = b[1][y] ^ 0x80008000u;
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
+        for (int mb = 0; mb < MB; ++mb) {
           acc[mb][nb][1] = mfma_bf(a[mb][0][x], b[1][y], acc[mb][nb][1]);
           acc[mb][nb][0] = mfma_bf(a[mb][1][x], bn, acc[mb][nb][0]);
         }
@@ -237,26 +260,26 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
   auto stage32 = [&](auto slot, int64_t kt) {
     constexpr int S = decltype(slot)::value;
     const float *rb = TN_FRING(S);
-    __builtin_amdgcn_s_waitcnt(f_wait_imm(0));
+    __builtin_amdgcn_s_waitcnt(f_wait_imm((NSLOT - 2) * NLOAD));
     __builtin_amdgcn_s_barrier();
-    issue(std::integral_constant<int, 1 - S>(), kt + 1);
+    issue(std::integral_constant<int, (S + NSLOT - 1) % NSLOT>(), kt + NSLOT - 1);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int fp = h ? fp1 : fp0;
-      v4f a[2][2], b[2][2];
+      v4f a[MB][2], b[MB][2];
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
+      for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int pl = 0; pl < 2; ++pl) {
-          a[mb][pl] = *(const v4f *)(rb + pl * APL + (wm * 64 + mb * 32 + fr) * FBK + fp);
-          b[mb][pl] = *(const v4f *)(rb + 2 * APL + pl * BPL + (wn * 64 + mb * 32 + fr) * FBK + fp);
+          a[mb][pl] = *(const v4f *)(rb + pl * APL + (wm * WT + mb * 32 + fr) * FBK + fp);
+          b[mb][pl] = *(const v4f *)(rb + 2 * APL + pl * BPL + (wn * WT + mb * 32 + fr) * FBK + fp);
         }
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-          for (int nb = 0; nb < 2; ++nb) {
+          for (int nb = 0; nb < MB; ++nb) {
             const float ar = a[mb][0][s], ai = a[mb][1][s], br = b[nb][0][s], bi = b[nb][1][s];
             acc[mb][nb][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar, br, acc[mb][nb][0], 0, 0, 0);
             acc[mb][nb][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ar, bi, acc[mb][nb][1], 0, 0, 0);
@@ -269,22 +292,38 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
 #undef TN_FRING
   const std::integral_constant<int, 0> s0;
   const std::integral_constant<int, 1> s1;
+  const std::integral_constant<int, NSLOT == 4 ? 2 : 0> s2;
+  const std::integral_constant<int, NSLOT == 4 ? 3 : 1> s3;
   __builtin_amdgcn_s_waitcnt(0);  // nothing else in flight when the ring starts
   issue(s0, 0);
-  int64_t kt = 0;
-  if (max(sa->maxbits, sb->maxbits) < 0x7f000000u) {
-    for (; kt + 2 <= nk; kt += 2) {
-      stage(s0, kt);
-      stage(s1, kt + 1);
-    }
-    if (kt < nk) stage(s0, kt);
-  } else {
-    for (; kt + 2 <= nk; kt += 2) {
-      stage32(s0, kt);
-      stage32(s1, kt + 1);
-    }
-    if (kt < nk) stage32(s0, kt);
+  if (NSLOT == 4) {
+    issue(s1, 1);
+    issue(s2, 2);
   }
+  auto run = [&](auto one) {
+    int64_t kt = 0;
+    if (NSLOT == 4) {
+      for (; kt + 4 <= nk; kt += 4) {
+        one(s0, kt);
+        one(s1, kt + 1);
+        one(s2, kt + 2);
+        one(s3, kt + 3);
+      }
+      if (kt < nk) one(s0, kt);
+      if (kt + 1 < nk) one(s1, kt + 1);
+      if (kt + 2 < nk) one(s2, kt + 2);
+    } else {
+      for (; kt + 2 <= nk; kt += 2) {
+        one(s0, kt);
+        one(s1, kt + 1);
+      }
+      if (kt < nk) one(s0, kt);
+    }
+  };
+  if (max(sa->maxbits, sb->maxbits) < 0x7f000000u)
+    run(stage);
+  else
+    run(stage32);
   __builtin_amdgcn_s_waitcnt(0);  // no load may still write LDS when the block ends
 
   const bool partial = g.ksplit > 1;
@@ -296,16 +335,16 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
   const bool fo = g.fo_on != 0;
   uint8_t *P = (uint8_t *)(g.C + q * g.cbs), *P1 = P + g.fo_plane * 4;
   PlaneOut<4> po;
-  if (fo) po.init(g, m0 + wm * 64 + (lane >> 5) * 4, n0 + wn * 64 + (lane & 31));
+  if (fo) po.init(g, m0 + wm * WT + (lane >> 5) * 4, n0 + wn * WT + (lane & 31));
   float mx = 0.0f;
 #pragma unroll
-  for (int mb = 0; mb < 2; ++mb)
+  for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
+    for (int nb = 0; nb < MB; ++nb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int row = wm * 64 + mb * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-        const int col = wn * 64 + nb * 32 + (lane & 31);
+        const int row = wm * WT + mb * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
+        const int col = wn * WT + nb * 32 + (lane & 31);
         const int64_t cm = m0 + row, cn = n0 + col;
         const float re = acc[mb][nb][0][v] * post, im = acc[mb][nb][1][v] * post;
         if (cm < g.M && cn < g.N) {
@@ -326,14 +365,15 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
   }
 }
 
-// Tile shape of variant v: 0 = 128 x 128, 1 = 64 x 256, 2 = 256 x 64.
-int gemm_planes_tile_m(int v) { return v == 1 ? 64 : v == 2 ? 256 : 128; }
-int gemm_planes_tile_n(int v) { return v == 1 ? 256 : v == 2 ? 64 : 128; }
+// Tile shape of variant v: 0 = 128 x 128, 1 = 64 x 256, 2 = 256 x 64, 3 = 64 x
+// 64, 4 = 32 x 128, 5 = 128 x 32.
+int gemm_planes_tile_m(int v) { return v == 1 || v == 3 ? 64 : v == 2 ? 256 : v == 4 ? 32 : 128; }
+int gemm_planes_tile_n(int v) { return v == 1 ? 256 : v == 2 || v == 3 ? 64 : v == 5 ? 32 : 128; }
 
 hipError_t launch_gemm_f32_planes(hipStream_t st, const GemmArgs &g0, int form, int nbatch) {
   GemmArgs g = g0;
   if (g.opA != 0 || g.opB != 1 || g.planes != 2 || !g.ktile || g.K % FBK != 0 ||
-      (form != kForm4M && form != kForm3M) || g.tile < 0 || g.tile > 2 || (g.fo_on && g.ksplit > 1))
+      (form != kForm4M && form != kForm3M) || g.tile < 0 || g.tile > 5 || (g.fo_on && g.ksplit > 1))
     return hipErrorInvalidValue;
   const int tm = gemm_planes_tile_m(g.tile), tn = gemm_planes_tile_n(g.tile);
   g.tiles_m = (int)((g.M + tm - 1) / tm);
@@ -346,10 +386,13 @@ hipError_t launch_gemm_f32_planes(hipStream_t st, const GemmArgs &g0, int form, 
   const int64_t blocks = (int64_t)g.tiles_m * g.tiles_n * g.ksplit;
   if (blocks <= 0 || blocks > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks, nbatch);
-#define TN_F32P(W) hipLaunchKernelGGL((k_cgemm_f32_planes<W>), grid, dim3(256), 0, st, g)
-  if (g.tile == 0) TN_F32P(2);
-  else if (g.tile == 1) TN_F32P(1);
-  else TN_F32P(4);
+#define TN_F32P(W, T) hipLaunchKernelGGL((k_cgemm_f32_planes<W, T>), grid, dim3(256), 0, st, g)
+  if (g.tile == 0) TN_F32P(2, 64);
+  else if (g.tile == 1) TN_F32P(1, 64);
+  else if (g.tile == 2) TN_F32P(4, 64);
+  else if (g.tile == 3) TN_F32P(2, 32);
+  else if (g.tile == 4) TN_F32P(1, 32);
+  else TN_F32P(4, 32);
 #undef TN_F32P
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || g.ksplit == 1) return e;
