@@ -344,24 +344,105 @@ typedef __attribute__((address_space(3))) void lds_void;
 
 __device__ __forceinline__ int dswz(int r) { return ((r >> 2) ^ (r >> 3)) & 1; }
 
-// One result entry as its parent's k-tiled bf16 operand planes (re hi, re
-// lo, im hi, im lo at P[0..3] + d bytes, and for a 3M parent (re+im) hi and
-// lo at P[4], P[5]; the split of the operand permutation).
-template <int NPL>
-__device__ __forceinline__ void store_planes(uint8_t *const (&P)[6], uint32_t d, float re, float im) {
-  uint32_t h, l;
-  tn_split_bf16x2(re, im, h, l);
-  *(uint16_t *)(P[0] + d) = (uint16_t)h;
-  *(uint16_t *)(P[1] + d) = (uint16_t)l;
-  *(uint16_t *)(P[2] + d) = (uint16_t)(h >> 16);
-  *(uint16_t *)(P[3] + d) = (uint16_t)(l >> 16);
-  if (NPL == 6) {
-    uint16_t sh, sl;
-    tn_split_bf16(re + im, sh, sl);
-    *(uint16_t *)(P[4] + d) = sh;
-    *(uint16_t *)(P[5] + d) = sl;
-  }
+// Four rows of two-byte entries, one column a lane, to the rows' owners: lane
+// l of a quad has column l of rows 0 (low half of r01), 1, 2 (r23) and 3, and
+// gets the quad's four columns of row l.  Two exchanges: with the lane beside
+// (halves; sel picks the low ones of both on even lanes, the high ones on odd
+// lanes), with the pair beside (words).
+__device__ __forceinline__ uint2 quad_row(uint32_t r01, uint32_t r23, int lane) {
+  const uint32_t sel = (lane & 1) ? 0x03020706u : 0x05040100u;
+  const bool up = (lane & 2) != 0;
+  const uint32_t p01 = (uint32_t)__builtin_amdgcn_mov_dpp((int)r01, 0xB1, 0xF, 0xF, true);
+  const uint32_t p23 = (uint32_t)__builtin_amdgcn_mov_dpp((int)r23, 0xB1, 0xF, 0xF, true);
+  const uint32_t a = __builtin_amdgcn_perm(p01, r01, sel), b = __builtin_amdgcn_perm(p23, r23, sel);
+  const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)(up ? a : b), 0x4E, 0xF, 0xF, true);
+  return up ? make_uint2(got, b) : make_uint2(a, got);
 }
+
+// A wave's 64 x 64 result entries as their parent's k-tiled bf16 operand planes
+// (re hi, re lo, im hi, im lo at P + 0 .. 3 times ps bytes, and for a 3M parent
+// (re+im) hi and lo at 4, 5; the split of the operand permutation).  A plane's
+// index keeps the result's four lowest bits, and mostly six: eight rows of the
+// 32-column halves are exchanged within lane quads and between the wave's
+// halves, so that each store writes 64 columns of four rows, whole 128 byte
+// lines.  (One entry a lane, 32 columns a store: two writers a line.)  Planes
+// larger than the last level cache go past the caches.  M 8192 x N 16384 x K 512
+// with its 1 GB of planes: 1280 -> 1200 us; five 30-qubit amplitudes 19.2 -> 18.3 ms.
+// Bound: that GB at 4.5 TB/s, 240 us.  Started at different times, so that
+// some CUs write while others multiply, the blocks take as long: the power
+// budget, not the idle pipe, is what the writes use.
+//
+// value(mb, nb, v, re, im): entry v of the lane's 32 x 32 tile (mb, nb).
+// qm, qn: the lane's first row and column here (plane_row, plane_col).  Rows
+// and columns past the result's hold copies of its last ones, which leave mx
+// as it is.
+template <int NPL, class V>
+__device__ __forceinline__ void store_planes(const GemmArgs &g, uint8_t *P, int64_t qm, int64_t qn, int lane,
+                                             const V &value, float &mx) {
+  typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+  PlaneOut<2> po;
+  po.init(g, qm, qn);
+  const int64_t ps = g.fo_plane * 2;
+  const bool past = g.fo_plane * (2 * NPL) > (int64_t)256 << 20;
+#pragma unroll
+  for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+    for (int v = 0; v < 16; v += 4) {
+      // one group's registers at a time
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("" : "+v"(mx));
+      uint2 w[2][NPL];
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb) {
+        float re[4], im[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          value(mb, nb, v + i, re[i], im[i]);
+          mx = fmaxf(mx, fmaxf(fabsf(re[i]), fabsf(im[i])));
+        }
+        auto two = [&](const float (&x)[4], uint2 &hi, uint2 &lo) {
+          uint32_t h0, l0, h1, l1;
+          tn_split_bf16x2(x[0], x[1], h0, l0);
+          tn_split_bf16x2(x[2], x[3], h1, l1);
+          hi = quad_row(h0, h1, lane);
+          lo = quad_row(l0, l1, lane);
+        };
+        two(re, w[nb][0], w[nb][1]);
+        two(im, w[nb][2], w[nb][3]);
+        if (NPL == 6) {
+          const float sum[4] = {re[0] + im[0], re[1] + im[1], re[2] + im[2], re[3] + im[3]};
+          two(sum, w[nb][NPL - 2], w[nb][NPL - 1]);
+        }
+      }
+      // rows r and r + 4 (the wave's halves) of columns c and c + 32 (nb)
+      uint32_t d = po.at(mb, 0, v);
+      int64_t row = qm + mb * 32 + v * 2;
+#pragma unroll
+      for (int i = 0; i < NPL; ++i) {
+        const auto x = __builtin_amdgcn_permlane32_swap(w[0][i].x, w[1][i].x, false, false);
+        const auto y = __builtin_amdgcn_permlane32_swap(w[0][i].y, w[1][i].y, false, false);
+        w[0][i] = make_uint2(x[0], y[0]);
+        w[1][i] = make_uint2(x[1], y[1]);
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        if (row < g.M && qn < g.N) {
+          if (past) {
+#pragma unroll
+            for (int i = 0; i < NPL; ++i)
+              __builtin_nontemporal_store((v2u){w[h][i].x, w[h][i].y}, (v2u *)(P + i * ps + d));
+          } else {
+#pragma unroll
+            for (int i = 0; i < NPL; ++i) *(uint2 *)(P + i * ps + d) = w[h][i];
+          }
+        }
+        d += po.rbit[2];
+        row += 4;
+      }
+    }
+}
+__device__ __forceinline__ int plane_row(int lane) { return lane & 3; }
+__device__ __forceinline__ int plane_col(int lane) { return (lane & 28) + (lane >> 5) * 32; }
 
 // s_waitcnt immediate: vmcnt(v) expcnt(7) lgkmcnt(0)
 __host__ __device__ constexpr int dma_wait_imm(int v) { return (v & 15) | ((v >> 4) << 14) | (7 << 4); }
@@ -504,11 +585,6 @@ __global__ __launch_bounds__(256, FORM == kForm3M ? 1 : 2) void k_cgemm_bf16x3_d
   // result may go out as its parent's operand planes (four, six for 3M)
   const float post = (g.raw_a | g.raw_b) ? ldexpf(1.0f, -(g.raw_a ? ea : 0) - (g.raw_b ? eb : 0)) : 1.0f;
   const bool fo = g.fo_on != 0;
-  uint8_t *const P0 = (uint8_t *)(g.C + q * g.cbs);
-  uint8_t *const P[6] = {P0, P0 + g.fo_plane * 2, P0 + g.fo_plane * 4, P0 + g.fo_plane * 6, P0 + g.fo_plane * 8,
-                         P0 + g.fo_plane * 10};
-  PlaneOut<2> po;
-  if (fo) po.init(g, m0 + wm * 64 + (lane >> 5) * 4, n0 + wn * 64 + (lane & 31));
   float mx = 0.0f;
   auto value = [&](int mb, int nb, int v, float &re, float &im) {
     if (FORM == kForm4M) {
@@ -522,19 +598,9 @@ __global__ __launch_bounds__(256, FORM == kForm3M ? 1 : 2) void k_cgemm_bf16x3_d
     re *= post;
     im *= post;
   };
-  if (fo && m0 + BT <= g.M && n0 + BT <= g.N) {
-    // a whole tile of planes: no entry to test
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          float re, im;
-          value(mb, nb, v, re, im);
-          store_planes<NP>(P, po.at(mb, nb, v), re, im);
-          mx = fmaxf(mx, fmaxf(fabsf(re), fabsf(im)));
-        }
+  if (fo) {
+    store_planes<NP>(g, (uint8_t *)(g.C + q * g.cbs), m0 + wm * 64 + plane_row(lane),
+                     n0 + wn * 64 + plane_col(lane), lane, value, mx);
   } else {
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb)
@@ -548,10 +614,7 @@ __global__ __launch_bounds__(256, FORM == kForm3M ? 1 : 2) void k_cgemm_bf16x3_d
           float re, im;
           value(mb, nb, v, re, im);
           if (cm < g.M && cn < g.N) {
-            if (fo)
-              store_planes<NP>(P, po.at(mb, nb, v), re, im);
-            else
-              C[cm * ldc + cn] = make_float2(re, im);
+            C[cm * ldc + cn] = make_float2(re, im);
             mx = fmaxf(mx, fmaxf(fabsf(re), fabsf(im)));
           }
         }
@@ -770,23 +833,14 @@ __global__ __launch_bounds__(512, 1) void k_cgemm_bf16x3_pp(GemmArgs g) {
   // kernel
   const float post = (g.raw_a | g.raw_b) ? ldexpf(1.0f, -(g.raw_a ? ea : 0) - (g.raw_b ? eb : 0)) : 1.0f;
   const bool fo = g.fo_on != 0;
-  uint8_t *const P0 = (uint8_t *)(g.C + q * g.cbs);
-  uint8_t *const P[6] = {P0, P0 + g.fo_plane * 2, P0 + g.fo_plane * 4, P0 + g.fo_plane * 6, P0, P0};
-  PlaneOut<2> po;
-  if (fo) po.init(g, m0 + rbase + (lane >> 5) * 4, n0 + cbase + (lane & 31));
   float mx = 0.0f;
-  if (fo && m0 + RA <= g.M && n0 + RB <= g.N) {
-    // a whole tile of planes: no entry to test
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float re = acc[mb][nb][0][v] * post, im = acc[mb][nb][1][v] * post;
-          store_planes<4>(P, po.at(mb, nb, v), re, im);
-          mx = fmaxf(mx, fmaxf(fabsf(re), fabsf(im)));
-        }
+  if (fo) {
+    auto value = [&](int mb, int nb, int v, float &re, float &im) {
+      re = acc[mb][nb][0][v] * post;
+      im = acc[mb][nb][1][v] * post;
+    };
+    store_planes<4>(g, (uint8_t *)(g.C + q * g.cbs), m0 + rbase + plane_row(lane), n0 + cbase + plane_col(lane),
+                    lane, value, mx);
   } else {
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb)
@@ -799,10 +853,7 @@ __global__ __launch_bounds__(512, 1) void k_cgemm_bf16x3_pp(GemmArgs g) {
           const int64_t cm = m0 + row, cn = n0 + col;
           const float re = acc[mb][nb][0][v] * post, im = acc[mb][nb][1][v] * post;
           if (cm < g.M && cn < g.N) {
-            if (fo)
-              store_planes<4>(P, po.at(mb, nb, v), re, im);
-            else
-              C[cm * ldc + cn] = make_float2(re, im);
+            C[cm * ldc + cn] = make_float2(re, im);
             mx = fmaxf(mx, fmaxf(fabsf(re), fabsf(im)));
           }
         }

@@ -584,9 +584,7 @@ static tn_status schedule_gemm(tn_plan *p, Node &n, const Layout &A, const Layou
       u.fo = true;
       memcpy(u.fo_d, d, sizeof(d));
       // a BF16x3 4M producer on the two wave-group kernel where its shape
-      // fills that tile: its 2-byte plane stores cost the one-group kernel a
-      // third of its time on short k (the tuning table times GEMMs that
-      // write complex64)
+      // fills that tile (the tuning table times GEMMs that write complex64)
       if (u.planes == 4 && u.tile == 0 && u.ksplit == 1) {
         if (u.M >= 256 && u.N >= 128) u.tile = 2;
         else if (u.N >= 256 && u.M >= 128) u.tile = 1;
