@@ -262,11 +262,12 @@ struct SinglePin {
 };
 
 static int64_t tiles_of(const Node &n, int tile) {
-  const int64_t m = gemm_planes_tile_m(tile), w = gemm_planes_tile_n(tile);
+  const int64_t m = n.planes == 2 ? gemm_planes_tile_m(tile) : gemm_bf16_tile_m(tile),
+                w = n.planes == 2 ? gemm_planes_tile_n(tile) : gemm_bf16_tile_n(tile);
   return ((n.M + m - 1) / m) * ((n.N + w - 1) / w);
 }
 
-// Tile of an FP32 GEMM launch over nb queries.  A stage of 16 k of the plan's
+// Tile of a GEMM launch over nb queries.  FP32: a stage of 16 k of the plan's
 // tile keeps its CU's matrix cores busy for 1.5 us, of a 64 x 64 tile for 0.4
 // us, so where the plan's tile leaves CUs without a block the small one takes
 // less than half the time (M 128 x N 512 x K 256, 3 queries: 46 us against 21);
@@ -275,13 +276,16 @@ static int64_t tiles_of(const Node &n, int tile) {
 // 128 or 128 x 32 once its blocks, k chunks of 64 included, give every CU one
 // (16 queries of 16 x 128 x 8192: 85 us against 33; M 32 x N 512 x K 16384: 28
 // against 20).
+// BF16x3 the same with 64 x 64 alone (GEMMs of a serving burst 14 us against
+// 10; M 64 x N 4096 x K 32768 282 against 246).
 static int launch_tile(const Node &n, int nb) {
-  if (n.planes != 2 || !n.wide_ok) return n.tile;
-  if (n.M <= 32 || n.N <= 32) {
+  if (n.planes < 2 || !n.wide_ok) return n.tile;
+  if (n.planes > 2 && (n.M <= 64 || n.N <= 64)) return 3;
+  if (n.planes == 2 && (n.M <= 32 || n.N <= 32)) {
     const int t = n.M <= 32 ? 4 : 5;
     if (tiles_of(n, t) * nb * (n.fo ? 1 : std::max<int64_t>(n.ksplit, n.K / 64)) >= 256) return t;
   }
-  return (int64_t)n.tiles * nb * n.ksplit < 256 ? 3 : n.tile;
+  return tiles_of(n, n.tile) * nb * n.ksplit < 256 ? 3 : n.tile;
 }
 
 // k chunks of a GEMM launch over nb queries: the plan's, or more when its

@@ -339,7 +339,6 @@ __global__ __launch_bounds__(256) void k_cgemm_bf16x3(GemmArgs g) {
 // r's 16-byte chunk c sits at position c ^ dswz(r), so the 16 rows read
 // together fall on distinct banks.
 constexpr int DBK = 16;               // k per stage
-constexpr int DPLANE = BT * DBK;      // bf16 per plane tile (4 KB)
 typedef __attribute__((address_space(3))) void lds_void;
 
 __device__ __forceinline__ int dswz(int r) { return ((r >> 2) ^ (r >> 3)) & 1; }
@@ -375,8 +374,8 @@ __device__ __forceinline__ uint2 quad_row(uint32_t r01, uint32_t r23, int lane) 
 // value(mb, nb, v, re, im): entry v of the lane's 32 x 32 tile (mb, nb).
 // qm, qn: the lane's first row and column here (plane_row, plane_col).  Rows
 // and columns past the result's hold copies of its last ones, which leave mx
-// as it is.
-template <int NPL, class V>
+// as it is.  MB = 1: a wave's 32 x 32 entries, eight rows of 32 columns a store.
+template <int NPL, int MB, class V>
 __device__ __forceinline__ void store_planes(const GemmArgs &g, uint8_t *P, int64_t qm, int64_t qn, int lane,
                                              const V &value, float &mx) {
   typedef unsigned int v2u __attribute__((ext_vector_type(2)));
@@ -385,15 +384,15 @@ __device__ __forceinline__ void store_planes(const GemmArgs &g, uint8_t *P, int6
   const int64_t ps = g.fo_plane * 2;
   const bool past = g.fo_plane * (2 * NPL) > (int64_t)256 << 20;
 #pragma unroll
-  for (int mb = 0; mb < 2; ++mb)
+  for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
     for (int v = 0; v < 16; v += 4) {
       // one group's registers at a time
       __builtin_amdgcn_sched_barrier(0);
       asm volatile("" : "+v"(mx));
-      uint2 w[2][NPL];
+      uint2 w[MB][NPL];
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
+      for (int nb = 0; nb < MB; ++nb) {
         float re[4], im[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -417,15 +416,17 @@ __device__ __forceinline__ void store_planes(const GemmArgs &g, uint8_t *P, int6
       // rows r and r + 4 (the wave's halves) of columns c and c + 32 (nb)
       uint32_t d = po.at(mb, 0, v);
       int64_t row = qm + mb * 32 + v * 2;
+      if constexpr (MB == 2) {
 #pragma unroll
-      for (int i = 0; i < NPL; ++i) {
-        const auto x = __builtin_amdgcn_permlane32_swap(w[0][i].x, w[1][i].x, false, false);
-        const auto y = __builtin_amdgcn_permlane32_swap(w[0][i].y, w[1][i].y, false, false);
-        w[0][i] = make_uint2(x[0], y[0]);
-        w[1][i] = make_uint2(x[1], y[1]);
+        for (int i = 0; i < NPL; ++i) {
+          const auto x = __builtin_amdgcn_permlane32_swap(w[0][i].x, w[1][i].x, false, false);
+          const auto y = __builtin_amdgcn_permlane32_swap(w[0][i].y, w[1][i].y, false, false);
+          w[0][i] = make_uint2(x[0], y[0]);
+          w[1][i] = make_uint2(x[1], y[1]);
+        }
       }
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < MB; ++h) {
         if (row < g.M && qn < g.N) {
           if (past) {
 #pragma unroll
@@ -441,21 +442,30 @@ __device__ __forceinline__ void store_planes(const GemmArgs &g, uint8_t *P, int6
       }
     }
 }
-__device__ __forceinline__ int plane_row(int lane) { return lane & 3; }
-__device__ __forceinline__ int plane_col(int lane) { return (lane & 28) + (lane >> 5) * 32; }
+template <int MB>
+__device__ __forceinline__ int plane_row(int lane) { return (lane & 3) + (MB == 1 ? (lane >> 5) * 4 : 0); }
+template <int MB>
+__device__ __forceinline__ int plane_col(int lane) { return (lane & 28) + (MB == 2 ? (lane >> 5) * 32 : 0); }
 
 // s_waitcnt immediate: vmcnt(v) expcnt(7) lgkmcnt(0)
 __host__ __device__ constexpr int dma_wait_imm(int v) { return (v & 15) | ((v >> 4) << 14) | (7 << 4); }
 
-template <int FORM>
-__global__ __launch_bounds__(256, FORM == kForm3M ? 1 : 2) void k_cgemm_bf16x3_dma(GemmArgs g) {
+// WT = 64: a wave's part of the 128 x 128 tile.  WT = 32: a 64 x 64 tile, for
+// launches of few blocks and for results of up to 64 rows or columns, whose
+// stage is a fourth of the products and half the bytes (the 128 x 128 tile of
+// such a result ran half empty: M 64 x N 4096 x K 32768 282 us, so 246; the small
+// GEMMs of a serving burst 14 us each, so 10).
+template <int FORM, int WT>
+__global__ __launch_bounds__(256, FORM == kForm3M && WT == 64 ? 1 : 2) void k_cgemm_bf16x3_dma(GemmArgs g) {
+  constexpr int MB = WT / 32, TB = 2 * WT, PLN = TB * DBK;  // rows and bf16 of a plane tile
   constexpr int NP = FORM == kForm3M ? 6 : 4;        // planes per operand
-  constexpr int NSLOT = FORM == kForm3M ? 3 : 2;     // ring slots
+  constexpr int NSLOT = FORM == kForm3M || WT == 32 ? 3 : 2;  // ring slots
   constexpr int NACC = FORM == kForm3M ? 3 : 2;
   constexpr int NPROD = FORM == kForm3M ? 9 : 12;
-  constexpr int STAGE = 2 * NP * DPLANE;
-  // loads of a wave per stage: one 1 KB instruction per plane of A and of B
-  constexpr int LOADS = 2 * NP;
+  constexpr int STAGE = 2 * NP * PLN;
+  // loads of a wave per stage: one 1 KB instruction (32 rows) per plane of A
+  // and of B; per second plane from wave / 2 on for the two of a 64-row tile
+  constexpr int LOADS = WT == 64 ? 2 * NP : NP;
   __shared__ __align__(16) uint16_t ring0[STAGE], ring1[STAGE], ring2[NSLOT == 3 ? STAGE : 8];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -468,30 +478,31 @@ __global__ __launch_bounds__(256, FORM == kForm3M ? 1 : 2) void k_cgemm_bf16x3_d
   int ks;
   int64_t t;
   gemm_block_tile(g, ks, t);  // XCD-aware block -> (k chunk, tile)
-  const int64_t m0 = (t % g.tiles_m) * BT, n0 = (t / g.tiles_m) * BT;
+  const int64_t m0 = (t % g.tiles_m) * TB, n0 = (t / g.tiles_m) * TB;
   const int64_t kbeg = (int64_t)ks * g.kchunk;
   const int64_t kend = g.K < kbeg + g.kchunk ? g.K : kbeg + g.kchunk;
   const int ea = tn_scale_exp(sa->maxbits), eb = tn_scale_exp(sb->maxbits);
   if (blockIdx.x == 0 && tid == 0) sc->log2s = sa->log2s + sb->log2s + (double)(ea + eb);
 
-  v16f_b acc[2][2][NACC];
+  v16f_b acc[MB][MB][NACC];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < MB; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < MB; ++b)
 #pragma unroll
       for (int c = 0; c < NACC; ++c)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[a][b][c][v] = 0.0f;
 
-  // this lane's load: row 32 * wave + lane / 2 of every plane tile, logical
+  // this lane's load: row 32 * wr + lane / 2 of the plane tiles, logical
   // chunk (lane % 2) ^ dswz(row) (rows past M or N clamped to the last one);
   // in the k-tiled planes row r of k block kb starts at (kb * rows + r) * 16
   const uint8_t *abase = (const uint8_t *)(A + m0 * DBK);
   const uint8_t *bbase = (const uint8_t *)(B + n0 * DBK);
   uint32_t aoff, boff;
+  const int wr = WT == 64 ? wave : wave & 1, wp = WT == 64 ? 0 : wave >> 1;
   {
-    const int r = 32 * wave + (lane >> 1);
+    const int r = 32 * wr + (lane >> 1);
     const int c = (lane & 1) ^ dswz(r);
     const int64_t ra_ = m0 + r < g.M ? r : g.M - 1 - m0;
     const int64_t rb_ = n0 + r < g.N ? r : g.N - 1 - n0;
@@ -502,39 +513,40 @@ __global__ __launch_bounds__(256, FORM == kForm3M ? 1 : 2) void k_cgemm_bf16x3_d
 #define TN_RING(S) ((S) == 0 ? ring0 : (S) == 1 ? ring1 : ring2)
   auto issue = [&](auto slot, int64_t stg) {
     constexpr int S = decltype(slot)::value;
-    uint16_t *rb = TN_RING(S) + wave * (DPLANE / 4);
+    uint16_t *rb = TN_RING(S) + wr * (32 * DBK);
     const int64_t kb = kbeg / DBK + (stg < nk ? stg : nk - 1);
     const uint8_t *ak = abase + kb * g.M * DBK * 2, *bk = bbase + kb * g.N * DBK * 2;
 #pragma unroll
-    for (int pl = 0; pl < NP; ++pl) {
+    for (int i = 0; i < LOADS / 2; ++i) {
+      const int pl = WT == 64 ? i : wp + 2 * i;
       __builtin_amdgcn_global_load_lds((const void *)(ak + pl * g.pa * 2 + aoff),
-                                       (lds_void *)(rb + pl * DPLANE), 16, 0, 0);
+                                       (lds_void *)(rb + pl * PLN), 16, 0, 0);
       __builtin_amdgcn_global_load_lds((const void *)(bk + pl * g.pb * 2 + boff),
-                                       (lds_void *)(rb + (NP + pl) * DPLANE), 16, 0, 0);
+                                       (lds_void *)(rb + (NP + pl) * PLN), 16, 0, 0);
     }
   };
   const int fr = lane & 31, fpos = ((lane >> 5) ^ dswz(fr)) * 8;
   // fragments in plane-pair order (A and B of pair 0, then pair 1, ...), so
   // that the products of one pair can start while the next pair is read
-  auto fread = [&](auto slot, v4u (&a)[2][NP], v4u (&b)[2][NP]) {
+  auto fread = [&](auto slot, v4u (&a)[MB][NP], v4u (&b)[MB][NP]) {
     constexpr int S = decltype(slot)::value;
     const uint16_t *rb = TN_RING(S);
 #pragma unroll
     for (int pp = 0; pp < NP; pp += 2) {
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
+      for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int pl = pp; pl < pp + 2; ++pl)
-          a[mb][pl] = *(const v4u *)(rb + pl * DPLANE + (wm * 64 + mb * 32 + fr) * DBK + fpos);
+          a[mb][pl] = *(const v4u *)(rb + pl * PLN + (wm * WT + mb * 32 + fr) * DBK + fpos);
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
+      for (int nb = 0; nb < MB; ++nb)
 #pragma unroll
         for (int pl = pp; pl < pp + 2; ++pl)
-          b[nb][pl] = *(const v4u *)(rb + (NP + pl) * DPLANE + (wn * 64 + nb * 32 + fr) * DBK + fpos);
+          b[nb][pl] = *(const v4u *)(rb + (NP + pl) * PLN + (wn * WT + nb * 32 + fr) * DBK + fpos);
     }
   };
 #undef TN_RING
-  auto mma = [&](const v4u (&a)[2][NP], const v4u (&b)[2][NP]) {
+  auto mma = [&](const v4u (&a)[MB][NP], const v4u (&b)[MB][NP]) {
 #pragma unroll
     for (int pi = 0; pi < NPROD; ++pi) {
       const int c = FORM == kForm3M ? prod_3m_g(pi, 0) : prod_4m(pi, 0);
@@ -542,16 +554,16 @@ __global__ __launch_bounds__(256, FORM == kForm3M ? 1 : 2) void k_cgemm_bf16x3_d
       const int bp = FORM == kForm3M ? prod_3m_g(pi, 2) : prod_4m(pi, 2);
       const int ng = FORM == kForm3M ? prod_3m_g(pi, 3) : prod_4m(pi, 3);
 #pragma unroll
-      for (int mb = 0; mb < 2; ++mb) {
+      for (int mb = 0; mb < MB; ++mb) {
         const v8bf av = as_bf(ng ? neg4(a[mb][ap]) : a[mb][ap]);
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
+        for (int nb = 0; nb < MB; ++nb)
           acc[mb][nb][c] =
               __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, as_bf(b[nb][bp]), acc[mb][nb][c], 0, 0, 0);
       }
     }
   };
-  v4u fa[2][NP], fb[2][NP];
+  v4u fa[MB][NP], fb[MB][NP];
   // one stage (ring slot S): wait for it (the loads of the NSLOT - 2 stages
   // after it may stay in flight), barrier (every wave has read the fragments
   // of stage kt - 1), request stage kt + NSLOT - 1 into the slot stage kt - 1
@@ -599,17 +611,17 @@ __global__ __launch_bounds__(256, FORM == kForm3M ? 1 : 2) void k_cgemm_bf16x3_d
     im *= post;
   };
   if (fo) {
-    store_planes<NP>(g, (uint8_t *)(g.C + q * g.cbs), m0 + wm * 64 + plane_row(lane),
-                     n0 + wn * 64 + plane_col(lane), lane, value, mx);
+    store_planes<NP, MB>(g, (uint8_t *)(g.C + q * g.cbs), m0 + wm * WT + plane_row<MB>(lane),
+                         n0 + wn * WT + plane_col<MB>(lane), lane, value, mx);
   } else {
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
+    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
+      for (int nb = 0; nb < MB; ++nb)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const int row = wm * 64 + mb * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-          const int col = wn * 64 + nb * 32 + (lane & 31);
+          const int row = wm * WT + mb * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
+          const int col = wn * WT + nb * 32 + (lane & 31);
           const int64_t cm = m0 + row, cn = n0 + col;
           float re, im;
           value(mb, nb, v, re, im);
@@ -651,8 +663,8 @@ __global__ __launch_bounds__(256, FORM == kForm3M ? 1 : 2) void k_cgemm_bf16x3_d
 // 128-row operand at rows 32 (w % 4) ...
 constexpr int PPW = 256;  // rows of the wide operand's tile
 
-int gemm_bf16_tile_m(int tile) { return tile == 2 ? PPW : BT; }
-int gemm_bf16_tile_n(int tile) { return tile == 1 ? PPW : BT; }
+int gemm_bf16_tile_m(int tile) { return tile == 2 ? PPW : tile == 3 ? 64 : BT; }
+int gemm_bf16_tile_n(int tile) { return tile == 1 ? PPW : tile == 3 ? 64 : BT; }
 
 template <bool WIDE_A>
 __global__ __launch_bounds__(512, 1) void k_cgemm_bf16x3_pp(GemmArgs g) {
@@ -839,8 +851,8 @@ __global__ __launch_bounds__(512, 1) void k_cgemm_bf16x3_pp(GemmArgs g) {
       re = acc[mb][nb][0][v] * post;
       im = acc[mb][nb][1][v] * post;
     };
-    store_planes<4>(g, (uint8_t *)(g.C + q * g.cbs), m0 + rbase + plane_row(lane), n0 + cbase + plane_col(lane),
-                    lane, value, mx);
+    store_planes<4, 2>(g, (uint8_t *)(g.C + q * g.cbs), m0 + rbase + plane_row<2>(lane),
+                       n0 + cbase + plane_col<2>(lane), lane, value, mx);
   } else {
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb)
@@ -868,13 +880,14 @@ __global__ __launch_bounds__(512, 1) void k_cgemm_bf16x3_pp(GemmArgs g) {
 hipError_t launch_gemm_bf16x3(hipStream_t st, const GemmArgs &g0, int form, int nbatch) {
   GemmArgs g = g0;
   if (g.opA != 0 || g.opB != 1 || g.planes != (form == kForm3M ? 6 : 4)) return hipErrorInvalidValue;
-  if (g.tile < 0 || g.tile > 2) return hipErrorInvalidValue;
+  if (g.tile < 0 || g.tile > 3 || (g.tile == 3 && !g.ktile)) return hipErrorInvalidValue;
   if ((g.raw_a || g.raw_b || g.fo_on) && !g.ktile) return hipErrorInvalidValue;
   if (g.fo_on && g.ksplit > 1) return hipErrorInvalidValue;
   // the two-group kernel: 4M from k-tiled planes with a wide tile
-  const bool pp = g.ktile && form == kForm4M && g.tile != 0;
-  g.tiles_m = (int)((g.M + (pp ? gemm_bf16_tile_m(g.tile) : BT) - 1) / (pp ? gemm_bf16_tile_m(g.tile) : BT));
-  g.tiles_n = (int)((g.N + (pp ? gemm_bf16_tile_n(g.tile) : BT) - 1) / (pp ? gemm_bf16_tile_n(g.tile) : BT));
+  const bool pp = g.ktile && form == kForm4M && (g.tile == 1 || g.tile == 2);
+  const int tm = pp || g.tile == 3 ? gemm_bf16_tile_m(g.tile) : BT, tn = pp || g.tile == 3 ? gemm_bf16_tile_n(g.tile) : BT;
+  g.tiles_m = (int)((g.M + tm - 1) / tm);
+  g.tiles_n = (int)((g.N + tn - 1) / tn);
   if (g.ksplit < 1) g.ksplit = 1;
   if (g.ksplit == 1) g.kchunk = g.K;
   if (g.kchunk < 1 || (int64_t)g.ksplit * g.kchunk < g.K || (g.ksplit > 1 && !g.part))
@@ -889,10 +902,14 @@ hipError_t launch_gemm_bf16x3(hipStream_t st, const GemmArgs &g0, int form, int 
       hipLaunchKernelGGL(k_cgemm_bf16x3_pp<true>, grid, dim3(512), 0, st, g);
     else if (pp)
       hipLaunchKernelGGL(k_cgemm_bf16x3_pp<false>, grid, dim3(512), 0, st, g);
+    else if (form == kForm4M && g.tile == 3)
+      hipLaunchKernelGGL((k_cgemm_bf16x3_dma<kForm4M, 32>), grid, dim3(256), 0, st, g);
     else if (form == kForm4M)
-      hipLaunchKernelGGL(k_cgemm_bf16x3_dma<kForm4M>, grid, dim3(256), 0, st, g);
+      hipLaunchKernelGGL((k_cgemm_bf16x3_dma<kForm4M, 64>), grid, dim3(256), 0, st, g);
+    else if (g.tile == 3)
+      hipLaunchKernelGGL((k_cgemm_bf16x3_dma<kForm3M, 32>), grid, dim3(256), 0, st, g);
     else
-      hipLaunchKernelGGL(k_cgemm_bf16x3_dma<kForm3M>, grid, dim3(256), 0, st, g);
+      hipLaunchKernelGGL((k_cgemm_bf16x3_dma<kForm3M, 64>), grid, dim3(256), 0, st, g);
   } else if (form == kForm4M) {
     if (exact)
       hipLaunchKernelGGL((k_cgemm_bf16x3<kForm4M, true>), grid, dim3(256), 0, st, g);

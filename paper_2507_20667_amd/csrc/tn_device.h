@@ -97,8 +97,9 @@ struct GemmArgs {
   // + k % 16, rows = M for A and N for B), K a multiple of 16
   int32_t ktile;
   // tile shape (M x N) of the FP32 plane kernel: 0 = 128 x 128, 1 = 64 x
-  // 256, 2 = 256 x 64; of the BF16x3 4M kernels on k-tiled planes: 0 = 128 x
-  // 128, 1 = 128 x 256, 2 = 256 x 128 (the two wave-group kernel)
+  // 256, 2 = 256 x 64, 3 = 64 x 64, 4 = 32 x 128, 5 = 128 x 32; of the BF16x3
+  // kernels on k-tiled planes: 0 = 128 x 128, 1 = 128 x 256, 2 = 256 x 128 (4M: the
+  // two wave-group kernel), 3 = 64 x 64
   int32_t tile;
   // Kernels on k-tiled planes only (FP32 and BF16x3).  raw_a / raw_b:
   // that operand's planes hold its values as they are, not divided by 2^e of
