@@ -1079,30 +1079,25 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
           const void *ga = A.p, *gb = B.p;
           int64_t gabs = A.bs, gbbs = B.bs;
           const double pbytes = n.planes > 2 ? 8.0 + 2.0 * n.planes : 16.0;
-          if (n.pa.needed) {
-            void *dst = pbase + L.scr_a[j];
-            TN_HIP(prof.timed(xs, TN_KCLASS_PERMUTE, pbytes * n.pa.h.nelem * nb, 0.0,
+          const PermArgs pa = {(const PermDesc *)(desc_base + n.pa.desc_off), &n.pa.h, A.p, A.bs,
+                               pbase + L.scr_a[j], pst, n.pa.h.nelem, A.slot, A.sbs, ktile_of(n, n.M)};
+          const PermArgs pb = {(const PermDesc *)(desc_base + n.pb.desc_off), &n.pb.h, B.p, B.bs,
+                               pbase + L.scr_b[j], pst, n.pb.h.nelem, B.slot, B.sbs, ktile_of(n, n.N)};
+          if (n.pa.needed || n.pb.needed) {
+            const int64_t moved = (n.pa.needed ? n.pa.h.nelem : 0) + (n.pb.needed ? n.pb.h.nelem : 0);
+            TN_HIP(prof.timed(xs, TN_KCLASS_PERMUTE, pbytes * moved * nb, 0.0,
                               [&] {
-                                return launch_permute(
-                                    xs, (const PermDesc *)(desc_base + n.pa.desc_off), n.pa.h,
-                                    A.p, A.bs, dst, pst, nb, n.planes, n.pa.h.nelem, A.slot,
-                                    A.sbs, ktile_of(n, n.M));
+                                return n.pa.needed && n.pb.needed ? launch_permute2(xs, pa, pb, nb, n.planes)
+                                                                  : launch_permute(xs, n.pa.needed ? pa : pb, nb, n.planes);
                               }),
-                   "permute A");
-            ga = dst;
+                   "permute");
+          }
+          if (n.pa.needed) {
+            ga = pa.out;
             gabs = pst;
           }
           if (n.pb.needed) {
-            void *dst = pbase + L.scr_b[j];
-            TN_HIP(prof.timed(xs, TN_KCLASS_PERMUTE, pbytes * n.pb.h.nelem * nb, 0.0,
-                              [&] {
-                                return launch_permute(
-                                    xs, (const PermDesc *)(desc_base + n.pb.desc_off), n.pb.h,
-                                    B.p, B.bs, dst, pst, nb, n.planes, n.pb.h.nelem, B.slot,
-                                    B.sbs, ktile_of(n, n.N));
-                              }),
-                   "permute B");
-            gb = dst;
+            gb = pb.out;
             gbbs = pst;
           }
           OutOperand C = outop(n.id);
@@ -1193,9 +1188,9 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
         const int nbf = L.shared[p->root] ? 1 : Q;
         TN_HIP(prof.timed(st, TN_KCLASS_PERMUTE, 16.0 * p->fperm.h.nelem * nbf, 0.0,
                           [&] {
-                            return launch_permute(
-                                st, (const PermDesc *)(desc_base + p->fperm.desc_off), p->fperm.h,
-                                R.p, R.bs, fin, (int64_t)(final_bytes / 8), nbf);
+                            const PermArgs f = {(const PermDesc *)(desc_base + p->fperm.desc_off), &p->fperm.h,
+                                                R.p, R.bs, fin, (int64_t)(final_bytes / 8), 0, nullptr, 0, KTile{}};
+                            return launch_permute(st, f, nbf, 0);
                           }),
                "output permutation");
       }

@@ -312,16 +312,40 @@ __device__ __forceinline__ void perm_emit2(void *out, int64_t pstride, int64_t i
   }
 }
 
+// One tiled permutation of a launch, and the launch's: a GEMM vertex that
+// permutes both operands takes one launch for them, the blocks of the first
+// and then those of the second (a launch of its own costs the shorter one 4 us
+// of the device, and the launch: 24 served requests 773 against 725 us, 10 open
+// legs of 22 qubits 146 against 142).  Read from the kernel argument segment: the
+// job is chosen at run time.
+struct PermJob {
+  BitTile t;
+  const float2 *in;
+  int64_t ibs;
+  void *out;
+  int64_t obs, pstride;
+  const Slot *sl;
+  int64_t sbs;
+};
+struct PermJobs {
+  PermJob job[2];
+  int32_t nblk[2];
+};
+typedef const PermJobs __attribute__((address_space(4))) *KernargPerm;
+
 template <int NP>
-__global__ __launch_bounds__(256) void k_perm_tiled(BitTile t, const float2 *in, int64_t ibs,
-                                                    void *out, int64_t obs, int64_t pstride,
-                                                    const Slot *sl, int64_t sbs) {
+__global__ __launch_bounds__(256) void k_perm_tiled(PermJobs) {
   __shared__ float2 tile[2][1 << kTileBits];
+  const KernargPerm jobs = (KernargPerm)__builtin_amdgcn_kernarg_segment_ptr();
+  const int which = (int)blockIdx.x >= jobs->nblk[0] ? 1 : 0;
+  const auto &t = jobs->job[which].t;
+  const int nblk = jobs->nblk[which], blk = (int)blockIdx.x - (which ? jobs->nblk[0] : 0);
   const int tid = threadIdx.x;
   const int q = blockIdx.y;
-  in += q * ibs;
-  void *ob = perm_out_base<NP>(out, obs, q);
-  const float fs = perm_scale<NP>(sl, sbs, q);
+  const int64_t pstride = jobs->job[which].pstride;
+  const float2 *in = jobs->job[which].in + q * jobs->job[which].ibs;
+  void *ob = perm_out_base<NP>(jobs->job[which].out, jobs->job[which].obs, q);
+  const float fs = perm_scale<NP>(jobs->job[which].sl, jobs->job[which].sbs, q);
   // this thread's pairs: tile bits 1-8 from its number, bit 9 from c
   int64_t lin = 0, lout = 0;
   int src = 0;
@@ -347,11 +371,11 @@ __global__ __launch_bounds__(256) void k_perm_tiled(BitTile t, const float2 *in,
       }
     }
   };
-  for (int64_t w = blockIdx.x; w < ntiles; w += 2 * (int64_t)gridDim.x) {
-    const bool two = w + gridDim.x < ntiles;
+  for (int64_t w = blk; w < ntiles; w += 2 * (int64_t)nblk) {
+    const bool two = w + nblk < ntiles;
     int64_t bin[2], bout[2];
     base(w, bin[0], bout[0]);
-    base(two ? w + gridDim.x : w, bin[1], bout[1]);
+    base(two ? w + nblk : w, bin[1], bout[1]);
     float4 v[2][2];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
@@ -434,27 +458,67 @@ static bool build_bit_tile(const PermDesc &h, int np, const KTile &kt, BitTile &
   return t.in_s[0] == 1 && t.out_s[0] == 1;
 }
 
-hipError_t launch_permute(hipStream_t st, const PermDesc *d_desc, const PermDesc &h, const float2 *in,
-                          int64_t ibs, void *out, int64_t obs, int nbatch, int np,
-                          int64_t pstride, const Slot *sl, int64_t sbs, KTile kt) {
-  if (np != 0 && np != 2 && np != 4 && np != 6) return hipErrorInvalidValue;
-  if (np != 0 && (!sl || pstride < h.nelem)) return hipErrorInvalidValue;
-  if (kt.on && (np == 0 || kt.kdim % 16 != 0 || kt.rows * kt.kdim != h.nelem ||
-                (kt.kshift >= 0 && ((int64_t)1 << kt.kshift) != kt.kdim)))
-    return hipErrorInvalidValue;
-  BitTile t;
+// Whether a permutation runs in tiles: its job, and its blocks.
+static bool perm_job(const PermArgs &a, int np, PermJob &job, int32_t &nblk) {
   // (planes are written two entries at a time: an even plane stride)
-  if (h.nelem >= 4096 && pstride % 2 == 0 && build_bit_tile(h, np, kt, t)) {
-    const int64_t ntiles = (int64_t)1 << t.nouter;
-    const dim3 grid(grid_for(ntiles, 1, 8192), nbatch);
-#define TN_PERM(NP) hipLaunchKernelGGL(k_perm_tiled<NP>, grid, dim3(256), 0, st, t, in, ibs, out, obs, pstride, sl, sbs)
-    if (np == 0) TN_PERM(0);
-    else if (np == 2) TN_PERM(2);
-    else if (np == 4) TN_PERM(4);
-    else TN_PERM(6);
+  if (a.h->nelem < 4096 || a.pstride % 2 != 0 || !build_bit_tile(*a.h, np, a.kt, job.t)) return false;
+  job.in = a.in;
+  job.ibs = a.ibs;
+  job.out = a.out;
+  job.obs = a.obs;
+  job.pstride = a.pstride;
+  job.sl = a.sl;
+  job.sbs = a.sbs;
+  nblk = grid_for((int64_t)1 << job.t.nouter, 1, 8192);
+  return true;
+}
+
+static hipError_t launch_perm_tiled(hipStream_t st, const PermJobs &p, int np, int nbatch) {
+  const dim3 grid((unsigned)(p.nblk[0] + p.nblk[1]), nbatch);
+#define TN_PERM(NP) hipLaunchKernelGGL(k_perm_tiled<NP>, grid, dim3(256), 0, st, p)
+  if (np == 0) TN_PERM(0);
+  else if (np == 2) TN_PERM(2);
+  else if (np == 4) TN_PERM(4);
+  else TN_PERM(6);
 #undef TN_PERM
-    return hipGetLastError();
+  return hipGetLastError();
+}
+
+static hipError_t perm_check(const PermArgs &a, int np) {
+  if (np != 0 && np != 2 && np != 4 && np != 6) return hipErrorInvalidValue;
+  if (np != 0 && (!a.sl || a.pstride < a.h->nelem)) return hipErrorInvalidValue;
+  if (a.kt.on && (np == 0 || a.kt.kdim % 16 != 0 || a.kt.rows * a.kt.kdim != a.h->nelem ||
+                  (a.kt.kshift >= 0 && ((int64_t)1 << a.kt.kshift) != a.kt.kdim)))
+    return hipErrorInvalidValue;
+  return hipSuccess;
+}
+
+hipError_t launch_permute2(hipStream_t st, const PermArgs &a, const PermArgs &b, int nbatch, int np) {
+  hipError_t e = perm_check(a, np);
+  if (e == hipSuccess) e = perm_check(b, np);
+  if (e != hipSuccess) return e;
+  PermJobs p;
+  if (perm_job(a, np, p.job[0], p.nblk[0]) && perm_job(b, np, p.job[1], p.nblk[1]))
+    return launch_perm_tiled(st, p, np, nbatch);
+  e = launch_permute(st, a, nbatch, np);
+  return e == hipSuccess ? launch_permute(st, b, nbatch, np) : e;
+}
+
+hipError_t launch_permute(hipStream_t st, const PermArgs &a, int nbatch, int np) {
+  const hipError_t e = perm_check(a, np);
+  if (e != hipSuccess) return e;
+  PermJobs p;
+  if (perm_job(a, np, p.job[0], p.nblk[0])) {
+    p.nblk[1] = 0;
+    return launch_perm_tiled(st, p, np, nbatch);
   }
+  const PermDesc *d_desc = a.d_desc;
+  const PermDesc &h = *a.h;
+  const float2 *in = a.in;
+  void *out = a.out;
+  const int64_t ibs = a.ibs, obs = a.obs, pstride = a.pstride, sbs = a.sbs;
+  const Slot *sl = a.sl;
+  const KTile kt = a.kt;
   const dim3 grid(grid_for(h.nelem, 256, 16384), nbatch);
   if (np == 0)
     hipLaunchKernelGGL(k_perm_generic<0>, grid, dim3(256), 0, st, d_desc, in, ibs, out, obs, pstride, sl, sbs, kt);

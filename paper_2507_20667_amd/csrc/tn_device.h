@@ -427,10 +427,23 @@ hipError_t launch_stream(hipStream_t st, const StreamDesc *d_desc, int64_t nfib,
 // out: complex64 (np = 0) or np bf16 planes `pstride` entries apart, holding
 // the input divided by 2^e of its scale record `sl` (query stride sbs); obs in
 // units of the output's entries (float2, or uint16 for planes)
-hipError_t launch_permute(hipStream_t st, const PermDesc *d_desc, const PermDesc &h_desc,
-                          const float2 *in, int64_t ibs, void *out, int64_t obs, int nbatch,
-                          int np = 0, int64_t pstride = 0, const Slot *sl = nullptr,
-                          int64_t sbs = 0, KTile kt = KTile{0, 0, -1, 0});
+// a permutation's operands: its descriptor (device and host copies), the batch
+// strides in entries of the buffers, the plane stride and the operand's record
+struct PermArgs {
+  const PermDesc *d_desc;
+  const PermDesc *h;
+  const float2 *in;
+  int64_t ibs;
+  void *out;
+  int64_t obs;
+  int64_t pstride;
+  const Slot *sl;
+  int64_t sbs;
+  KTile kt;
+};
+hipError_t launch_permute(hipStream_t st, const PermArgs &a, int nbatch, int np);
+// both operands of a GEMM, in one launch where both run in tiles
+hipError_t launch_permute2(hipStream_t st, const PermArgs &a, const PermArgs &b, int nbatch, int np);
 hipError_t launch_gemm(hipStream_t st, const GemmArgs &g, int prec, int form, int variant,
                        int nbatch);
 hipError_t launch_gemm_small(hipStream_t st, const SmallGemm &g, int prec, int form, int nbatch);
