@@ -901,6 +901,13 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       // scaled to 1, a closed root computed by the subtree kernel, no graph
       const bool direct = so && so->dout && out_dtype == TN_C128 && !(flags & TN_FLAG_KEEP_SCALE) &&
                           dot_root && !root_shared && trees && p->in_tree[p->root] && !gmode;
+      // or, of many, as values in the caller's type into the staging buffer: to
+      // read back and convert a record of 32 bytes takes the host longer than to
+      // copy 8 or 16 (4096 amplitudes: 72.5 us a call against 68.7), while the
+      // conversion at the end of a short launch takes longer than a record
+      // (333: 88.5 against 90.2)
+      const bool staged = Q >= 1024 && !direct && !devout && !sum && !gmode && !keep && dot_root && !root_shared &&
+                          trees && p->in_tree[p->root];
       const Operand R = operand(p->root);
       // TN_FLAG_GRAPH: replay the launch sequence captured with the same
       // workspace, layout and in-place overrides, or capture it now
@@ -968,8 +975,9 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
         tl.slots_q = slots_q;
         tl.slot_stride = perq_sl;
         tl.res = res_out;
-        tl.dres = direct ? so->dout + (int64_t)q0 * so->dout_stride : nullptr;
-        tl.dres_stride = so ? so->dout_stride : 0;
+        tl.dres = direct ? so->dout + (int64_t)q0 * so->dout_stride : staged ? (double2 *)h : nullptr;
+        tl.dres_stride = staged ? 1 : so ? so->dout_stride : 0;
+        tl.dres_c64 = staged && out_dtype != TN_C128;
         tl.fac_m = fac.m;
         tl.fac_e = fac.e;
         if (L.n_tree_shared && rcm != RC_READ) {
@@ -1263,7 +1271,10 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       }
       for (int qi = 0; qi < Q && !direct && !devout && !sum; ++qi) {
         const QueryIO &q = qs[q0 + qi];
-        if (dot_root) {
+        if (staged) {
+          memcpy(q.out, h + (size_t)qi * esz, esz);
+          if (q.log2s) *q.log2s = 0.0;
+        } else if (dot_root) {
           Result r = hr[root_shared ? 0 : qi];
           r.re *= fac.m;
           r.im *= fac.m;

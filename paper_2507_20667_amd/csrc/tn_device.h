@@ -370,11 +370,13 @@ struct TreeLaunch {
   int64_t slot_stride;  // Slot records per query
   Result *res;
   // when set, a closed root's value goes straight to dres[q * dres_stride]
-  // as complex128 (scaled to 1) instead of a Result record
+  // as complex128, or complex64 (dres_c64), scaled to 1, instead of a Result
+  // record
   double2 *dres;
   int64_t dres_stride;
   double fac_m;         // that value is multiplied by fac_m 2^fac_e
   int32_t fac_e;
+  int32_t dres_c64;
   int32_t nq;           // queries in this launch
   int32_t qw;           // queries per workgroup
 };

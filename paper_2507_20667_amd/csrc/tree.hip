@@ -947,7 +947,11 @@ __device__ __forceinline__ void tree_emit_result(const TreeLaunch &t, int q, dou
   Result r;
   tree_write_result(&r, vr, vi, za, zb);
   const int e = (int)r.log2s + t.fac_e;
-  t.dres[(int64_t)q * t.dres_stride] = make_double2(ldexp(r.re * t.fac_m, e), ldexp(r.im * t.fac_m, e));
+  const double2 v = make_double2(ldexp(r.re * t.fac_m, e), ldexp(r.im * t.fac_m, e));
+  if (t.dres_c64)
+    ((float2 *)t.dres)[(int64_t)q * t.dres_stride] = make_float2((float)v.x, (float)v.y);
+  else
+    t.dres[(int64_t)q * t.dres_stride] = v;
 }
 
 // The leaves into LDS, by the whole workgroup: the shared leaves from the
