@@ -260,7 +260,7 @@ def tn_contract_batch(ctx, queries, result_shapes, out_dtype=TN_C128, flags=0):
         q["plan"] = [plan or 0 for plan, _ in queries]
         q["num_overrides"] = np.diff(first)
         q["overrides"] = _addr(rec) + _LEAF.itemsize * np.array(first[:-1])
-    outs = [np.zeros(shape, dtype=dt) for shape in result_shapes]
+    outs = [np.zeros(result_shapes[i], dtype=dt) for i in range(n)]  # a shape per query
     optrs = np.array([_addr(o) for o in outs] or [0], dtype=np.uint64)
     l2 = np.zeros(max(1, n), dtype=np.float64)
     st = np.zeros(max(1, n), dtype=np.int32)

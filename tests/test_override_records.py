@@ -1,5 +1,5 @@
 """The binding's override records (no GPU): every value numpy can make an array
-of is accepted."""
+of is accepted, and a batch takes one result shape per query."""
 import ctypes
 
 import numpy as np
@@ -35,3 +35,10 @@ def test_override_values(a, b):
     assert rec["tensor"].tolist() == [2, 7] and (rec["dtype"] == lib.TN_C128).all()
     for i in range(2):
         assert np.array_equal(entries(rec, i, 6), X.reshape(-1))
+
+
+def test_batch_needs_a_shape_per_query():
+    """Too few shapes are refused before any result pointer is passed on (no
+    context here: the library would refuse the call as well)."""
+    with pytest.raises(IndexError):
+        lib.tn_contract_batch(None, [(None, None), (None, None)], [()])
