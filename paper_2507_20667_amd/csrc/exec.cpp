@@ -1180,11 +1180,14 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
           }
         } else {
           const bool is_root = n.id == p->root;
+          // (partitions side by side: each inner product's partial sums in its
+          // partition's region, not in the one that all of a stream share)
+          double2 *sums = conc ? (double2 *)(perq_base + L.partial[j]) : partials;
           TN_HIP(prof.timed(xs, TN_KCLASS_DOT, nodeb, wflops,
                             [&] {
                               return launch_dot(xs, (const DotDesc *)(desc_base + n.ddesc_off),
                                                 n.nelem, operand(n.c1), operand(n.c2), outop(n.id),
-                                                is_root ? res_out : nullptr, 1, partials,
+                                                is_root ? res_out : nullptr, 1, sums,
                                                 n.dot_blocks, nb);
                             }),
                  "dot");
