@@ -1088,9 +1088,9 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
           int64_t gabs = A.bs, gbbs = B.bs;
           const double pbytes = n.planes > 2 ? 8.0 + 2.0 * n.planes : 16.0;
           const PermArgs pa = {(const PermDesc *)(desc_base + n.pa.desc_off), &n.pa.h, A.p, A.bs,
-                               pbase + L.scr_a[j], pst, n.pa.h.nelem, A.slot, A.sbs, ktile_of(n, n.M)};
+                               pbase + L.scr_a[j], pst, n.pa.h.nelem, const_cast<Slot *>(A.slot), A.sbs, ktile_of(n, n.M)};
           const PermArgs pb = {(const PermDesc *)(desc_base + n.pb.desc_off), &n.pb.h, B.p, B.bs,
-                               pbase + L.scr_b[j], pst, n.pb.h.nelem, B.slot, B.sbs, ktile_of(n, n.N)};
+                               pbase + L.scr_b[j], pst, n.pb.h.nelem, const_cast<Slot *>(B.slot), B.sbs, ktile_of(n, n.N)};
           if (n.pa.needed || n.pb.needed) {
             const int64_t moved = (n.pa.needed ? n.pa.h.nelem : 0) + (n.pb.needed ? n.pb.h.nelem : 0);
             TN_HIP(prof.timed(xs, TN_KCLASS_PERMUTE, pbytes * moved * nb, 0.0,

@@ -15,10 +15,12 @@
 //
 // Products.  A value is the sum of three bfloat16 terms, x = h + m + l with
 // h = bf16(x), m = bf16(x - h), l = x - h - m, exactly (24 significant bits
-// are 3 times 8; |x| above 2^-110), and a product is ha hb + ha mb + ma hb +
-// ma mb + ha lb + la hb: the dropped terms are below 2^-25 of it, less than
-// the rounding of one FP32 addition.  bfloat16 has FP32's exponent range, so
-// this holds for entries of any size.  Six v_mfma_f32_32x32x16_bf16 do 16 k in
+// are 3 times 8), for |x| from 2^-110 (SplitRange), and a product is ha hb + ha mb
+// + ma hb + ma mb + ha lb + la hb: the dropped terms are at most 2^-24 of it (the
+// rounding of one FP32 addition; 2^-27.5 in the mean square of pairs in [1, 2),
+// 2^-26.5 with both mantissas below 1 + 2^-8, of which 2.8 % pass 2^-25).  An operand with an entry outside
+// that range, as its record's mark says, is multiplied on the FP32 matrix cores.
+// Six v_mfma_f32_32x32x16_bf16 do 16 k in
 // 192 cycles where eight v_mfma_f32_32x32x2_f32 took 512, and an accumulator
 // is rounded once per 16 k instead of per 2: the error against 64 bits is
 // smaller than the FP32 matrix cores' (2-norm, 256 x 192 outputs of normally
@@ -255,8 +257,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
     __builtin_amdgcn_sched_barrier(0);
   };
   // the same stage on the FP32 matrix cores (four real products per complex
-  // one): a split of infinity is not one, so an operand that holds one
-  // (its scale record says) takes this path
+  // one), for an operand with entries that three terms do not hold
   auto stage32 = [&](auto slot, int64_t kt) {
     constexpr int S = decltype(slot)::value;
     const float *rb = TN_FRING(S);
@@ -320,7 +321,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
       if (kt < nk) one(s0, kt);
     }
   };
-  if (max(sa->maxbits, sb->maxbits) < 0x7f000000u)
+  if ((sa->mark | sb->mark) == 0u)
     run(stage);
   else
     run(stage32);
@@ -337,6 +338,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
   PlaneOut<4> po;
   if (fo) po.init(g, m0 + wm * WT + (lane >> 5) * 4, n0 + wn * WT + (lane & 31));
   float mx = 0.0f;
+  SplitRange range;
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -352,6 +354,8 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
             const uint32_t d = po.at(mb, nb, v);
             *(float *)(P + d) = re;
             *(float *)(P1 + d) = im;
+            range.add(re);
+            range.add(im);
           } else {
             C[cm * ldc + cn] = make_float2(re, im);
           }
@@ -362,6 +366,7 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
     if (lane == 0) slot_max(&sc->maxbits, mx);
+    if (fo) range.mark(sc);
   }
 }
 

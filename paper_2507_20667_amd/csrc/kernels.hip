@@ -34,7 +34,7 @@ __global__ void k_init_slots(Slot *s, int64_t n) {
   if (i < n) {
     s[i].log2s = 0.0;
     s[i].maxbits = 0u;
-    s[i].pad = 0u;
+    s[i].mark = 0u;
   }
 }
 
@@ -176,13 +176,17 @@ hipError_t launch_stream(hipStream_t st, const StreamDesc *d_desc, int64_t nfib,
 // element here instead of once per GEMM tile that reads it.
 template <int NP>
 __device__ __forceinline__ void perm_emit(void *out, int64_t pstride, int64_t idx, float2 v,
-                                          float fs) {
+                                          float fs, SplitRange &range) {
   if (NP == 0) {
     ((float2 *)out)[idx] = v;
   } else if (NP == 2) {
     float *o = (float *)out;
-    o[idx] = v.x * fs;
-    o[pstride + idx] = v.y * fs;
+    v.x *= fs;
+    v.y *= fs;
+    range.add(v.x);
+    range.add(v.y);
+    o[idx] = v.x;
+    o[pstride + idx] = v.y;
   } else {
     uint16_t *o = (uint16_t *)out;
     uint16_t h, l;
@@ -235,7 +239,7 @@ template <int NP>
 __global__ __launch_bounds__(256) void k_perm_generic(const PermDesc *__restrict__ d,
                                                       const float2 *in, int64_t ibs, void *out,
                                                       int64_t obs, int64_t pstride,
-                                                      const Slot *sl, int64_t sbs, KTile kt) {
+                                                      Slot *sl, int64_t sbs, KTile kt) {
   __shared__ SegLds L;
   const int tid = threadIdx.x;
   const int q = blockIdx.y;
@@ -247,11 +251,13 @@ __global__ __launch_bounds__(256) void k_perm_generic(const PermDesc *__restrict
   const int nseg = d->map.nseg;
   const bool p2 = d->map.pow2 != 0;
   const int64_t n = d->nelem;
+  SplitRange range;
   for (int64_t o = (int64_t)blockIdx.x * 256 + tid; o < n; o += (int64_t)gridDim.x * 256) {
     int64_t io, oo;
     seg_decode(L, nseg, p2, o, io, oo);
-    perm_emit<NP>(ob, pstride, ktile_index(kt, oo), in[io], fs);
+    perm_emit<NP>(ob, pstride, ktile_index(kt, oo), in[io], fs, range);
   }
+  if (NP == 2) range.mark(sl + q * sbs);
 }
 
 // Tiled bit permutation.  With every extent a power of two the permutation
@@ -283,14 +289,23 @@ __device__ __forceinline__ int tile_at(int e) { return e ^ (e >> 5); }
 
 // the two consecutive entries idx, idx + 1 of the output
 template <int NP>
-__device__ __forceinline__ void perm_emit2(void *out, int64_t pstride, int64_t idx, float2 v, float2 w, float fs) {
+__device__ __forceinline__ void perm_emit2(void *out, int64_t pstride, int64_t idx, float2 v, float2 w, float fs,
+                                           SplitRange &range) {
   if (NP == 0) {
     ((float2 *)out)[idx] = v;
     ((float2 *)out)[idx + 1] = w;
   } else if (NP == 2) {
     float *o = (float *)out;
-    *(float2 *)(o + idx) = make_float2(v.x * fs, w.x * fs);
-    *(float2 *)(o + pstride + idx) = make_float2(v.y * fs, w.y * fs);
+    v.x *= fs;
+    v.y *= fs;
+    w.x *= fs;
+    w.y *= fs;
+    range.add(v.x);
+    range.add(v.y);
+    range.add(w.x);
+    range.add(w.y);
+    *(float2 *)(o + idx) = make_float2(v.x, w.x);
+    *(float2 *)(o + pstride + idx) = make_float2(v.y, w.y);
   } else {
     uint16_t *o = (uint16_t *)out;
     uint32_t h, l;
@@ -324,7 +339,7 @@ struct PermJob {
   int64_t ibs;
   void *out;
   int64_t obs, pstride;
-  const Slot *sl;
+  Slot *sl;
   int64_t sbs;
 };
 struct PermJobs {
@@ -371,6 +386,7 @@ __global__ __launch_bounds__(256) void k_perm_tiled(PermJobs) {
       }
     }
   };
+  SplitRange range;
   for (int64_t w = blk; w < ntiles; w += 2 * (int64_t)nblk) {
     const bool two = w + nblk < ntiles;
     int64_t bin[2], bout[2];
@@ -404,10 +420,11 @@ __global__ __launch_bounds__(256) void k_perm_tiled(PermJobs) {
         if (h == 0 || two) {
           const int e = src | (c ? src9 : 0);
           perm_emit2<NP>(ob, pstride, bout[h] + lout + (c ? out9 : 0), tile[h][tile_at(e)],
-                         tile[h][tile_at(e | src0)], fs);
+                         tile[h][tile_at(e | src0)], fs, range);
         }
     __syncthreads();
   }
+  if (NP == 2) range.mark(jobs->job[which].sl + q * jobs->job[which].sbs);
 }
 
 static bool build_bit_tile(const PermDesc &h, int np, const KTile &kt, BitTile &t) {
@@ -517,7 +534,7 @@ hipError_t launch_permute(hipStream_t st, const PermArgs &a, int nbatch, int np)
   const float2 *in = a.in;
   void *out = a.out;
   const int64_t ibs = a.ibs, obs = a.obs, pstride = a.pstride, sbs = a.sbs;
-  const Slot *sl = a.sl;
+  Slot *sl = a.sl;
   const KTile kt = a.kt;
   const dim3 grid(grid_for(h.nelem, 256, 16384), nbatch);
   if (np == 0)
@@ -778,7 +795,7 @@ hipError_t launch_gemm(hipStream_t st, const GemmArgs &g0, int prec, int form, i
 // Partial sums per block in FP64; the last block of a query to arrive adds
 // the partials in a fixed order (deterministic), normalises the FP64 value to
 // a mantissa in [0.5, 1) and writes both the FP64 result and a complex64 copy.
-// Arrivals are counted in the result's scale record (its pad word, zero when
+// Arrivals are counted in the result's scale record (its mark, zero when
 // the call starts and again afterwards).  The operands are small: the launch
 // is bound by latency, so a block has 1024 threads of two entries each and
 // there is no second launch (16384 entries: 12.4 + 4.2 us in two launches of
@@ -834,7 +851,7 @@ __global__ __launch_bounds__(kDotThreads) void k_dot(const DotDesc *__restrict__
     if (tid == 0) {
       __hip_atomic_store(part + 2 * blockIdx.x, s.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_store(part + 2 * blockIdx.x + 1, s.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last = __hip_atomic_fetch_add(&sc->pad, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
+      last = __hip_atomic_fetch_add(&sc->mark, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
              (uint32_t)nblocks - 1;
     }
     __syncthreads();
@@ -870,7 +887,7 @@ __global__ __launch_bounds__(kDotThreads) void k_dot(const DotDesc *__restrict__
     C.p[q * C.bs] = c;
     sc->log2s = log2s;
     sc->maxbits = __float_as_uint(fmaxf(fabsf(c.x), fabsf(c.y)));
-    sc->pad = 0u;
+    sc->mark = 0u;
   }
 }
 

@@ -16,7 +16,9 @@ namespace tn {
 struct Slot {
   double log2s;
   uint32_t maxbits;
-  uint32_t pad;
+  // an operand of an FP32 GEMM: nonzero when an entry of its planes is outside
+  // split_range; an inner product: the blocks that have arrived
+  uint32_t mark;
 };
 
 constexpr int kMaxSeg = 40;     // fused index segments per map (>= legs of dim > 1 of any tensor below 2^40 elements)
@@ -399,6 +401,29 @@ __device__ __forceinline__ void slot_max(uint32_t *maxbits, float v) {
   if (b > __hip_atomic_load(maxbits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(maxbits, b);
 }
 
+// The FP32 GEMM holds a value as three bfloat16 terms: exactly, for magnitudes
+// in [2^-110, 2^60) and zero (the last bit of a smaller one lies below
+// bfloat16's smallest, 2^-133; of two larger ones a term's product can be
+// infinite where the value's is not, as the terms of an infinity are).  Whatever
+// writes an operand's planes marks the operand's record when an entry lies
+// outside, and the GEMM then multiplies on the FP32 matrix cores.
+constexpr uint32_t kSplitLo = (127u - 110u) << 23, kSplitHi = (127u + 60u) << 23;
+struct SplitRange {
+  uint32_t lo = 0xffffffffu, hi = 0u;
+  __device__ __forceinline__ void add(float x) {
+    const uint32_t u = __float_as_uint(x) & 0x7fffffffu;
+    lo = min(lo, u - 1u);  // (zero wraps to the largest)
+    hi = max(hi, u);
+  }
+  // by a whole wave
+  __device__ __forceinline__ void mark(Slot *s) const {
+    const bool out = lo < kSplitLo - 1u || hi >= kSplitHi;
+    if (__ballot(out) != 0ull && (threadIdx.x & 63) == 0 &&
+        __hip_atomic_load(&s->mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
+      atomicOr(&s->mark, 1u);
+  }
+};
+
 // Split x = h + l with h = bf16(x) and l = bf16(x - h), both rounded to nearest
 // even (finite inputs; the hardware conversion): the two terms carry 16
 // significant bits of x.
@@ -431,6 +456,7 @@ hipError_t launch_stream(hipStream_t st, const StreamDesc *d_desc, int64_t nfib,
 // units of the output's entries (float2, or uint16 for planes)
 // a permutation's operands: its descriptor (device and host copies), the batch
 // strides in entries of the buffers, the plane stride and the operand's record
+// (float planes mark it, see SplitRange)
 struct PermArgs {
   const PermDesc *d_desc;
   const PermDesc *h;
@@ -439,7 +465,7 @@ struct PermArgs {
   void *out;
   int64_t obs;
   int64_t pstride;
-  const Slot *sl;
+  Slot *sl;
   int64_t sbs;
   KTile kt;
 };

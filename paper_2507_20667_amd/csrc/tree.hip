@@ -1174,7 +1174,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree(TreeLaunch t) {
                                : t.slots_sh + h.root_slot;
       s->log2s = (double)z.x;
       s->maxbits = (uint32_t)z.y;
-      s->pad = 0u;
+      s->mark = 0u;
     }
   }
 }
@@ -1331,7 +1331,7 @@ __global__ __launch_bounds__(256, DEV ? 3 : 4) void k_tree_wave(TreeLaunch t) {
                        : t.slots_sh + root_slot;
     sl->log2s = (double)z.x;
     sl->maxbits = (uint32_t)z.y;
-    sl->pad = 0u;
+    sl->mark = 0u;
   }
 }
 
