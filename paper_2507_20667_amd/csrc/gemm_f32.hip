@@ -15,21 +15,29 @@
 //
 // Products.  A value is the sum of three bfloat16 terms, x = h + m + l with
 // h = bf16(x), m = bf16(x - h), l = x - h - m, exactly (24 significant bits
-// are 3 times 8), for |x| from 2^-110 (SplitRange), and a product is ha hb + ha mb
-// + ma hb + ma mb + ha lb + la hb: the dropped terms are at most 2^-24 of it (the
-// rounding of one FP32 addition; 2^-27.5 in the mean square of pairs in [1, 2),
-// 2^-26.5 with both mantissas below 1 + 2^-8, of which 2.8 % pass 2^-25).  An operand with an entry outside
-// that range, as its record's mark says, is multiplied on the FP32 matrix cores.
-// Six v_mfma_f32_32x32x16_bf16 do 16 k in
-// 192 cycles where eight v_mfma_f32_32x32x2_f32 took 512, and an accumulator
-// is rounded once per 16 k instead of per 2: the error against 64 bits is
-// smaller than the FP32 matrix cores' (2-norm, 256 x 192 outputs of normally
-// distributed entries: 0.68e-7 against 1.02e-7 at K = 16, 2.4e-7 against 2.9e-7 at
-// 128, 7.0e-7 against 8.1e-7 at 1024; positive entries 3.8e-7 against 6.0e-7
-// at 1024; entries spread over 2^20 5.4e-7 against 6.6e-7).  The terms are formed in registers
-// from the float fragments (seven instructions for two values, 32 rows x 16
-// k of each operand half per wave and stage), so the planes, the permutations
-// and the fused epilogues stay FP32 and no operand takes more memory.
+// are 3 times 8), for |x| from 2^-110 (SplitRange), and a product is ha hb +
+// ha mb + ma hb + ma mb + ha lb + la hb: the dropped terms are at most 2^-24
+// of it (the rounding of one FP32 addition; 2^-27.5 in the mean square of
+// pairs in [1, 2), 2^-26.5 with both mantissas below 1 + 2^-8, of which 2.8 %
+// pass 2^-25).  An operand with an entry outside that range, as its record's
+// mark says, is multiplied on the FP32 matrix cores.
+// Six v_mfma_f32_32x32x16_bf16 do 16 k in 192 cycles where eight
+// v_mfma_f32_32x32x2_f32 took 512, and an accumulator is added to 12 times per
+// 16 k (two real products) instead of 32, the small terms of both products
+// first, so that only the last two additions round in the last bits of a short
+// sum (product by product, 0.6 % faster, the first and last columns were 0.69e-7 at
+// K = 16 and 0.52e-7).  Error against 64 bits of 1024 x 1152 outputs (2-norm),
+// here and on the FP32 matrix cores:
+//              normal          positive      modulus 1     one entry a row
+//     K = 16   0.38e-7 1.03e-7 0.38e-7 0.85e-7 0.36e-7 1.03e-7 0.35e-7 0.31e-7
+//     K = 64   1.52e-7 2.03e-7 1.17e-7 1.59e-7 1.50e-7 2.03e-7 0.35e-7 0.31e-7
+//     K = 256  3.36e-7 4.06e-7 2.35e-7 3.06e-7 3.29e-7 4.05e-7 0.35e-7 0.31e-7
+// (one complex64 multiplication: 0.38e-7).  The two products of order three as
+// well change these numbers in the third digit, at 1.19 times the time.
+// The terms are formed in registers from the float fragments (seven
+// instructions for two values, 32 rows x 16 k of each operand half per wave
+// and stage), so the planes, the permutations and the fused epilogues stay FP32
+// and no operand takes more memory.
 // The complex product takes four real ones whatever the form flag says
 // (Gauss's three would need a third accumulator set: one block per CU).
 //
@@ -233,24 +241,21 @@ __global__ __launch_bounds__(256, 2) void k_cgemm_f32_planes(GemmArgs g) {
       v4u_f b[2][3];
 #pragma unroll
       for (int pl = 0; pl < 2; ++pl) split(rb + 2 * APL + pl * BPL + (wn * WT + nb * 32 + fr) * FBK, b[pl]);
-      // the six products of total order at most two, smallest first
-#pragma unroll
-      for (int pi = 0; pi < 6; ++pi) {
-        const int x = kSplitA[pi], y = kSplitB[pi];
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-          acc[mb][nb][0] = mfma_bf(a[mb][0][x], b[0][y], acc[mb][nb][0]);
-          acc[mb][nb][1] = mfma_bf(a[mb][1][x], b[0][y], acc[mb][nb][1]);
-        }
-      }
+      // the six products of total order at most two, smallest first, and of
+      // both of a part's real products before the next larger
 #pragma unroll
       for (int pi = 0; pi < 6; ++pi) {
         const int x = kSplitA[pi], y = kSplitB[pi];
         const v4u_f bn = b[1][y] ^ 0x80008000u;
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) {
-          acc[mb][nb][1] = mfma_bf(a[mb][0][x], b[1][y], acc[mb][nb][1]);
+          acc[mb][nb][0] = mfma_bf(a[mb][0][x], b[0][y], acc[mb][nb][0]);
+          acc[mb][nb][1] = mfma_bf(a[mb][1][x], b[0][y], acc[mb][nb][1]);
+        }
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
           acc[mb][nb][0] = mfma_bf(a[mb][1][x], bn, acc[mb][nb][0]);
+          acc[mb][nb][1] = mfma_bf(a[mb][0][x], b[1][y], acc[mb][nb][1]);
         }
       }
     }
