@@ -1095,13 +1095,14 @@ tn_status build_plan(tn_plan *p, const tn_plan_desc *d) {
       for (int64_t i = 0; i < n; ++i) dst[i] = make_float2((float)s[2 * i], (float)s[2 * i + 1]);
       if (n > kStreamMax || (p->flags & TN_PREC_BF16X3)) continue;
       bool rounds = false;
-      double big = 0.0;
+      double big = 0.0, least = 1e300;  // least: of those that FP32 holds
       for (int64_t i = 0; i < 2 * n; ++i) {
         rounds = rounds || (double)(float)s[i] != s[i];
         big = std::max(big, std::fabs(s[i]));
+        if ((float)s[i] != 0.0f) least = std::min(least, std::fabs(s[i]));
       }
-      // (sizes for which neither the divisor nor a quotient leaves the normal range)
-      if (!rounds || !(big > 1e-30 && big < 1e30)) continue;
+      // (neither the divisor nor a quotient that was normal may leave the normal range)
+      if (!rounds || !(big > 1e-30 && big < 1e30) || (big > 1.0 && least < big * 0x1p-126)) continue;
       p->leaf_div[v] = big;
       p->leaf_raw_off[v] = (int64_t)p->leaf_raw.size();
       for (int64_t i = 0; i < n; ++i) {
