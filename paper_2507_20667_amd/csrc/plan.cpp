@@ -338,14 +338,21 @@ static void interleave_rows(std::vector<int64_t> &FB, int npc, const Layout &B, 
   FB = out;
 }
 
+// tile shape of the FP32 matrix core kernel
+static int f32_variant(int64_t M, int64_t N) { return M >= 128 && N >= 128 ? 0 : 1; }
+
 // Whether a GEMM vertex runs on k_cgemm_small (M, N up to 2^15: the size of
 // its tables).  Times are of one vertex with its permutations, two queries.
 //   k up to 15: the kernels on k-tiled planes need a multiple of 16, and the
 //     result's bytes bound the vertex: 1024 x 2048 at k = 8 takes 15 us against
 //     41.  Operands up to 2^18 entries, which the L2 holds.
-//   a longer k that is no multiple of 16: in FP32 always (the alternative's
-//     FP32 matrix core kernel has no rate to set against it: 200 x 200 x 50 11 us
-//     against 34, 407 x 523 x 405 65 against 177, 1400 x 1400 x 1400 717 against 852);
+//   a longer k that is no multiple of 16: in FP32 where the alternative, the FP32
+//     matrix core kernel, would not split k (it has no rate to set against this
+//     one: 200 x 200 x 50 11 us against 34, 407 x 523 x 405 65 against 177, 1400 x
+//     1400 x 1401 508 against 824, 6000 x 6000 x 2049 8.95 ms against 10.9).  Where it
+//     does, from k = 2048 on, its chunks fill the chip and their sums round less
+//     (20 x 24 x 20001 2569 us and an error of 3.5e-6 here, 184 and 0.88e-6 there;
+//     1000 x 1000 x 8191 2656 and 2.3e-6, 1144 and 1.15e-6).
 //     BF16x3's split products cost the vector units three times as much, so
 //     k up to 128 and 2^24 multiply-adds (300 x 300 x 100 31 against 58, 600 x 600 x
 //     333 199 against 152).
@@ -362,7 +369,10 @@ static bool small_gemm(int64_t M, int64_t N, int64_t K, bool bf16, bool fusable)
   if (M > 1 << 15 || N > 1 << 15) return false;
   const int64_t macs = K <= 1 << 15 ? M * N * K : INT64_MAX;
   if (K < 16) return M * K <= 1 << 18 && N * K <= 1 << 18;
-  if (K % 16 != 0) return K <= 1 << 15 && (!bf16 || (K <= 128 && macs <= 1 << 24));
+  if (K % 16 != 0) {
+    const int tile = gemm_variant_tile_m(f32_variant(M, N));
+    return K <= 1 << 15 && (bf16 ? K <= 128 && macs <= 1 << 24 : gemm_ksplit(M, N, K, tile, tile, nullptr) == 1);
+  }
   if (fusable || K > 128) return false;
   return bf16 ? macs <= (K <= 64 ? 1 << 23 : 1 << 19) : macs <= 1 << 24;
 }
@@ -523,7 +533,7 @@ static tn_status schedule_gemm(tn_plan *p, Node &n, const Layout &A, const Layou
   std::vector<int64_t> out = FA;
   out.insert(out.end(), FB.begin(), FB.end());
   n.out = make_layout(out, A, B);
-  n.variant = (n.M >= 128 && n.N >= 128) ? 0 : 1;
+  n.variant = f32_variant(n.M, n.N);
   // FP32 planes: a 64-row or 64-column tile when that side is that small
   // (a 128 x 128 tile would run half empty), unless the tuning table says
   // otherwise
