@@ -640,13 +640,15 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
     // the caller wants them) or closed-root records
     const size_t esz = out_dtype == TN_C128 ? 16 : 8;
     const bool keep = (flags & TN_FLAG_KEEP_SCALE) != 0;
-    const int out_mode = (out_dtype == TN_C128 ? 1 : 0) | (keep ? 2 : 0);
-    auto staging_bytes = [&](int nq) { return (size_t)nq * (relems * esz + sizeof(Slot) + sizeof(Result)); };
+    // (a graph's staging serves calls of either type)
+    auto staging_bytes = [&](int nq) {
+      return (size_t)nq * (relems * (want_graph ? 16 : esz) + sizeof(Slot) + sizeof(Result));
+    };
     size_t rb_bytes = staging_bytes(Q);
     if (gmode) {
       if (!p->graph) p->graph.reset(new GraphEntry());
       GraphEntry &E = *p->graph;
-      if (E.layout != &L || E.Q != Q || E.ws_bytes != total || E.out_mode != out_mode) {
+      if (E.layout != &L || E.Q != Q || E.ws_bytes != total) {
         hipStreamSynchronize(st);
         release_graph(ctx, E);
         E.ws = arena_alloc(ctx, total, true);
@@ -660,7 +662,6 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
           E.pinned_bytes = rb_bytes;
           E.layout = &L;
           E.Q = Q;
-          E.out_mode = out_mode;
         }
       }
     }
@@ -879,7 +880,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       // still read it)
       const bool root_shared = L.shared[p->root] != 0;
       const bool dot_root = nv > 1 && p->nodes[p->root - nv].kind == NK_DOT;
-      size_t rb_vals = (size_t)Q * relems * esz, rb_slots = (size_t)Q * sizeof(Slot);
+      size_t rb_vals = (size_t)Q * relems * (gmode ? 16 : esz), rb_slots = (size_t)Q * sizeof(Slot);
       // results into device memory (no host staging at all)
       const bool devout = so && so->device_out;
       uint8_t *h = nullptr;
@@ -1226,7 +1227,19 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
                  "slice sum");
         }
       }
-      // open results, converted on the way out
+      if (capturing) {
+        hipGraph_t g = nullptr;
+        capturing = false;
+        TN_HIP(hipStreamEndCapture(st, &g), "graph capture end");
+        hipError_t e = hipGraphInstantiate(&p->graph->exec, g, nullptr, nullptr, 0);
+        hipGraphDestroy(g);
+        if (e != hipSuccess) p->graph->exec = nullptr;
+        TN_HIP(e, "graph instantiate");
+        TN_HIP(hipGraphLaunch(p->graph->exec, st), "graph launch");
+      }
+      }  // not a replay
+      // open results, converted on the way out (not part of a graph, which so
+      // serves calls of either type, scales kept or not)
       if (!dot_root && !devout && !sum) {
         const int rq = root_shared ? 1 : Q;
         Operand S = R;
@@ -1241,17 +1254,6 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
                                   sizeof(Slot), rq, hipMemcpyDeviceToHost, st),
                  "scale copy");
       }
-      if (capturing) {
-        hipGraph_t g = nullptr;
-        capturing = false;
-        TN_HIP(hipStreamEndCapture(st, &g), "graph capture end");
-        hipError_t e = hipGraphInstantiate(&p->graph->exec, g, nullptr, nullptr, 0);
-        hipGraphDestroy(g);
-        if (e != hipSuccess) p->graph->exec = nullptr;
-        TN_HIP(e, "graph instantiate");
-        TN_HIP(hipGraphLaunch(p->graph->exec, st), "graph launch");
-      }
-      }  // not a replay
       const double t_launched = dbg ? ms_since(t_enter) : 0.0;
       TN_HIP(hipStreamSynchronize(st), "stream synchronize");
       if (dbg)

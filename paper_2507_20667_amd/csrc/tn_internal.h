@@ -310,7 +310,6 @@ namespace tn {
 struct GraphEntry {
   const ExecLayout *layout = nullptr;
   int Q = 0;
-  int out_mode = 0;                // result type, and whether scales are kept
   size_t ws_bytes = 0;
   int64_t ws = -1;                 // arena offset of the group's workspace (kept)
   void *pinned = nullptr;          // result staging the graph copies into (kept)
