@@ -540,7 +540,12 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
   // wide: the whole group fits with room for wide_split's partial sums
   size_t chunk;
   bool wide = false;
-  if (rs.ext_ws) {
+  bool want_graph = (flags & TN_FLAG_GRAPH) && rs.ws < 0 && !rs.ext_ws && !prof.on && !dbg_gemm;
+  if (want_graph && p->graph && p->graph->layout == &L && p->graph->Q == (int)qs.size()) {
+    // a graph's workspace is kept as it is
+    chunk = qs.size();
+    wide = p->graph->wide;
+  } else if (rs.ext_ws) {
     const size_t need = group_workspace_bytes(p, L, (int)qs.size());
     if (need > rs.ext_ws_bytes) {
       set_error("the workspace of %zu queries (%zu bytes) exceeds the static scratch (%zu bytes)",
@@ -581,13 +586,14 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
     chunk = (avail - shared_fixed - 4096) / (per_query + 1024);
     chunk = std::min<size_t>(chunk, 65535);
     chunk = std::max<size_t>(chunk, 1);
-    wide = chunk >= qs.size() && group_workspace_bytes(p, L, (int)qs.size(), true) + 4096 <= avail;
+    // (a workspace that a graph keeps: with a quarter of the room at most)
+    wide = chunk >= qs.size() &&
+           (group_workspace_bytes(p, L, (int)qs.size(), true) + 4096) * (want_graph ? 4 : 1) <= avail;
   }
   tn_status rc = TN_OK;
   // TN_FLAG_GRAPH (the whole group in one chunk, not profiled, not serving):
   // the call runs on the context's graph stream, after the caller's stream
-  bool want_graph = (flags & TN_FLAG_GRAPH) && rs.ws < 0 && !rs.ext_ws && !prof.on && !dbg_gemm &&
-                    chunk >= qs.size();
+  want_graph = want_graph && chunk >= qs.size();
   hipStream_t gst = nullptr;
   // a caller's stream other than the context's (a batch lane, never the null
   // stream) is captured on directly
@@ -662,6 +668,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
           E.pinned_bytes = rb_bytes;
           E.layout = &L;
           E.Q = Q;
+          E.wide = wide;
         }
       }
     }

@@ -310,6 +310,7 @@ namespace tn {
 struct GraphEntry {
   const ExecLayout *layout = nullptr;
   int Q = 0;
+  bool wide = false;               // room for wide_split's partial sums in ws
   size_t ws_bytes = 0;
   int64_t ws = -1;                 // arena offset of the group's workspace (kept)
   void *pinned = nullptr;          // result staging the graph copies into (kept)
