@@ -109,6 +109,32 @@ static bool rcache_evict_one(tn_ctx *ctx, const ExecLayout *keep) {
   return true;
 }
 
+// Subtree programs that only single calls (tn_contract) have used so far stay
+// in the arena for the next one, but give way to any allocation that fails:
+// they take room from no other call.  ctx->singles lists their layouts; a call
+// that runs one pins it.  Both, and the fields they guard, under rcache_mu.
+static bool drop_single_locked(tn_ctx *ctx) {
+  bool any = false;
+  for (size_t i = 0; i < ctx->singles.size();) {
+    ExecLayout *e = ctx->singles[i];
+    if (e->single_pins > 0) {
+      ++i;
+      continue;
+    }
+    ctx->arena.release(e->tree_dev, e->tree_dev_bytes, true);
+    e->tree_dev = -1;
+    e->single_prog = false;
+    ctx->singles.erase(ctx->singles.begin() + (long)i);
+    any = true;
+  }
+  return any;
+}
+
+bool drop_single_programs(tn_ctx *ctx) {
+  std::lock_guard<std::mutex> g(ctx->rcache_mu);
+  return drop_single_locked(ctx);
+}
+
 // RC_READ: the cache holds the shared part; RC_FILL: this call computes it
 // into the cache; RC_NONE: it computes it in its own workspace.
 static int rcache_acquire(tn_ctx *ctx, ExecLayout &L, size_t bytes, bool may_fill) {
@@ -124,6 +150,7 @@ static int rcache_acquire(tn_ctx *ctx, ExecLayout &L, size_t bytes, bool may_fil
     }
     if (ctx->rcache_bytes + bytes > ctx->rcache_budget) return RC_NONE;
     int64_t off = ctx->arena.alloc(bytes, true);
+    if (off < 0 && drop_single_locked(ctx)) off = ctx->arena.alloc(bytes, true);
     while (off < 0 && rcache_evict_one(ctx, &L)) off = ctx->arena.alloc(bytes, true);
     if (off < 0) return RC_NONE;
     L.rc_off = off;
@@ -153,28 +180,6 @@ void rcache_drop(tn_ctx *ctx, ExecLayout &L) {
   L.rc_off = -1;
   L.rc_bytes = 0;
   L.rc_state = 0;
-}
-
-// Subtree programs that only single calls (tn_contract) have used so far stay
-// in the arena for the next one, but give way to any allocation that fails:
-// they take room from no other call.  ctx->singles lists their layouts; a call
-// that runs one pins it.  Both, and the fields they guard, under rcache_mu.
-bool drop_single_programs(tn_ctx *ctx) {
-  std::lock_guard<std::mutex> g(ctx->rcache_mu);
-  bool any = false;
-  for (size_t i = 0; i < ctx->singles.size();) {
-    ExecLayout *e = ctx->singles[i];
-    if (e->single_pins > 0) {
-      ++i;
-      continue;
-    }
-    ctx->arena.release(e->tree_dev, e->tree_dev_bytes, true);
-    e->tree_dev = -1;
-    e->single_prog = false;
-    ctx->singles.erase(ctx->singles.begin() + (long)i);
-    any = true;
-  }
-  return any;
 }
 
 // the layout's programs are no longer a single call's alone (rcache_mu held)
