@@ -218,6 +218,7 @@ int64_t arena_alloc(tn_ctx *ctx, size_t bytes, bool persistent) {
 tn_status upload_tree_programs(tn_ctx *ctx, const ExecLayout &L, hipStream_t st, bool single) {
   if (L.n_tree_shared + L.n_tree_perq == 0) return TN_OK;
   ExecLayout &Lm = const_cast<ExecLayout &>(L);
+  const size_t bytes = std::max<size_t>(L.tree_blob.size(), 256);
   {
     std::lock_guard<std::mutex> g(ctx->rcache_mu);
     if (single)
@@ -225,32 +226,34 @@ tn_status upload_tree_programs(tn_ctx *ctx, const ExecLayout &L, hipStream_t st,
     else
       single_keep(ctx, Lm);
     if (L.tree_dev >= 0) return TN_OK;
-  }
-  const size_t bytes = std::max<size_t>(L.tree_blob.size(), 256);
-  const int64_t off = arena_alloc(ctx, bytes, true);
-  hipError_t e = hipSuccess;
-  if (off >= 0) {
-    e = hipMemcpyAsync(ctx->arena.base() + off, L.tree_blob.data(), L.tree_blob.size(), hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-  }
-  std::lock_guard<std::mutex> g(ctx->rcache_mu);
-  if (off < 0 || e != hipSuccess) {
-    if (single) Lm.single_pins--;
-    ctx->arena.release(off, bytes, true);
-    if (off < 0) {
+    // (taken and listed at once: whoever asks for the work capacity meanwhile
+    // counts these bytes as room that comes back)
+    Lm.tree_dev = ctx->arena.alloc(bytes, true);
+    if (L.tree_dev < 0 && drop_single_locked(ctx)) Lm.tree_dev = ctx->arena.alloc(bytes, true);
+    if (L.tree_dev < 0) {
+      if (single) Lm.single_pins--;
       set_error("arena cannot hold the subtree programs (%zu bytes)", bytes);
       return TN_E_NOMEM;
     }
-    set_error("subtree program upload: %s", hipGetErrorString(e));
-    return TN_E_DEVICE;
+    Lm.tree_dev_bytes = bytes;
+    if (single) {
+      Lm.single_prog = true;
+      ctx->singles.push_back(&Lm);
+    }
   }
-  Lm.tree_dev = off;
-  Lm.tree_dev_bytes = bytes;
+  hipError_t e =
+      hipMemcpyAsync(ctx->arena.base() + L.tree_dev, L.tree_blob.data(), L.tree_blob.size(), hipMemcpyHostToDevice, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  if (e == hipSuccess) return TN_OK;
+  std::lock_guard<std::mutex> g(ctx->rcache_mu);
   if (single) {
-    Lm.single_prog = true;
-    ctx->singles.push_back(&Lm);
+    Lm.single_pins--;
+    single_keep(ctx, Lm);
   }
-  return TN_OK;
+  ctx->arena.release(L.tree_dev, bytes, true);
+  Lm.tree_dev = -1;
+  set_error("subtree program upload: %s", hipGetErrorString(e));
+  return TN_E_DEVICE;
 }
 
 // Pin of a single call on its layout's programs, released when the call ends.
