@@ -1766,7 +1766,9 @@ static void build_tree_programs(const tn_plan *p, ExecLayout &L, const std::vect
   }
   L.lds_perq = tree_lds_bytes(L.tree_qw, max_scale_q, max_sh_q, max_pq_q, L.tree_wave);
   L.lds_perq1 = tree_lds_bytes(1, max_scale_q, max_sh_q, max_pq_q);
-  if (L.lds_perq1 > lim) {
+  // (a program that only the batch kernel has room for runs there always)
+  const bool level_fits = L.lds_perq1 <= lim;
+  if (!level_fits && !L.tree_wave) {
     L.tree_error = true;
     return;
   }
@@ -2208,7 +2210,7 @@ static void build_tree_programs(const tn_plan *p, ExecLayout &L, const std::vect
       level = std::max(level, (h.nsteps <= 2 * kTreeChunk ? 8.0 : 11.0) * h.nchunks + 0.75 * wl / 8);
       batch = std::max(batch, steps_b + 0.75 * wb);
     }
-    L.tree_few = level < batch;
+    L.tree_few = level_fits && level < batch;
   }
   if (getenv("TN_DEBUG"))
     for (const TreeHdr &h : hdrs) {
