@@ -84,6 +84,12 @@ static tn_status ensure_pinned(ExecRes &r, size_t bytes, hipStream_t st) {
   return TN_OK;
 }
 
+// Staging of open results, as values in the caller's type (16 bytes an entry
+// for complex128): larger ones go through it in pieces.  64 MB takes a
+// millisecond over the host link, against which a piece's launch and wait of
+// some 15 us are nothing.
+constexpr size_t kStageBytes = (size_t)64 << 20;
+
 // ------------------------------------------------------ shared-part cache
 // A layout's shared part (the vertices no override reaches, computed once per
 // call for all its queries) depends only on the plan's own leaves, so it is
@@ -654,9 +660,13 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
     // the caller wants them) or closed-root records
     const size_t esz = out_dtype == TN_C128 ? 16 : 8;
     const bool keep = (flags & TN_FLAG_KEEP_SCALE) != 0;
-    // (a graph's staging serves calls of either type)
+    // (a graph's staging serves calls of either type; open results of more than
+    // kStageBytes go through it in pieces)
+    auto staging_vals = [&](int nq, bool graph) {
+      return std::min((size_t)nq * relems * (graph ? 16 : esz), std::max(kStageBytes, (size_t)nq * 16));
+    };
     auto staging_bytes = [&](int nq) {
-      return (size_t)nq * (relems * (want_graph ? 16 : esz) + sizeof(Slot) + sizeof(Result));
+      return staging_vals(nq, want_graph) + (size_t)nq * (sizeof(Slot) + sizeof(Result));
     };
     size_t rb_bytes = staging_bytes(Q);
     if (gmode) {
@@ -895,7 +905,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       // still read it)
       const bool root_shared = L.shared[p->root] != 0;
       const bool dot_root = nv > 1 && p->nodes[p->root - nv].kind == NK_DOT;
-      size_t rb_vals = (size_t)Q * relems * (gmode ? 16 : esz), rb_slots = (size_t)Q * sizeof(Slot);
+      size_t rb_vals = staging_vals(Q, gmode), rb_slots = (size_t)Q * sizeof(Slot);
       // results into device memory (no host staging at all)
       const bool devout = so && so->device_out;
       uint8_t *h = nullptr;
@@ -1255,15 +1265,18 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       }  // not a replay
       // open results, converted on the way out (not part of a graph, which so
       // serves calls of either type, scales kept or not)
-      if (!dot_root && !devout && !sum) {
-        const int rq = root_shared ? 1 : Q;
-        Operand S = R;
-        if (p->fperm.needed) {
-          S.p = fin;
-          S.bs = (int64_t)(final_bytes / 8);
-        }
-        TN_HIP(launch_results_out(st, S, rq, (int64_t)relems, fac.m, fac.e, keep, out_dtype == TN_C128, h),
-               "result copy");
+      const bool open_out = !dot_root && !devout && !sum;
+      const int rq = root_shared ? 1 : Q;
+      const bool pieces = open_out && (size_t)rq * relems * esz > kStageBytes;
+      Operand S = R;
+      if (p->fperm.needed) {
+        S.p = fin;
+        S.bs = (int64_t)(final_bytes / 8);
+      }
+      if (open_out) {
+        if (!pieces)
+          TN_HIP(launch_results_out(st, S, rq, (int64_t)relems, fac.m, fac.e, keep, out_dtype == TN_C128, h),
+                 "result copy");
         if (keep)
           TN_HIP(hipMemcpy2DAsync(hs, sizeof(Slot), R.slot, (R.sbs ? R.sbs : 1) * sizeof(Slot),
                                   sizeof(Slot), rq, hipMemcpyDeviceToHost, st),
@@ -1289,6 +1302,17 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
           sum->add(v, relems, *(const double *)(h + relems * 16) + fac.e);
         }
       }
+      for (int src = 0; src < rq && pieces; ++src)
+        for (size_t i = 0; i < relems; i += kStageBytes / esz) {
+          const size_t n = std::min(relems - i, kStageBytes / esz);
+          Operand P = S;
+          P.p += src * S.bs + (int64_t)i;
+          P.slot += src * S.sbs;
+          TN_HIP(launch_results_out(st, P, 1, (int64_t)n, fac.m, fac.e, keep, out_dtype == TN_C128, h), "result copy");
+          TN_HIP(hipStreamSynchronize(st), "stream synchronize");
+          for (int qi = root_shared ? 0 : src; qi < (root_shared ? Q : src + 1); ++qi)
+            memcpy((char *)qs[q0 + qi].out + i * esz, h, n * esz);
+        }
       for (int qi = 0; qi < Q && !direct && !devout && !sum; ++qi) {
         const QueryIO &q = qs[q0 + qi];
         if (staged) {
@@ -1318,7 +1342,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
           }
         } else {
           const int src = root_shared ? 0 : qi;
-          memcpy(q.out, h + (size_t)src * relems * esz, relems * esz);
+          if (!pieces) memcpy(q.out, h + (size_t)src * relems * esz, relems * esz);
           if (q.log2s) *q.log2s = keep ? hs[src].log2s + fac.e : 0.0;
         }
         if (q.status) *q.status = TN_OK;
