@@ -32,8 +32,14 @@
  *     the arena handed to tn_ctx_create, which stays owned by the caller and
  *     must outlive the context.
  *   - Precision: data on the GPU are complex64; the GEMMs run either in FP32
- *     on the FP32 matrix cores or as a three-term split-BF16 product with FP32
- *     accumulation.  Every intermediate carries an FP64 power-of-two scale
+ *     or as a three-term split-BF16 product with FP32 accumulation (the FP32
+ *     ones mostly on the bf16 matrix cores too, every value held exactly as
+ *     the sum of three bf16 terms and six products of terms added in FP32: a
+ *     product is off by at most 2^-24 of it before it is added, and a sum by
+ *     less than on the FP32 matrix cores, except that a result of one or two
+ *     products can be off by one more unit of its last place; operands with
+ *     an entry that is infinite, not a number, from 2^60 on or below 2^-110 are
+ *     multiplied on the FP32 matrix cores).  Every intermediate carries an FP64 power-of-two scale
  *     (log2) so that amplitudes cannot underflow, and the final contraction of
  *     a closed network accumulates in FP64.
  */
@@ -70,10 +76,11 @@ typedef enum { TN_C64 = 0, TN_C128 = 1, TN_C64_DEVICE = 2 } tn_dtype;
 
 /* flags of tn_plan_load (precision and GEMM form) and of tn_contract* */
 enum {
-  TN_PREC_FP32 = 0,        /* FP32 complex GEMM on the FP32 matrix cores */
+  TN_PREC_FP32 = 0,        /* FP32 complex GEMM (see Precision above) */
   TN_PREC_BF16X3 = 1,      /* x = h + l split into two BF16 terms; a*b ~ hh + hl + lh */
   TN_FORM_4M = 0,          /* four real products per complex product */
-  TN_FORM_3M = 1 << 4,     /* three real products (Gauss) */
+  TN_FORM_3M = 1 << 4,     /* three real products (Gauss) in BF16x3; FP32 plans form
+                              four except where k is no multiple of 16 and long */
   TN_FLAG_KEEP_SCALE = 1 << 8, /* return mantissa and log2 scale separately */
   TN_FLAG_GRAPH = 1 << 9,      /* batched calls: capture each plan group's launch
                                   sequence as a HIP graph and replay it (see
@@ -233,8 +240,17 @@ tn_status tn_plan_slice(tn_plan *plan, int32_t num_labels, const int64_t *labels
  * partition takes memory of its own (the workspace is the sum of the
  * partitions' live peaks plus the reduction path's, not their maximum). The
  * results are bit-identical to the serial order: every vertex computes the
- * same values either way (where the arena holds both layouts).  Without
- * effect on a plan of one partition.
+ * same values either way, where the arena has room for both layouts and, in
+ * both, for the partial sums of skinny products (up to 34 MB; one region per
+ * partition and one for the reduction path here).  Small vertices run in the
+ * subtree kernels before the streams part, and shared parts of a subtree are
+ * not computed apart, so a call of many small vertices is mostly slower than
+ * without the flag (uneven circuits of 12 to 26 qubits: 0.7 of the rate).
+ * Without effect on a plan of one partition.
+ * The last bits of a result depend on the call: a GEMM's tile and the number of
+ * chunks its k is summed in follow the number of queries in the call and, for
+ * skinny products, whether the arena has room for the chunks' partial sums.
+ * Equal calls in equal circumstances give equal bits.
  * Errors: TN_E_INVALID_ARG (host-only plan, bad override or flag), TN_E_NOMEM
  * (the arena cannot hold the workspace), TN_E_DEVICE.
  */
@@ -249,7 +265,7 @@ tn_status tn_contract(tn_plan *plan, int32_t num_overrides, const tn_leaf *overr
  * status (may be NULL).  Returns the first error, or TN_OK.
  * TN_FLAG_GRAPH: the launch sequence of each plan's group is captured as a
  * HIP graph on its first run and replayed on later calls with the same plan,
- * overridden leaves, query count and output type (overrides are staged into
+ * overridden leaves and query count (overrides are staged into
  * the group's own workspace first; device overrides read in place are part of
  * the match).  The plan then keeps that workspace and a pinned result buffer
  * until it is freed or a call with another group replaces the graph.  Groups

@@ -929,9 +929,10 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
                           dot_root && !root_shared && trees && p->in_tree[p->root] && !gmode;
       // or, of many, as values in the caller's type into the staging buffer: to
       // read back and convert a record of 32 bytes takes the host longer than to
-      // copy 8 or 16 (4096 amplitudes: 72.5 us a call against 68.7), while the
-      // conversion at the end of a short launch takes longer than a record
-      // (333: 88.5 against 90.2)
+      // copy 8 or 16.  Calls of 20-qubit brickwork amplitudes, records against
+      // values: 4096 71.3 us against 68.5, 2048 56.3 against 55.5, 1024 51.8
+      // against 51.3, 333 50.8 against 50.4; of 17-qubit ones with host vectors
+      // the same at every size.  From 1024 on, where it shows.
       const bool staged = Q >= 1024 && !direct && !devout && !sum && !gmode && !keep && dot_root && !root_shared &&
                           trees && p->in_tree[p->root];
       const Operand R = operand(p->root);

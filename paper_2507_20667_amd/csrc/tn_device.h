@@ -108,7 +108,8 @@ struct GemmArgs {
   // its scale record (a producer GEMM wrote them, see fo_on): the result is
   // multiplied by 2^-e instead, which is exact (and so is the bf16 split of
   // a value times a power of two), so it is the same as from divided planes
-  // (values in the normal FP32 range).
+  // (values in the normal FP32 range; FP32: where both forms are inside or both
+  // outside SplitRange).
   // fo_on: write the result not to C as complex64 but as the consumer's
   // k-tiled operand planes, d of the result index m N + n given bit by bit
   // (bit b of it goes to bit fo_d[b] of d; fo_nbits = log2 N bits of n, then
