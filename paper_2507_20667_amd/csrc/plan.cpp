@@ -2308,6 +2308,7 @@ ExecLayout make_exec_layout(const tn_plan *p, const std::vector<int> &overridden
     if (!ovr[t]) L.fac.mul(p->leaf_div[t]);
   for (int v = 0; v < nv; ++v) L.shared[v] = ovr[v] ? 0 : 1;
   for (const Node &n : p->nodes) L.shared[n.id] = L.shared[n.c1] && L.shared[n.c2];
+  const std::vector<uint8_t> untouched = L.shared;  // no override reaches it
   if (!share)  // plain execution: every intermediate belongs to the query
     for (int v = nv; v < nn; ++v) L.shared[v] = 0;
   const bool trees = allow_trees && !p->tree_roots.empty();
@@ -2349,16 +2350,17 @@ ExecLayout make_exec_layout(const tn_plan *p, const std::vector<int> &overridden
     // of the workspace (their whole lifetime), which keeps each query's LDS
     // small enough for more queries per CU
     L.spill.clear();
-    // (the plan's choice: tuning table, TN_TREE_SPILL; a layout without a
-    // shared part runs one query, alone in its CU)
-    const int64_t spill_at = share ? p->knobs.spill : kTreeMaxElems + 1;
+    // (the plan's choice: tuning table, TN_TREE_SPILL.  A layout without a
+    // shared part spills the same vertices, though it runs one query, alone in
+    // its CU: a step on device memory adds its terms in another order)
+    const int64_t spill_at = p->knobs.spill;
     for (int r : p->tree_roots) {
       if (L.shared[r]) continue;
       std::vector<int> stack{p->nodes[r - nv].c1, p->nodes[r - nv].c2};
       while (!stack.empty()) {
         const int u = stack.back();
         stack.pop_back();
-        if (u < nv || L.shared[u]) continue;  // leaves, islands
+        if (u < nv || untouched[u]) continue;  // leaves, islands
         const Node &n = p->nodes[u - nv];
         if ((int64_t)n.out.size() >= spill_at) L.spill.push_back(u);
         stack.push_back(n.c1);
