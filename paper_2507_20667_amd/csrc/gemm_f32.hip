@@ -41,11 +41,11 @@
 // The complex product takes four real ones whatever the form flag says
 // (Gauss's three would need a third accumulator set: one block per CU).
 //
-// Bound: the matrix cores, at the clock their power allows.  Eight 30-qubit
-// amplitudes: 76.7 -> 51.7 ms of GEMM against the FP32 matrix cores' 3M form
-// (12.9 -> 7.7 ms for one amplitude against 4M), 1540 TFLOP/s of bf16
-// products, matrix cores busy 0.70 at 2.05-2.15 GHz (they sustain 1794 TFLOP/s
-// with no memory traffic on operands that change).
+// Bound: the matrix cores, at the clock their power allows.  The five GEMMs of
+// eight 30-qubit amplitudes: 43.3 ms, against 66.5 on the FP32 matrix cores in
+// their 3M form; 1636 TFLOP/s of bf16 products, 0.91 of the 1800 that the matrix
+// cores sustain with no memory traffic on operands that change; matrix cores
+// busy 0.66-0.68.
 //
 // Block = 4 waves in a 2 x 2 grid over a 128 x 128 output tile, two blocks per
 // CU (64 KB of LDS, 248 registers): one block's splits, fragment reads and

@@ -118,3 +118,20 @@ def test_fused_operand(ctx, fuse, side, form, monkeypatch):
     ref = np.einsum(e, x.astype(np.complex128), y.astype(np.complex128), z.astype(np.complex128), optimize=True)
     size = np.einsum(e, *(np.abs(v).astype(np.float64) for v in (x, y, z)), optimize=True)
     assert (np.abs(got - ref) <= (rel(16) + rel(32)) * size + 64 * TINY).all()
+
+
+@pytest.mark.parametrize("M,K,N", [(130, 144, 140), (64, 528, 300), (64, 48, 64), (65, 100, 33)])
+@pytest.mark.parametrize("form", [0, lib.TN_FORM_3M])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_not_finite_bf16x3(ctx, M, K, N, form, value):
+    """BF16x3 (on planes and in place): the row's results are not finite, all
+    others are."""
+    rng = np.random.default_rng([M, N, K, 3])
+    A, B = entries(rng, (M, K)), entries(rng, (K, N))
+    A[M // 2, K // 3] = value
+    p = ctx.plan_load([[0, 1], [1, 2]], {0: M, 1: K, 2: N}, [A, B], [0, 0], 1, [(0, 1)], [0, 2],
+                      lib.TN_PREC_BF16X3 | form, lib.TN_C64)
+    got, _ = lib.tn_contract(p, None, (M, N), lib.TN_C64)
+    ctx.free_plan(p)
+    assert not np.isfinite(got[M // 2]).any()
+    assert np.isfinite(np.delete(got, M // 2, axis=0)).all()
