@@ -1317,7 +1317,10 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       for (int qi = 0; qi < Q && !direct && !devout && !sum; ++qi) {
         const QueryIO &q = qs[q0 + qi];
         if (staged) {
-          memcpy(q.out, h + (size_t)qi * esz, esz);
+          if (esz == 16)
+            memcpy(q.out, h + (size_t)qi * 16, 16);
+          else
+            memcpy(q.out, h + (size_t)qi * 8, 8);
           if (q.log2s) *q.log2s = 0.0;
         } else if (dot_root) {
           Result r = hr[root_shared ? 0 : qi];

@@ -225,10 +225,11 @@ def _leaves(queries):
     rec = np.zeros(max(1, len(ids)), dtype=_LEAF)
     if not ids:
         return rec, None, first
-    # (anything numpy makes an array of: lists, scalars, tensors on the host)
-    if not all(isinstance(d, np.ndarray) for d in data):
+    try:
+        ends = np.cumsum([d.size for d in data], dtype=np.int64)
+    except (AttributeError, TypeError):  # not arrays: lists, scalars, tensors on the host
         data = [np.asarray(d, dtype=np.complex128) for d in data]
-    ends = np.cumsum([d.size for d in data])
+        ends = np.cumsum([d.size for d in data])
     buf = np.concatenate(data, axis=None, dtype=np.complex128, casting="unsafe")
     base = _addr(buf)
     rec["tensor"] = ids
