@@ -930,10 +930,10 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
       // or, of many, as values in the caller's type into the staging buffer: to
       // read back and convert a record of 32 bytes takes the host longer than to
       // copy 8 or 16.  Calls of 20-qubit brickwork amplitudes, records against
-      // values: 4096 71.3 us against 68.5, 2048 56.3 against 55.5, 1024 51.8
-      // against 51.3, 333 50.8 against 50.4; of 17-qubit ones with host vectors
-      // the same at every size.  From 1024 on, where it shows.
-      const bool staged = Q >= 1024 && !direct && !devout && !sum && !gmode && !keep && dot_root && !root_shared &&
+      // values: 4096 72.1 us against 65.3, 2048 56.7 against 53.6, 1024 51.8
+      // against 50.5, 256 50.6 against 49.8; of 17-qubit ones with host vectors
+      // 549 against 544 at 4096, 78 against 77 at 256
+      const bool staged = Q >= 256 && !direct && !devout && !sum && !gmode && !keep && dot_root && !root_shared &&
                           trees && p->in_tree[p->root];
       const Operand R = operand(p->root);
       // TN_FLAG_GRAPH: replay the launch sequence captured with the same
