@@ -97,7 +97,31 @@ __device__ __forceinline__ void seg2r(const int32_t (&ext)[kTreeSeg], const int3
 // and operand scales are the same for every item (uniform, computed once).
 struct ItemScale {
   int2 za, zb;
-  __device__ __forceinline__ int e() const { return tn_scale_exp((uint32_t)za.y) + tn_scale_exp((uint32_t)zb.y); }
+  __device__ __forceinline__ int ea() const { return tn_scale_exp((uint32_t)za.y); }
+  __device__ __forceinline__ int eb() const { return tn_scale_exp((uint32_t)zb.y); }
+};
+
+// How a step applies its operands' scale exponents.  EACH: to every operand
+// entry before its products, as the one-launch-a-vertex kernels do: right
+// wherever the operands themselves fit FP32.  Otherwise to the sum of the
+// products: one factor instead of two and four multiplications a term less,
+// but the products of two operands whose entries are both beyond about 2^63
+// or 2^-63 (each a contraction of two unscaled leaves of 1e-10, say) leave
+// FP32's range before it.  Single calls take EACH (an amplitude of a 10-qubit
+// phase polynomial: 94 us instead of 92); the batched ones do not: vector issue
+// bounds a batch launch (a chain link has 55 vector instructions), and with
+// EACH in the level kernel alone, three queries of ten open legs took 144 us
+// instead of 138.  The factors are powers of two: inside the range both give
+// the same bits.
+template <bool EACH>
+struct Fold {
+  float fa, fb;
+  __device__ __forceinline__ Fold(int ea, int eb)
+      : fa(ldexpf(1.0f, EACH ? -ea : -(ea + eb))), fb(EACH ? ldexpf(1.0f, -eb) : 1.0f) {}
+  __device__ __forceinline__ explicit Fold(const ItemScale &z) : Fold(z.ea(), z.eb()) {}
+  __device__ __forceinline__ float2 a(float2 v) const { return EACH ? make_float2(v.x * fa, v.y * fa) : v; }
+  __device__ __forceinline__ float2 b(float2 v) const { return EACH ? make_float2(v.x * fb, v.y * fb) : v; }
+  __device__ __forceinline__ float out(float v) const { return EACH ? v : v * fa; }
 };
 
 __device__ __forceinline__ ItemScale item_scale(const int2 *sc, int asl, int bsl) {
@@ -130,7 +154,7 @@ __device__ __forceinline__ void fold_max(int2 *scl, int nscale, int csl, int q, 
 // Kind 2: one thread per fiber of the large operand X (and query) reads the
 // fiber's ns entries once and writes nfy results; the small operand Y sits in
 // registers.
-template <bool ONE, bool P2, int NS, int NFY, class SP>
+template <bool EACH, bool ONE, bool P2, int NS, int NFY, class SP>
 __device__ __forceinline__ void tree_stream_impl(SP Sp, int lane, int nthr, int nqw, float2 *pq,
                                                  int perq, const float2 *shr, int2 *scl,
                                                  int nscale) {
@@ -179,18 +203,19 @@ __device__ __forceinline__ void tree_stream_impl(SP Sp, int lane, int nthr, int 
         yv[s] = at_bytes(Y, ym[s * NFY] + dj);
       }
       const ItemScale z = uniform_scale(scl, asl, bsl);
-      const int e = z.e();
-      const float f = ldexpf(1.0f, -e);
+      const int e = z.ea() + z.eb();
+      const Fold<EACH> f(z);
       float re = 0.f, im = 0.f;
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
-        re = fmaf(x[s].x, yv[s].x, re);
-        re = fmaf(-x[s].y, yv[s].y, re);
-        im = fmaf(x[s].x, yv[s].y, im);
-        im = fmaf(x[s].y, yv[s].x, im);
+        const float2 xv = f.a(x[s]), yf = f.b(yv[s]);
+        re = fmaf(xv.x, yf.x, re);
+        re = fmaf(-xv.y, yf.y, re);
+        im = fmaf(xv.x, yf.y, im);
+        im = fmaf(xv.y, yf.x, im);
       }
-      re *= f;
-      im *= f;
+      re = f.out(re);
+      im = f.out(im);
       *(float2 *)((char *)(C + co) + cj) = make_float2(re, im);
       if (lane == 0) scl[csl].x = z.za.x + z.zb.x + e;
       atomicMax((unsigned int *)&scl[csl].y, __float_as_uint(fmaxf(fabsf(re), fabsf(im))));
@@ -201,15 +226,17 @@ __device__ __forceinline__ void tree_stream_impl(SP Sp, int lane, int nthr, int 
 #pragma unroll
     for (int v = 0; v < NS * NFY; ++v) y[v] = at_bytes(Y, ym[v]);
     const ItemScale z = uniform_scale(scl, asl, bsl);
-    const int e = z.e();
-    const float f = ldexpf(1.0f, -e);
+    const int e = z.ea() + z.eb();
+    const Fold<EACH> f(z);
+#pragma unroll
+    for (int v = 0; v < NS * NFY; ++v) y[v] = f.b(y[v]);
     float mx = 0.f;
     for (int fi = lane; fi < nfib; fi += nthr) {
       int xo, co;
       seg2r<P2>(fext, fx, fc, flg, ncs, fi, xo, co);
       float2 x[NS];
 #pragma unroll
-      for (int s = 0; s < NS; ++s) x[s] = at_bytes(X + xo, xs[s]);
+      for (int s = 0; s < NS; ++s) x[s] = f.a(at_bytes(X + xo, xs[s]));
 #pragma unroll
       for (int j = 0; j < NFY; ++j) {
         float re = 0.f, im = 0.f;
@@ -221,8 +248,8 @@ __device__ __forceinline__ void tree_stream_impl(SP Sp, int lane, int nthr, int 
           im = fmaf(x[s].x, yv.y, im);
           im = fmaf(x[s].y, yv.x, im);
         }
-        re *= f;
-        im *= f;
+        re = f.out(re);
+        im = f.out(im);
         *(float2 *)((char *)(C + co) + cy[j]) = make_float2(re, im);
         mx = fmaxf(mx, fmaxf(fabsf(re), fabsf(im)));
       }
@@ -247,8 +274,12 @@ __device__ __forceinline__ void tree_stream_impl(SP Sp, int lane, int nthr, int 
       for (int v = 0; v < NS * NFY; ++v) y[v] = at_bytes(Y, ym[v]);
 #pragma unroll
       for (int s = 0; s < NS; ++s) x[s] = at_bytes(X + xo, xs[s]);
-      const int e = z.e();
-      const float f = ldexpf(1.0f, -e);
+      const int e = z.ea() + z.eb();
+      const Fold<EACH> f(z);
+#pragma unroll
+      for (int v = 0; v < NS * NFY; ++v) y[v] = f.b(y[v]);
+#pragma unroll
+      for (int s = 0; s < NS; ++s) x[s] = f.a(x[s]);
       float2 *C = base + (c & ~kPerQuery);
       float m = 0.f;
 #pragma unroll
@@ -262,8 +293,8 @@ __device__ __forceinline__ void tree_stream_impl(SP Sp, int lane, int nthr, int 
           im = fmaf(x[s].x, yv.y, im);
           im = fmaf(x[s].y, yv.x, im);
         }
-        re *= f;
-        im *= f;
+        re = f.out(re);
+        im = f.out(im);
         *(float2 *)((char *)(C + co) + cy[j]) = make_float2(re, im);
         m = fmaxf(m, fmaxf(fabsf(re), fabsf(im)));
       }
@@ -276,9 +307,9 @@ __device__ __forceinline__ void tree_stream_impl(SP Sp, int lane, int nthr, int 
 
 // The shared index of a kind 0 item summed four terms at a time (offsets of
 // term s in lane s of soa/sob when ns <= 64).
-template <bool P2>
-__device__ __forceinline__ float2 dot_terms(const float2 *A, const float2 *B, int ns, bool stab, int soa,
-                                            int sob, const int32_t (&sext)[kTreeSeg],
+template <bool P2, bool EACH>
+__device__ __forceinline__ float2 dot_terms(const Fold<EACH> &f, const float2 *A, const float2 *B, int ns,
+                                            bool stab, int soa, int sob, const int32_t (&sext)[kTreeSeg],
                                             const int32_t (&sa)[kTreeSeg], const int32_t (&sb)[kTreeSeg],
                                             const int32_t (&slg)[kTreeSeg], int nss) {
   float re0 = 0.f, im0 = 0.f, re1 = 0.f, im1 = 0.f;
@@ -290,6 +321,11 @@ __device__ __forceinline__ float2 dot_terms(const float2 *A, const float2 *B, in
       for (int t = 0; t < 4; ++t) {
         x[t] = A[__builtin_amdgcn_readlane(soa, s + t)];
         y[t] = B[__builtin_amdgcn_readlane(sob, s + t)];
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        x[t] = f.a(x[t]);
+        y[t] = f.b(y[t]);
       }
 #pragma unroll
       for (int t = 0; t < 4; t += 2) {
@@ -304,7 +340,7 @@ __device__ __forceinline__ float2 dot_terms(const float2 *A, const float2 *B, in
       }
     }
     for (; s < ns; ++s) {
-      const float2 x = A[__builtin_amdgcn_readlane(soa, s)], y = B[__builtin_amdgcn_readlane(sob, s)];
+      const float2 x = f.a(A[__builtin_amdgcn_readlane(soa, s)]), y = f.b(B[__builtin_amdgcn_readlane(sob, s)]);
       re0 = fmaf(x.x, y.x, re0);
       re0 = fmaf(-x.y, y.y, re0);
       im0 = fmaf(x.x, y.y, im0);
@@ -314,18 +350,18 @@ __device__ __forceinline__ float2 dot_terms(const float2 *A, const float2 *B, in
     for (int s = 0; s < ns; ++s) {
       int oa, ob;
       seg2r<P2>(sext, sa, sb, slg, nss, s, oa, ob);
-      const float2 x = A[oa], y = B[ob];
+      const float2 x = f.a(A[oa]), y = f.b(B[ob]);
       re0 = fmaf(x.x, y.x, re0);
       re0 = fmaf(-x.y, y.y, re0);
       im0 = fmaf(x.x, y.y, im0);
       im0 = fmaf(x.y, y.x, im0);
     }
   }
-  return make_float2(re0 + re1, im0 + im1);
+  return make_float2(f.out(re0 + re1), f.out(im0 + im1));
 }
 
 // Kind 0: one thread per result entry (and query).
-template <bool ONE, bool P2, class SP>
+template <bool EACH, bool ONE, bool P2, class SP>
 __device__ __forceinline__ void tree_step_impl(SP Sp, int lane, int nthr, int nqw, float2 *pq,
                                                int perq, const float2 *shr, int2 *scl, int nscale) {
   const int a = Sp->a, b = Sp->b, c = Sp->c, asl = Sp->asl, bsl = Sp->bsl, csl = Sp->csl;
@@ -357,16 +393,15 @@ __device__ __forceinline__ void tree_step_impl(SP Sp, int lane, int nthr, int nq
     float2 *C = pq + (c & ~kPerQuery);
     if (lane >= nc) return;
     const ItemScale z = uniform_scale(scl, asl, bsl);
-    const int e = z.e();
-    const float f = ldexpf(1.0f, -e);
+    const int e = z.ea() + z.eb();
+    const Fold<EACH> f(z);
     float mx = 0.f;
     for (int ci = lane; ci < nc; ci += nthr) {
       int ao, bo;
       seg2r<P2>(cext, ca, cb, clg, ncs, ci, ao, bo);
-      const float2 r = dot_terms<P2>(A0 + ao, B0 + bo, ns, stab, soa, sob, sext, sa, sb, slg, nss);
-      const float rr = r.x * f, ii = r.y * f;
-      C[ci] = make_float2(rr, ii);
-      mx = fmaxf(mx, fmaxf(fabsf(rr), fabsf(ii)));
+      const float2 r = dot_terms<P2>(f, A0 + ao, B0 + bo, ns, stab, soa, sob, sext, sa, sb, slg, nss);
+      C[ci] = r;
+      mx = fmaxf(mx, fmaxf(fabsf(r.x), fabsf(r.y)));
     }
     if (lane == 0) scl[csl].x = z.za.x + z.zb.x + e;
     atomicMax((unsigned int *)&scl[csl].y, __float_as_uint(mx));
@@ -383,13 +418,10 @@ __device__ __forceinline__ void tree_step_impl(SP Sp, int lane, int nthr, int nq
       const float2 *A = ((a & kPerQuery) ? base + (a & ~kPerQuery) : shr + a) + ao;
       const float2 *B = ((b & kPerQuery) ? base + (b & ~kPerQuery) : shr + b) + bo;
       const ItemScale z = item_scale(scl + mad24(q, nscale, 0), asl, bsl);
-      const float2 r = dot_terms<P2>(A, B, ns, stab, soa, sob, sext, sa, sb, slg, nss);
-      const int e = z.e();
-      const float f = ldexpf(1.0f, -e);
-      const float rr = r.x * f, ii = r.y * f;
-      base[(c & ~kPerQuery) + ci] = make_float2(rr, ii);
-      if (ci == 0) scl[mad24(q, nscale, csl)].x = z.za.x + z.zb.x + e;
-      fold_max(scl, nscale, csl, q, qprev, mx, fmaxf(fabsf(rr), fabsf(ii)));
+      const float2 r = dot_terms<P2>(Fold<EACH>(z), A, B, ns, stab, soa, sob, sext, sa, sb, slg, nss);
+      base[(c & ~kPerQuery) + ci] = r;
+      if (ci == 0) scl[mad24(q, nscale, csl)].x = z.za.x + z.zb.x + z.ea() + z.eb();
+      fold_max(scl, nscale, csl, q, qprev, mx, fmaxf(fabsf(r.x), fabsf(r.y)));
     }
     if (qprev >= 0) atomicMax((unsigned int *)&scl[mad24(qprev, nscale, csl)].y, __float_as_uint(mx));
   }
@@ -399,13 +431,13 @@ __device__ __forceinline__ void tree_step_impl(SP Sp, int lane, int nthr, int nq
 // `lane`.  The step's maps live in registers; each thread keeps the running
 // max of its results per query and folds it into the scale record once per
 // query.
-template <bool ONE, class SP>
+template <bool EACH, bool ONE, class SP>
 __device__ __forceinline__ void tree_step_q(SP Sp, int lane, int nthr, int nqw, float2 *pq, int perq,
                                             const float2 *shr, int2 *scl, int nscale) {
   if (Sp->kind == 2) {
     // a small operand along the fibers of a large one: ns, nfy in {1, 2, 4}
     const int sel = (Sp->ns >> 1) * 3 + (Sp->nss >> 1) + (Sp->pow2 ? 0 : 9);
-#define TN_TS(P, A, B) tree_stream_impl<ONE, P, A, B>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale)
+#define TN_TS(P, A, B) tree_stream_impl<EACH, ONE, P, A, B>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale)
     switch (sel) {
       case 0: TN_TS(true, 1, 1); break;
       case 1: TN_TS(true, 1, 2); break;
@@ -430,16 +462,16 @@ __device__ __forceinline__ void tree_step_q(SP Sp, int lane, int nthr, int nqw, 
     return;
   }
   if (Sp->pow2)
-    tree_step_impl<ONE, true>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale);
+    tree_step_impl<EACH, ONE, true>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale);
   else
-    tree_step_impl<ONE, false>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale);
+    tree_step_impl<EACH, ONE, false>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale);
 }
 
 // Kind 3: the kind 0 form with some operands in the query's device workspace
 // (a large intermediate of a per-query subtree), reached through generic
 // pointers.  gq: the device workspace of the group's first query, gstride
 // float2 apart.
-template <bool P2, class SP>
+template <bool EACH, bool P2, class SP>
 __device__ __forceinline__ void tree_dev_impl(SP Sp, int lane, int nthr, int nqw, float2 *pq, int perq,
                               const float2 *shr, int2 *scl, int nscale, float2 *gq, int64_t gstride) {
   const int a = Sp->a, b = Sp->b, c = Sp->c, asl = Sp->asl, bsl = Sp->bsl, csl = Sp->csl;
@@ -475,13 +507,10 @@ __device__ __forceinline__ void tree_dev_impl(SP Sp, int lane, int nthr, int nqw
     int ao, bo;
     seg2r<P2>(cext, ca, cb, clg, ncs, ci, ao, bo);
     const ItemScale z = item_scale(scl + mad24(q, nscale, 0), asl, bsl);
-    const float2 r = dot_terms<P2>(A + ao, B + bo, ns, stab, soa, sob, sext, sa, sb, slg, nss);
-    const int e = z.e();
-    const float f = ldexpf(1.0f, -e);
-    const float rr = r.x * f, ii = r.y * f;
-    C[ci] = make_float2(rr, ii);
-    if (ci == 0) scl[mad24(q, nscale, csl)].x = z.za.x + z.zb.x + e;
-    fold_max(scl, nscale, csl, q, qprev, mx, fmaxf(fabsf(rr), fabsf(ii)));
+    const float2 r = dot_terms<P2>(Fold<EACH>(z), A + ao, B + bo, ns, stab, soa, sob, sext, sa, sb, slg, nss);
+    C[ci] = r;
+    if (ci == 0) scl[mad24(q, nscale, csl)].x = z.za.x + z.zb.x + z.ea() + z.eb();
+    fold_max(scl, nscale, csl, q, qprev, mx, fmaxf(fabsf(r.x), fabsf(r.y)));
   }
   if (qprev >= 0) atomicMax((unsigned int *)&scl[mad24(qprev, nscale, csl)].y, __float_as_uint(mx));
 }
@@ -493,7 +522,7 @@ __device__ __forceinline__ void tree_dev_impl(SP Sp, int lane, int nthr, int nqw
 // may point at either compiles to the slower flat instructions).  The items
 // are dealt as in the single-query kind 0 form: operand scales read once,
 // no division per item.
-template <int GLOB, class SP>
+template <bool EACH, int GLOB, class SP>
 __device__ __forceinline__ void tree_dev_one(SP Sp, int lane, int nthr, float2 *pq, const float2 *shr,
                                              int2 *scl, float2 *gq) {
   const int a = Sp->a, b = Sp->b, c = Sp->c, asl = Sp->asl, bsl = Sp->bsl, csl = Sp->csl;
@@ -530,16 +559,15 @@ __device__ __forceinline__ void tree_dev_one(SP Sp, int lane, int nthr, float2 *
   else
     C = pq + (c & ~kPerQuery);
   const ItemScale z = uniform_scale(scl, asl, bsl);
-  const int e = z.e();
-  const float f = ldexpf(1.0f, -e);
+  const int e = z.ea() + z.eb();
+  const Fold<EACH> f(z);
   float mx = 0.f;
   for (int ci = lane; ci < nc; ci += nthr) {
     int ao, bo;
     seg2r<true>(cext, ca, cb, clg, ncs, ci, ao, bo);
-    const float2 r = dot_terms<true>(A0 + ao, B0 + bo, ns, stab, soa, sob, sext, sa, sb, slg, nss);
-    const float rr = r.x * f, ii = r.y * f;
-    C[ci] = make_float2(rr, ii);
-    mx = fmaxf(mx, fmaxf(fabsf(rr), fabsf(ii)));
+    const float2 r = dot_terms<true>(f, A0 + ao, B0 + bo, ns, stab, soa, sob, sext, sa, sb, slg, nss);
+    C[ci] = r;
+    mx = fmaxf(mx, fmaxf(fabsf(r.x), fabsf(r.y)));
   }
   if (lane == 0) scl[csl].x = z.za.x + z.zb.x + e;
   atomicMax((unsigned int *)&scl[csl].y, __float_as_uint(mx));
@@ -551,7 +579,7 @@ __device__ __forceinline__ void tree_dev_one(SP Sp, int lane, int nthr, float2 *
 // launch reads) instead of decoding a step's maps, so several independent
 // small steps cost one step of the wave.  Single-query groups only.
 // r0, r1: the lane's record (r1 for ns = 4 only).
-template <int NS>
+template <bool EACH, int NS>
 __device__ __forceinline__ void tree_lane_exec(uint4 r0, uint4 r1, float2 *pq, const float2 *shr,
                                                int2 *scl) {
   // each operand's region once (bits 15 and 31 of w[3]), then byte offsets
@@ -573,18 +601,19 @@ __device__ __forceinline__ void tree_lane_exec(uint4 r0, uint4 r1, float2 *pq, c
   }
   // a leaf operand's index is that of a record that stays zero
   const int2 za = scl[r0.w & 0x7fffu], zb = scl[(r0.w >> 16) & 0x7fffu];
-  const int e = tn_scale_exp((uint32_t)za.y) + tn_scale_exp((uint32_t)zb.y);
-  const float f = ldexpf(1.0f, -e);
+  const int ea = tn_scale_exp((uint32_t)za.y), eb = tn_scale_exp((uint32_t)zb.y), e = ea + eb;
+  const Fold<EACH> f(ea, eb);
   float re = 0.f, im = 0.f;
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
-    re = fmaf(x[s].x, y[s].x, re);
-    re = fmaf(-x[s].y, y[s].y, re);
-    im = fmaf(x[s].x, y[s].y, im);
-    im = fmaf(x[s].y, y[s].x, im);
+    const float2 xv = f.a(x[s]), yv = f.b(y[s]);
+    re = fmaf(xv.x, yv.x, re);
+    re = fmaf(-xv.y, yv.y, re);
+    im = fmaf(xv.x, yv.y, im);
+    im = fmaf(xv.y, yv.x, im);
   }
-  re *= f;
-  im *= f;
+  re = f.out(re);
+  im = f.out(im);
   *(float2 *)((char *)pq + (r0.z & 0xffffu)) = make_float2(re, im);
   const int csl = (int)((r0.z >> 16) & 0x7fffu);
   if (r0.z >> 31) scl[csl].x = za.x + zb.x + e;
@@ -627,6 +656,7 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
 //
 // Every choice is uniform across the wave, and the forms share this one body:
 // the stream's loop holds it kBlkAhead times.
+template <bool EACH>
 __device__ __forceinline__ void tree_block(uint4 r0, uint4 r1, int lane, float2 *pq, const float2 *shr,
                                            int2 *scl, float &vre, float &vim, int &zx, int &zy) {
   const uint32_t w6 = (uint32_t)__builtin_amdgcn_readfirstlane((int)r1.z);
@@ -635,11 +665,11 @@ __device__ __forceinline__ void tree_block(uint4 r0, uint4 r1, int lane, float2 
   if (w6 & kBlkPacked << 16) {
     if (act) {
       if (ns == 1)
-        tree_lane_exec<1>(r0, r1, pq, shr, scl);
+        tree_lane_exec<EACH, 1>(r0, r1, pq, shr, scl);
       else if (ns == 2)
-        tree_lane_exec<2>(r0, r1, pq, shr, scl);
+        tree_lane_exec<EACH, 2>(r0, r1, pq, shr, scl);
       else
-        tree_lane_exec<4>(r0, r1, pq, shr, scl);
+        tree_lane_exec<EACH, 4>(r0, r1, pq, shr, scl);
     }
     return;
   }
@@ -686,10 +716,11 @@ __device__ __forceinline__ void tree_block(uint4 r0, uint4 r1, int lane, float2 
     zy = __builtin_amdgcn_readfirstlane(za.y);
   }
   const int zbx = __builtin_amdgcn_readfirstlane(zb.x), zby = __builtin_amdgcn_readfirstlane(zb.y);
-  const int e = tn_scale_exp((uint32_t)zy) + tn_scale_exp((uint32_t)zby);
-  const float f = ldexpf(1.0f, -e);
+  const int ea = tn_scale_exp((uint32_t)zy), eb = tn_scale_exp((uint32_t)zby), e = ea + eb;
+  const Fold<EACH> f(ea, eb);
   float re = 0.f, im = 0.f;
-  auto term = [&](const float2 &a, const float2 &b) {
+  auto term = [&](const float2 &x, const float2 &y) {
+    const float2 a = f.a(x), b = f.b(y);
     re = fmaf(a.x, b.x, re);
     re = fmaf(-a.y, b.y, re);
     im = fmaf(a.x, b.y, im);
@@ -703,8 +734,8 @@ __device__ __forceinline__ void tree_block(uint4 r0, uint4 r1, int lane, float2 
       term(x[3], y[3]);
     }
   }
-  re *= f;
-  im *= f;
+  re = f.out(re);
+  im = f.out(im);
   const float m = act ? fmaxf(fabsf(re), fabsf(im)) : 0.f;
   const unsigned mx = wave_max_u32(__float_as_uint(m));
   zx = zx + zbx + e;
@@ -717,12 +748,12 @@ __device__ __forceinline__ void tree_block(uint4 r0, uint4 r1, int lane, float2 
   vim = im;
 }
 
-template <int NS>
+template <bool EACH, int NS>
 __device__ __forceinline__ void tree_lane_step(const TreeLaneRec *rec, int lane, int nl, float2 *pq,
                                                const float2 *shr, int2 *scl) {
   if (lane >= nl) return;
   const uint4 *r = (const uint4 *)(rec + lane);
-  tree_lane_exec<NS>(r[0], NS == 4 ? r[1] : make_uint4(0u, 0u, 0u, 0u), pq, shr, scl);
+  tree_lane_exec<EACH, NS>(r[0], NS == 4 ? r[1] : make_uint4(0u, 0u, 0u, 0u), pq, shr, scl);
 }
 
 // DEV: the program may hold kind 3 steps (per-query subtrees with
@@ -730,24 +761,24 @@ __device__ __forceinline__ void tree_lane_step(const TreeLaneRec *rec, int lane,
 // A kind 3 step (operands in the query's device workspace), whatever its
 // kind field says (a kind 6 pair runs as two of these when a wave holds more
 // than one query).
-template <class SP>
+template <bool EACH, class SP>
 __device__ __forceinline__ void tree_kind3(SP Sp, int lane, int nthr, int nqw, float2 *pq, int perq,
                                            const float2 *shr, int2 *scl, int nscale, float2 *gq,
                                            int64_t gstride) {
   if (nqw == 1 && Sp->pow2) {
     switch (Sp->glob) {  // 1 .. 7 (checked on the host)
-      case 1: tree_dev_one<1>(Sp, lane, nthr, pq, shr, scl, gq); break;
-      case 2: tree_dev_one<2>(Sp, lane, nthr, pq, shr, scl, gq); break;
-      case 3: tree_dev_one<3>(Sp, lane, nthr, pq, shr, scl, gq); break;
-      case 4: tree_dev_one<4>(Sp, lane, nthr, pq, shr, scl, gq); break;
-      case 5: tree_dev_one<5>(Sp, lane, nthr, pq, shr, scl, gq); break;
-      case 6: tree_dev_one<6>(Sp, lane, nthr, pq, shr, scl, gq); break;
-      default: tree_dev_one<7>(Sp, lane, nthr, pq, shr, scl, gq); break;
+      case 1: tree_dev_one<EACH, 1>(Sp, lane, nthr, pq, shr, scl, gq); break;
+      case 2: tree_dev_one<EACH, 2>(Sp, lane, nthr, pq, shr, scl, gq); break;
+      case 3: tree_dev_one<EACH, 3>(Sp, lane, nthr, pq, shr, scl, gq); break;
+      case 4: tree_dev_one<EACH, 4>(Sp, lane, nthr, pq, shr, scl, gq); break;
+      case 5: tree_dev_one<EACH, 5>(Sp, lane, nthr, pq, shr, scl, gq); break;
+      case 6: tree_dev_one<EACH, 6>(Sp, lane, nthr, pq, shr, scl, gq); break;
+      default: tree_dev_one<EACH, 7>(Sp, lane, nthr, pq, shr, scl, gq); break;
     }
   } else if (Sp->pow2) {
-    tree_dev_impl<true>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale, gq, gstride);
+    tree_dev_impl<EACH, true>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale, gq, gstride);
   } else {
-    tree_dev_impl<false>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale, gq, gstride);
+    tree_dev_impl<EACH, false>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale, gq, gstride);
   }
   // a later step of this wave reads what this one stored to device memory
   __builtin_amdgcn_s_waitcnt(0);
@@ -764,6 +795,7 @@ __device__ __forceinline__ void tree_kind3(SP Sp, int lane, int nthr, int nqw, f
 // and Q's results come from the same operations in the same order as when
 // the two steps run apart, so the results are bit-identical.  Q: nc <= 256,
 // ns <= 4; P: ns <= 64; both power-of-two maps.
+template <bool EACH>
 __device__ __forceinline__ void tree_pair(CStep P, CStep Q, int lane, float2 *pq, const float2 *shr,
                                           int2 *scl) {
   int32_t pcext[kTreeSeg], pca[kTreeSeg], pcb[kTreeSeg], pclg[kTreeSeg];
@@ -809,8 +841,8 @@ __device__ __forceinline__ void tree_pair(CStep P, CStep Q, int lane, float2 *pq
   const float2 *B0 = (qb & kPerQuery) ? pq + (qb & ~kPerQuery) : shr + qb;
   float2 *C = pq + (Q->c & ~kPerQuery);
   const ItemScale zp = uniform_scale(scl, P->asl, P->bsl);
-  const int ep = zp.e();
-  const float fp = ldexpf(1.0f, -ep);
+  const int ep = zp.ea() + zp.eb();
+  const Fold<EACH> fp(zp);
   // T's entries of this lane's results
   float2 tv[4][4];
   int bo[4];
@@ -830,9 +862,8 @@ __device__ __forceinline__ void tree_pair(CStep P, CStep Q, int lane, float2 *pq
       for (int sh = 0; sh < 4; ++sh)
         if (sh < qns) {
           const int xo = xb + __builtin_amdgcn_readlane(pxs, sh), yo = yb + __builtin_amdgcn_readlane(pys, sh);
-          const float2 r =
-              dot_terms<true>(X0 + xo, Y0 + yo, pns, true, psoa, psob, psext, psa, psb, pslg, pnss);
-          tv[j][sh] = make_float2(r.x * fp, r.y * fp);
+          tv[j][sh] =
+              dot_terms<true>(fp, X0 + xo, Y0 + yo, pns, true, psoa, psob, psext, psa, psb, pslg, pnss);
           mt = fmaxf(mt, fmaxf(fabsf(tv[j][sh].x), fabsf(tv[j][sh].y)));
         }
     }
@@ -844,8 +875,8 @@ __device__ __forceinline__ void tree_pair(CStep P, CStep Q, int lane, float2 *pq
   int2 zb = Q->bsl >= 0 ? scl[Q->bsl] : make_int2(0, 0);
   zb.x = __builtin_amdgcn_readfirstlane(zb.x);
   zb.y = __builtin_amdgcn_readfirstlane(zb.y);
-  const int eq = tn_scale_exp(tbits) + tn_scale_exp((uint32_t)zb.y);
-  const float fq = ldexpf(1.0f, -eq);
+  const int et = tn_scale_exp(tbits), eb = tn_scale_exp((uint32_t)zb.y), eq = et + eb;
+  const Fold<EACH> fq(et, eb);
   float mx = 0.f;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -858,10 +889,10 @@ __device__ __forceinline__ void tree_pair(CStep P, CStep Q, int lane, float2 *pq
       if (qns == 4) {
         float2 y[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) y[u] = B0[bo[j] + __builtin_amdgcn_readlane(qsob, u)];
+        for (int u = 0; u < 4; ++u) y[u] = fq.b(B0[bo[j] + __builtin_amdgcn_readlane(qsob, u)]);
 #pragma unroll
         for (int u = 0; u < 4; u += 2) {
-          const float2 x0 = tv[j][u], x1 = tv[j][u + 1];
+          const float2 x0 = fq.a(tv[j][u]), x1 = fq.a(tv[j][u + 1]);
           re0 = fmaf(x0.x, y[u].x, re0);
           re0 = fmaf(-x0.y, y[u].y, re0);
           im0 = fmaf(x0.x, y[u].y, im0);
@@ -875,14 +906,14 @@ __device__ __forceinline__ void tree_pair(CStep P, CStep Q, int lane, float2 *pq
 #pragma unroll
         for (int u = 0; u < 3; ++u)
           if (u < qns) {
-            const float2 x = tv[j][u], y = B0[bo[j] + __builtin_amdgcn_readlane(qsob, u)];
+            const float2 x = fq.a(tv[j][u]), y = fq.b(B0[bo[j] + __builtin_amdgcn_readlane(qsob, u)]);
             re0 = fmaf(x.x, y.x, re0);
             re0 = fmaf(-x.y, y.y, re0);
             im0 = fmaf(x.x, y.y, im0);
             im0 = fmaf(x.y, y.x, im0);
           }
       }
-      const float rr = (re0 + re1) * fq, ii = (im0 + im1) * fq;
+      const float rr = fq.out(re0 + re1), ii = fq.out(im0 + im1);
       C[co] = make_float2(rr, ii);
       mx = fmaxf(mx, fmaxf(fabsf(rr), fabsf(ii)));
     }
@@ -891,7 +922,7 @@ __device__ __forceinline__ void tree_pair(CStep P, CStep Q, int lane, float2 *pq
   atomicMax((unsigned int *)&scl[Q->csl].y, __float_as_uint(mx));
 }
 
-template <bool DEV, class SP>
+template <bool DEV, bool EACH, class SP>
 __device__ __forceinline__ void tree_step(SP Sp, int lane, int nthr, int nqw, float2 *pq, int perq,
                                           const float2 *shr, int2 *scl, int nscale, float2 *gq,
                                           int64_t gstride, const TreeLaneRec *lanes, int lane0) {
@@ -900,21 +931,21 @@ __device__ __forceinline__ void tree_step(SP Sp, int lane, int nthr, int nqw, fl
     // (lane0 = its first record's index)
     const TreeLaneRec *rec = lanes + (Sp->tab - lane0);
     if (Sp->ns == 1)
-      tree_lane_step<1>(rec, lane, Sp->nc, pq, shr, scl);
+      tree_lane_step<EACH, 1>(rec, lane, Sp->nc, pq, shr, scl);
     else if (Sp->ns == 2)
-      tree_lane_step<2>(rec, lane, Sp->nc, pq, shr, scl);
+      tree_lane_step<EACH, 2>(rec, lane, Sp->nc, pq, shr, scl);
     else
-      tree_lane_step<4>(rec, lane, Sp->nc, pq, shr, scl);
+      tree_lane_step<EACH, 4>(rec, lane, Sp->nc, pq, shr, scl);
     return;
   }
   if (DEV && Sp->kind == 3) {
-    tree_kind3(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale, gq, gstride);
+    tree_kind3<EACH>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale, gq, gstride);
     return;
   }
   if (nqw == 1)
-    tree_step_q<true>(Sp, lane, nthr, 1, pq, perq, shr, scl, nscale);
+    tree_step_q<EACH, true>(Sp, lane, nthr, 1, pq, perq, shr, scl, nscale);
   else
-    tree_step_q<false>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale);
+    tree_step_q<EACH, false>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale);
 }
 
 // Closed root of one query: the FP64 inner product and its result record
@@ -1017,7 +1048,7 @@ __device__ __forceinline__ void tree_prologue(const TreeLaunch &t, KernargLaunch
   }
 }
 
-template <bool DEV>
+template <bool DEV, bool EACH>
 __global__ __launch_bounds__(kTreeThreads) void k_tree(TreeLaunch t) {
   constexpr int W = kTreeStepWords;
   constexpr int CW = kTreeChunk * W;
@@ -1137,13 +1168,13 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree(TreeLaunch t) {
       }
     } else if (cur == 1) {
       // one step (a spine contraction): the whole workgroup on it
-      tree_step<DEV>(S, tid, NT, nqw, pq, perq, shr, scl, h.nscale, gq, gstride, lrec, lrec0);
+      tree_step<DEV, EACH>(S, tid, NT, nqw, pq, perq, shr, scl, h.nscale, gq, gstride, lrec, lrec0);
     } else {
       // several independent steps of one level (largest first): one wave per
       // step, round robin
       const int wave = tid >> 6, lane = tid & 63;
       for (int i = wave; i < cur; i += NT / 64)
-        tree_step<DEV>(S + i, lane, 64, nqw, pq, perq, shr, scl, h.nscale, gq, gstride, lrec, lrec0);
+        tree_step<DEV, EACH>(S + i, lane, 64, nqw, pq, perq, shr, scl, h.nscale, gq, gstride, lrec, lrec0);
     }
     if (k + 1 < h.nchunks && !whole) {
       int32_t *dst = sbuf + ((k + 1) & 1) * CW;
@@ -1179,7 +1210,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree(TreeLaunch t) {
   }
 }
 
-template <bool DEV>
+template <bool DEV, bool EACH>
 __global__ __launch_bounds__(256, DEV ? 3 : 4) void k_tree_wave(TreeLaunch t) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -1239,15 +1270,15 @@ __global__ __launch_bounds__(256, DEV ? 3 : 4) void k_tree_wave(TreeLaunch t) {
       uint4 a0 = r[0], a1 = r[1], b0 = r[BS], b1 = r[BS + 1], c0 = r[2 * BS], c1 = r[2 * BS + 1];
       for (int left = n;;) {
         r += kBlkAhead * BS;
-        tree_block(a0, a1, lane, wpq, shr, wscl, vre, vim, zx, zy);
+        tree_block<EACH>(a0, a1, lane, wpq, shr, wscl, vre, vim, zx, zy);
         if (--left == 0) break;
         a0 = r[0];
         a1 = r[1];
-        tree_block(b0, b1, lane, wpq, shr, wscl, vre, vim, zx, zy);
+        tree_block<EACH>(b0, b1, lane, wpq, shr, wscl, vre, vim, zx, zy);
         if (--left == 0) break;
         b0 = r[BS];
         b1 = r[BS + 1];
-        tree_block(c0, c1, lane, wpq, shr, wscl, vre, vim, zx, zy);
+        tree_block<EACH>(c0, c1, lane, wpq, shr, wscl, vre, vim, zx, zy);
         if (--left == 0) break;
         c0 = r[2 * BS];
         c1 = r[2 * BS + 1];
@@ -1257,16 +1288,16 @@ __global__ __launch_bounds__(256, DEV ? 3 : 4) void k_tree_wave(TreeLaunch t) {
     const CStep S = prog + step;
     if (DEV && S->kind == 6 && wn == 1) {
       // a kind 3 pair: this step and the next
-      tree_pair(S, S + 1, lane, wpq, shr, wscl);
+      tree_pair<EACH>(S, S + 1, lane, wpq, shr, wscl);
     } else if (DEV && S->kind == 6) {
-      tree_kind3(S, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
-      tree_kind3(S + 1, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
+      tree_kind3<EACH>(S, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
+      tree_kind3<EACH>(S + 1, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
     } else if (DEV && S->kind == 3) {
-      tree_kind3(S, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
+      tree_kind3<EACH>(S, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
     } else if (wn == 1) {
-      tree_step_q<true>(S, lane, 64, 1, wpq, perq, shr, wscl, nscale);
+      tree_step_q<EACH, true>(S, lane, 64, 1, wpq, perq, shr, wscl, nscale);
     } else {
-      tree_step_q<false>(S, lane, 64, wn, wpq, perq, shr, wscl, nscale);
+      tree_step_q<EACH, false>(S, lane, 64, wn, wpq, perq, shr, wscl, nscale);
     }
   }
 
@@ -1336,7 +1367,7 @@ __global__ __launch_bounds__(256, DEV ? 3 : 4) void k_tree_wave(TreeLaunch t) {
 }
 
 // LDS a workgroup may use: the device's per-block limit (160 KiB on gfx950),
-// raised for both subtree kernels once.
+// raised for the subtree kernels once.
 size_t tree_lds_limit() {
   static size_t limit = 0;
   if (limit == 0) {
@@ -1347,40 +1378,38 @@ size_t tree_lds_limit() {
         v > 0)
       l = (size_t)v;
     if (l > 163840) l = 163840;
-    if (l > 65536 &&
-        (hipFuncSetAttribute((const void *)k_tree<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)l) != hipSuccess ||
-         hipFuncSetAttribute((const void *)k_tree<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)l) != hipSuccess ||
-         hipFuncSetAttribute((const void *)k_tree_wave<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)l) != hipSuccess ||
-         hipFuncSetAttribute((const void *)k_tree_wave<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)l) != hipSuccess))
-      l = 65536;
+    if (l > 65536)
+      for (const void *k : {(const void *)k_tree<false, false>, (const void *)k_tree<false, true>,
+                            (const void *)k_tree<true, false>, (const void *)k_tree<true, true>,
+                            (const void *)k_tree_wave<false, false>, (const void *)k_tree_wave<false, true>,
+                            (const void *)k_tree_wave<true, false>, (const void *)k_tree_wave<true, true>})
+        if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)l) != hipSuccess) {
+          l = 65536;
+          break;
+        }
     limit = l;
   }
   return limit;
 }
 
-hipError_t launch_tree(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes, bool dev) {
+hipError_t launch_tree(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes, bool dev, bool each) {
   if (nsub <= 0 || t.nq <= 0) return hipSuccess;
   if (lds_bytes > tree_lds_limit()) return hipErrorInvalidValue;
   const int groups = (t.nq + t.qw - 1) / t.qw;
-  if (dev)
-    hipLaunchKernelGGL(k_tree<true>, dim3(nsub, groups), dim3(kTreeThreads), lds_bytes, st, t);
-  else
-    hipLaunchKernelGGL(k_tree<false>, dim3(nsub, groups), dim3(kTreeThreads), lds_bytes, st, t);
+  const auto kernel = dev ? (each ? k_tree<true, true> : k_tree<true, false>)
+                          : (each ? k_tree<false, true> : k_tree<false, false>);
+  hipLaunchKernelGGL(kernel, dim3(nsub, groups), dim3(kTreeThreads), lds_bytes, st, t);
   return hipGetLastError();
 }
 
-hipError_t launch_tree_wave(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes, bool dev) {
+hipError_t launch_tree_wave(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes, bool dev,
+                            bool each) {
   if (nsub <= 0 || t.nq <= 0) return hipSuccess;
   if (lds_bytes > tree_lds_limit() || t.qw < 1 || t.qw > 16) return hipErrorInvalidValue;
   const int groups = (t.nq + t.qw - 1) / t.qw;
-  if (dev)
-    hipLaunchKernelGGL(k_tree_wave<true>, dim3(nsub, groups), dim3(256), lds_bytes, st, t);
-  else
-    hipLaunchKernelGGL(k_tree_wave<false>, dim3(nsub, groups), dim3(256), lds_bytes, st, t);
+  const auto kernel = dev ? (each ? k_tree_wave<true, true> : k_tree_wave<true, false>)
+                          : (each ? k_tree_wave<false, true> : k_tree_wave<false, false>);
+  hipLaunchKernelGGL(kernel, dim3(nsub, groups), dim3(256), lds_bytes, st, t);
   return hipGetLastError();
 }
 
