@@ -1011,7 +1011,7 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
           tl.nq = 1;
           tl.qw = 1;
           TN_HIP(prof.timed(st, TN_KCLASS_TREE, tree_bytes_sh, tree_flops_sh,
-                            [&] { return launch_tree(st, tl, L.n_tree_shared, L.lds_shared, false, rs.single); }),
+                            [&] { return launch_tree(st, tl, L.n_tree_shared, L.lds_shared, false); }),
                  "subtree kernel (shared)");
         }
         if (L.n_tree_perq) {
@@ -1027,8 +1027,8 @@ tn_status run_group(tn_ctx *ctx, tn_plan *p, const std::vector<QueryIO> &qs, tn_
           TN_HIP(prof.timed(st, L.tree_wave && Q > 1 ? TN_KCLASS_TREE_BATCH : TN_KCLASS_TREE, tree_bytes_q * Q,
                             tree_flops_q * Q,
                             [&] {
-                              return wave ? launch_tree_wave(st, tl, L.n_tree_perq, lds, !L.spill.empty(), rs.single)
-                                          : launch_tree(st, tl, L.n_tree_perq, lds, !L.spill.empty(), rs.single);
+                              return wave ? launch_tree_wave(st, tl, L.n_tree_perq, lds, !L.spill.empty())
+                                          : launch_tree(st, tl, L.n_tree_perq, lds, !L.spill.empty());
                             }),
                  "subtree kernel");
         }

@@ -492,11 +492,10 @@ hipError_t launch_dot(hipStream_t st, const DotDesc *d_desc, int64_t nelem, Oper
                       int nbatch);
 
 // dev: the subtrees may hold kind 3 steps (per-query subtrees)
-// each: every operand entry is scaled before its products (Fold)
-hipError_t launch_tree(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes, bool dev, bool each);
+hipError_t launch_tree(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes, bool dev);
 // Per-query launches: every wave takes ceil(qw / 4) queries of its workgroup
 // through the whole program on its own (no barrier after the leaves load).
-hipError_t launch_tree_wave(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes, bool dev, bool each);
+hipError_t launch_tree_wave(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes, bool dev);
 size_t tree_lds_limit();
 
 // The static scratch array of tn_contract_strided_noalloc (kernels.hip): its

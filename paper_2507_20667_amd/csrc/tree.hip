@@ -101,28 +101,43 @@ struct ItemScale {
   __device__ __forceinline__ int eb() const { return tn_scale_exp((uint32_t)zb.y); }
 };
 
-// How a step applies its operands' scale exponents.  EACH: to every operand
-// entry before its products, as the one-launch-a-vertex kernels do: right
-// wherever the operands themselves fit FP32.  Otherwise to the sum of the
-// products: one factor instead of two and four multiplications a term less,
-// but the products of two operands whose entries are both beyond about 2^63
-// or 2^-63 (each a contraction of two unscaled leaves of 1e-10, say) leave
-// FP32's range before it.  Single calls take EACH (an amplitude of a 10-qubit
-// phase polynomial: 94 us instead of 92); the batched ones do not: vector issue
-// bounds a batch launch (a chain link has 55 vector instructions), and with
-// EACH in the level kernel alone, three queries of ten open legs took 144 us
-// instead of 138.  The factors are powers of two: inside the range both give
-// the same bits.
-template <bool EACH>
-struct Fold {
-  float fa, fb;
-  __device__ __forceinline__ Fold(int ea, int eb)
-      : fa(ldexpf(1.0f, EACH ? -ea : -(ea + eb))), fb(EACH ? ldexpf(1.0f, -eb) : 1.0f) {}
-  __device__ __forceinline__ explicit Fold(const ItemScale &z) : Fold(z.ea(), z.eb()) {}
-  __device__ __forceinline__ float2 a(float2 v) const { return EACH ? make_float2(v.x * fa, v.y * fa) : v; }
-  __device__ __forceinline__ float2 b(float2 v) const { return EACH ? make_float2(v.x * fb, v.y * fb) : v; }
-  __device__ __forceinline__ float out(float v) const { return EACH ? v : v * fa; }
-};
+// One result entry from its sum of products, scaled by 2^-(ea + eb), the
+// operands' scale exponents.  sum(A, B) adds the products of the operands'
+// entries passed through A and B.
+//
+// The factor goes to the finished sum, so that the chain from the scale
+// records to it runs beside the products.  That is exact while the products
+// stay in FP32's range, which two exponents of at most 16 do not change
+// (circuits' stay near 0).  Beyond, where both operands may be of 1e-20 or 1e20
+// (contractions of two unscaled leaves of 1e-10, say), the products are formed
+// again from entries scaled first, as the one-launch-a-vertex kernels form them.
+// The factors are powers of two: inside the range both give the same bits.
+// Measured on the 20-qubit brickwork, without the second form, with it, and
+// scaling first always (the records' chain then runs ahead of the products): one
+// amplitude's level kernel 55.0, 56.4 and 62.7 us; the batch kernel's 4096
+// amplitudes 58.7 and 61.2 us.
+template <class Sum>
+__device__ __forceinline__ float2 scaled_sum(int ea, int eb, Sum sum) {
+  const auto as_is = [](float2 v) { return v; };
+  float2 r = sum(as_is, as_is);
+  const float f = ldexpf(1.0f, -(ea + eb));
+  r.x *= f;
+  r.y *= f;
+  if (__builtin_expect(max(abs(ea), abs(eb)) > 16, 0)) {
+    const float fa = ldexpf(1.0f, -ea), fb = ldexpf(1.0f, -eb);
+    r = sum([fa](float2 v) { return make_float2(v.x * fa, v.y * fa); },
+            [fb](float2 v) { return make_float2(v.x * fb, v.y * fb); });
+  }
+  return r;
+}
+
+// re + i im += a * b
+__device__ __forceinline__ void mac(float &re, float &im, float2 a, float2 b) {
+  re = fmaf(a.x, b.x, re);
+  re = fmaf(-a.y, b.y, re);
+  im = fmaf(a.x, b.y, im);
+  im = fmaf(a.y, b.x, im);
+}
 
 __device__ __forceinline__ ItemScale item_scale(const int2 *sc, int asl, int bsl) {
   ItemScale z;
@@ -154,7 +169,7 @@ __device__ __forceinline__ void fold_max(int2 *scl, int nscale, int csl, int q, 
 // Kind 2: one thread per fiber of the large operand X (and query) reads the
 // fiber's ns entries once and writes nfy results; the small operand Y sits in
 // registers.
-template <bool EACH, bool ONE, bool P2, int NS, int NFY, class SP>
+template <bool ONE, bool P2, int NS, int NFY, class SP>
 __device__ __forceinline__ void tree_stream_impl(SP Sp, int lane, int nthr, int nqw, float2 *pq,
                                                  int perq, const float2 *shr, int2 *scl,
                                                  int nscale) {
@@ -203,22 +218,16 @@ __device__ __forceinline__ void tree_stream_impl(SP Sp, int lane, int nthr, int 
         yv[s] = at_bytes(Y, ym[s * NFY] + dj);
       }
       const ItemScale z = uniform_scale(scl, asl, bsl);
-      const int e = z.ea() + z.eb();
-      const Fold<EACH> f(z);
-      float re = 0.f, im = 0.f;
+      const int ea = z.ea(), eb = z.eb();
+      const float2 r = scaled_sum(ea, eb, [&](auto A, auto B) {
+        float re = 0.f, im = 0.f;
 #pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        const float2 xv = f.a(x[s]), yf = f.b(yv[s]);
-        re = fmaf(xv.x, yf.x, re);
-        re = fmaf(-xv.y, yf.y, re);
-        im = fmaf(xv.x, yf.y, im);
-        im = fmaf(xv.y, yf.x, im);
-      }
-      re = f.out(re);
-      im = f.out(im);
-      *(float2 *)((char *)(C + co) + cj) = make_float2(re, im);
-      if (lane == 0) scl[csl].x = z.za.x + z.zb.x + e;
-      atomicMax((unsigned int *)&scl[csl].y, __float_as_uint(fmaxf(fabsf(re), fabsf(im))));
+        for (int s = 0; s < NS; ++s) mac(re, im, A(x[s]), B(yv[s]));
+        return make_float2(re, im);
+      });
+      *(float2 *)((char *)(C + co) + cj) = r;
+      if (lane == 0) scl[csl].x = z.za.x + z.zb.x + ea + eb;
+      atomicMax((unsigned int *)&scl[csl].y, __float_as_uint(fmaxf(fabsf(r.x), fabsf(r.y))));
       return;
     }
     if (lane >= nfib) return;
@@ -226,35 +235,27 @@ __device__ __forceinline__ void tree_stream_impl(SP Sp, int lane, int nthr, int 
 #pragma unroll
     for (int v = 0; v < NS * NFY; ++v) y[v] = at_bytes(Y, ym[v]);
     const ItemScale z = uniform_scale(scl, asl, bsl);
-    const int e = z.ea() + z.eb();
-    const Fold<EACH> f(z);
-#pragma unroll
-    for (int v = 0; v < NS * NFY; ++v) y[v] = f.b(y[v]);
+    const int ea = z.ea(), eb = z.eb();
     float mx = 0.f;
     for (int fi = lane; fi < nfib; fi += nthr) {
       int xo, co;
       seg2r<P2>(fext, fx, fc, flg, ncs, fi, xo, co);
       float2 x[NS];
 #pragma unroll
-      for (int s = 0; s < NS; ++s) x[s] = f.a(at_bytes(X + xo, xs[s]));
+      for (int s = 0; s < NS; ++s) x[s] = at_bytes(X + xo, xs[s]);
 #pragma unroll
       for (int j = 0; j < NFY; ++j) {
-        float re = 0.f, im = 0.f;
+        const float2 r = scaled_sum(ea, eb, [&](auto A, auto B) {
+          float re = 0.f, im = 0.f;
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const float2 yv = y[s * NFY + j];
-          re = fmaf(x[s].x, yv.x, re);
-          re = fmaf(-x[s].y, yv.y, re);
-          im = fmaf(x[s].x, yv.y, im);
-          im = fmaf(x[s].y, yv.x, im);
-        }
-        re = f.out(re);
-        im = f.out(im);
-        *(float2 *)((char *)(C + co) + cy[j]) = make_float2(re, im);
-        mx = fmaxf(mx, fmaxf(fabsf(re), fabsf(im)));
+          for (int s = 0; s < NS; ++s) mac(re, im, A(x[s]), B(y[s * NFY + j]));
+          return make_float2(re, im);
+        });
+        *(float2 *)((char *)(C + co) + cy[j]) = r;
+        mx = fmaxf(mx, fmaxf(fabsf(r.x), fabsf(r.y)));
       }
     }
-    if (lane == 0) scl[csl].x = z.za.x + z.zb.x + e;
+    if (lane == 0) scl[csl].x = z.za.x + z.zb.x + ea + eb;
     atomicMax((unsigned int *)&scl[csl].y, __float_as_uint(mx));
   } else {
     const int total = nqw * nfib;
@@ -274,31 +275,21 @@ __device__ __forceinline__ void tree_stream_impl(SP Sp, int lane, int nthr, int 
       for (int v = 0; v < NS * NFY; ++v) y[v] = at_bytes(Y, ym[v]);
 #pragma unroll
       for (int s = 0; s < NS; ++s) x[s] = at_bytes(X + xo, xs[s]);
-      const int e = z.ea() + z.eb();
-      const Fold<EACH> f(z);
-#pragma unroll
-      for (int v = 0; v < NS * NFY; ++v) y[v] = f.b(y[v]);
-#pragma unroll
-      for (int s = 0; s < NS; ++s) x[s] = f.a(x[s]);
+      const int ea = z.ea(), eb = z.eb();
       float2 *C = base + (c & ~kPerQuery);
       float m = 0.f;
 #pragma unroll
       for (int j = 0; j < NFY; ++j) {
-        float re = 0.f, im = 0.f;
+        const float2 r = scaled_sum(ea, eb, [&](auto A, auto B) {
+          float re = 0.f, im = 0.f;
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const float2 yv = y[s * NFY + j];
-          re = fmaf(x[s].x, yv.x, re);
-          re = fmaf(-x[s].y, yv.y, re);
-          im = fmaf(x[s].x, yv.y, im);
-          im = fmaf(x[s].y, yv.x, im);
-        }
-        re = f.out(re);
-        im = f.out(im);
-        *(float2 *)((char *)(C + co) + cy[j]) = make_float2(re, im);
-        m = fmaxf(m, fmaxf(fabsf(re), fabsf(im)));
+          for (int s = 0; s < NS; ++s) mac(re, im, A(x[s]), B(y[s * NFY + j]));
+          return make_float2(re, im);
+        });
+        *(float2 *)((char *)(C + co) + cy[j]) = r;
+        m = fmaxf(m, fmaxf(fabsf(r.x), fabsf(r.y)));
       }
-      if (fi == 0) scl[mad24(q, nscale, csl)].x = z.za.x + z.zb.x + e;
+      if (fi == 0) scl[mad24(q, nscale, csl)].x = z.za.x + z.zb.x + ea + eb;
       fold_max(scl, nscale, csl, q, qprev, mx, m);
     }
     if (qprev >= 0) atomicMax((unsigned int *)&scl[mad24(qprev, nscale, csl)].y, __float_as_uint(mx));
@@ -306,62 +297,44 @@ __device__ __forceinline__ void tree_stream_impl(SP Sp, int lane, int nthr, int 
 }
 
 // The shared index of a kind 0 item summed four terms at a time (offsets of
-// term s in lane s of soa/sob when ns <= 64).
-template <bool P2, bool EACH>
-__device__ __forceinline__ float2 dot_terms(const Fold<EACH> &f, const float2 *A, const float2 *B, int ns,
-                                            bool stab, int soa, int sob, const int32_t (&sext)[kTreeSeg],
+// term s in lane s of soa/sob when ns <= 64), and scaled.
+template <bool P2>
+__device__ __forceinline__ float2 dot_terms(int ea, int eb, const float2 *A, const float2 *B, int ns, bool stab,
+                                            int soa, int sob, const int32_t (&sext)[kTreeSeg],
                                             const int32_t (&sa)[kTreeSeg], const int32_t (&sb)[kTreeSeg],
                                             const int32_t (&slg)[kTreeSeg], int nss) {
-  float re0 = 0.f, im0 = 0.f, re1 = 0.f, im1 = 0.f;
-  if (stab) {
-    int s = 0;
-    for (; s + 4 <= ns; s += 4) {
-      float2 x[4], y[4];
+  return scaled_sum(ea, eb, [&](auto fa, auto fb) {
+    float re0 = 0.f, im0 = 0.f, re1 = 0.f, im1 = 0.f;
+    if (stab) {
+      int s = 0;
+      for (; s + 4 <= ns; s += 4) {
+        float2 x[4], y[4];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        x[t] = A[__builtin_amdgcn_readlane(soa, s + t)];
-        y[t] = B[__builtin_amdgcn_readlane(sob, s + t)];
+        for (int t = 0; t < 4; ++t) {
+          x[t] = A[__builtin_amdgcn_readlane(soa, s + t)];
+          y[t] = B[__builtin_amdgcn_readlane(sob, s + t)];
+        }
+#pragma unroll
+        for (int t = 0; t < 4; t += 2) {
+          mac(re0, im0, fa(x[t]), fb(y[t]));
+          mac(re1, im1, fa(x[t + 1]), fb(y[t + 1]));
+        }
       }
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        x[t] = f.a(x[t]);
-        y[t] = f.b(y[t]);
-      }
-#pragma unroll
-      for (int t = 0; t < 4; t += 2) {
-        re0 = fmaf(x[t].x, y[t].x, re0);
-        re0 = fmaf(-x[t].y, y[t].y, re0);
-        im0 = fmaf(x[t].x, y[t].y, im0);
-        im0 = fmaf(x[t].y, y[t].x, im0);
-        re1 = fmaf(x[t + 1].x, y[t + 1].x, re1);
-        re1 = fmaf(-x[t + 1].y, y[t + 1].y, re1);
-        im1 = fmaf(x[t + 1].x, y[t + 1].y, im1);
-        im1 = fmaf(x[t + 1].y, y[t + 1].x, im1);
+      for (; s < ns; ++s)
+        mac(re0, im0, fa(A[__builtin_amdgcn_readlane(soa, s)]), fb(B[__builtin_amdgcn_readlane(sob, s)]));
+    } else {
+      for (int s = 0; s < ns; ++s) {
+        int oa, ob;
+        seg2r<P2>(sext, sa, sb, slg, nss, s, oa, ob);
+        mac(re0, im0, fa(A[oa]), fb(B[ob]));
       }
     }
-    for (; s < ns; ++s) {
-      const float2 x = f.a(A[__builtin_amdgcn_readlane(soa, s)]), y = f.b(B[__builtin_amdgcn_readlane(sob, s)]);
-      re0 = fmaf(x.x, y.x, re0);
-      re0 = fmaf(-x.y, y.y, re0);
-      im0 = fmaf(x.x, y.y, im0);
-      im0 = fmaf(x.y, y.x, im0);
-    }
-  } else {
-    for (int s = 0; s < ns; ++s) {
-      int oa, ob;
-      seg2r<P2>(sext, sa, sb, slg, nss, s, oa, ob);
-      const float2 x = f.a(A[oa]), y = f.b(B[ob]);
-      re0 = fmaf(x.x, y.x, re0);
-      re0 = fmaf(-x.y, y.y, re0);
-      im0 = fmaf(x.x, y.y, im0);
-      im0 = fmaf(x.y, y.x, im0);
-    }
-  }
-  return make_float2(f.out(re0 + re1), f.out(im0 + im1));
+    return make_float2(re0 + re1, im0 + im1);
+  });
 }
 
 // Kind 0: one thread per result entry (and query).
-template <bool EACH, bool ONE, bool P2, class SP>
+template <bool ONE, bool P2, class SP>
 __device__ __forceinline__ void tree_step_impl(SP Sp, int lane, int nthr, int nqw, float2 *pq,
                                                int perq, const float2 *shr, int2 *scl, int nscale) {
   const int a = Sp->a, b = Sp->b, c = Sp->c, asl = Sp->asl, bsl = Sp->bsl, csl = Sp->csl;
@@ -393,17 +366,16 @@ __device__ __forceinline__ void tree_step_impl(SP Sp, int lane, int nthr, int nq
     float2 *C = pq + (c & ~kPerQuery);
     if (lane >= nc) return;
     const ItemScale z = uniform_scale(scl, asl, bsl);
-    const int e = z.ea() + z.eb();
-    const Fold<EACH> f(z);
+    const int ea = z.ea(), eb = z.eb();
     float mx = 0.f;
     for (int ci = lane; ci < nc; ci += nthr) {
       int ao, bo;
       seg2r<P2>(cext, ca, cb, clg, ncs, ci, ao, bo);
-      const float2 r = dot_terms<P2>(f, A0 + ao, B0 + bo, ns, stab, soa, sob, sext, sa, sb, slg, nss);
+      const float2 r = dot_terms<P2>(ea, eb, A0 + ao, B0 + bo, ns, stab, soa, sob, sext, sa, sb, slg, nss);
       C[ci] = r;
       mx = fmaxf(mx, fmaxf(fabsf(r.x), fabsf(r.y)));
     }
-    if (lane == 0) scl[csl].x = z.za.x + z.zb.x + e;
+    if (lane == 0) scl[csl].x = z.za.x + z.zb.x + ea + eb;
     atomicMax((unsigned int *)&scl[csl].y, __float_as_uint(mx));
   } else {
     const int total = nqw * nc;
@@ -418,9 +390,10 @@ __device__ __forceinline__ void tree_step_impl(SP Sp, int lane, int nthr, int nq
       const float2 *A = ((a & kPerQuery) ? base + (a & ~kPerQuery) : shr + a) + ao;
       const float2 *B = ((b & kPerQuery) ? base + (b & ~kPerQuery) : shr + b) + bo;
       const ItemScale z = item_scale(scl + mad24(q, nscale, 0), asl, bsl);
-      const float2 r = dot_terms<P2>(Fold<EACH>(z), A, B, ns, stab, soa, sob, sext, sa, sb, slg, nss);
+      const int ea = z.ea(), eb = z.eb();
+      const float2 r = dot_terms<P2>(ea, eb, A, B, ns, stab, soa, sob, sext, sa, sb, slg, nss);
       base[(c & ~kPerQuery) + ci] = r;
-      if (ci == 0) scl[mad24(q, nscale, csl)].x = z.za.x + z.zb.x + z.ea() + z.eb();
+      if (ci == 0) scl[mad24(q, nscale, csl)].x = z.za.x + z.zb.x + ea + eb;
       fold_max(scl, nscale, csl, q, qprev, mx, fmaxf(fabsf(r.x), fabsf(r.y)));
     }
     if (qprev >= 0) atomicMax((unsigned int *)&scl[mad24(qprev, nscale, csl)].y, __float_as_uint(mx));
@@ -431,13 +404,13 @@ __device__ __forceinline__ void tree_step_impl(SP Sp, int lane, int nthr, int nq
 // `lane`.  The step's maps live in registers; each thread keeps the running
 // max of its results per query and folds it into the scale record once per
 // query.
-template <bool EACH, bool ONE, class SP>
+template <bool ONE, class SP>
 __device__ __forceinline__ void tree_step_q(SP Sp, int lane, int nthr, int nqw, float2 *pq, int perq,
                                             const float2 *shr, int2 *scl, int nscale) {
   if (Sp->kind == 2) {
     // a small operand along the fibers of a large one: ns, nfy in {1, 2, 4}
     const int sel = (Sp->ns >> 1) * 3 + (Sp->nss >> 1) + (Sp->pow2 ? 0 : 9);
-#define TN_TS(P, A, B) tree_stream_impl<EACH, ONE, P, A, B>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale)
+#define TN_TS(P, A, B) tree_stream_impl<ONE, P, A, B>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale)
     switch (sel) {
       case 0: TN_TS(true, 1, 1); break;
       case 1: TN_TS(true, 1, 2); break;
@@ -462,16 +435,16 @@ __device__ __forceinline__ void tree_step_q(SP Sp, int lane, int nthr, int nqw, 
     return;
   }
   if (Sp->pow2)
-    tree_step_impl<EACH, ONE, true>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale);
+    tree_step_impl<ONE, true>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale);
   else
-    tree_step_impl<EACH, ONE, false>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale);
+    tree_step_impl<ONE, false>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale);
 }
 
 // Kind 3: the kind 0 form with some operands in the query's device workspace
 // (a large intermediate of a per-query subtree), reached through generic
 // pointers.  gq: the device workspace of the group's first query, gstride
 // float2 apart.
-template <bool EACH, bool P2, class SP>
+template <bool P2, class SP>
 __device__ __forceinline__ void tree_dev_impl(SP Sp, int lane, int nthr, int nqw, float2 *pq, int perq,
                               const float2 *shr, int2 *scl, int nscale, float2 *gq, int64_t gstride) {
   const int a = Sp->a, b = Sp->b, c = Sp->c, asl = Sp->asl, bsl = Sp->bsl, csl = Sp->csl;
@@ -507,9 +480,10 @@ __device__ __forceinline__ void tree_dev_impl(SP Sp, int lane, int nthr, int nqw
     int ao, bo;
     seg2r<P2>(cext, ca, cb, clg, ncs, ci, ao, bo);
     const ItemScale z = item_scale(scl + mad24(q, nscale, 0), asl, bsl);
-    const float2 r = dot_terms<P2>(Fold<EACH>(z), A + ao, B + bo, ns, stab, soa, sob, sext, sa, sb, slg, nss);
+    const int ea = z.ea(), eb = z.eb();
+    const float2 r = dot_terms<P2>(ea, eb, A + ao, B + bo, ns, stab, soa, sob, sext, sa, sb, slg, nss);
     C[ci] = r;
-    if (ci == 0) scl[mad24(q, nscale, csl)].x = z.za.x + z.zb.x + z.ea() + z.eb();
+    if (ci == 0) scl[mad24(q, nscale, csl)].x = z.za.x + z.zb.x + ea + eb;
     fold_max(scl, nscale, csl, q, qprev, mx, fmaxf(fabsf(r.x), fabsf(r.y)));
   }
   if (qprev >= 0) atomicMax((unsigned int *)&scl[mad24(qprev, nscale, csl)].y, __float_as_uint(mx));
@@ -522,7 +496,7 @@ __device__ __forceinline__ void tree_dev_impl(SP Sp, int lane, int nthr, int nqw
 // may point at either compiles to the slower flat instructions).  The items
 // are dealt as in the single-query kind 0 form: operand scales read once,
 // no division per item.
-template <bool EACH, int GLOB, class SP>
+template <int GLOB, class SP>
 __device__ __forceinline__ void tree_dev_one(SP Sp, int lane, int nthr, float2 *pq, const float2 *shr,
                                              int2 *scl, float2 *gq) {
   const int a = Sp->a, b = Sp->b, c = Sp->c, asl = Sp->asl, bsl = Sp->bsl, csl = Sp->csl;
@@ -559,17 +533,16 @@ __device__ __forceinline__ void tree_dev_one(SP Sp, int lane, int nthr, float2 *
   else
     C = pq + (c & ~kPerQuery);
   const ItemScale z = uniform_scale(scl, asl, bsl);
-  const int e = z.ea() + z.eb();
-  const Fold<EACH> f(z);
+  const int ea = z.ea(), eb = z.eb();
   float mx = 0.f;
   for (int ci = lane; ci < nc; ci += nthr) {
     int ao, bo;
     seg2r<true>(cext, ca, cb, clg, ncs, ci, ao, bo);
-    const float2 r = dot_terms<true>(f, A0 + ao, B0 + bo, ns, stab, soa, sob, sext, sa, sb, slg, nss);
+    const float2 r = dot_terms<true>(ea, eb, A0 + ao, B0 + bo, ns, stab, soa, sob, sext, sa, sb, slg, nss);
     C[ci] = r;
     mx = fmaxf(mx, fmaxf(fabsf(r.x), fabsf(r.y)));
   }
-  if (lane == 0) scl[csl].x = z.za.x + z.zb.x + e;
+  if (lane == 0) scl[csl].x = z.za.x + z.zb.x + ea + eb;
   atomicMax((unsigned int *)&scl[csl].y, __float_as_uint(mx));
 }
 
@@ -579,7 +552,7 @@ __device__ __forceinline__ void tree_dev_one(SP Sp, int lane, int nthr, float2 *
 // launch reads) instead of decoding a step's maps, so several independent
 // small steps cost one step of the wave.  Single-query groups only.
 // r0, r1: the lane's record (r1 for ns = 4 only).
-template <bool EACH, int NS>
+template <int NS>
 __device__ __forceinline__ void tree_lane_exec(uint4 r0, uint4 r1, float2 *pq, const float2 *shr,
                                                int2 *scl) {
   // each operand's region once (bits 15 and 31 of w[3]), then byte offsets
@@ -601,23 +574,17 @@ __device__ __forceinline__ void tree_lane_exec(uint4 r0, uint4 r1, float2 *pq, c
   }
   // a leaf operand's index is that of a record that stays zero
   const int2 za = scl[r0.w & 0x7fffu], zb = scl[(r0.w >> 16) & 0x7fffu];
-  const int ea = tn_scale_exp((uint32_t)za.y), eb = tn_scale_exp((uint32_t)zb.y), e = ea + eb;
-  const Fold<EACH> f(ea, eb);
-  float re = 0.f, im = 0.f;
+  const int ea = tn_scale_exp((uint32_t)za.y), eb = tn_scale_exp((uint32_t)zb.y);
+  const float2 r = scaled_sum(ea, eb, [&](auto A, auto B) {
+    float re = 0.f, im = 0.f;
 #pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    const float2 xv = f.a(x[s]), yv = f.b(y[s]);
-    re = fmaf(xv.x, yv.x, re);
-    re = fmaf(-xv.y, yv.y, re);
-    im = fmaf(xv.x, yv.y, im);
-    im = fmaf(xv.y, yv.x, im);
-  }
-  re = f.out(re);
-  im = f.out(im);
-  *(float2 *)((char *)pq + (r0.z & 0xffffu)) = make_float2(re, im);
+    for (int s = 0; s < NS; ++s) mac(re, im, A(x[s]), B(y[s]));
+    return make_float2(re, im);
+  });
+  *(float2 *)((char *)pq + (r0.z & 0xffffu)) = r;
   const int csl = (int)((r0.z >> 16) & 0x7fffu);
-  if (r0.z >> 31) scl[csl].x = za.x + zb.x + e;
-  atomicMax((unsigned int *)&scl[csl].y, __float_as_uint(fmaxf(fabsf(re), fabsf(im))));
+  if (r0.z >> 31) scl[csl].x = za.x + zb.x + ea + eb;
+  atomicMax((unsigned int *)&scl[csl].y, __float_as_uint(fmaxf(fabsf(r.x), fabsf(r.y))));
 }
 
 // The largest of v over the wave, in a scalar register (every lane of the
@@ -656,7 +623,6 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
 //
 // Every choice is uniform across the wave, and the forms share this one body:
 // the stream's loop holds it kBlkAhead times.
-template <bool EACH>
 __device__ __forceinline__ void tree_block(uint4 r0, uint4 r1, int lane, float2 *pq, const float2 *shr,
                                            int2 *scl, float &vre, float &vim, int &zx, int &zy) {
   const uint32_t w6 = (uint32_t)__builtin_amdgcn_readfirstlane((int)r1.z);
@@ -665,11 +631,11 @@ __device__ __forceinline__ void tree_block(uint4 r0, uint4 r1, int lane, float2 
   if (w6 & kBlkPacked << 16) {
     if (act) {
       if (ns == 1)
-        tree_lane_exec<EACH, 1>(r0, r1, pq, shr, scl);
+        tree_lane_exec<1>(r0, r1, pq, shr, scl);
       else if (ns == 2)
-        tree_lane_exec<EACH, 2>(r0, r1, pq, shr, scl);
+        tree_lane_exec<2>(r0, r1, pq, shr, scl);
       else
-        tree_lane_exec<EACH, 4>(r0, r1, pq, shr, scl);
+        tree_lane_exec<4>(r0, r1, pq, shr, scl);
     }
     return;
   }
@@ -716,44 +682,37 @@ __device__ __forceinline__ void tree_block(uint4 r0, uint4 r1, int lane, float2 
     zy = __builtin_amdgcn_readfirstlane(za.y);
   }
   const int zbx = __builtin_amdgcn_readfirstlane(zb.x), zby = __builtin_amdgcn_readfirstlane(zb.y);
-  const int ea = tn_scale_exp((uint32_t)zy), eb = tn_scale_exp((uint32_t)zby), e = ea + eb;
-  const Fold<EACH> f(ea, eb);
-  float re = 0.f, im = 0.f;
-  auto term = [&](const float2 &x, const float2 &y) {
-    const float2 a = f.a(x), b = f.b(y);
-    re = fmaf(a.x, b.x, re);
-    re = fmaf(-a.y, b.y, re);
-    im = fmaf(a.x, b.y, im);
-    im = fmaf(a.y, b.x, im);
-  };
-  term(x[0], y[0]);
-  if (ns >= 2) {
-    term(x[1], y[1]);
-    if (ns == 4) {
-      term(x[2], y[2]);
-      term(x[3], y[3]);
+  const int ea = tn_scale_exp((uint32_t)zy), eb = tn_scale_exp((uint32_t)zby);
+  const float2 r = scaled_sum(ea, eb, [&](auto A, auto B) {
+    float re = 0.f, im = 0.f;
+    mac(re, im, A(x[0]), B(y[0]));
+    if (ns >= 2) {
+      mac(re, im, A(x[1]), B(y[1]));
+      if (ns == 4) {
+        mac(re, im, A(x[2]), B(y[2]));
+        mac(re, im, A(x[3]), B(y[3]));
+      }
     }
-  }
-  re = f.out(re);
-  im = f.out(im);
-  const float m = act ? fmaxf(fabsf(re), fabsf(im)) : 0.f;
+    return make_float2(re, im);
+  });
+  const float m = act ? fmaxf(fabsf(r.x), fabsf(r.y)) : 0.f;
   const unsigned mx = wave_max_u32(__float_as_uint(m));
-  zx = zx + zbx + e;
+  zx = zx + zbx + ea + eb;
   zy = (int)mx;
   if (w6 & kBlkStore << 16) {
-    if (act) *(float2 *)((char *)pq + (r0.z & 0xffffu)) = make_float2(re, im);
+    if (act) *(float2 *)((char *)pq + (r0.z & 0xffffu)) = r;
     if (lane == 0) scl[(wz >> 16) & 0x7fffu] = make_int2(zx, zy);
   }
-  vre = re;
-  vim = im;
+  vre = r.x;
+  vim = r.y;
 }
 
-template <bool EACH, int NS>
+template <int NS>
 __device__ __forceinline__ void tree_lane_step(const TreeLaneRec *rec, int lane, int nl, float2 *pq,
                                                const float2 *shr, int2 *scl) {
   if (lane >= nl) return;
   const uint4 *r = (const uint4 *)(rec + lane);
-  tree_lane_exec<EACH, NS>(r[0], NS == 4 ? r[1] : make_uint4(0u, 0u, 0u, 0u), pq, shr, scl);
+  tree_lane_exec<NS>(r[0], NS == 4 ? r[1] : make_uint4(0u, 0u, 0u, 0u), pq, shr, scl);
 }
 
 // DEV: the program may hold kind 3 steps (per-query subtrees with
@@ -761,24 +720,24 @@ __device__ __forceinline__ void tree_lane_step(const TreeLaneRec *rec, int lane,
 // A kind 3 step (operands in the query's device workspace), whatever its
 // kind field says (a kind 6 pair runs as two of these when a wave holds more
 // than one query).
-template <bool EACH, class SP>
+template <class SP>
 __device__ __forceinline__ void tree_kind3(SP Sp, int lane, int nthr, int nqw, float2 *pq, int perq,
                                            const float2 *shr, int2 *scl, int nscale, float2 *gq,
                                            int64_t gstride) {
   if (nqw == 1 && Sp->pow2) {
     switch (Sp->glob) {  // 1 .. 7 (checked on the host)
-      case 1: tree_dev_one<EACH, 1>(Sp, lane, nthr, pq, shr, scl, gq); break;
-      case 2: tree_dev_one<EACH, 2>(Sp, lane, nthr, pq, shr, scl, gq); break;
-      case 3: tree_dev_one<EACH, 3>(Sp, lane, nthr, pq, shr, scl, gq); break;
-      case 4: tree_dev_one<EACH, 4>(Sp, lane, nthr, pq, shr, scl, gq); break;
-      case 5: tree_dev_one<EACH, 5>(Sp, lane, nthr, pq, shr, scl, gq); break;
-      case 6: tree_dev_one<EACH, 6>(Sp, lane, nthr, pq, shr, scl, gq); break;
-      default: tree_dev_one<EACH, 7>(Sp, lane, nthr, pq, shr, scl, gq); break;
+      case 1: tree_dev_one<1>(Sp, lane, nthr, pq, shr, scl, gq); break;
+      case 2: tree_dev_one<2>(Sp, lane, nthr, pq, shr, scl, gq); break;
+      case 3: tree_dev_one<3>(Sp, lane, nthr, pq, shr, scl, gq); break;
+      case 4: tree_dev_one<4>(Sp, lane, nthr, pq, shr, scl, gq); break;
+      case 5: tree_dev_one<5>(Sp, lane, nthr, pq, shr, scl, gq); break;
+      case 6: tree_dev_one<6>(Sp, lane, nthr, pq, shr, scl, gq); break;
+      default: tree_dev_one<7>(Sp, lane, nthr, pq, shr, scl, gq); break;
     }
   } else if (Sp->pow2) {
-    tree_dev_impl<EACH, true>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale, gq, gstride);
+    tree_dev_impl<true>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale, gq, gstride);
   } else {
-    tree_dev_impl<EACH, false>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale, gq, gstride);
+    tree_dev_impl<false>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale, gq, gstride);
   }
   // a later step of this wave reads what this one stored to device memory
   __builtin_amdgcn_s_waitcnt(0);
@@ -795,7 +754,6 @@ __device__ __forceinline__ void tree_kind3(SP Sp, int lane, int nthr, int nqw, f
 // and Q's results come from the same operations in the same order as when
 // the two steps run apart, so the results are bit-identical.  Q: nc <= 256,
 // ns <= 4; P: ns <= 64; both power-of-two maps.
-template <bool EACH>
 __device__ __forceinline__ void tree_pair(CStep P, CStep Q, int lane, float2 *pq, const float2 *shr,
                                           int2 *scl) {
   int32_t pcext[kTreeSeg], pca[kTreeSeg], pcb[kTreeSeg], pclg[kTreeSeg];
@@ -841,8 +799,7 @@ __device__ __forceinline__ void tree_pair(CStep P, CStep Q, int lane, float2 *pq
   const float2 *B0 = (qb & kPerQuery) ? pq + (qb & ~kPerQuery) : shr + qb;
   float2 *C = pq + (Q->c & ~kPerQuery);
   const ItemScale zp = uniform_scale(scl, P->asl, P->bsl);
-  const int ep = zp.ea() + zp.eb();
-  const Fold<EACH> fp(zp);
+  const int epa = zp.ea(), epb = zp.eb();
   // T's entries of this lane's results
   float2 tv[4][4];
   int bo[4];
@@ -863,7 +820,7 @@ __device__ __forceinline__ void tree_pair(CStep P, CStep Q, int lane, float2 *pq
         if (sh < qns) {
           const int xo = xb + __builtin_amdgcn_readlane(pxs, sh), yo = yb + __builtin_amdgcn_readlane(pys, sh);
           tv[j][sh] =
-              dot_terms<true>(fp, X0 + xo, Y0 + yo, pns, true, psoa, psob, psext, psa, psb, pslg, pnss);
+              dot_terms<true>(epa, epb, X0 + xo, Y0 + yo, pns, true, psoa, psob, psext, psa, psb, pslg, pnss);
           mt = fmaxf(mt, fmaxf(fabsf(tv[j][sh].x), fabsf(tv[j][sh].y)));
         }
     }
@@ -871,12 +828,11 @@ __device__ __forceinline__ void tree_pair(CStep P, CStep Q, int lane, float2 *pq
   // T's scale record as P leaves it (max bits: non-negative floats order as
   // their bit patterns), and Q's operand scales
   const unsigned tbits = wave_max_u32(__float_as_uint(mt));
-  const int tlog = zp.za.x + zp.zb.x + ep;
+  const int tlog = zp.za.x + zp.zb.x + epa + epb;
   int2 zb = Q->bsl >= 0 ? scl[Q->bsl] : make_int2(0, 0);
   zb.x = __builtin_amdgcn_readfirstlane(zb.x);
   zb.y = __builtin_amdgcn_readfirstlane(zb.y);
-  const int et = tn_scale_exp(tbits), eb = tn_scale_exp((uint32_t)zb.y), eq = et + eb;
-  const Fold<EACH> fq(et, eb);
+  const int eqt = tn_scale_exp(tbits), eqb = tn_scale_exp((uint32_t)zb.y);
   float mx = 0.f;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
@@ -885,44 +841,33 @@ __device__ __forceinline__ void tree_pair(CStep P, CStep Q, int lane, float2 *pq
       // the order of dot_terms: four terms at a time, the even ones into
       // (re0, im0) and the odd ones into (re1, im1), then the rest into
       // (re0, im0)
-      float re0 = 0.f, im0 = 0.f, re1 = 0.f, im1 = 0.f;
-      if (qns == 4) {
-        float2 y[4];
+      const float2 r = scaled_sum(eqt, eqb, [&](auto ft, auto fb) {
+        float re0 = 0.f, im0 = 0.f, re1 = 0.f, im1 = 0.f;
+        if (qns == 4) {
+          float2 y[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) y[u] = fq.b(B0[bo[j] + __builtin_amdgcn_readlane(qsob, u)]);
+          for (int u = 0; u < 4; ++u) y[u] = B0[bo[j] + __builtin_amdgcn_readlane(qsob, u)];
 #pragma unroll
-        for (int u = 0; u < 4; u += 2) {
-          const float2 x0 = fq.a(tv[j][u]), x1 = fq.a(tv[j][u + 1]);
-          re0 = fmaf(x0.x, y[u].x, re0);
-          re0 = fmaf(-x0.y, y[u].y, re0);
-          im0 = fmaf(x0.x, y[u].y, im0);
-          im0 = fmaf(x0.y, y[u].x, im0);
-          re1 = fmaf(x1.x, y[u + 1].x, re1);
-          re1 = fmaf(-x1.y, y[u + 1].y, re1);
-          im1 = fmaf(x1.x, y[u + 1].y, im1);
-          im1 = fmaf(x1.y, y[u + 1].x, im1);
-        }
-      } else {
-#pragma unroll
-        for (int u = 0; u < 3; ++u)
-          if (u < qns) {
-            const float2 x = fq.a(tv[j][u]), y = fq.b(B0[bo[j] + __builtin_amdgcn_readlane(qsob, u)]);
-            re0 = fmaf(x.x, y.x, re0);
-            re0 = fmaf(-x.y, y.y, re0);
-            im0 = fmaf(x.x, y.y, im0);
-            im0 = fmaf(x.y, y.x, im0);
+          for (int u = 0; u < 4; u += 2) {
+            mac(re0, im0, ft(tv[j][u]), fb(y[u]));
+            mac(re1, im1, ft(tv[j][u + 1]), fb(y[u + 1]));
           }
-      }
-      const float rr = fq.out(re0 + re1), ii = fq.out(im0 + im1);
-      C[co] = make_float2(rr, ii);
-      mx = fmaxf(mx, fmaxf(fabsf(rr), fabsf(ii)));
+        } else {
+#pragma unroll
+          for (int u = 0; u < 3; ++u)
+            if (u < qns) mac(re0, im0, ft(tv[j][u]), fb(B0[bo[j] + __builtin_amdgcn_readlane(qsob, u)]));
+        }
+        return make_float2(re0 + re1, im0 + im1);
+      });
+      C[co] = r;
+      mx = fmaxf(mx, fmaxf(fabsf(r.x), fabsf(r.y)));
     }
   }
-  if (lane == 0) scl[Q->csl].x = tlog + zb.x + eq;
+  if (lane == 0) scl[Q->csl].x = tlog + zb.x + eqt + eqb;
   atomicMax((unsigned int *)&scl[Q->csl].y, __float_as_uint(mx));
 }
 
-template <bool DEV, bool EACH, class SP>
+template <bool DEV, class SP>
 __device__ __forceinline__ void tree_step(SP Sp, int lane, int nthr, int nqw, float2 *pq, int perq,
                                           const float2 *shr, int2 *scl, int nscale, float2 *gq,
                                           int64_t gstride, const TreeLaneRec *lanes, int lane0) {
@@ -931,21 +876,21 @@ __device__ __forceinline__ void tree_step(SP Sp, int lane, int nthr, int nqw, fl
     // (lane0 = its first record's index)
     const TreeLaneRec *rec = lanes + (Sp->tab - lane0);
     if (Sp->ns == 1)
-      tree_lane_step<EACH, 1>(rec, lane, Sp->nc, pq, shr, scl);
+      tree_lane_step<1>(rec, lane, Sp->nc, pq, shr, scl);
     else if (Sp->ns == 2)
-      tree_lane_step<EACH, 2>(rec, lane, Sp->nc, pq, shr, scl);
+      tree_lane_step<2>(rec, lane, Sp->nc, pq, shr, scl);
     else
-      tree_lane_step<EACH, 4>(rec, lane, Sp->nc, pq, shr, scl);
+      tree_lane_step<4>(rec, lane, Sp->nc, pq, shr, scl);
     return;
   }
   if (DEV && Sp->kind == 3) {
-    tree_kind3<EACH>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale, gq, gstride);
+    tree_kind3(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale, gq, gstride);
     return;
   }
   if (nqw == 1)
-    tree_step_q<EACH, true>(Sp, lane, nthr, 1, pq, perq, shr, scl, nscale);
+    tree_step_q<true>(Sp, lane, nthr, 1, pq, perq, shr, scl, nscale);
   else
-    tree_step_q<EACH, false>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale);
+    tree_step_q<false>(Sp, lane, nthr, nqw, pq, perq, shr, scl, nscale);
 }
 
 // Closed root of one query: the FP64 inner product and its result record
@@ -1048,7 +993,7 @@ __device__ __forceinline__ void tree_prologue(const TreeLaunch &t, KernargLaunch
   }
 }
 
-template <bool DEV, bool EACH>
+template <bool DEV>
 __global__ __launch_bounds__(kTreeThreads) void k_tree(TreeLaunch t) {
   constexpr int W = kTreeStepWords;
   constexpr int CW = kTreeChunk * W;
@@ -1168,13 +1113,13 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree(TreeLaunch t) {
       }
     } else if (cur == 1) {
       // one step (a spine contraction): the whole workgroup on it
-      tree_step<DEV, EACH>(S, tid, NT, nqw, pq, perq, shr, scl, h.nscale, gq, gstride, lrec, lrec0);
+      tree_step<DEV>(S, tid, NT, nqw, pq, perq, shr, scl, h.nscale, gq, gstride, lrec, lrec0);
     } else {
       // several independent steps of one level (largest first): one wave per
       // step, round robin
       const int wave = tid >> 6, lane = tid & 63;
       for (int i = wave; i < cur; i += NT / 64)
-        tree_step<DEV, EACH>(S + i, lane, 64, nqw, pq, perq, shr, scl, h.nscale, gq, gstride, lrec, lrec0);
+        tree_step<DEV>(S + i, lane, 64, nqw, pq, perq, shr, scl, h.nscale, gq, gstride, lrec, lrec0);
     }
     if (k + 1 < h.nchunks && !whole) {
       int32_t *dst = sbuf + ((k + 1) & 1) * CW;
@@ -1210,7 +1155,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree(TreeLaunch t) {
   }
 }
 
-template <bool DEV, bool EACH>
+template <bool DEV>
 __global__ __launch_bounds__(256, DEV ? 3 : 4) void k_tree_wave(TreeLaunch t) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -1270,15 +1215,15 @@ __global__ __launch_bounds__(256, DEV ? 3 : 4) void k_tree_wave(TreeLaunch t) {
       uint4 a0 = r[0], a1 = r[1], b0 = r[BS], b1 = r[BS + 1], c0 = r[2 * BS], c1 = r[2 * BS + 1];
       for (int left = n;;) {
         r += kBlkAhead * BS;
-        tree_block<EACH>(a0, a1, lane, wpq, shr, wscl, vre, vim, zx, zy);
+        tree_block(a0, a1, lane, wpq, shr, wscl, vre, vim, zx, zy);
         if (--left == 0) break;
         a0 = r[0];
         a1 = r[1];
-        tree_block<EACH>(b0, b1, lane, wpq, shr, wscl, vre, vim, zx, zy);
+        tree_block(b0, b1, lane, wpq, shr, wscl, vre, vim, zx, zy);
         if (--left == 0) break;
         b0 = r[BS];
         b1 = r[BS + 1];
-        tree_block<EACH>(c0, c1, lane, wpq, shr, wscl, vre, vim, zx, zy);
+        tree_block(c0, c1, lane, wpq, shr, wscl, vre, vim, zx, zy);
         if (--left == 0) break;
         c0 = r[2 * BS];
         c1 = r[2 * BS + 1];
@@ -1288,16 +1233,16 @@ __global__ __launch_bounds__(256, DEV ? 3 : 4) void k_tree_wave(TreeLaunch t) {
     const CStep S = prog + step;
     if (DEV && S->kind == 6 && wn == 1) {
       // a kind 3 pair: this step and the next
-      tree_pair<EACH>(S, S + 1, lane, wpq, shr, wscl);
+      tree_pair(S, S + 1, lane, wpq, shr, wscl);
     } else if (DEV && S->kind == 6) {
-      tree_kind3<EACH>(S, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
-      tree_kind3<EACH>(S + 1, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
+      tree_kind3(S, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
+      tree_kind3(S + 1, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
     } else if (DEV && S->kind == 3) {
-      tree_kind3<EACH>(S, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
+      tree_kind3(S, lane, 64, wn, wpq, perq, shr, wscl, nscale, wgq, gstride);
     } else if (wn == 1) {
-      tree_step_q<EACH, true>(S, lane, 64, 1, wpq, perq, shr, wscl, nscale);
+      tree_step_q<true>(S, lane, 64, 1, wpq, perq, shr, wscl, nscale);
     } else {
-      tree_step_q<EACH, false>(S, lane, 64, wn, wpq, perq, shr, wscl, nscale);
+      tree_step_q<false>(S, lane, 64, wn, wpq, perq, shr, wscl, nscale);
     }
   }
 
@@ -1367,7 +1312,7 @@ __global__ __launch_bounds__(256, DEV ? 3 : 4) void k_tree_wave(TreeLaunch t) {
 }
 
 // LDS a workgroup may use: the device's per-block limit (160 KiB on gfx950),
-// raised for the subtree kernels once.
+// raised for both subtree kernels once.
 size_t tree_lds_limit() {
   static size_t limit = 0;
   if (limit == 0) {
@@ -1378,38 +1323,40 @@ size_t tree_lds_limit() {
         v > 0)
       l = (size_t)v;
     if (l > 163840) l = 163840;
-    if (l > 65536)
-      for (const void *k : {(const void *)k_tree<false, false>, (const void *)k_tree<false, true>,
-                            (const void *)k_tree<true, false>, (const void *)k_tree<true, true>,
-                            (const void *)k_tree_wave<false, false>, (const void *)k_tree_wave<false, true>,
-                            (const void *)k_tree_wave<true, false>, (const void *)k_tree_wave<true, true>})
-        if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)l) != hipSuccess) {
-          l = 65536;
-          break;
-        }
+    if (l > 65536 &&
+        (hipFuncSetAttribute((const void *)k_tree<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)l) != hipSuccess ||
+         hipFuncSetAttribute((const void *)k_tree<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)l) != hipSuccess ||
+         hipFuncSetAttribute((const void *)k_tree_wave<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)l) != hipSuccess ||
+         hipFuncSetAttribute((const void *)k_tree_wave<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)l) != hipSuccess))
+      l = 65536;
     limit = l;
   }
   return limit;
 }
 
-hipError_t launch_tree(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes, bool dev, bool each) {
+hipError_t launch_tree(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes, bool dev) {
   if (nsub <= 0 || t.nq <= 0) return hipSuccess;
   if (lds_bytes > tree_lds_limit()) return hipErrorInvalidValue;
   const int groups = (t.nq + t.qw - 1) / t.qw;
-  const auto kernel = dev ? (each ? k_tree<true, true> : k_tree<true, false>)
-                          : (each ? k_tree<false, true> : k_tree<false, false>);
-  hipLaunchKernelGGL(kernel, dim3(nsub, groups), dim3(kTreeThreads), lds_bytes, st, t);
+  if (dev)
+    hipLaunchKernelGGL(k_tree<true>, dim3(nsub, groups), dim3(kTreeThreads), lds_bytes, st, t);
+  else
+    hipLaunchKernelGGL(k_tree<false>, dim3(nsub, groups), dim3(kTreeThreads), lds_bytes, st, t);
   return hipGetLastError();
 }
 
-hipError_t launch_tree_wave(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes, bool dev,
-                            bool each) {
+hipError_t launch_tree_wave(hipStream_t st, const TreeLaunch &t, int nsub, size_t lds_bytes, bool dev) {
   if (nsub <= 0 || t.nq <= 0) return hipSuccess;
   if (lds_bytes > tree_lds_limit() || t.qw < 1 || t.qw > 16) return hipErrorInvalidValue;
   const int groups = (t.nq + t.qw - 1) / t.qw;
-  const auto kernel = dev ? (each ? k_tree_wave<true, true> : k_tree_wave<true, false>)
-                          : (each ? k_tree_wave<false, true> : k_tree_wave<false, false>);
-  hipLaunchKernelGGL(kernel, dim3(nsub, groups), dim3(256), lds_bytes, st, t);
+  if (dev)
+    hipLaunchKernelGGL(k_tree_wave<true>, dim3(nsub, groups), dim3(256), lds_bytes, st, t);
+  else
+    hipLaunchKernelGGL(k_tree_wave<false>, dim3(nsub, groups), dim3(256), lds_bytes, st, t);
   return hipGetLastError();
 }
 

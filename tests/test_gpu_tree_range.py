@@ -1,9 +1,8 @@
-"""Single calls on leaves far from one: two leaves of 2^-40 make an intermediate
-of 2^-80, which fits FP32 as it is, and the product of two such intermediates
-fits it only once their scale records are applied.  A single call runs small
-vertices in the subtree kernels, and there too an operand is scaled before its
-products.  Every leaf is a power of two away from one of order one, so the
-result, read as mantissa and scale, is the unscaled network's.
+"""Leaves far from one in the subtree kernels: two leaves of 2^-40 make an
+intermediate of 2^-80, which fits FP32 as it is, and the product of two such
+intermediates fits it only once their scale records are applied, to the operands
+before the products.  Every leaf is a power of two away from one of order one,
+so the result, read as mantissa and scale, is the unscaled network's.
 
 Bounds: an entry of the chain is a sum of products of eight entries, three
 levels of four roundings each (complex: times sqrt(2)) and eight leaf
@@ -22,15 +21,15 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("shift", [-40, 40])
 @pytest.mark.parametrize("how", ["complex64 leaves", "bf16x3 leaves", "host overrides", "device overrides",
-                                 "concurrent"])
+                                 "concurrent", "batch", "strided"])
 def test_chain_of_pairs(shift, how):
     rng = np.random.default_rng(8)
     T = [rng.standard_normal((2, 2)) + 1j * rng.standard_normal((2, 2)) for _ in range(8)]
     S = [t * 2.0 ** shift for t in T]
-    dtype = lib.TN_C64 if how in ("complex64 leaves", "concurrent") else lib.TN_C128
+    dtype = lib.TN_C64 if how in ("complex64 leaves", "concurrent", "batch") else lib.TN_C128
     prec = lib.TN_PREC_BF16X3 if how == "bf16x3 leaves" else 0
     flags = lib.TN_FLAG_KEEP_SCALE | (lib.TN_FLAG_CONCURRENT if how == "concurrent" else 0)
-    over = how.endswith("overrides")
+    over = how.endswith("overrides") or how == "strided"
     with lib.Context(64 << 20) as ctx:
         p = ctx.plan_load([[i, i + 1] for i in range(8)], {i: 2 for i in range(9)}, T if over else S, [0] * 4 + [1] * 4, 2,
                           [(0, 1), (2, 3), (8, 9), (4, 5), (6, 7), (11, 12), (10, 13)], [0, 8], prec, dtype)
@@ -43,6 +42,13 @@ def test_chain_of_pairs(shift, how):
                                         lib.TN_C128, ctypes.byref(l2), flags)
             assert rc == lib.TN_OK, lib.tn_last_error()
             l2 = l2.value
+        elif how == "batch":
+            out, l2s, _ = lib.tn_contract_batch(ctx.handle, [(p, {0: S[0] * f}) for f in (2, 1, -1)], [(2, 2)] * 3, flags=flags)
+            m, l2 = out[1], l2s[1]
+        elif how == "strided":
+            out, l2s = lib.tn_contract_strided(p, 300, [(i, np.stack([t] * 300).astype(np.complex64), 32, lib.TN_C64)
+                                                        for i, t in enumerate(S)], (2, 2), flags=flags)
+            m, l2 = out[299], l2s[299]
         else:
             m, l2 = lib.tn_contract(p, dict(enumerate(S)) if over else None, (2, 2), flags=flags)
     got = m * 2.0 ** (float(l2) - 8 * shift)
@@ -52,10 +58,11 @@ def test_chain_of_pairs(shift, how):
     assert (np.abs(got - ref) <= 32 * 2.0 ** -24 * size).all()
 
 
+@pytest.mark.parametrize("Q", [1, 300])
 @pytest.mark.parametrize("shift", [-50, 50])
-def test_single_on_the_batch_kernel(shift):
+def test_on_the_batch_kernel(shift, Q):
     # a chain of five shared matrices, each an outer product times k numbers,
-    # whose query fits beside them only in the batch kernel
+    # whose queries fit beside them only in the batch kernel
     rng = np.random.default_rng(50)
 
     def entries(*shape):
@@ -88,7 +95,12 @@ def test_single_on_the_batch_kernel(shift):
         p = ctx.plan_load(legs, {k: n for k, n in enumerate(dim)}, S, [0] * nv, 1, tree, None, 0, lib.TN_C64)
         lib.tn_profile_enable(ctx.handle, True)
         lib.tn_profile_read(ctx.handle)
-        m, l2 = lib.tn_contract(p, {0: S[0]}, (), flags=lib.TN_FLAG_KEEP_SCALE)
+        if Q == 1:
+            m, l2 = lib.tn_contract(p, {0: S[0]}, (), flags=lib.TN_FLAG_KEEP_SCALE)
+        else:
+            out, l2s = lib.tn_contract_strided(p, Q, [(0, np.stack([S[0]] * Q), 512, lib.TN_C64)],
+                                               flags=lib.TN_FLAG_KEEP_SCALE)
+            m, l2 = out[Q - 1], l2s[Q - 1]
         n = {k: x["launches"] for k, x in lib.tn_profile_read(ctx.handle).items() if x["launches"]}
     assert "stream" not in n, n
     ref, size = leaves[0].astype(np.complex128), np.abs(leaves[0]).astype(np.float64)
