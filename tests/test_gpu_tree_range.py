@@ -15,6 +15,8 @@ import pytest
 import torch
 
 from paper_2507_20667_amd import lib
+from paper_2507_20667_amd.inputs import output_tensor_ids, random_bitstrings
+from paper_2507_20667_amd.planner.workloads import brickwork20
 
 pytestmark = pytest.mark.gpu
 
@@ -110,3 +112,34 @@ def test_on_the_batch_kernel(shift, Q):
     ref, size = ref @ leaves[w], size @ np.abs(leaves[w])
     got = complex(m.item()) * 2.0 ** (float(l2) - nv * shift)
     assert abs(got - ref) <= 8 * np.sqrt(5 * 2 * 64) * 2.0 ** -24 * size
+
+
+@pytest.mark.parametrize("shift", [-40, 40])
+@pytest.mark.parametrize("queries", [1, 3, 300])
+def test_brickwork(queries, shift):
+    # the 20-qubit brickwork with every gate tensor scaled: gate chains, the
+    # fused pair and packed gate steps (300), the level kernel (1)
+    w = brickwork20()
+    net, plan = w.net, w.plan
+    ids = output_tensor_ids(net)
+    xs = random_bitstrings(w.circ.n, queries, 7)
+    vecs = np.zeros((len(ids), queries, 2), np.complex64)
+    for q, x in enumerate(xs):
+        for k in range(len(ids)):
+            vecs[k, q, (x >> k) & 1] = 1.0
+    gates = [i for i, l in enumerate(net.legs) if len(l) >= 2]
+    got = {}
+    with lib.Context(1 << 30) as ctx:
+        for s in (0, shift):
+            tensors = [np.asarray(t, np.complex64) * np.float32(2.0 ** (s if i in gates else 0))
+                       for i, t in enumerate(net.tensors)]
+            p = ctx.plan_load(net.legs, net.dims, tensors, plan.partition_of, w.num_partitions, plan.tree, None, 0, lib.TN_C64)
+            if queries == 1:
+                m, l2 = lib.tn_contract(p, {t: vecs[k, 0] for k, t in enumerate(ids)}, flags=lib.TN_FLAG_KEEP_SCALE)
+                m, l2 = np.array([m.item()]), np.array([l2])
+            else:
+                m, l2 = lib.tn_contract_strided(p, queries, [(t, vecs[k], 16, lib.TN_C64) for k, t in enumerate(ids)],
+                                                flags=lib.TN_FLAG_KEEP_SCALE)
+            got[s] = m * 2.0 ** (l2 - s * len(gates))
+    # powers of two: only entries at the end of FP32's range may round elsewhere
+    assert (np.abs(got[shift] - got[0]) <= 2.0 ** -30 * 2.0 ** (-w.circ.n / 2)).all()
