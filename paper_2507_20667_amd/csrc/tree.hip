@@ -101,6 +101,11 @@ struct ItemScale {
   __device__ __forceinline__ int eb() const { return tn_scale_exp((uint32_t)zb.y); }
 };
 
+// Exponents with which an unscaled product may leave FP32's range
+__device__ __forceinline__ bool far_off(int ea, int eb) {
+  return max((unsigned)(ea + 16), (unsigned)(eb + 16)) > 32u;
+}
+
 // One result entry from its sum of products, scaled by 2^-(ea + eb), the
 // operands' scale exponents.  sum(A, B) adds the products of the operands'
 // entries passed through A and B.
@@ -112,10 +117,10 @@ struct ItemScale {
 // (contractions of two unscaled leaves of 1e-10, say), the products are formed
 // again from entries scaled first, as the one-launch-a-vertex kernels form them.
 // The factors are powers of two: inside the range both give the same bits.
-// Measured on the 20-qubit brickwork, without the second form, with it, and
-// scaling first always (the records' chain then runs ahead of the products): one
-// amplitude's level kernel 55.0, 56.4 and 62.7 us; the batch kernel's 4096
-// amplitudes 58.7 and 61.2 us.
+// Measured on the 20-qubit brickwork: without the second form one amplitude's
+// level kernel takes 55.1 us, with it 55.8, and scaling first always, which puts
+// the records' chain ahead of the products, 62.7; the batch kernel's 4096
+// amplitudes 58.5 and 59.9 us.
 template <class Sum>
 __device__ __forceinline__ float2 scaled_sum(int ea, int eb, Sum sum) {
   const auto as_is = [](float2 v) { return v; };
@@ -123,7 +128,7 @@ __device__ __forceinline__ float2 scaled_sum(int ea, int eb, Sum sum) {
   const float f = ldexpf(1.0f, -(ea + eb));
   r.x *= f;
   r.y *= f;
-  if (__builtin_expect(max(abs(ea), abs(eb)) > 16, 0)) {
+  if (__builtin_expect(far_off(ea, eb), 0)) {
     const float fa = ldexpf(1.0f, -ea), fb = ldexpf(1.0f, -eb);
     r = sum([fa](float2 v) { return make_float2(v.x * fa, v.y * fa); },
             [fb](float2 v) { return make_float2(v.x * fb, v.y * fb); });
@@ -683,28 +688,40 @@ __device__ __forceinline__ void tree_block(uint4 r0, uint4 r1, int lane, float2 
   }
   const int zbx = __builtin_amdgcn_readfirstlane(zb.x), zby = __builtin_amdgcn_readfirstlane(zb.y);
   const int ea = tn_scale_exp((uint32_t)zy), eb = tn_scale_exp((uint32_t)zby);
-  const float2 r = scaled_sum(ea, eb, [&](auto A, auto B) {
-    float re = 0.f, im = 0.f;
-    mac(re, im, A(x[0]), B(y[0]));
-    if (ns >= 2) {
-      mac(re, im, A(x[1]), B(y[1]));
-      if (ns == 4) {
-        mac(re, im, A(x[2]), B(y[2]));
-        mac(re, im, A(x[3]), B(y[3]));
-      }
+  // as scaled_sum, but the operands scaled in place before the one sum (the
+  // records are read ahead of the entries): with a second copy of the sum the
+  // launch of 4096 took 61.8 us instead of 59.9, eight moves a link
+  float f = ldexpf(1.0f, -(ea + eb));
+  if (__builtin_expect(far_off(ea, eb), 0)) {
+    const float fa = ldexpf(1.0f, -ea), fb = ldexpf(1.0f, -eb);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      x[s] = make_float2(x[s].x * fa, x[s].y * fa);
+      y[s] = make_float2(y[s].x * fb, y[s].y * fb);
     }
-    return make_float2(re, im);
-  });
-  const float m = act ? fmaxf(fabsf(r.x), fabsf(r.y)) : 0.f;
+    f = 1.0f;
+  }
+  float re = 0.f, im = 0.f;
+  mac(re, im, x[0], y[0]);
+  if (ns >= 2) {
+    mac(re, im, x[1], y[1]);
+    if (ns == 4) {
+      mac(re, im, x[2], y[2]);
+      mac(re, im, x[3], y[3]);
+    }
+  }
+  re *= f;
+  im *= f;
+  const float m = act ? fmaxf(fabsf(re), fabsf(im)) : 0.f;
   const unsigned mx = wave_max_u32(__float_as_uint(m));
   zx = zx + zbx + ea + eb;
   zy = (int)mx;
   if (w6 & kBlkStore << 16) {
-    if (act) *(float2 *)((char *)pq + (r0.z & 0xffffu)) = r;
+    if (act) *(float2 *)((char *)pq + (r0.z & 0xffffu)) = make_float2(re, im);
     if (lane == 0) scl[(wz >> 16) & 0x7fffu] = make_int2(zx, zy);
   }
-  vre = r.x;
-  vim = r.y;
+  vre = re;
+  vim = im;
 }
 
 template <int NS>
